@@ -356,6 +356,30 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 #define EPARA_COST_PANEL 2040
 #define EPARA_COST_PARTIAL 24
 
+/* Block tiles.  A launch whose panel tiles do not fill the chip, or leave a nearly empty last round, can be cut into
+ * tiles of a quarter of the size instead: 128 rows x 128 columns (EPARA_ACT_SWIGLU: 64 hidden columns), two workgroups
+ * per compute unit, for batches of every size (the block table of epara_kernel_classes; a panel class of
+ * EPARA_BLOCK_ROWS rows always means block tiles).  The visit order still holds W lists, one per unit: the grid is 2 W, workgroup
+ * b takes the entries 0, 2, 4, .. of list b and workgroup b + W the entries 1, 3, 5, ...  In a tile of f = ceil(rows / 32) row fragments that shares its
+ * weight columns with the s = ceil(M / 128) row tiles of its group, one K costs
+ *     max(EPARA_COST_BLOCK_STREAM / s + EPARA_COST_BLOCK_STREAM_PER_32 * f, EPARA_COST_BLOCK_PER_32 * f)
+ * of a unit's time (the first where weights come from HBM, the second where the batch is tall), a tile another
+ * EPARA_COST_BLOCK_START.
+ * Measured, bf16, 512 tiles at a time: K = 4096, own weights: 94 / 100 / 114 us for f = 1 / 2 / 4; weights shared by many row
+ * tiles: 8.0 ns (K = 3072, N = 768) to 9.3 ns (K = 5120, N = 13824) per K and compute unit for f = 4, against 5.9 ns for a quarter of
+ * a panel tile, which moves fewer bytes per product and so runs at higher clocks.  But a panel tile costs another 7 us of
+ * start and finish (EPARA_COST_PANEL_START), which one wave per SIMD cannot overlap with anything and two workgroups
+ * per unit hide from each other. */
+#define EPARA_TABLE_BLOCK 2               /* `narrow` of the block table */
+#define EPARA_BLOCK_ROWS 128
+#define EPARA_BLOCK_MIN_M 64              /* launches of batches up to this keep the streaming classes */
+#define EPARA_BLOCK_MIN_WORKGROUPS 128    /* smaller grids leave units free, where workgroups do not pair up */
+#define EPARA_COST_BLOCK_STREAM 1000
+#define EPARA_COST_BLOCK_STREAM_PER_32 50
+#define EPARA_COST_BLOCK_PER_32 165
+#define EPARA_COST_BLOCK_START 40000
+#define EPARA_COST_PANEL_START 600000
+
 /* Splitting K.  A streaming tile of a class with BM >= 32 streams its weights while re-reading BM activation
  * rows per weight column, which is cheapest with wide tiles; wide tiles of a long K are too coarse to balance,
  * so the scheduler can cut their K instead: a tile of a streaming class with split_K > 0 and K >= split_K is
@@ -429,9 +453,10 @@ int32_t epara_workspace_init(void* d_workspace, int64_t bytes, void* stream);
  * The first n_stream_classes classes of the table are weight-streaming classes (small batches,
  * bandwidth bound), the others are panel classes (matrix-core bound).
  *   1. panel tiles: classes by descending BM*BN (ties: lower class), inside a class groups by
- *      descending K (ties: lower group), inside a group panels of panel_m x panel_n tiles,
- *      n-panel outermost, m fastest inside a panel.  Each tile of that sequence goes to the workgroup
- *      with the smallest accumulated cost (EPARA_COST_PANEL * K per panel tile); among equally loaded
+ *      descending cost of their first tile (panel tiles: by descending K; ties: lower group), inside a group panels
+ *      of panel_m x panel_n tiles, n-panel outermost, m fastest inside a panel.  Each tile of that sequence goes to
+ *      the workgroup with the smallest accumulated cost (EPARA_COST_PANEL * K per panel tile, "Block tiles" above for
+ *      a class of EPARA_BLOCK_ROWS rows); among equally loaded
  *      workgroups the smallest die-major rank wins, rank r standing for workgroup (r mod (W/X)) * X +
  *      r div (W/X)  (X = n_xcd).  Tiles of equal cost therefore go round robin, the l-th to rank l mod W,
  *      so that the W/X workgroups of one compute die (workgroup b runs on die b mod X) work on
@@ -471,7 +496,7 @@ int32_t epara_schedule_chain(epara_phase_schedule* phases, int32_t n_phases,
 typedef struct {
     epara_tile_class classes[4];      /* the class table the launch was cut with */
     int32_t n_classes, n_stream_classes;
-    int32_t narrow;                   /* 1: the narrow table (see epara_kernel_classes) */
+    int32_t narrow;                   /* 0 / 1 / EPARA_TABLE_BLOCK: the wide, narrow or block table (see epara_kernel_classes) */
     int32_t gated;                    /* 1: every group is EPARA_ACT_SWIGLU */
     int64_t n_tiles, n_slots;
     int64_t makespan;                 /* cost of the most loaded workgroup under the cost model */
@@ -481,9 +506,12 @@ typedef struct {
 
 /* The whole planning decision of one launch (Sec. 3.1: the parallel mode of each task): picks the class
  * table -- the wide one, or the narrow one when some batch has more than 32 rows and the narrow
- * table's schedule has the smaller makespan under the cost model (ties: wide) -- then plans
+ * table's schedule has the smaller makespan under the cost model (ties: wide); or the block table ("Block tiles"), for
+ * bf16 / fp8 launches with a batch of more than EPARA_BLOCK_MIN_M rows and n_workgroups >= EPARA_BLOCK_MIN_WORKGROUPS, when
+ * its makespan T is below U - U / 15, U = the largest load of a workgroup in the order of the other choice with
+ * EPARA_COST_PANEL_START added to every visit to a panel tile -- then plans
  * (epara_plan_groups) and schedules (epara_schedule_tiles) with it.  The groups must be all
- * EPARA_ACT_SWIGLU or none (ERR_DTYPE).  *plan is always written (sizes included); tiles / order are
+ * EPARA_ACT_SWIGLU or none (ERR_DTYPE).  (A chain, epara_plan_chain with more than one phase, has no block tiles.)  *plan is always written (sizes included); tiles / order are
  * written when given and large enough, else ERR_CAPACITY (give NULL and 0 to ask for the sizes only;
  * that returns EPARA_OK).  row_off / x_off / y_off and split_base (G entries, epara_split_layout) may be NULL.
  * plan->n_split_tiles, n_panel_split_tiles and workspace_bytes say what the launch needs for tiles visited in
@@ -532,10 +560,11 @@ int32_t epara_chain_waits(const epara_tile* producer_tiles, int64_t n_producer_t
 /* The tile classes the kernels implement for an input dtype (gated = EPARA_ACT_SWIGLU
  * launches, whose BN counts hidden columns).  Writes up to cap classes, *n_classes = count and
  * *n_stream_classes = how many of them (the first ones) are weight-streaming classes.
- * bf16 / fp8 have two tables: the wide one (narrow = 0) gives batches of 33..64 rows tiles of 128
+ * bf16 / fp8 have three tables: the wide one (narrow = 0) gives batches of 33..64 rows tiles of 128
  * (gated: 64) columns, which halves the activation re-reads; the narrow one (narrow = 1) gives
  * them 64 (gated: 32) columns, for launches with too few columns to keep every workgroup busy
- * with wide tiles.  A launch may use either.  fp32: batches of up to 16 rows in 16 x 64 tiles (the sum
+ * with wide tiles.  narrow = EPARA_TABLE_BLOCK: block tiles (see there) for every batch.  A launch may use any of them
+ * (a chain only the first two).  fp32: batches of up to 16 rows in 16 x 64 tiles (the sum
  * over K is formed in four contiguous quarters that are added in order), larger ones in 64 x 64
  * tiles (K ascending). */
 int32_t epara_kernel_classes(int32_t in_dtype, int32_t gated, int32_t narrow,

@@ -210,6 +210,15 @@ def plan_groups(groups, classes):
     return row_off, x_off, y_off, tiles
 
 
+def panel_cost(M, K, cls, rows):
+    """Cost of a tile of a panel class cls = (max_M, BM, BN[, split_K]) with `rows` rows of a group of M: 2040 * K, or for
+    a class of 128 rows (block tiles, f = ceil(rows / 32), s = ceil(M / 128)) K * max(1000 // s + 50 f, 165 f) + 40000."""
+    if cls[1] != 128:
+        return 2040 * K
+    f, s = -(-min(rows, 128) // 32), -(-M // 128)
+    return K * max(1000 // s + 50 * f, 165 * f) + 40000
+
+
 def split_parts(K, cls):
     """Visits a streaming tile of class cls = (max_M, BM, BN[, split_K]) is cut into: two when the class names a
     K (split_K > 0) and the group's K reaches it (see schedule_tiles)."""
@@ -310,10 +319,10 @@ def schedule_tiles(groups, classes, n_stream_classes, tiles, n_workgroups, n_xcd
     n_stream_classes classes are weight-streaming classes, the others panel classes.
 
     1. Panel tiles.  Classes by descending BM*BN (ties: lower class first); inside a class the
-       groups by descending K (ties: lower group first); inside a group the tile grid TM x TN
-       is cut into panels of panel_m x panel_n tiles, panels taken with the n-panel index
+       groups by descending cost of their first tile (panel_cost; tiles of 256 rows: by descending
+       K; ties: lower group first); inside a group the tile grid TM x TN is cut into panels of panel_m x panel_n tiles, panels taken with the n-panel index
        outermost, and inside a panel the m index runs fastest.  Each tile of that sequence goes to the
-       workgroup with the smallest accumulated cost (a panel tile costs 2040 * K); among equally loaded
+       workgroup with the smallest accumulated cost (panel_cost); among equally loaded
        workgroups the one of smallest die-major rank, rank r standing for workgroup (r mod (W/X)) * X + r div (W/X).
        Tiles of equal cost therefore go round robin, the l-th to rank l mod W, and the W/X tiles that run
        together on one die are consecutive in the sequence; a workgroup that got a long-K tile gets fewer
@@ -358,7 +367,7 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
             first.setdefault(tile[0], t)
         panel_classes = sorted(range(n_stream_classes, len(classes)), key=lambda c: (-classes[c][1] * classes[c][2], c))
         for c in panel_classes:
-            members = sorted({t[0] for t in tiles if t[5] == c}, key=lambda g: (-groups[g][1], g))
+            members = sorted({t[0] for t in tiles if t[5] == c}, key=lambda g: (-panel_cost(groups[g][0], groups[g][1], classes[c], groups[g][0]), g))
             bm, bn = classes[c][1], classes[c][2]
             for g in members:
                 M, K, N = groups[g][:3]
@@ -374,7 +383,7 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
                                 x, i = divmod(r, per)
                                 b = i * X + x
                                 lists[p][b].append(t)
-                                load[b] += 2040 * K
+                                load[b] += panel_cost(M, K, classes[c], M - tm * bm)
                                 heapq.heappush(rank_heap, (load[b], r))
         for t in range(len(tiles) - n_panel_split, len(tiles)):    # the parts: tile by tile, part by part, same rule
             parts_t = panel_parts + (1 if t >= len(tiles) - panel_more else 0)      # the last panel_more tiles: one part more
@@ -415,6 +424,40 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
                 order[j * W + b] = t
         orders.append(order)
     return orders
+
+
+def block_choice(groups, block_classes, other_classes, other_n_stream, other_tiles, other_order, n_workgroups, n_xcd, panel_m, panel_n):
+    """Whether a single bf16 / fp8 launch takes the block table instead of the best of the other tables (class table, tiles
+    and visit order of which are given) -> (taken, tiles, order, finish).  Considered when a batch has more than 64 rows
+    and W >= 128.  finish = the largest load of a list of the block tiles' order; taken if that is below `other` - other // 15 with `other` = the largest load of
+    a workgroup in the other order where every visit to a panel tile costs 600000 more."""
+    W = n_workgroups
+    if max((g[0] for g in groups), default=0) <= 64 or W < 128:
+        return False, None, None, None
+    loads = [0] * W
+    for slot, e in enumerate(other_order):
+        if e < 0:
+            continue
+        t, _, parts = order_decode(e)
+        tile = other_tiles[t]
+        g, cl = groups[tile[0]], other_classes[tile[5]]
+        if tile[5] >= other_n_stream:
+            cost = panel_cost(g[0], g[1], cl, tile[3])
+            loads[slot % W] += (cost if parts == 1 else cost // parts + 1020000) + 600000
+        else:
+            wide = tile[4] * (2 if len(g) > 3 and g[3] else 1)
+            cost = g[1] * (6 * wide + (2 * cl[1] if cl[1] >= 32 else 0))
+            loads[slot % W] += cost if parts == 1 else cost // parts + 24 * cl[1] * wide
+    other = max(loads)
+    _, _, _, tiles = plan_groups([g[:3] for g in groups], block_classes)
+    order = schedule_tiles(groups, block_classes, 0, tiles, W, n_xcd, panel_m, panel_n)
+    loads = [0] * W
+    for slot, t in enumerate(order):
+        if t >= 0:
+            g = groups[tiles[t][0]]
+            loads[slot % W] += panel_cost(g[0], g[1], block_classes[0], tiles[t][3])
+    finish = max(loads)
+    return finish < other - other // 15, tiles, order, finish
 
 
 def chain_waits(producer_tiles, counter_base, producer):

@@ -567,7 +567,7 @@ def epara_kernel_classes(in_dtype, gated, narrow=False):
     """-> (classes, n_stream_classes)."""
     n = np.zeros(2, dtype=np.int32)
     classes = np.zeros(8, dtype=TILE_CLASS)
-    _check(lib().epara_kernel_classes(int(in_dtype), int(bool(gated)), int(bool(narrow)), _ptr(classes), len(classes),
+    _check(lib().epara_kernel_classes(int(in_dtype), int(bool(gated)), int(narrow), _ptr(classes), len(classes),
                                       _ptr(n[0:1]), _ptr(n[1:2])),
            "epara_kernel_classes")
     return classes[: int(n[0])].copy(), int(n[1])

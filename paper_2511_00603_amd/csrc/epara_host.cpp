@@ -19,10 +19,19 @@ namespace {
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// The cost model of the scheduler (the constants are the header's).
+// The cost model of the scheduler (the constants are the header's).  A panel class of EPARA_BLOCK_ROWS rows holds
+// block tiles, whose cost depends on the rows that hold data and on how many tiles share a column of weights.
+inline int64_t panel_cost(const epara_group_desc& d, const epara_tile_class& c, int64_t rows)
+{
+    if (c.BM != EPARA_BLOCK_ROWS) return static_cast<int64_t>(EPARA_COST_PANEL) * d.K;
+    const int64_t frags = (std::min<int64_t>(rows, c.BM) + 31) / 32, shared = ceil_div(d.M, c.BM);
+    return std::max(EPARA_COST_BLOCK_STREAM / shared + EPARA_COST_BLOCK_STREAM_PER_32 * frags, EPARA_COST_BLOCK_PER_32 * frags) * static_cast<int64_t>(d.K) +
+           EPARA_COST_BLOCK_START;
+}
+
 inline int64_t tile_cost(const epara_group_desc& d, const epara_tile& tl, const epara_tile_class* classes, int32_t n_stream_classes)
 {
-    if (tl.cls >= n_stream_classes) return static_cast<int64_t>(EPARA_COST_PANEL) * d.K;
+    if (tl.cls >= n_stream_classes) return panel_cost(d, classes[tl.cls], tl.rows);
     const int64_t BM = classes[tl.cls].BM;
     const int64_t units = static_cast<int64_t>(EPARA_COST_PER_COLUMN) * tl.cols * (d.act == EPARA_ACT_SWIGLU ? 2 : 1) +
                           (BM >= 32 ? EPARA_COST_PER_ROW * BM : 0);
@@ -584,8 +593,10 @@ int32_t epara_schedule_chain(epara_phase_schedule* phases, int32_t n_phases,
             members.clear();
             for (int32_t g = 0; g < ph.G; ++g)
                 if (cls[p][g] == c) members.push_back(g);
-            std::stable_sort(members.begin(), members.end(),
-                             [&](int32_t a, int32_t b) { return ph.groups[a].K > ph.groups[b].K; });
+            // by descending cost of a group's first tile (panel tiles of 256 rows: by descending K)
+            std::stable_sort(members.begin(), members.end(), [&](int32_t a, int32_t b) {
+                return panel_cost(ph.groups[a], ph.classes[c], ph.groups[a].M) > panel_cost(ph.groups[b], ph.classes[c], ph.groups[b].M);
+            });
             const int64_t BM = ph.classes[c].BM, BN = ph.classes[c].BN;
             for (int32_t g : members) {
                 const int64_t TM = ceil_div(ph.groups[g].M, BM), TN = ceil_div(ph.groups[g].N, BN);
@@ -599,7 +610,7 @@ int32_t epara_schedule_chain(epara_phase_schedule* phases, int32_t n_phases,
                                 panel_heap.pop();
                                 const int64_t x = top.second / per_die, i = top.second % per_die, b = i * X + x;
                                 lists[p][b].push_back(static_cast<int32_t>(tile));
-                                load[b] += static_cast<int64_t>(EPARA_COST_PANEL) * ph.groups[g].K;
+                                load[b] += panel_cost(ph.groups[g], ph.classes[c], ph.groups[g].M - tm * BM);
                                 panel_heap.push({load[b], top.second});
                             }
             }
@@ -693,6 +704,16 @@ struct phase_option {
     std::vector<epara_tile> tiles;
 };
 
+int32_t make_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype, int32_t gated, int32_t narrow, phase_option& o)
+{
+    o.narrow = narrow;
+    if (int32_t st = epara_kernel_classes(in_dtype, gated, narrow, o.classes, 4, &o.n_classes, &o.n_stream)) return st;
+    int64_t n = 0;
+    if (int32_t st = epara_plan_groups(groups, G, o.classes, o.n_classes, nullptr, nullptr, nullptr, nullptr, 0, &n)) return st;
+    o.tiles.resize(static_cast<size_t>(n));
+    return epara_plan_groups(groups, G, o.classes, o.n_classes, nullptr, nullptr, nullptr, o.tiles.data(), n, &n);
+}
+
 int32_t phase_options(const epara_group_desc* groups, int32_t G, int32_t in_dtype, std::vector<phase_option>& out)
 {
     if (G < 0) return EPARA_ERR_SHAPE;
@@ -703,15 +724,44 @@ int32_t phase_options(const epara_group_desc* groups, int32_t G, int32_t in_dtyp
     for (int32_t g = 0; g < G; ++g) max_M = std::max(max_M, groups[g].M);
     const int n_opt = (in_dtype != EPARA_F32 && max_M > 32) ? 2 : 1;
     out.resize(static_cast<size_t>(n_opt));
-    for (int narrow = 0; narrow < n_opt; ++narrow) {
-        phase_option& o = out[narrow];
-        o.narrow = narrow;
-        if (int32_t st = epara_kernel_classes(in_dtype, gated, narrow, o.classes, 4, &o.n_classes, &o.n_stream)) return st;
-        int64_t n = 0;
-        if (int32_t st = epara_plan_groups(groups, G, o.classes, o.n_classes, nullptr, nullptr, nullptr, nullptr, 0, &n)) return st;
-        o.tiles.resize(static_cast<size_t>(n));
-        if (int32_t st = epara_plan_groups(groups, G, o.classes, o.n_classes, nullptr, nullptr, nullptr, o.tiles.data(), n, &n)) return st;
+    for (int narrow = 0; narrow < n_opt; ++narrow)
+        if (int32_t st = make_option(groups, G, in_dtype, gated, narrow, out[narrow])) return st;
+    return EPARA_OK;
+}
+
+// The block table of a single launch (see epara_plan_launch): schedules it into `order` and says whether it is expected to finish earlier than `best`, the choice among the other tables with its order.
+int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype, int32_t gated, int64_t W, int32_t n_xcd,
+                     int32_t panel_m, int32_t panel_n, const phase_option& best, const std::vector<int32_t>& best_order,
+                     phase_option& o, std::vector<int32_t>& order, int64_t* finish, bool* take)
+{
+    *take = false;
+    int32_t max_M = 0;
+    for (int32_t g = 0; g < G; ++g) max_M = std::max(max_M, groups[g].M);
+    if (in_dtype == EPARA_F32 || max_M <= EPARA_BLOCK_MIN_M || W < EPARA_BLOCK_MIN_WORKGROUPS) return EPARA_OK;
+    std::vector<int64_t> load(static_cast<size_t>(W), 0);
+    for (size_t i = 0; i < best_order.size(); ++i)
+        if (best_order[i] >= 0) {
+            const epara_tile& tl = best.tiles[EPARA_ORDER_TILE(best_order[i])];
+            const bool panel = tl.cls >= best.n_stream;
+            load[i % W] += visit_cost(tile_cost(groups[tl.group], tl, best.classes, best.n_stream), (best_order[i] >> 28) + 1, groups[tl.group], tl,
+                                      best.classes[tl.cls], panel) + (panel ? EPARA_COST_PANEL_START : 0);
+        }
+    const int64_t other = *std::max_element(load.begin(), load.end());
+    if (int32_t st = make_option(groups, G, in_dtype, gated, EPARA_TABLE_BLOCK, o)) return st;
+    epara_phase_schedule ph;
+    std::memset(&ph, 0, sizeof ph);
+    ph.groups = groups; ph.classes = o.classes; ph.tiles = o.tiles.data();
+    ph.n_tiles = static_cast<int64_t>(o.tiles.size());
+    ph.G = G; ph.n_classes = o.n_classes; ph.n_stream_classes = o.n_stream;
+    for (int pass = 0; pass < 2; ++pass) {
+        if (int32_t st = epara_schedule_chain(&ph, 1, static_cast<int32_t>(W), n_xcd, panel_m, panel_n)) return st;
+        if (pass == 0) { order.assign(static_cast<size_t>(ph.n_slots), -1); ph.order = order.data(); ph.order_cap = ph.n_slots; }
     }
+    load.assign(static_cast<size_t>(W), 0);
+    for (size_t i = 0; i < order.size(); ++i)
+        if (order[i] >= 0) load[i % W] += tile_cost(groups[o.tiles[order[i]].group], o.tiles[order[i]], o.classes, o.n_stream);
+    *finish = *std::max_element(load.begin(), load.end());
+    *take = *finish < other - other / 15;
     return EPARA_OK;
 }
 
@@ -793,10 +843,20 @@ int32_t epara_plan_chain(epara_chain_plan_phase* phases, int32_t n_phases, int32
         while (p >= 0 && ++pick[p] == static_cast<int>(options[p].size())) pick[p--] = 0;
         if (p < 0) break;
     }
+    // a single launch may do better with block tiles
+    phase_option block;
+    bool use_block = false;
+    if (n_phases == 1) {
+        std::vector<int32_t> order;
+        int64_t fin = 0;
+        if (int32_t st = block_option(phases[0].groups, phases[0].G, in_dtype, gated[0], W, n_xcd, panel_m, panel_n, options[0][best_pick[0]],
+                                      best_order[0], block, order, &fin, &use_block)) return st;
+        if (use_block) { best_finish = fin; best_order[0] = std::move(order); }
+    }
     if (finish) *finish = best_finish;
     int32_t status = EPARA_OK, base = 0;
     for (int32_t p = 0; p < n_phases; ++p) {
-        const phase_option& o = options[p][best_pick[p]];
+        const phase_option& o = use_block ? block : options[p][best_pick[p]];
         epara_chain_plan_phase& ph = phases[p];
         // a phase's own makespan: its workgroups' costs in this phase alone
         std::vector<int64_t> load(static_cast<size_t>(W), 0);
@@ -807,7 +867,8 @@ int32_t epara_plan_chain(epara_chain_plan_phase* phases, int32_t n_phases, int32
                 load[i % W] += visit_cost(tile_cost(ph.groups[tl.group], tl, o.classes, o.n_stream), (e >> 28) + 1, ph.groups[tl.group], tl,
                                           o.classes[tl.cls], tl.cls >= o.n_stream);
             }
-        fill_plan(ph.plan, o, gated[p], static_cast<int64_t>(best_order[p].size()), *std::max_element(load.begin(), load.end()));
+        fill_plan(ph.plan, o, gated[p], static_cast<int64_t>(best_order[p].size()),
+                  use_block ? best_finish : *std::max_element(load.begin(), load.end()));
         ph.counter_base = base;
         base += ph.G;
         if (ph.tiles) {
@@ -964,6 +1025,15 @@ int32_t epara_kernel_classes(int32_t in_dtype, int32_t gated, int32_t narrow,
         table[n++] = {16, 16, 64, 0};       // K split over the four waves of a workgroup
         table[n++] = {INT32_MAX, 64, 64, 0};
     } else if (in_dtype == EPARA_BF16 || in_dtype == EPARA_FP8_E4M3) {
+        if (narrow == EPARA_TABLE_BLOCK) {
+            table[n++] = {INT32_MAX, EPARA_BLOCK_ROWS, gated ? 64 : 128, 0};
+            *n_classes = n;
+            *n_stream_classes = 0;
+            if (!classes) return EPARA_OK;
+            if (cap < n) return EPARA_ERR_CAPACITY;
+            classes[0] = table[0];
+            return EPARA_OK;
+        }
         // weight-streaming classes: the whole batch (1, 2 or 4 blocks of 16 rows) against 2, 4 or 8
         // weight column blocks, so that activations re-read per weight byte stay constant
         const int32_t split_K = in_dtype == EPARA_BF16 ? EPARA_SPLIT_K_BF16 : 0;   // where two visits pay (measured)

@@ -32,6 +32,10 @@ EPARA_HIDDEN hipError_t epara_enqueue_fp8_plain(int panel_only, unsigned grid, h
 EPARA_HIDDEN hipError_t epara_enqueue_fp8_gated(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split);
 EPARA_HIDDEN hipError_t epara_enqueue_f32(unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots);
 
+// One grouped launch of block tiles (the block table of epara_kernel_classes).
+EPARA_HIDDEN hipError_t epara_enqueue_block_bf16(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype);
+EPARA_HIDDEN hipError_t epara_enqueue_block_fp8(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype);
+
 // Chain kernels.  resident != NULL: no launch, *resident = workgroups of that kernel the current device holds at once.
 EPARA_HIDDEN hipError_t epara_chain_bf16_plain(const epara_chain_tables&, const epara_chain_scalars&, unsigned grid, hipStream_t, int64_t* resident);
 EPARA_HIDDEN hipError_t epara_chain_bf16_ffn(const epara_chain_tables&, const epara_chain_scalars&, unsigned grid, hipStream_t, int64_t* resident);

@@ -54,7 +54,7 @@ int32_t validate_launch(const epara_launch* L, int32_t in_dtype, int32_t out_dty
     if (L->G < 0 || L->n_tiles < 0 || L->n_slots < 0) return EPARA_ERR_SHAPE;
     if (L->n_tiles == 0) return EPARA_OK;
     if (!L->h_args || !L->d_args || !L->h_tiles || !L->d_tiles || !L->d_order) return EPARA_ERR_NULL;
-    if (L->n_workgroups <= 0 || L->n_slots < L->n_tiles || L->n_slots % L->n_workgroups != 0 || L->n_tiles > INT32_MAX)
+    if (L->n_workgroups <= 0 || L->n_workgroups > INT32_MAX / 2 || L->n_slots < L->n_tiles || L->n_slots % L->n_workgroups != 0 || L->n_tiles > INT32_MAX)
         return EPARA_ERR_SHAPE;
     const int esz = f32 ? 4 : (in_dtype == EPARA_BF16 ? 2 : 1);
     for (int32_t g = 0; g < L->G; ++g) {
@@ -78,7 +78,7 @@ int32_t validate_launch(const epara_launch* L, int32_t in_dtype, int32_t out_dty
         if (n_gated != 0 && n_gated != n_live) return EPARA_ERR_DTYPE;
     }
     int32_t last = EPARA_OK, narrow = 0;
-    for (; narrow < (f32 ? 1 : 2); ++narrow) {
+    for (; narrow < (f32 ? 1 : 3); ++narrow) {
         last = check_tiles(L, in_dtype, narrow);
         if (last == EPARA_OK) break;
     }
@@ -123,6 +123,10 @@ int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int 
     const long n_slots = static_cast<long>(L->n_slots);
     (void)hipGetLastError();
     hipError_t e;
+    if (narrow == EPARA_TABLE_BLOCK) {        // two workgroups per compute unit
+        e = (in_dtype == EPARA_BF16 ? epara_enqueue_block_bf16 : epara_enqueue_block_fp8)(gated, 2 * grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype);
+        return e == hipSuccess ? EPARA_OK : EPARA_ERR_HIP;
+    }
     if (in_dtype == EPARA_F32)       e = epara_enqueue_f32(grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots);
     else if (in_dtype == EPARA_BF16) e = (gated ? epara_enqueue_bf16_gated : epara_enqueue_bf16_plain)(panel_only, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype, narrow, static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, L->n_panel_split_tiles, static_cast<int>(L->n_tiles - L->n_panel_split_tiles));
     else                             e = (gated ? epara_enqueue_fp8_gated : epara_enqueue_fp8_plain)(panel_only, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype, narrow, static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, L->n_panel_split_tiles, static_cast<int>(L->n_tiles - L->n_panel_split_tiles));
@@ -234,6 +238,7 @@ static int32_t chain_impl(const epara_chain_phase* phases, int32_t n_phases, int
         const epara_launch* L = ph.launch;
         int narrow = 0;
         if (int32_t st = validate_launch(L, in_dtype, ph.out_dtype, &narrow)) return st;
+        if (narrow == EPARA_TABLE_BLOCK) return EPARA_ERR_SHAPE;                            // the chain kernels hold no block tiles
         if (L->n_split_tiles != 0 || L->n_panel_split_tiles != 0) return EPARA_ERR_SHAPE;   // the phases of a chain are scheduled without splitting K
         if (ph.counter_base < 0 || ph.counter_base > INT32_MAX - L->G) return EPARA_ERR_SHAPE;
         for (int32_t q = 0; q < p; ++q)       // counter ranges must not overlap

@@ -520,6 +520,55 @@ def test_plan_launch_is_a_valid_plan_and_makes_the_choice_the_header_states(inde
         assert [tuple(int(v) for v in t) for t in tiles] == best[3] and order.tolist() == best[4]
 
 
+VIT_ROWS = [6304, 3152, 197, 1576, 788, 788, 394, 1576]
+
+
+@pytest.mark.parametrize("shapes,act,dtype,block", [
+    ([(75, 4096, 11008), (130, 4096, 11008), (237, 4096, 11008)], 5, B.EPARA_BF16, True),     # 258 panel tiles on 256 workgroups
+    ([(3, 11008, 4096), (40, 11008, 4096), (1501, 11008, 4096)], 0, B.EPARA_BF16, True),      # 96 panel tiles next to streaming ones
+    ([(75, 11008, 4096), (237, 11008, 4096)], 0, B.EPARA_FP8_E4M3, True),
+    ([(m, 768, 2304) for m in VIT_ROWS], 0, B.EPARA_BF16, True),
+    ([(m, 768, 3072) for m in VIT_ROWS], 2, B.EPARA_BF16, False),                              # three full rounds of panel tiles
+    ([(4692, 5120, 13824), (3500, 5120, 13824)], 5, B.EPARA_FP8_E4M3, False),
+    ([(65, 16, 10)], 1, B.EPARA_BF16, True), ([(64, 16, 10)], 1, B.EPARA_BF16, False), ([], 0, B.EPARA_BF16, False)])
+def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype, block):
+    """The choice between block tiles and the other tables, and the integers of a block plan, against the reference
+    planner; the tiles cover every output once; a grid of fewer than 128 workgroups and a chain never use them."""
+    gated, W = act == 5, 256
+    ref = [g + (gated,) for g in shapes]
+    info, _, _, _, tiles, order, _ = B.epara_plan_launch(_desc(shapes, act), dtype, W, 8, 1, 4)
+    assert (info.narrow == 2) == block
+    best = None
+    for narrow in (0, 1) if max((g[0] for g in shapes), default=0) > 32 else (0,):
+        cls, ns = B.epara_kernel_classes(dtype, gated, narrow)
+        cls = [tuple(int(v) for v in c) for c in cls]
+        rt = P.plan_groups(shapes, cls)[3]
+        ro = P.schedule_tiles(ref, cls, ns, rt, W, 8, 1, 4)
+        loads = [0] * W
+        for slot, e in enumerate(ro):
+            if e >= 0:
+                t, _, parts = P.order_decode(e)
+                loads[slot % W] += _ref_cost(shapes[rt[t][0]], rt[t], cls, ns, gated, parts)
+        if best is None or max(loads) < best[0]:
+            best = (max(loads), cls, ns, rt, ro)
+    bc, bn = B.epara_kernel_classes(dtype, gated, 2)
+    bc = [tuple(int(v) for v in c) for c in bc]
+    assert bc == [(P.INT32_MAX, 128, 64 if gated else 128, 0)] and bn == 0
+    taken, rt, ro, finish = P.block_choice(ref, bc, *best[1:], W, 8, 1, 4)
+    assert bool(taken) == block
+    if block:
+        assert [tuple(int(v) for v in t) for t in tiles] == rt and order.tolist() == ro and info.makespan == finish
+        cover = {g: np.zeros((M, N), dtype=np.int32) for g, (M, K, N) in enumerate(shapes)}
+        for t in tiles:
+            cover[int(t["group"])][t["m0"]: t["m0"] + t["rows"], t["n0"]: t["n0"] + t["cols"]] += 1
+        assert all(np.all(c == 1) for c in cover.values())
+        assert info.n_split_tiles == info.n_panel_split_tiles == info.workspace_bytes == 0
+    assert B.epara_plan_launch(_desc(shapes, act), dtype, 120, 8, 1, 4)[0].narrow != 2
+    if shapes and not gated:
+        _, phases = B.epara_plan_chain([_desc(shapes, act), _desc(shapes, act)], [None, None], dtype, W, 8, 1, 4)
+        assert all(ph["info"].narrow != 2 for ph in phases)
+
+
 def test_plan_chain_picks_tables_jointly_and_writes_waits():
     """epara_plan_chain on the decode FFN (gate/up then down): both phases may take either table; whatever it
     picks, the plan is valid, the waits are those of epara_chain_waits, and no other combination finishes

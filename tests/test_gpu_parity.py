@@ -176,6 +176,44 @@ def test_last_round_panel_tiles_visited_in_parts(dtype_name="bf16"):
         assert_close(y, yref, TOL[dtype_name], "panel split K %s" % ((M, K, N),))
 
 
+@pytest.mark.parametrize("dtype_name,out_name", [("bf16", None), ("fp8", None), ("fp8", "fp8")])
+def test_block_tiles_at_the_edges_of_their_range(dtype_name, out_name):
+    """Launches planned with block tiles (128 x 128): one to four row fragments, rows just below and above a tile, columns
+    that leave a wave idle or cut a 16-byte piece short, K from one chunk through every place of the four-pair ring.
+    Integer-valued operands make every order of addition exact: bf16 outputs must be the oracle's bit for bit, twice."""
+    rng = np.random.default_rng(23)
+    k = 1 if dtype_name == "bf16" else 2
+    shapes = [(65, 16, 10), (96, 64 * k, 128), (97, 72 * k, 130), (128, 128 * k, 200), (129, 136 * k, 72), (160, 256 * k, 127), (200, 272 * k, 264),
+              (31, 384 * k, 64), (1, 520 * k, 33), (300, 768 * k, 16), (64, 1040 * k, 136), (33, 896 * k, 8)]
+    acts = ["relu", "none"] * 6
+    specs = []
+    for (M, K, N), act in zip(shapes, acts):
+        specs.append({"X": rng.integers(-4, 5, (M, K)).astype(np.float32), "W": rng.integers(-3, 4, (K, N)).astype(np.float32),
+                      "b": rng.integers(-8, 9, N).astype(np.float32), "act": act, "s_x": 0.125, "s_w": 0.25})
+    G = U.Groups(specs, dtype_name, out_dtype_name=out_name)
+    assert [tuple(int(v) for v in c)[:3] for c in G.plan.classes] == [(2**31 - 1, 128, 128)]
+    for rep in range(2):
+        for (M, K, N), y, yref in zip(shapes, G.run(), G.expected()):
+            if out_name is None:
+                assert np.array_equal(y, ref.bf16_decode(ref.bf16_encode(yref))), (dtype_name, rep, M, K, N)
+            else:
+                assert np.array_equal(y, ref.e4m3_decode(ref.e4m3_encode(yref, 1.0), 1.0)), (dtype_name, rep, M, K, N)
+    specs = [U.rand_spec(rng, M, K, N, act, bias=i % 2 == 0) for i, ((M, K, N), act) in
+             enumerate(zip(shapes, ["gelu_erf", "silu", "none", "relu", "gelu_tanh", "none"] * 2))]
+    G = U.Groups(specs, dtype_name)
+    for (M, K, N), y, yref in zip(shapes, G.run(), G.expected()):
+        assert_close(y, yref, TOL[dtype_name], "block tiles %s" % ((M, K, N),))
+
+
+@pytest.mark.parametrize("dtype_name", ["bf16", "fp8"])
+@pytest.mark.parametrize("rows,d,ffn", [([3, 40, 300], 128, 352), ([75, 130, 237], 272, 208), ([97, 1], 48, 80)])
+def test_gated_block_tiles(dtype_name, rows, d, ffn):
+    mix = make_mix(4, d=d, ffn=ffn, rows=rows)
+    staged = StagedMix(mix, dtype_name, U.DEV, s_h=[1.0] * len(rows) if dtype_name == "fp8" else None)
+    assert all([tuple(int(v) for v in c)[1] for c in p.classes] == [128] for p in staged.plans())
+    check_mix(mix, dtype_name)
+
+
 def test_identity_zero_and_ones_weights_bf16():
     rng = np.random.default_rng(12)
     X = rng.standard_normal((37, 64)).astype(np.float32)
