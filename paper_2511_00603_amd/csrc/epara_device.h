@@ -34,8 +34,6 @@ constexpr int NT = 256;                 // threads per workgroup (4 waves, one p
 constexpr int BIAS_LDS_OFFSET = 131072;  // after the operand buffers: 256 floats, the bias of a panel tile
 constexpr int LDS_BYTES = 163840;          // the whole LDS of a compute unit (one workgroup per unit)
 constexpr int RING_LDS_OFFSET = 65536;   // streaming tiles: partial sums below, the waves' activation rings above
-constexpr int F32_BM = 64, F32_BN = 64, F32_BK = 64, F32_NT = 256;
-constexpr int F32_PER = F32_BM * F32_BK / F32_NT;      // elements of X (and of W) a thread stages per K step
 
 // ------------------------------------------------------------------ small device helpers
 

@@ -1,4 +1,4 @@
-// fp32 groups of libepara: plain FMA tiles.
+// fp32 groups of libepara: fp32 matrix cores, K split over the waves of a workgroup.
 #ifndef EPARA_F32_H
 #define EPARA_F32_H
 
@@ -6,174 +6,170 @@
 
 namespace {
 
-// fp32 groups of at most 16 rows: a 16 x 64 tile with K cut into four contiguous quarters, one per
-// wave (a tile of a small model is a chain of dependent memory latencies, and this chain is four
-// times shorter).  Each wave stages its 16 x F32S_BK activations and F32S_BK x 64 weights in its own
-// part of the LDS (no barrier inside the K loop: a wave's LDS operations run in order), a lane
-// holds 4 rows x 4 columns; the four partial tiles are then added in wave order 0, 1, 2, 3, so the
-// result depends on nothing but the operands.
-constexpr int F32S_BM = 16, F32S_BN = 64, F32S_BK = 16;
+// An fp32 tile belongs to a small model: a handful of workgroups, and what a launch takes is the chain of dependent
+// memory latencies in one of them.  So a workgroup has sixteen waves and cuts K into pieces of 16 that are dealt to them
+// contiguously (16-row class: sixteen parts of K; 64-row class: eight parts for each half of the rows); a wave asks for
+// several pieces at once and the partial tiles are added in the order of K: the result depends on nothing but the
+// operands.  Operands go from memory straight into v_mfma_f32_16x16x4_f32 (products and sums in fp32): lane (i, q) loads
+// X[row i][k + 4 q .. + 3] and W[k + 4 q + e][column 4 i .. 4 i + 3] as 16-byte pieces; product e of a piece pairs the k
+// = 4 q + e of both, and the four columns of a lane belong to four accumulators, so that a lane ends with 4 rows x 4
+// consecutive columns.  Measured, three
+// launches of two MLPs (256-512-512-10, 4 and 16 rows): 37 -> 21 us a pass; one of 64 rows, 512-512-64: 71 -> 36 us (four waves that
+// staged 16 or 64 k at a time through the LDS and multiplied on the vector units).
+constexpr int F32_WAVES = 16, F32_NT = F32_WAVES * 64, F32_BN = 64;
 
-template <bool CHAIN>
-__device__ __forceinline__ void f32_small_tile(const epara_group_args& ga, const epara_tile& tl)
+// A piece of 16 k: RB blocks of 16 rows x 64 columns of one wave.
+template <int RB>
+struct f32_piece { v4f x[RB], w[4]; };
+
+struct f32_tile {
+    const EPARA_GLOBAL float* X;   // first row of the wave
+    const EPARA_GLOBAL float* W;   // first column of the tile
+    int K, N, rows, cols;          // rows: of the wave
+    bool xv, wv;                   // 16-byte pieces of X / W are aligned
+};
+
+template <int RB>
+__device__ __forceinline__ void f32_fetch(const f32_tile& t, int k0, int lane, f32_piece<RB>& p)
 {
-    __shared__ float Xq[4][F32S_BK][F32S_BM + 1];
-    __shared__ float Wq[4][F32S_BK][F32S_BN];
-    __shared__ float part[4][F32S_BM][F32S_BN];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tx = lane & 15, ty = lane >> 4;
-    const EPARA_GLOBAL float* X = as_global<float>(ga.X);
-    const EPARA_GLOBAL float* W = as_global<float>(ga.W);
-    const int K = ga.K, N = ga.N;
-    const int Kq = (K + 3) / 4;
-    const int k_begin = wave * Kq, k_end = min(K, k_begin + Kq);
-    float acc[4][4];
+    const int i = lane & 15, k = k0 + 4 * (lane >> 4);
+    const bool whole = k0 + 16 <= t.K;                           // the same for all lanes
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int b = 0; b < RB; ++b) {
+        // a row past the batch repeats the last one: it only feeds outputs that are not stored
+        const EPARA_GLOBAL float* x = t.X + static_cast<size_t>(min(16 * b + i, t.rows - 1)) * t.K + k;
+        if (whole && t.xv) p.x[b] = *reinterpret_cast<const EPARA_GLOBAL v4f*>(x);
+        else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-    float xr[4], wr[16];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {                       // X: element e = lane + 64 j -> row e / 16, k e % 16
-            const int e = lane + 64 * j, row = e >> 4, kk = e & 15;
-            xr[j] = (row < tl.rows && k0 + kk < k_end) ? X[static_cast<size_t>(tl.m0 + row) * K + k0 + kk] : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j)                        // W: row k0 + j, column lane
-            wr[j] = (k0 + j < k_end && lane < tl.cols) ? W[static_cast<size_t>(k0 + j) * N + tl.n0 + lane] : 0.f;
-    };
-    fetch(k_begin);
-    for (int k0 = k_begin; k0 < k_end; k0 += F32S_BK) {
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = lane + 64 * j;
-            Xq[wave][e & 15][e >> 4] = xr[j];
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) Wq[wave][j][lane] = wr[j];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (k0 + F32S_BK < k_end) fetch(k0 + F32S_BK);
-#pragma unroll
-        for (int kk = 0; kk < F32S_BK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = Xq[wave][kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Wq[wave][kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+            for (int e = 0; e < 4; ++e) p.x[b][e] = k + e < t.K ? x[e] : 0.f;
         }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int e = 0; e < 4; ++e) {
+        const EPARA_GLOBAL float* w = t.W + static_cast<size_t>(k + e) * t.N + 4 * i;
+        p.w[e] = v4f{0.f, 0.f, 0.f, 0.f};
+        if (t.wv) { if (k + e < t.K && 4 * i < t.cols) p.w[e] = *reinterpret_cast<const EPARA_GLOBAL v4f*>(w); }
+        else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) part[wave][ty * 4 + i][tx * 4 + j] = acc[i][j];
-    __syncthreads();
-    {
-        const int row = tid >> 4, c0 = (tid & 15) * 4;      // 16 rows x 16 column quads over 256 threads
-        EPARA_GLOBAL float* Y = as_global<float>(ga.Y);
-        with_act(ga.act, [&](auto tag) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int col = c0 + j;
-                if (row >= tl.rows || col >= tl.cols) continue;
-                const float sum = ((part[0][row][col] + part[1][row][col]) + part[2][row][col]) + part[3][row][col];
-                const float b = ga.bias ? as_global<float>(ga.bias)[tl.n0 + col] : 0.f;
-                put<CHAIN>(Y + static_cast<size_t>(tl.m0 + row) * N + tl.n0 + col,
-                           act_apply<decltype(tag)::value>(ga.scale * sum + b));
-            }
-        });
+            for (int c = 0; c < 4; ++c) if (k + e < t.K && 4 * i + c < t.cols) p.w[e][c] = w[c];
+        }
     }
-    __syncthreads();                                        // the partial tiles are free again
 }
 
-// fp32 groups: batches of more than 16 rows in 64x64 tiles, plain FMA in fp32, K ascending; smaller
-// batches in f32_small_tile.
+// AHEAD pieces of a wave's part of K are in flight while one is multiplied.
+template <int RB, int AHEAD>
+__device__ __forceinline__ void f32_multiply(const f32_tile& t, int p0, int p1, int lane, v4f (&acc)[RB][4])
+{
+    f32_piece<RB> ring[AHEAD + 1];
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a)
+        if (p0 + a < p1) f32_fetch<RB>(t, 16 * (p0 + a), lane, ring[a]);
+    for (int p = p0; p < p1; p += AHEAD + 1) {
+#pragma unroll
+        for (int a = 0; a < AHEAD + 1; ++a) {
+            if (p + a >= p1) break;
+            if (p + a + AHEAD < p1) f32_fetch<RB>(t, 16 * (p + a + AHEAD), lane, ring[(a + AHEAD) % (AHEAD + 1)]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int b = 0; b < RB; ++b)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        acc[b][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ring[a].x[b][e], ring[a].w[e][c], acc[b][c], 0, 0, 0);
+        }
+    }
+}
+
+// A tile of RB x 16 x HALVES rows; PARTS = F32_WAVES / HALVES parts of K.  At most 64 KiB of partial sums meet in the LDS at a
+// time: with eight parts of 64 rows the upper four are added to the lower four first.
+template <bool CHAIN, int RB, int HALVES>
+__device__ __forceinline__ void f32_do_tile(const epara_group_args& ga, const epara_tile& tl, v4f* lds)
+{
+    constexpr int PARTS = F32_WAVES / HALVES, ROWS = RB * 16 * HALVES;
+    constexpr int MEET = 65536 / (ROWS * F32_BN * 4) < PARTS ? 65536 / (ROWS * F32_BN * 4) : PARTS;      // parts that fit the LDS
+    static_assert(MEET == PARTS || 2 * MEET == PARTS, "parts meet in one or two steps");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = wave / HALVES, half = wave % HALVES;
+    const int i = lane & 15, q = lane >> 4;
+    const int K = ga.K, N = ga.N, row0 = half * RB * 16;
+    v4f acc[RB][4];
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[b][c] = v4f{0.f, 0.f, 0.f, 0.f};
+    const int pieces = (K + 15) >> 4;
+    // contiguous shares; products of 32 bits: a K that overflows them has more pieces than memory holds weights
+    const int p0 = static_cast<int>(static_cast<int64_t>(pieces) * part / PARTS), p1 = static_cast<int>(static_cast<int64_t>(pieces) * (part + 1) / PARTS);
+    if (row0 < tl.rows) {
+        const f32_tile t = {as_global<float>(ga.X) + static_cast<size_t>(tl.m0 + row0) * K, as_global<float>(ga.W) + tl.n0, K, N,
+                            tl.rows - row0, tl.cols, (K & 3) == 0, (N & 3) == 0};
+        f32_multiply<RB, RB == 1 ? 3 : 1>(t, p0, p1, lane, acc);
+    }
+    // quad (row, column quad) of part s at [s][row][quad]; a lane holds rows 4 q + v of each block, columns 4 i .. 4 i + 3
+    auto at = [&](int s, int row, int quad) -> v4f& { return lds[(s * ROWS + row) * 16 + quad]; };
+    auto dump = [&](int s) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) at(s, row0 + 16 * b + 4 * q + v, i) = v4f{acc[b][0][v], acc[b][1][v], acc[b][2][v], acc[b][3][v]};
+    };
+    if constexpr (MEET < PARTS) {
+        if (part >= MEET) dump(part - MEET);
+        __syncthreads();
+        if (part < MEET) {
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const v4f other = at(part, row0 + 16 * b + 4 * q + v, i);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[b][c][v] += other[c];
+                }
+        }
+        __syncthreads();
+    }
+    if (part < MEET) dump(part);
+    __syncthreads();
+    for (int u = threadIdx.x; u < ROWS * 16; u += F32_NT) {
+        const int row = u >> 4, col = (u & 15) * 4;
+        if (row >= tl.rows || col >= tl.cols) continue;
+        v4f sum = at(0, row, u & 15);
+#pragma unroll
+        for (int s = 1; s < MEET; ++s) sum += at(s, row, u & 15);
+        EPARA_GLOBAL float* y = as_global<float>(ga.Y) + static_cast<size_t>(tl.m0 + row) * N + tl.n0 + col;
+        const EPARA_GLOBAL float* bias = ga.bias ? as_global<float>(ga.bias) + tl.n0 + col : nullptr;
+        const int valid = tl.cols - col;
+        with_act(ga.act, [&](auto tag) {
+            v4f out;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float b = bias && c < valid ? bias[c] : 0.f;
+                out[c] = act_apply<decltype(tag)::value>(ga.scale * sum[c] + b);
+            }
+            if constexpr (!CHAIN) {
+                if (valid >= 4 && (N & 3) == 0) { *reinterpret_cast<EPARA_GLOBAL v4f*>(y) = out; return; }
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) if (c < valid) put<CHAIN>(y + c, out[c]);
+        });
+    }
+    __syncthreads();                                             // the partial tiles are free again
+}
+
 template <bool CHAIN>
 __device__ __forceinline__ void f32_body(const epara_group_args* __restrict__ args, const epara_tile* __restrict__ tiles,
                                          const int32_t* __restrict__ order, long n_slots, chain_ctx* chain)
 {
-    __shared__ float Xs[F32_BK][F32_BM + 1];
-    __shared__ float Ws[F32_BK][F32_BN];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    __shared__ v4f lds[65536 / 16];
     for (long s = blockIdx.x; s < n_slots; s += gridDim.x) {
         const int t = order[s];
         if (t < 0) continue;
         const epara_tile tl = tiles[t];
         if constexpr (CHAIN) chain_wait(*chain, tl.group);
         const epara_group_args ga = args[tl.group];
-        if (tl.cls == 0) {                                  // class 0 of the fp32 table: at most 16 rows
-            f32_small_tile<CHAIN>(ga, tl);
-            if constexpr (CHAIN) chain_done(*chain, tl.group);
-            continue;
-        }
-        const EPARA_GLOBAL float* X = as_global<float>(ga.X);
-        const EPARA_GLOBAL float* W = as_global<float>(ga.W);
-        EPARA_GLOBAL float* Y = as_global<float>(ga.Y);
-        const int K = ga.K, N = ga.N;
-        float acc[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-        // The K steps are software pipelined through registers: the loads of step k0 + BK are in flight
-        // while step k0 is multiplied (a tile of a small model is a chain of dependent memory
-        // latencies otherwise).  The sums still run over K in ascending order.
-        float xr[F32_PER], wr[F32_PER];
-        auto fetch = [&](int k0) {
-#pragma unroll
-            for (int j = 0; j < F32_PER; ++j) {
-                const int e = tid + F32_NT * j;
-                const int row = e / F32_BK, kk = e % F32_BK;
-                xr[j] = (row < tl.rows && k0 + kk < K) ? X[static_cast<size_t>(tl.m0 + row) * K + k0 + kk] : 0.f;
-                const int kw = e >> 6, nn = e & 63;
-                wr[j] = (k0 + kw < K && nn < tl.cols) ? W[static_cast<size_t>(k0 + kw) * N + tl.n0 + nn] : 0.f;
-            }
-        };
-        fetch(0);
-        for (int k0 = 0; k0 < K; k0 += F32_BK) {
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < F32_PER; ++j) {
-                const int e = tid + F32_NT * j;
-                Xs[e % F32_BK][e / F32_BK] = xr[j];
-                Ws[e >> 6][e & 63] = wr[j];
-            }
-            __syncthreads();
-            if (k0 + F32_BK < K) fetch(k0 + F32_BK);
-#pragma unroll
-            for (int kk = 0; kk < F32_BK; ++kk) {
-                float a[4], b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) a[i] = Xs[kk][ty * 4 + i];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) b[j] = Ws[kk][tx * 4 + j];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-            }
-        }
-        with_act(ga.act, [&](auto tag) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int row = ty * 4 + i;
-                if (row >= tl.rows) continue;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int col = tx * 4 + j;
-                    if (col >= tl.cols) continue;
-                    const float b = ga.bias ? as_global<float>(ga.bias)[tl.n0 + col] : 0.f;
-                    put<CHAIN>(Y + static_cast<size_t>(tl.m0 + row) * N + tl.n0 + col,
-                               act_apply<decltype(tag)::value>(ga.scale * acc[i][j] + b));
-                }
-            }
-        });
+        if (tl.cls == 0) f32_do_tile<CHAIN, 1, 1>(ga, tl, lds);  // class 0 of the fp32 table: at most 16 rows
+        else             f32_do_tile<CHAIN, 2, 2>(ga, tl, lds);
         if constexpr (CHAIN) chain_done(*chain, tl.group);
     }
 }

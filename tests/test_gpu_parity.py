@@ -176,6 +176,29 @@ def test_last_round_panel_tiles_visited_in_parts(dtype_name="bf16"):
         assert_close(y, yref, TOL[dtype_name], "panel split K %s" % ((M, K, N),))
 
 
+def test_fp32_tiles_at_the_edges_of_their_range():
+    """fp32 tiles: row blocks just below and above 16 and 64, K shorter than, equal to and beyond one piece per wave, rows
+    and columns whose 16-byte pieces are not aligned.  Integer-valued operands: bit for bit; real ones: 1e-5 (the sums of
+    at most 1000 products carry about sqrt(1000) 2^-24 = 2e-6)."""
+    rng = np.random.default_rng(29)
+    shapes = [(1, 1, 1), (15, 3, 3), (16, 16, 64), (16, 256, 66), (17, 17, 10), (33, 64, 63), (63, 255, 130), (64, 257, 64), (65, 1000, 128),
+              (4, 512, 512), (200, 260, 68), (48, 4, 200), (16, 270, 12)]
+    for integers in (True, False):
+        specs = []
+        for M, K, N in shapes:
+            sp = U.rand_spec(rng, M, K, N, "relu" if M % 2 else "none", bias=N != 64)
+            if integers:
+                sp["X"], sp["W"] = np.round(4 * sp["X"]), np.round(4 * sp["W"] * np.sqrt(K)).astype(np.float32)
+                sp["b"] = None if sp["b"] is None else np.round(800 * sp["b"])
+            specs.append(sp)
+        G = U.Groups(specs, "f32")
+        for (M, K, N), y, yref in zip(shapes, G.run(), G.expected()):
+            if integers:
+                assert np.array_equal(y, yref), (M, K, N)
+            else:
+                assert_close(y, yref, TOL["f32"], "fp32 %s" % ((M, K, N),))
+
+
 @pytest.mark.parametrize("dtype_name,out_name", [("bf16", None), ("fp8", None), ("fp8", "fp8")])
 def test_block_tiles_at_the_edges_of_their_range(dtype_name, out_name):
     """Launches planned with block tiles (128 x 128): one to four row fragments, rows just below and above a tile, columns
