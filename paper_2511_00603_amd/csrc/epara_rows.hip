@@ -143,31 +143,42 @@ __global__ __launch_bounds__(NT) void quantize_segments_kernel(const epara_segme
         const EPARA_GLOBAL char* src = (const EPARA_GLOBAL char*)sg.src + base;
         EPARA_GLOBAL char* dst = (EPARA_GLOBAL char*)sg.dst + base / ESZ;
         const int64_t left = sg.bytes - base;
+        // a lane takes PIECE consecutive 16-byte pieces of a row run, so that its codes leave as one 16-byte store
+        constexpr int PIECE = 16 / (16 / ESZ);                 // bf16: 2, fp32: 4
         v4i v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int64_t off = (i * NT + threadIdx.x) * 16;
+            const int64_t off = ((i / PIECE) * NT + threadIdx.x) * (16 * PIECE) + (i % PIECE) * 16;
+            v[i] = v4i{0, 0, 0, 0};
             if (off < left) v[i] = *reinterpret_cast<const EPARA_GLOBAL v4i*>(src + off);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t off = (i * NT + threadIdx.x) * 16;
+        for (int k = 0; k < 4 / PIECE; ++k) {
+            const int64_t off = (k * NT + threadIdx.x) * (16 * PIECE);
             if (off >= left) continue;
-            if constexpr (SRC == EPARA_F32) {
-                *reinterpret_cast<EPARA_GLOBAL uint32_t*>(dst + off / 4) =
-                    epara_cast::f32x4_to_e4m3(__int_as_float(v[i][0]) * inv, __int_as_float(v[i][1]) * inv, __int_as_float(v[i][2]) * inv, __int_as_float(v[i][3]) * inv);
-            } else {
-                float f[8];
+            uint32_t code[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t u = static_cast<uint32_t>(v[i][j]);
-                    f[2 * j] = __uint_as_float(u << 16) * inv;
-                    f[2 * j + 1] = __uint_as_float(u & 0xffff0000u) * inv;
+            for (int j = 0; j < 4; ++j) {                      // four codes from 4 fp32 = one piece, or 4 bf16 = half a piece
+                float f[4];
+                if constexpr (SRC == EPARA_F32) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) f[e] = __int_as_float(v[k * PIECE + j][e]) * inv;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const uint32_t u = static_cast<uint32_t>(v[k * PIECE + j / 2][2 * (j & 1) + e]);
+                        f[2 * e] = __uint_as_float(u << 16) * inv;
+                        f[2 * e + 1] = __uint_as_float(u & 0xffff0000u) * inv;
+                    }
                 }
-                v2u pk;
-                pk[0] = epara_cast::f32x4_to_e4m3(f[0], f[1], f[2], f[3]);
-                pk[1] = epara_cast::f32x4_to_e4m3(f[4], f[5], f[6], f[7]);
-                *reinterpret_cast<EPARA_GLOBAL v2u*>(dst + off / 2) = pk;
+                code[j] = epara_cast::f32x4_to_e4m3(f[0], f[1], f[2], f[3]);
+            }
+            EPARA_GLOBAL char* out = dst + off / ESZ;
+            if (off + 16 * PIECE <= left) *reinterpret_cast<EPARA_GLOBAL v4i*>(out) = v4i{static_cast<int>(code[0]), static_cast<int>(code[1]), static_cast<int>(code[2]), static_cast<int>(code[3])};
+            else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)                    // the end of a run that is no multiple of 16 codes
+                    if (off + j * (4 * ESZ) < left) reinterpret_cast<EPARA_GLOBAL uint32_t*>(out)[j] = code[j];
             }
         }
     }
