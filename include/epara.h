@@ -356,12 +356,14 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 #define EPARA_COST_PANEL 2040
 #define EPARA_COST_PARTIAL 24
 
-/* Block tiles.  A launch whose panel tiles do not fill the chip, or leave a nearly empty last round, can be cut into
- * tiles of a quarter of the size instead: 128 rows x 128 columns (EPARA_ACT_SWIGLU: 64 hidden columns), two workgroups
- * per compute unit, for batches of every size (the block table of epara_kernel_classes; a panel class of
- * EPARA_BLOCK_ROWS rows always means block tiles).  The visit order still holds W lists, one per unit: the grid is 2 W, workgroup
- * b takes the entries 0, 2, 4, .. of list b and workgroup b + W the entries 1, 3, 5, ...  In a tile of f = ceil(rows / 32) row fragments that shares its
- * weight columns with the s = ceil(M / 128) row tiles of its group, one K costs
+/* Block tiles.  A launch whose panel tiles do not fill the chip, or leave a nearly empty last round, can cut its batches of
+ * more than 64 rows into tiles of a quarter of the size instead: 128 rows x 128 columns (EPARA_ACT_SWIGLU: 64 hidden
+ * columns), two workgroups per compute unit (the block table of epara_kernel_classes; a panel class of EPARA_BLOCK_ROWS rows always
+ * means block tiles).  Sums are formed as in panel tiles, bit for bit.  The visit order still holds W lists, one per unit: the
+ * grid is 2 W, workgroup b takes the block tiles among the entries 0, 2, 4, .. of list b, workgroup b + W those among the entries
+ * 1, 3, 5, ...  Streaming tiles of the launch run before them in a kernel of their own (grid W, whole lists) and are
+ * scheduled on level workgroups.  In a block tile of f = ceil(rows / 32) row fragments that shares its weight columns
+ * with the s = ceil(M / 128) row tiles of its group, one K costs
  *     max(EPARA_COST_BLOCK_STREAM / s + EPARA_COST_BLOCK_STREAM_PER_32 * f, EPARA_COST_BLOCK_PER_32 * f)
  * of a unit's time (the first where weights come from HBM, the second where the batch is tall), a tile another
  * EPARA_COST_BLOCK_START.
@@ -372,13 +374,13 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * per unit hide from each other. */
 #define EPARA_TABLE_BLOCK 2               /* `narrow` of the block table */
 #define EPARA_BLOCK_ROWS 128
-#define EPARA_BLOCK_MIN_M 64              /* launches of batches up to this keep the streaming classes */
 #define EPARA_BLOCK_MIN_WORKGROUPS 128    /* smaller grids leave units free, where workgroups do not pair up */
 #define EPARA_COST_BLOCK_STREAM 1000
 #define EPARA_COST_BLOCK_STREAM_PER_32 50
 #define EPARA_COST_BLOCK_PER_32 165
 #define EPARA_COST_BLOCK_START 40000
 #define EPARA_COST_PANEL_START 600000
+#define EPARA_COST_KERNEL 400000          /* a second kernel: about 5 us */
 
 /* Splitting K.  A streaming tile of a class with BM >= 32 streams its weights while re-reading BM activation
  * rows per weight column, which is cheapest with wide tiles; wide tiles of a long K are too coarse to balance,
@@ -507,8 +509,9 @@ typedef struct {
 /* The whole planning decision of one launch (Sec. 3.1: the parallel mode of each task): picks the class
  * table -- the wide one, or the narrow one when some batch has more than 32 rows and the narrow
  * table's schedule has the smaller makespan under the cost model (ties: wide); or the block table ("Block tiles"), for
- * bf16 / fp8 launches with a batch of more than EPARA_BLOCK_MIN_M rows and n_workgroups >= EPARA_BLOCK_MIN_WORKGROUPS, when
- * its makespan T is below U - U / 15, U = the largest load of a workgroup in the order of the other choice with
+ * bf16 / fp8 launches with a batch of more than 64 rows and n_workgroups >= EPARA_BLOCK_MIN_WORKGROUPS, when its makespan T
+ * (the largest load of block tiles, plus the largest load of streaming tiles and EPARA_COST_KERNEL if there are any) is
+ * below U - U / 15, U = the largest load of a workgroup in the order of the other choice with
  * EPARA_COST_PANEL_START added to every visit to a panel tile -- then plans
  * (epara_plan_groups) and schedules (epara_schedule_tiles) with it.  The groups must be all
  * EPARA_ACT_SWIGLU or none (ERR_DTYPE).  (A chain, epara_plan_chain with more than one phase, has no block tiles.)  *plan is always written (sizes included); tiles / order are
@@ -563,7 +566,8 @@ int32_t epara_chain_waits(const epara_tile* producer_tiles, int64_t n_producer_t
  * bf16 / fp8 have three tables: the wide one (narrow = 0) gives batches of 33..64 rows tiles of 128
  * (gated: 64) columns, which halves the activation re-reads; the narrow one (narrow = 1) gives
  * them 64 (gated: 32) columns, for launches with too few columns to keep every workgroup busy
- * with wide tiles.  narrow = EPARA_TABLE_BLOCK: block tiles (see there) for every batch.  A launch may use any of them
+ * with wide tiles.  narrow = EPARA_TABLE_BLOCK: the narrow
+ * table with block tiles (see there) instead of panel tiles.  A launch may use any of them
  * (a chain only the first two).  fp32: batches of up to 16 rows in 16 x 64 tiles,
  * larger ones in 64 x 64 tiles; K is cut into pieces of 16 that are dealt contiguously to sixteen (64 rows: eight) partial
  * sums, which are added in a fixed order. */

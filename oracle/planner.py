@@ -408,7 +408,9 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
                     each = cost // parts + 24 * bm * tile[4] * (2 if gated else 1)
                     stream += [(-each, p, t, j, order_entry(t, j, parts)) for j in range(parts)]
     stream.sort()
-    heap = [(load[b], b) for b in range(W)]
+    # next to block tiles (a panel class of 128 rows) the streaming tiles run in a kernel of their own, on level workgroups
+    apart = len(phases) == 1 and any(cl[1] == 128 for cl in phases[0][1][phases[0][2]:])
+    heap = [(0 if apart else load[b], b) for b in range(W)]
     heapq.heapify(heap)
     for negcost, p, _, _, entry in stream:
         ld, b = heapq.heappop(heap)
@@ -429,34 +431,37 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
 def block_choice(groups, block_classes, other_classes, other_n_stream, other_tiles, other_order, n_workgroups, n_xcd, panel_m, panel_n):
     """Whether a single bf16 / fp8 launch takes the block table instead of the best of the other tables (class table, tiles
     and visit order of which are given) -> (taken, tiles, order, finish).  Considered when a batch has more than 64 rows
-    and W >= 128.  finish = the largest load of a list of the block tiles' order; taken if that is below `other` - other // 15 with `other` = the largest load of
+    and W >= 128.  finish = the largest load of
+    a list in block tiles, plus the largest load in streaming tiles and 400000 if there are any; taken if that is below `other` - other // 15 with `other` = the largest load of
     a workgroup in the other order where every visit to a panel tile costs 600000 more."""
     W = n_workgroups
     if max((g[0] for g in groups), default=0) <= 64 or W < 128:
         return False, None, None, None
-    loads = [0] * W
-    for slot, e in enumerate(other_order):
-        if e < 0:
-            continue
-        t, _, parts = order_decode(e)
-        tile = other_tiles[t]
-        g, cl = groups[tile[0]], other_classes[tile[5]]
-        if tile[5] >= other_n_stream:
-            cost = panel_cost(g[0], g[1], cl, tile[3])
-            loads[slot % W] += (cost if parts == 1 else cost // parts + 1020000) + 600000
-        else:
-            wide = tile[4] * (2 if len(g) > 3 and g[3] else 1)
-            cost = g[1] * (6 * wide + (2 * cl[1] if cl[1] >= 32 else 0))
-            loads[slot % W] += cost if parts == 1 else cost // parts + 24 * cl[1] * wide
-    other = max(loads)
+
+    def loads(classes, n_stream, tiles, order, start):
+        panel, stream = [0] * W, [0] * W
+        for slot, e in enumerate(order):
+            if e < 0:
+                continue
+            t, _, parts = order_decode(e)
+            tile = tiles[t]
+            g, cl = groups[tile[0]], classes[tile[5]]
+            if tile[5] >= n_stream:
+                cost = panel_cost(g[0], g[1], cl, tile[3])
+                panel[slot % W] += (cost if parts == 1 else cost // parts + 1020000) + start
+            else:
+                wide = tile[4] * (2 if len(g) > 3 and g[3] else 1)
+                cost = g[1] * (6 * wide + (2 * cl[1] if cl[1] >= 32 else 0))
+                stream[slot % W] += cost if parts == 1 else cost // parts + 24 * cl[1] * wide
+        return panel, stream
+
+    panel, stream = loads(other_classes, other_n_stream, other_tiles, other_order, 600000)
+    other = max(a + b for a, b in zip(panel, stream))
+    n_stream = len(block_classes) - 1
     _, _, _, tiles = plan_groups([g[:3] for g in groups], block_classes)
-    order = schedule_tiles(groups, block_classes, 0, tiles, W, n_xcd, panel_m, panel_n)
-    loads = [0] * W
-    for slot, t in enumerate(order):
-        if t >= 0:
-            g = groups[tiles[t][0]]
-            loads[slot % W] += panel_cost(g[0], g[1], block_classes[0], tiles[t][3])
-    finish = max(loads)
+    order = schedule_tiles(groups, block_classes, n_stream, tiles, W, n_xcd, panel_m, panel_n)
+    panel, stream = loads(block_classes, n_stream, tiles, order, 0)
+    finish = max(panel) + (max(stream) + 400000 if any(t[5] < n_stream for t in tiles) else 0)
     return finish < other - other // 15, tiles, order, finish
 
 

@@ -397,14 +397,20 @@ def epara_plan_launch(groups, in_dtype, n_workgroups, n_xcd=8, panel_m=1, panel_
     G = len(groups)
     gp = _ptr(groups) if G else None
     info = LaunchPlanInfo()
-    _check(lib().epara_plan_launch(gp, G, int(in_dtype), n_workgroups, n_xcd, panel_m, panel_n, None, None, None, None, 0, None, 0,
-                                   None, ctypes.addressof(info)), "epara_plan_launch")
-    row_off, x_off, y_off = (np.zeros(G + 1, dtype=np.int64) for _ in range(3))
-    tiles, order = np.zeros(info.n_tiles, dtype=TILE), np.zeros(info.n_slots, dtype=np.int32)
+    row_off, x_off, y_off = (np.empty(G + 1, dtype=np.int64) for _ in range(3))
     split_base = np.full(G, -1, dtype=np.int32)
-    _check(lib().epara_plan_launch(gp, G, int(in_dtype), n_workgroups, n_xcd, panel_m, panel_n, _ptr(row_off), _ptr(x_off), _ptr(y_off),
-                                   _ptr(tiles) if len(tiles) else None, len(tiles), _ptr(order) if len(order) else None, len(order),
-                                   _ptr(split_base) if G else None, ctypes.addressof(info)), "epara_plan_launch")
+    # The sizes of a plan are known when it is made, so it is made into arrays that hold what most launches need (some
+    # thousand tiles, lists of sixteen) and once more, into arrays of the right size, where that was not enough.
+    n_tiles, n_slots = 4096, 16 * n_workgroups
+    while True:
+        tiles, order = np.empty(n_tiles, dtype=TILE), np.empty(n_slots, dtype=np.int32)
+        status = lib().epara_plan_launch(gp, G, int(in_dtype), n_workgroups, n_xcd, panel_m, panel_n, _ptr(row_off), _ptr(x_off), _ptr(y_off),
+                                         _ptr(tiles), n_tiles, _ptr(order), n_slots, _ptr(split_base) if G else None, ctypes.addressof(info))
+        if status != EPARA_ERR_CAPACITY or (info.n_tiles <= n_tiles and info.n_slots <= n_slots):
+            break
+        n_tiles, n_slots = max(n_tiles, info.n_tiles), max(n_slots, info.n_slots)
+    _check(status, "epara_plan_launch")
+    tiles, order = tiles[: info.n_tiles].copy(), order[: info.n_slots].copy()
     return info, row_off, x_off, y_off, tiles, order, split_base
 
 

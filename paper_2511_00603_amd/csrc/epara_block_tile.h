@@ -295,6 +295,7 @@ __global__ __launch_bounds__(NT, 2) void grouped_block_kernel(const epara_group_
         const int t = order[s];
         if (t < 0) continue;
         const epara_tile tl = tiles[order_tile(t)];
+        if (tl.cls < N_STREAM_CLASSES) continue;                 // the streaming tiles of the launch have a kernel of their own
         const epara_group_args ga = args[tl.group];
         const int fm = (tl.rows + 31) >> 5;
         if (fm > 3)       block_tile<DT, GATED, 4>(ga, tl, out_dtype, lds);

@@ -88,6 +88,7 @@ __device__ __forceinline__ void grouped_body(const epara_group_args* __restrict_
             tl = tiles[order_tile(t)];
         }
         nx.known = false;
+        if constexpr (!CHAIN && !PANEL_ONLY) { if (narrow == EPARA_STREAM_TILES_ONLY && tl.cls >= N_STREAM_CLASSES) { s += stride; continue; } }
         if constexpr (CHAIN) chain_wait(*chain, tl.group);
         if constexpr (HAS_SPLIT) { if (pend.count >= 63) split_flush<DT, GATED, PANEL_ONLY>(args, tiles, out_dtype, narrow, lds, sp, pend); }
         if constexpr (!PANEL_ONLY) {

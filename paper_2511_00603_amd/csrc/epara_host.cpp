@@ -530,8 +530,41 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
     return EPARA_OK;
 }
 
-int32_t epara_schedule_chain(epara_phase_schedule* phases, int32_t n_phases,
-                             int32_t n_workgroups, int32_t n_xcd, int32_t panel_m, int32_t panel_n)
+namespace {
+
+// Workgroups by (load, index): the smallest on top, costs added to it.
+class least_loaded {
+public:
+    least_loaded(int64_t n, const int64_t* load)                 // load: null = all level
+    {
+        heap_.reserve(static_cast<size_t>(n));
+        for (int64_t i = 0; i < n; ++i) heap_.push_back({load ? load[i] : 0, i});
+        std::make_heap(heap_.begin(), heap_.end(), std::greater<std::pair<int64_t, int64_t>>());
+    }
+    int64_t top() const { return heap_[0].second; }
+    void add_to_top(int64_t cost)                                // back into place with one walk down
+    {
+        std::pair<int64_t, int64_t> moved = heap_[0];
+        moved.first += cost;
+        size_t i = 0;
+        for (const size_t n = heap_.size();;) {
+            size_t child = 2 * i + 1;
+            if (child >= n) break;
+            if (child + 1 < n && heap_[child + 1] < heap_[child]) ++child;
+            if (!(heap_[child] < moved)) break;
+            heap_[i] = heap_[child];
+            i = child;
+        }
+        heap_[i] = moved;
+    }
+private:
+    std::vector<std::pair<int64_t, int64_t>> heap_;
+};
+
+// epara_schedule_chain; keep (n_phases vectors, or null): receives the orders whatever their size, so that a planner that
+// does not know the size yet schedules once.
+int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workgroups, int32_t n_xcd, int32_t panel_m, int32_t panel_n,
+                 std::vector<int32_t>* keep)
 {
     if (n_phases < 0) return EPARA_ERR_SHAPE;
     if (n_phases > 0 && !phases) return EPARA_ERR_NULL;
@@ -567,16 +600,21 @@ int32_t epara_schedule_chain(epara_phase_schedule* phases, int32_t n_phases,
         if (expect != ph.n_tiles) return EPARA_ERR_SHAPE;
     }
 
-    std::vector<std::vector<std::vector<int32_t>>> lists(static_cast<size_t>(n_phases),
-                                                          std::vector<std::vector<int32_t>>(static_cast<size_t>(W)));
+    // what goes to which workgroup, in the order in which a workgroup visits it
+    struct visit { int32_t workgroup, entry; };
+    std::vector<std::vector<visit>> visits(static_cast<size_t>(n_phases));
     std::vector<int64_t> load(static_cast<size_t>(W), 0);
 
     // 1. panel tiles, phase after phase, each to the least loaded workgroup; among equally loaded ones the
     // die-major rank decides (rank r = workgroup (r mod per_die) * X + r div per_die), so that tiles of equal
     // cost go round robin and the per_die tiles that run together on one die are consecutive in the sequence
-    typedef std::pair<int64_t, int64_t> ranked;                 // (load, rank): smallest first
-    std::priority_queue<ranked, std::vector<ranked>, std::greater<ranked>> panel_heap;
-    for (int64_t r = 0; r < W; ++r) panel_heap.push({0, r});
+    least_loaded ranks(W, nullptr);
+    auto to_panel_workgroup = [&](int32_t p, int32_t entry, int64_t cost) {
+        const int64_t r = ranks.top(), b = (r % per_die) * X + r / per_die;
+        visits[p].push_back({static_cast<int32_t>(b), entry});
+        load[b] += cost;
+        ranks.add_to_top(cost);
+    };
     std::vector<int32_t> class_order, members;
     // a single launch of equal panel tiles may visit the tiles of its last round in parts of K
     int32_t panel_parts = 1, panel_more = 0;
@@ -584,6 +622,7 @@ int32_t epara_schedule_chain(epara_phase_schedule* phases, int32_t n_phases,
                                                                  phases[0].n_stream_classes, W, &panel_parts, &panel_more) : 0;
     for (int32_t p = 0; p < n_phases; ++p) {
         const epara_phase_schedule& ph = phases[p];
+        visits[p].reserve(static_cast<size_t>(ph.n_tiles));
         class_order.clear();
         for (int32_t c = ph.n_stream_classes; c < ph.n_classes; ++c) class_order.push_back(c);
         std::stable_sort(class_order.begin(), class_order.end(), [&](int32_t a, int32_t b) {
@@ -606,12 +645,7 @@ int32_t epara_schedule_chain(epara_phase_schedule* phases, int32_t n_phases,
                             for (int64_t tm = pm; tm < std::min<int64_t>(pm + panel_m, TM); ++tm) {
                                 const int64_t tile = first[p][g] + tm * TN + tn;
                                 if (tile >= ph.n_tiles - n_panel_split) continue;      // visited in parts, after the whole tiles
-                                const ranked top = panel_heap.top();
-                                panel_heap.pop();
-                                const int64_t x = top.second / per_die, i = top.second % per_die, b = i * X + x;
-                                lists[p][b].push_back(static_cast<int32_t>(tile));
-                                load[b] += panel_cost(ph.groups[g], ph.classes[c], ph.groups[g].M - tm * BM);
-                                panel_heap.push({load[b], top.second});
+                                to_panel_workgroup(p, static_cast<int32_t>(tile), panel_cost(ph.groups[g], ph.classes[c], ph.groups[g].M - tm * BM));
                             }
             }
         }
@@ -622,20 +656,22 @@ int32_t epara_schedule_chain(epara_phase_schedule* phases, int32_t n_phases,
         for (int64_t tile = ph.n_tiles - n_panel_split; tile < ph.n_tiles; ++tile) {
             const int32_t P = panel_parts + (tile >= ph.n_tiles - panel_more ? 1 : 0);       // the last panel_more tiles: one part more
             const int64_t each = static_cast<int64_t>(EPARA_COST_PANEL) * ph.groups[ph.tiles[tile].group].K / P + EPARA_COST_PANEL_PARTIAL;
-            for (int32_t j = 0; j < P; ++j) {
-                const ranked top = panel_heap.top();
-                panel_heap.pop();
-                const int64_t x = top.second / per_die, i = top.second % per_die, b = i * X + x;
-                lists[0][b].push_back(EPARA_ORDER_ENTRY(static_cast<int32_t>(tile), j, P));
-                load[b] += each;
-                panel_heap.push({load[b], top.second});
-            }
+            for (int32_t j = 0; j < P; ++j) to_panel_workgroup(0, EPARA_ORDER_ENTRY(static_cast<int32_t>(tile), j, P), each);
         }
     }
 
-    // 2. streaming tiles of every phase together, longest first onto the least loaded workgroup
-    struct item { int64_t cost; int32_t phase; int32_t tile; };
-    std::vector<item> stream;
+    // 2. streaming tiles of every phase together, longest first onto the least loaded workgroup.  A group has at most two
+    // different costs (its last column of tiles may be narrower), so equal costs are gathered instead of sorting items.
+    struct bucket { int64_t cost; std::vector<std::pair<int32_t, int32_t>> items; };       // (phase, entry), in the order of ties
+    std::vector<bucket> buckets;
+    size_t last = 0;
+    auto bucket_of = [&](int64_t cost) -> bucket& {
+        if (last < buckets.size() && buckets[last].cost == cost) return buckets[last];
+        for (last = 0; last < buckets.size(); ++last)
+            if (buckets[last].cost == cost) return buckets[last];
+        buckets.push_back({cost, {}});
+        return buckets[last];
+    };
     for (int32_t p = 0; p < n_phases; ++p) {
         const epara_phase_schedule& ph = phases[p];
         for (int64_t t = 0; t < ph.n_tiles; ++t)
@@ -644,37 +680,57 @@ int32_t epara_schedule_chain(epara_phase_schedule* phases, int32_t n_phases,
                 const epara_tile_class& c = ph.classes[ph.tiles[t].cls];
                 const int64_t cost = tile_cost(d, ph.tiles[t], ph.classes, ph.n_stream_classes);
                 const int32_t parts = n_phases == 1 ? split_parts(d, c) : 1;       // the phases of a chain are not split
-                if (parts == 1) { stream.push_back({cost, p, static_cast<int32_t>(t)}); continue; }
+                if (parts == 1) { bucket_of(cost).items.push_back({p, static_cast<int32_t>(t)}); continue; }
                 if (ph.n_tiles > 0xFFFFFF) return EPARA_ERR_SHAPE;
-                const int64_t each = visit_cost(cost, parts, d, ph.tiles[t], c);
-                for (int32_t j = 0; j < parts; ++j) stream.push_back({each, p, EPARA_ORDER_ENTRY(static_cast<int32_t>(t), j, parts)});
+                bucket& bk = bucket_of(visit_cost(cost, parts, d, ph.tiles[t], c));
+                for (int32_t j = 0; j < parts; ++j) bk.items.push_back({p, EPARA_ORDER_ENTRY(static_cast<int32_t>(t), j, parts)});
             }
     }
-    std::stable_sort(stream.begin(), stream.end(), [](const item& a, const item& b) { return a.cost > b.cost; });
-    typedef std::pair<int64_t, int32_t> entry;                  // (load, workgroup): smallest first
-    std::priority_queue<entry, std::vector<entry>, std::greater<entry>> heap;
-    for (int32_t b = 0; b < W; ++b) heap.push({load[b], b});
-    for (const item& it : stream) {
-        entry e = heap.top();
-        heap.pop();
-        lists[it.phase][e.second].push_back(it.tile);
-        heap.push({e.first + it.cost, e.second});
+    if (!buckets.empty()) {
+        std::sort(buckets.begin(), buckets.end(), [](const bucket& a, const bucket& b) { return a.cost > b.cost; });
+        // next to block tiles they run in a kernel of their own, on level workgroups
+        bool apart = false;
+        if (n_phases == 1)
+            for (int32_t c = phases[0].n_stream_classes; c < phases[0].n_classes; ++c) apart = apart || phases[0].classes[c].BM == EPARA_BLOCK_ROWS;
+        least_loaded bins(W, apart ? nullptr : load.data());
+        for (const bucket& bk : buckets)
+            for (const auto& it : bk.items) {
+                visits[it.first].push_back({static_cast<int32_t>(bins.top()), it.second});
+                bins.add_to_top(bk.cost);
+            }
     }
 
     int32_t status = EPARA_OK;
+    std::vector<int64_t> count(static_cast<size_t>(W));
     for (int32_t p = 0; p < n_phases; ++p) {
         epara_phase_schedule& ph = phases[p];
-        size_t longest = 0, total = 0;
-        for (const auto& v : lists[p]) { longest = std::max(longest, v.size()); total += v.size(); }
-        if (static_cast<int64_t>(total) < ph.n_tiles) return EPARA_ERR_SHAPE;
-        ph.n_slots = static_cast<int64_t>(longest) * W;
+        if (static_cast<int64_t>(visits[p].size()) < ph.n_tiles) return EPARA_ERR_SHAPE;
+        std::fill(count.begin(), count.end(), 0);
+        int64_t longest = 0;
+        for (const visit& v : visits[p]) longest = std::max(longest, ++count[v.workgroup]);
+        ph.n_slots = longest * W;
+        auto write = [&](int32_t* order) {
+            std::fill(order, order + ph.n_slots, -1);
+            std::fill(count.begin(), count.end(), 0);
+            for (const visit& v : visits[p]) order[W * count[v.workgroup]++ + v.workgroup] = v.entry;
+        };
+        if (keep) {
+            keep[p].resize(static_cast<size_t>(ph.n_slots));
+            write(keep[p].data());
+        }
         if (!ph.order) continue;
         if (ph.order_cap < ph.n_slots) { status = EPARA_ERR_CAPACITY; continue; }
-        std::fill(ph.order, ph.order + ph.n_slots, -1);
-        for (int64_t b = 0; b < W; ++b)
-            for (size_t j = 0; j < lists[p][b].size(); ++j) ph.order[static_cast<int64_t>(j) * W + b] = lists[p][b][j];
+        write(ph.order);
     }
     return status;
+}
+
+}  // namespace
+
+int32_t epara_schedule_chain(epara_phase_schedule* phases, int32_t n_phases,
+                             int32_t n_workgroups, int32_t n_xcd, int32_t panel_m, int32_t panel_n)
+{
+    return schedule(phases, n_phases, n_workgroups, n_xcd, panel_m, panel_n, nullptr);
 }
 
 int32_t epara_schedule_tiles(const epara_group_desc* groups, int32_t G,
@@ -737,7 +793,7 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
     *take = false;
     int32_t max_M = 0;
     for (int32_t g = 0; g < G; ++g) max_M = std::max(max_M, groups[g].M);
-    if (in_dtype == EPARA_F32 || max_M <= EPARA_BLOCK_MIN_M || W < EPARA_BLOCK_MIN_WORKGROUPS) return EPARA_OK;
+    if (in_dtype == EPARA_F32 || max_M <= 64 || W < EPARA_BLOCK_MIN_WORKGROUPS) return EPARA_OK;
     std::vector<int64_t> load(static_cast<size_t>(W), 0);
     for (size_t i = 0; i < best_order.size(); ++i)
         if (best_order[i] >= 0) {
@@ -753,14 +809,19 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
     ph.groups = groups; ph.classes = o.classes; ph.tiles = o.tiles.data();
     ph.n_tiles = static_cast<int64_t>(o.tiles.size());
     ph.G = G; ph.n_classes = o.n_classes; ph.n_stream_classes = o.n_stream;
-    for (int pass = 0; pass < 2; ++pass) {
-        if (int32_t st = epara_schedule_chain(&ph, 1, static_cast<int32_t>(W), n_xcd, panel_m, panel_n)) return st;
-        if (pass == 0) { order.assign(static_cast<size_t>(ph.n_slots), -1); ph.order = order.data(); ph.order_cap = ph.n_slots; }
-    }
+    if (int32_t st = schedule(&ph, 1, static_cast<int32_t>(W), n_xcd, panel_m, panel_n, &order)) return st;
     load.assign(static_cast<size_t>(W), 0);
+    std::vector<int64_t> stream(static_cast<size_t>(W), 0);
+    bool any_stream = false;
     for (size_t i = 0; i < order.size(); ++i)
-        if (order[i] >= 0) load[i % W] += tile_cost(groups[o.tiles[order[i]].group], o.tiles[order[i]], o.classes, o.n_stream);
-    *finish = *std::max_element(load.begin(), load.end());
+        if (order[i] >= 0) {
+            const epara_tile& tl = o.tiles[EPARA_ORDER_TILE(order[i])];
+            const int64_t cost = visit_cost(tile_cost(groups[tl.group], tl, o.classes, o.n_stream), (order[i] >> 28) + 1, groups[tl.group], tl, o.classes[tl.cls]);
+            if (tl.cls >= o.n_stream) load[i % W] += cost;
+            else { stream[i % W] += cost; any_stream = true; }
+        }
+    *finish = *std::max_element(load.begin(), load.end()) +
+              (any_stream ? *std::max_element(stream.begin(), stream.end()) + EPARA_COST_KERNEL : 0);
     *take = *finish < other - other / 15;
     return EPARA_OK;
 }
@@ -801,22 +862,15 @@ int32_t epara_plan_chain(epara_chain_plan_phase* phases, int32_t n_phases, int32
     for (;;) {
         std::vector<epara_phase_schedule> sched(static_cast<size_t>(n_phases));
         std::vector<std::vector<int32_t>> order(static_cast<size_t>(n_phases));
-        for (int pass = 0; pass < 2; ++pass) {
-            for (int32_t p = 0; p < n_phases; ++p) {
-                const phase_option& o = options[p][pick[p]];
-                epara_phase_schedule& ph = sched[p];
-                if (pass == 0) {
-                    std::memset(&ph, 0, sizeof ph);
-                    ph.groups = phases[p].groups; ph.classes = o.classes; ph.tiles = o.tiles.data();
-                    ph.n_tiles = static_cast<int64_t>(o.tiles.size());
-                    ph.G = phases[p].G; ph.n_classes = o.n_classes; ph.n_stream_classes = o.n_stream;
-                } else {
-                    order[p].assign(static_cast<size_t>(ph.n_slots), -1);
-                    ph.order = order[p].data(); ph.order_cap = ph.n_slots;
-                }
-            }
-            if (int32_t st = epara_schedule_chain(sched.data(), n_phases, n_workgroups, n_xcd, panel_m, panel_n)) return st;
+        for (int32_t p = 0; p < n_phases; ++p) {
+            const phase_option& o = options[p][pick[p]];
+            epara_phase_schedule& ph = sched[p];
+            std::memset(&ph, 0, sizeof ph);
+            ph.groups = phases[p].groups; ph.classes = o.classes; ph.tiles = o.tiles.data();
+            ph.n_tiles = static_cast<int64_t>(o.tiles.size());
+            ph.G = phases[p].G; ph.n_classes = o.n_classes; ph.n_stream_classes = o.n_stream;
         }
+        if (int32_t st = schedule(sched.data(), n_phases, n_workgroups, n_xcd, panel_m, panel_n, order.data())) return st;
         // replay under the cost model, waits included
         std::vector<int64_t> clock(static_cast<size_t>(W), 0), ready_prev;
         for (int32_t p = 0; p < n_phases; ++p) {
@@ -1025,15 +1079,6 @@ int32_t epara_kernel_classes(int32_t in_dtype, int32_t gated, int32_t narrow,
         table[n++] = {16, 16, 64, 0};       // K split over the four waves of a workgroup
         table[n++] = {INT32_MAX, 64, 64, 0};
     } else if (in_dtype == EPARA_BF16 || in_dtype == EPARA_FP8_E4M3) {
-        if (narrow == EPARA_TABLE_BLOCK) {
-            table[n++] = {INT32_MAX, EPARA_BLOCK_ROWS, gated ? 64 : 128, 0};
-            *n_classes = n;
-            *n_stream_classes = 0;
-            if (!classes) return EPARA_OK;
-            if (cap < n) return EPARA_ERR_CAPACITY;
-            classes[0] = table[0];
-            return EPARA_OK;
-        }
         // weight-streaming classes: the whole batch (1, 2 or 4 blocks of 16 rows) against 2, 4 or 8
         // weight column blocks, so that activations re-read per weight byte stay constant
         const int32_t split_K = in_dtype == EPARA_BF16 ? EPARA_SPLIT_K_BF16 : 0;   // where two visits pay (measured)
@@ -1041,7 +1086,8 @@ int32_t epara_kernel_classes(int32_t in_dtype, int32_t gated, int32_t narrow,
         table[n++] = {32, 32, gated ? 32 : 64, split_K};
         table[n++] = {64, 64, (gated ? 64 : 128) >> (narrow ? 1 : 0), split_K};
         ns = 3;
-        table[n++] = {INT32_MAX, 256, gated ? 128 : 256, (gated || in_dtype != EPARA_BF16) ? 0 : EPARA_PANEL_SPLIT_K};  // matrix-core class
+        if (narrow == EPARA_TABLE_BLOCK) table[n++] = {INT32_MAX, EPARA_BLOCK_ROWS, gated ? 64 : 128, 0};
+        else table[n++] = {INT32_MAX, 256, gated ? 128 : 256, (gated || in_dtype != EPARA_BF16) ? 0 : EPARA_PANEL_SPLIT_K};  // matrix-core class
     } else {
         return EPARA_ERR_DTYPE;
     }

@@ -10,6 +10,9 @@
 
 #define EPARA_HIDDEN __attribute__((visibility("hidden")))
 
+// `narrow` of a grouped kernel: 0 / 1, or this: the streaming tiles of the narrow table, tiles of other classes are passed over.
+#define EPARA_STREAM_TILES_ONLY 3
+
 struct epara_chain_scalars {
     long n_slots[EPARA_MAX_CHAIN_PHASES];
     int out_dtype[EPARA_MAX_CHAIN_PHASES], narrow[EPARA_MAX_CHAIN_PHASES], counter_base[EPARA_MAX_CHAIN_PHASES];

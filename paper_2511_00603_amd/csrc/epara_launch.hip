@@ -43,7 +43,43 @@ int32_t check_tiles(const epara_launch* L, int32_t in_dtype, int narrow)
     return EPARA_OK;
 }
 
-int32_t validate_launch(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int* narrow_out = nullptr)
+// Split tiles: the groups' slots and the counts must be the layout's, and the workspace must hold them.
+int32_t check_split(const epara_launch* L, int32_t in_dtype, int narrow)
+{
+    if (L->n_split_tiles < 0 || L->n_panel_split_tiles < 0) return EPARA_ERR_SHAPE;
+    if (L->n_split_tiles == 0 && L->n_panel_split_tiles == 0) return EPARA_OK;
+    if (in_dtype == EPARA_F32) return EPARA_ERR_DTYPE;
+    int gated = 0;
+    for (int32_t g = 0; g < L->G; ++g)
+        if (L->h_args[g].M > 0 && L->h_args[g].act == EPARA_ACT_SWIGLU) gated = 1;
+    epara_tile_class cls[4];
+    int32_t ncls = 0, nstream = 0, n_split = 0, n_panel = 0, parts = 1, more = 0;
+    int64_t bytes = 0;
+    epara_kernel_classes(in_dtype, gated, narrow, cls, 4, &ncls, &nstream);
+    std::vector<epara_group_desc> d(static_cast<size_t>(L->G));
+    std::vector<int32_t> base(static_cast<size_t>(L->G));
+    for (int32_t g = 0; g < L->G; ++g) d[g] = {L->h_args[g].M, L->h_args[g].K, L->h_args[g].N, L->h_args[g].act, 0, 0};
+    if (int32_t st = epara_split_layout(d.data(), L->G, cls, ncls, nstream, base.data(), &n_split, &bytes)) return st;
+    if (int32_t st = epara_panel_split(d.data(), L->G, cls, ncls, nstream, L->n_workgroups, &n_panel, &parts, &more)) return st;
+    if (n_split != L->n_split_tiles || n_panel != L->n_panel_split_tiles) return EPARA_ERR_SHAPE;
+    for (int32_t g = 0; g < L->G; ++g)
+        if (base[g] >= 0 && L->h_args[g].reserved != base[g]) return EPARA_ERR_SHAPE;
+    if (!L->d_workspace) return EPARA_ERR_NULL;
+    if (reinterpret_cast<uintptr_t>(L->d_workspace) % 256 != 0) return EPARA_ERR_ALIGN;
+    if (L->workspace_bytes < epara_split_workspace_bytes(n_split, n_panel)) return EPARA_ERR_CAPACITY;
+    return EPARA_OK;
+}
+
+// Does the launch hold a tile that is no streaming tile (bf16 / fp8)
+bool any_panel(const epara_launch* L)
+{
+    for (int64_t t = 0; t < L->n_tiles; ++t)
+        if (L->h_tiles[t].cls >= N_STREAM_CLASSES) return true;
+    return false;
+}
+
+// blocks: whether block tiles are welcome (a chain has no kernel for them).
+int32_t validate_launch(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int* narrow_out = nullptr, bool blocks = true)
 {
     if (!L) return EPARA_ERR_NULL;
     const bool f32 = in_dtype == EPARA_F32;
@@ -77,37 +113,21 @@ int32_t validate_launch(const epara_launch* L, int32_t in_dtype, int32_t out_dty
             if (L->h_args[g].M > 0) { ++n_live; n_gated += L->h_args[g].act == EPARA_ACT_SWIGLU; }
         if (n_gated != 0 && n_gated != n_live) return EPARA_ERR_DTYPE;
     }
-    int32_t last = EPARA_OK, narrow = 0;
-    for (; narrow < (f32 ? 1 : 3); ++narrow) {
-        last = check_tiles(L, in_dtype, narrow);
-        if (last == EPARA_OK) break;
+    // The table the launch was cut with, by its tiles and its split counts.  One that fits several of them gives the same
+    // results with each; block tiles come first, where the caller has a kernel for them.
+    int32_t first_error = EPARA_OK;
+    static const int tables[3] = {EPARA_TABLE_BLOCK, 0, 1};
+    for (int i = (f32 || !blocks || !any_panel(L)) ? 1 : 0; i < (f32 ? 2 : 3); ++i) {
+        int32_t st = check_tiles(L, in_dtype, tables[i]);
+        if (st == EPARA_OK) st = check_split(L, in_dtype, tables[i]);
+        if (st == EPARA_OK) {
+            if (narrow_out) *narrow_out = tables[i];
+            return EPARA_OK;
+        }
+        // what a launch is refused for: the wide table's objection to its split, else the last table's to its tiles
+        if (tables[i] != EPARA_TABLE_BLOCK && (first_error == EPARA_OK || first_error == EPARA_ERR_SHAPE)) first_error = st;
     }
-    if (last != EPARA_OK) return last;
-    if (narrow_out) *narrow_out = narrow;
-    // split tiles: the groups' slots and the counts must be the layout's, and the workspace must hold them
-    if (L->n_split_tiles < 0 || L->n_panel_split_tiles < 0) return EPARA_ERR_SHAPE;
-    if (L->n_split_tiles > 0 || L->n_panel_split_tiles > 0) {
-        if (f32) return EPARA_ERR_DTYPE;
-        int gated = 0;
-        for (int32_t g = 0; g < L->G; ++g)
-            if (L->h_args[g].M > 0 && L->h_args[g].act == EPARA_ACT_SWIGLU) gated = 1;
-        epara_tile_class cls[4];
-        int32_t ncls = 0, nstream = 0, n_split = 0, n_panel = 0, parts = 1, more = 0;
-        int64_t bytes = 0;
-        epara_kernel_classes(in_dtype, gated, narrow, cls, 4, &ncls, &nstream);
-        std::vector<epara_group_desc> d(static_cast<size_t>(L->G));
-        std::vector<int32_t> base(static_cast<size_t>(L->G));
-        for (int32_t g = 0; g < L->G; ++g) d[g] = {L->h_args[g].M, L->h_args[g].K, L->h_args[g].N, L->h_args[g].act, 0, 0};
-        if (int32_t st = epara_split_layout(d.data(), L->G, cls, ncls, nstream, base.data(), &n_split, &bytes)) return st;
-        if (int32_t st = epara_panel_split(d.data(), L->G, cls, ncls, nstream, L->n_workgroups, &n_panel, &parts, &more)) return st;
-        if (n_split != L->n_split_tiles || n_panel != L->n_panel_split_tiles) return EPARA_ERR_SHAPE;
-        for (int32_t g = 0; g < L->G; ++g)
-            if (base[g] >= 0 && L->h_args[g].reserved != base[g]) return EPARA_ERR_SHAPE;
-        if (!L->d_workspace) return EPARA_ERR_NULL;
-        if (reinterpret_cast<uintptr_t>(L->d_workspace) % 256 != 0) return EPARA_ERR_ALIGN;
-        if (L->workspace_bytes < epara_split_workspace_bytes(n_split, n_panel)) return EPARA_ERR_CAPACITY;
-    }
-    return EPARA_OK;
+    return first_error;
 }
 
 int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int narrow, hipStream_t stream)
@@ -116,14 +136,22 @@ int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int 
     int gated = 0;
     for (int32_t g = 0; g < L->G; ++g)
         if (L->h_args[g].M > 0 && L->h_args[g].act == EPARA_ACT_SWIGLU) gated = 1;
-    int panel_only = 1;                       // launches without streaming tiles run a kernel without that code
-    for (int64_t t = 0; t < L->n_tiles; ++t)
-        if (L->h_tiles[t].cls < N_STREAM_CLASSES) { panel_only = 0; break; }
+    int64_t n_stream = 0;
+    for (int64_t t = 0; t < L->n_tiles; ++t) n_stream += L->h_tiles[t].cls < N_STREAM_CLASSES;
+    const int panel_only = n_stream == 0;     // launches without streaming tiles run a kernel without that code
     const unsigned grid = static_cast<unsigned>(L->n_workgroups);
     const long n_slots = static_cast<long>(L->n_slots);
     (void)hipGetLastError();
     hipError_t e;
-    if (narrow == EPARA_TABLE_BLOCK) {        // two workgroups per compute unit
+    if (narrow == EPARA_TABLE_BLOCK) {
+        // streaming tiles first, in a kernel that passes over the block tiles; then those, two workgroups per compute unit
+        if (n_stream > 0) {
+            e = (in_dtype == EPARA_BF16 ? (gated ? epara_enqueue_bf16_gated : epara_enqueue_bf16_plain)
+                                        : (gated ? epara_enqueue_fp8_gated : epara_enqueue_fp8_plain))(
+                0, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype, EPARA_STREAM_TILES_ONLY, static_cast<uint32_t*>(L->d_workspace),
+                L->n_split_tiles, 0, 0);
+            if (e != hipSuccess) return EPARA_ERR_HIP;
+        }
         e = (in_dtype == EPARA_BF16 ? epara_enqueue_block_bf16 : epara_enqueue_block_fp8)(gated, 2 * grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype);
         return e == hipSuccess ? EPARA_OK : EPARA_ERR_HIP;
     }
@@ -237,8 +265,7 @@ static int32_t chain_impl(const epara_chain_phase* phases, int32_t n_phases, int
         const epara_chain_phase& ph = phases[p];
         const epara_launch* L = ph.launch;
         int narrow = 0;
-        if (int32_t st = validate_launch(L, in_dtype, ph.out_dtype, &narrow)) return st;
-        if (narrow == EPARA_TABLE_BLOCK) return EPARA_ERR_SHAPE;                            // the chain kernels hold no block tiles
+        if (int32_t st = validate_launch(L, in_dtype, ph.out_dtype, &narrow, false)) return st;
         if (L->n_split_tiles != 0 || L->n_panel_split_tiles != 0) return EPARA_ERR_SHAPE;   // the phases of a chain are scheduled without splitting K
         if (ph.counter_base < 0 || ph.counter_base > INT32_MAX - L->G) return EPARA_ERR_SHAPE;
         for (int32_t q = 0; q < p; ++q)       // counter ranges must not overlap

@@ -24,6 +24,20 @@ def _upload(a, device):
     return torch.from_numpy(raw.copy()).to(device)
 
 
+def _upload_all(arrays, device):
+    """numpy arrays -> one uint8 device tensor per array holding the same bytes, all with one copy: they are pieces of one
+    buffer, each at a multiple of 256 bytes and never empty."""
+    sizes = [max(a.nbytes, 16) for a in arrays]
+    starts = [0]
+    for n in sizes:
+        starts.append(starts[-1] + (n + 255) // 256 * 256)
+    raw = np.zeros(starts[-1], dtype=np.uint8)
+    for a, at in zip(arrays, starts):
+        raw[at: at + a.nbytes] = a.view(np.uint8).reshape(-1)
+    whole = torch.from_numpy(raw).to(device)
+    return [whole[at: at + n] for at, n in zip(starts, sizes)]
+
+
 def current_stream_handle():
     return torch.cuda.current_stream().cuda_stream
 
@@ -97,9 +111,7 @@ class LaunchPlan:
         self.makespan, self.narrow, self.classes, self.n_stream_classes = info.makespan, bool(info.narrow), info.class_table(), info.n_stream_classes
         self.plan_seconds = time.perf_counter() - t0
         t0 = time.perf_counter()
-        self.d_args = _upload(self.args, device)
-        self.d_tiles = _upload(self.tiles, device)
-        self.d_order = _upload(self.order, device)
+        self.d_args, self.d_tiles, self.d_order = _upload_all([self.args, self.tiles, self.order], device)
         self.d_workspace = None
         if self.workspace_bytes:
             self.d_workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=device)

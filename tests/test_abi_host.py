@@ -536,7 +536,7 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
     planner; the tiles cover every output once; a grid of fewer than 128 workgroups and a chain never use them."""
     gated, W = act == 5, 256
     ref = [g + (gated,) for g in shapes]
-    info, _, _, _, tiles, order, _ = B.epara_plan_launch(_desc(shapes, act), dtype, W, 8, 1, 4)
+    info, _, _, _, tiles, order, split_base = B.epara_plan_launch(_desc(shapes, act), dtype, W, 8, 1, 4)
     assert (info.narrow == 2) == block
     best = None
     for narrow in (0, 1) if max((g[0] for g in shapes), default=0) > 32 else (0,):
@@ -553,7 +553,8 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
             best = (max(loads), cls, ns, rt, ro)
     bc, bn = B.epara_kernel_classes(dtype, gated, 2)
     bc = [tuple(int(v) for v in c) for c in bc]
-    assert bc == [(P.INT32_MAX, 128, 64 if gated else 128, 0)] and bn == 0
+    assert bc[3] == (P.INT32_MAX, 128, 64 if gated else 128, 0) and bn == 3
+    assert bc[:3] == [tuple(int(v) for v in c) for c in B.epara_kernel_classes(dtype, gated, 1)[0][:3]]
     taken, rt, ro, finish = P.block_choice(ref, bc, *best[1:], W, 8, 1, 4)
     assert bool(taken) == block
     if block:
@@ -562,7 +563,8 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
         for t in tiles:
             cover[int(t["group"])][t["m0"]: t["m0"] + t["rows"], t["n0"]: t["n0"] + t["cols"]] += 1
         assert all(np.all(c == 1) for c in cover.values())
-        assert info.n_split_tiles == info.n_panel_split_tiles == info.workspace_bytes == 0
+        base, n_split, nbytes = P.split_layout(shapes, bc, bn)
+        assert (split_base.tolist(), info.n_split_tiles, info.workspace_bytes, info.n_panel_split_tiles) == (base, n_split, nbytes, 0)
     assert B.epara_plan_launch(_desc(shapes, act), dtype, 120, 8, 1, 4)[0].narrow != 2
     if shapes and not gated:
         _, phases = B.epara_plan_chain([_desc(shapes, act), _desc(shapes, act)], [None, None], dtype, W, 8, 1, 4)
