@@ -369,17 +369,35 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * EPARA_COST_BLOCK_START.
  * Measured, bf16, 512 tiles at a time: K = 4096, own weights: 94 / 100 / 114 us for f = 1 / 2 / 4; weights shared by many row
  * tiles: 8.0 ns (K = 3072, N = 768) to 9.3 ns (K = 5120, N = 13824) per K and compute unit for f = 4, against 5.9 ns for a quarter of
- * a panel tile, which moves fewer bytes per product and so runs at higher clocks.  But a panel tile costs another 7 us of
+ * a panel tile, which moves fewer bytes per product and so runs at higher clocks.  But a panel tile costs about 10 us of
  * start and finish (EPARA_COST_PANEL_START), which one wave per SIMD cannot overlap with anything and two workgroups
- * per unit hide from each other. */
+ * per unit hide from each other.  The constants are fitted to both kernels' times on 112 launches (SwiGLU batches of 1
+ * .. 2048 rows, K = 1120 .. 13824, bf16 and fp8; layers of vision transformers of 192 .. 1024 columns): where the model takes
+ * block tiles they were 1.0 .. 4.3 times as fast, where it does not at most 1.3 times.
+ *
+ * Block tiles of a long K.  Few tiles of a long K (a down projection) leave units idle, so the tiles of the groups with
+ * K >= EPARA_BLOCK_SPLIT_K (the block class's split_K) are visited in P = 1 .. EPARA_SPLIT_MAX_PARTS parts of K, the same P for the
+ * whole launch: part j covers the units floor(U j / P) .. floor(U (j+1) / P) - 1 of the U = ceil(ceil(K / stage) / 4) units of
+ * four 64-byte stages.  P is the one whose visits, the groups by descending cost of their first tile (ties: lower group), tiles
+ * in table order, part by part, each to the least loaded of W lists, finish first (ties: fewer parts); 1 if the launch has more than
+ * EPARA_BLOCK_SPLIT_MAX_PER_LIST * W block tiles.  A visit costs cost / P + EPARA_COST_BLOCK_PARTIAL.  Every visit leaves its raw
+ * sums (64 KiB) in the workspace and counts itself at the tile; whoever counts last adds the parts in index order and
+ * runs the epilogue.  Three split tiles share a slot of a split panel tile: epara_launch.n_panel_split_tiles =
+ * ceil(split block tiles / EPARA_BLOCK_TILES_PER_SLOT), and split_base[g] = index of the group's first tile among them.
+ * Measured, bf16, 75 rows, K = 11008, N = 4096 (32 tiles): 106 -> 34 us in four parts; 563 rows, K = 2416, N = 2192 (90 tiles): 21 us in
+ * three (panel tiles: 51). */
 #define EPARA_TABLE_BLOCK 2               /* `narrow` of the block table */
 #define EPARA_BLOCK_ROWS 128
 #define EPARA_BLOCK_MIN_WORKGROUPS 128    /* smaller grids leave units free, where workgroups do not pair up */
-#define EPARA_COST_BLOCK_STREAM 1000
-#define EPARA_COST_BLOCK_STREAM_PER_32 50
-#define EPARA_COST_BLOCK_PER_32 165
+#define EPARA_COST_BLOCK_STREAM 1300
+#define EPARA_COST_BLOCK_STREAM_PER_32 90
+#define EPARA_COST_BLOCK_PER_32 210
 #define EPARA_COST_BLOCK_START 40000
-#define EPARA_COST_PANEL_START 600000
+#define EPARA_COST_PANEL_START 900000
+#define EPARA_BLOCK_SPLIT_K 1024
+#define EPARA_BLOCK_SPLIT_MAX_PER_LIST 3
+#define EPARA_BLOCK_TILES_PER_SLOT 3
+#define EPARA_COST_BLOCK_PARTIAL 500000
 #define EPARA_COST_KERNEL 400000          /* a second kernel: about 5 us */
 
 /* Splitting K.  A streaming tile of a class with BM >= 32 streams its weights while re-reading BM activation
@@ -511,7 +529,7 @@ typedef struct {
  * table's schedule has the smaller makespan under the cost model (ties: wide); or the block table ("Block tiles"), for
  * bf16 / fp8 launches with a batch of more than 64 rows and n_workgroups >= EPARA_BLOCK_MIN_WORKGROUPS, when its makespan T
  * (the largest load of block tiles, plus the largest load of streaming tiles and EPARA_COST_KERNEL if there are any) is
- * below U - U / 15, U = the largest load of a workgroup in the order of the other choice with
+ * below U, the largest load of a workgroup in the order of the other choice with
  * EPARA_COST_PANEL_START added to every visit to a panel tile -- then plans
  * (epara_plan_groups) and schedules (epara_schedule_tiles) with it.  The groups must be all
  * EPARA_ACT_SWIGLU or none (ERR_DTYPE).  (A chain, epara_plan_chain with more than one phase, has no block tiles.)  *plan is always written (sizes included); tiles / order are

@@ -212,11 +212,11 @@ def plan_groups(groups, classes):
 
 def panel_cost(M, K, cls, rows):
     """Cost of a tile of a panel class cls = (max_M, BM, BN[, split_K]) with `rows` rows of a group of M: 2040 * K, or for
-    a class of 128 rows (block tiles, f = ceil(rows / 32), s = ceil(M / 128)) K * max(1000 // s + 50 f, 165 f) + 40000."""
+    a class of 128 rows (block tiles, f = ceil(rows / 32), s = ceil(M / 128)) K * max(1300 // s + 90 f, 210 f) + 40000."""
     if cls[1] != 128:
         return 2040 * K
     f, s = -(-min(rows, 128) // 32), -(-M // 128)
-    return K * max(1000 // s + 50 * f, 165 * f) + 40000
+    return K * max(1300 // s + 90 * f, 210 * f) + 40000
 
 
 def split_parts(K, cls):
@@ -275,7 +275,7 @@ def panel_split(groups, classes, n_stream_classes, n_workgroups):
             continue
         c = pick_class(M, classes)
         cl = classes[c]
-        if c < n_stream_classes or (len(g) > 3 and g[3]):
+        if c < n_stream_classes or (len(g) > 3 and g[3]) or cl[1] == 128:
             return 0, 1, 0
         if cls is not None and (c != cls or Kg != K):
             return 0, 1, 0
@@ -307,6 +307,51 @@ def panel_split(groups, classes, n_stream_classes, n_workgroups):
         if t < best:
             best, parts, more = t, base, extra
     return (m, parts, more) if parts > 1 else (0, 1, 0)
+
+
+def block_split(groups, classes, n_stream_classes, n_workgroups):
+    """-> (P, split_base per group or None, slots): in how many parts of K a single launch visits the block tiles (a panel
+    class of 128 rows with split_K > 0) of the groups with K >= split_K, where they meet, and how many slots of three tiles
+    that takes.  P = 1 with more than 3 W block tiles or none to split; otherwise the P = 1 .. 4 whose visits (cost of a
+    tile, or cost // P + 500000), groups by descending cost of the first tile, tiles in table order, each to the least
+    loaded of W lists, finish first; fewer parts on ties."""
+    import heapq
+    W = n_workgroups
+    members, n, n_split, base, at = [], 0, 0, [None] * len(groups), 0
+    for g, gr in enumerate(groups):
+        M, K, N = gr[:3]
+        if M <= 0:
+            continue
+        c = pick_class(M, classes)
+        cl = classes[c]
+        if c < n_stream_classes or cl[1] != 128:
+            continue
+        count = -(-M // cl[1]) * -(-N // cl[2])
+        members.append((g, cl))
+        n += count
+        if len(cl) > 3 and cl[3] > 0 and K >= cl[3]:
+            n_split += count
+            base[g] = at
+            at += count
+    if n_split == 0 or n > 3 * W:
+        return 1, [None] * len(groups), 0
+    members.sort(key=lambda m: -panel_cost(groups[m[0]][0], groups[m[0]][1], m[1], groups[m[0]][0]))
+    best = None
+    for P in (1, 2, 3, 4):
+        bins = [0] * W
+        for g, cl in members:
+            M, K, N = groups[g][:3]
+            p = P if base[g] is not None else 1
+            for m0 in range(0, M, cl[1]):
+                cost = panel_cost(M, K, cl, M - m0)
+                each = cost if p == 1 else cost // p + 500000
+                for _ in range(-(-N // cl[2]) * p):
+                    heapq.heapreplace(bins, bins[0] + each)
+        if best is None or max(bins) < best[0]:
+            best = (max(bins), P)
+    if best[1] == 1:
+        return 1, [None] * len(groups), 0
+    return best[1], base, -(-n_split // 3)
 
 
 def schedule_tiles(groups, classes, n_stream_classes, tiles, n_workgroups, n_xcd, panel_m, panel_n):
@@ -360,6 +405,7 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
     stream = []
     n_panel_split, panel_parts, panel_more = panel_split(*phases[0][:3], W) if len(phases) == 1 else (0, 1, 0)
     for p, (groups, classes, n_stream_classes, tiles) in enumerate(phases):
+        block_parts, block_base = block_split(groups, classes, n_stream_classes, W)[:2] if len(phases) == 1 else (1, [None] * len(groups))
         if not 0 <= n_stream_classes <= len(classes):
             raise ValueError("bad number of streaming classes")
         first = {}
@@ -379,12 +425,15 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
                                 t = first[g] + tm * TN + tn
                                 if t >= len(tiles) - n_panel_split:      # visited in parts, after the whole tiles
                                     continue
-                                _, r = heapq.heappop(rank_heap)
-                                x, i = divmod(r, per)
-                                b = i * X + x
-                                lists[p][b].append(t)
-                                load[b] += panel_cost(M, K, classes[c], M - tm * bm)
-                                heapq.heappush(rank_heap, (load[b], r))
+                                cost = panel_cost(M, K, classes[c], M - tm * bm)
+                                parts = block_parts if block_base[g] is not None else 1
+                                for j in range(parts):
+                                    _, r = heapq.heappop(rank_heap)
+                                    x, i = divmod(r, per)
+                                    b = i * X + x
+                                    lists[p][b].append(order_entry(t, j, parts))
+                                    load[b] += cost if parts == 1 else cost // parts + 500000
+                                    heapq.heappush(rank_heap, (load[b], r))
         for t in range(len(tiles) - n_panel_split, len(tiles)):    # the parts: tile by tile, part by part, same rule
             parts_t = panel_parts + (1 if t >= len(tiles) - panel_more else 0)      # the last panel_more tiles: one part more
             each = 2040 * groups[tiles[t][0]][1] // parts_t + 1020000
@@ -432,8 +481,8 @@ def block_choice(groups, block_classes, other_classes, other_n_stream, other_til
     """Whether a single bf16 / fp8 launch takes the block table instead of the best of the other tables (class table, tiles
     and visit order of which are given) -> (taken, tiles, order, finish).  Considered when a batch has more than 64 rows
     and W >= 128.  finish = the largest load of
-    a list in block tiles, plus the largest load in streaming tiles and 400000 if there are any; taken if that is below `other` - other // 15 with `other` = the largest load of
-    a workgroup in the other order where every visit to a panel tile costs 600000 more."""
+    a list in block tiles, plus the largest load in streaming tiles and 400000 if there are any; taken if that is below the largest load of
+    a workgroup in the other order where every visit to a panel tile costs 900000 more."""
     W = n_workgroups
     if max((g[0] for g in groups), default=0) <= 64 or W < 128:
         return False, None, None, None
@@ -448,21 +497,21 @@ def block_choice(groups, block_classes, other_classes, other_n_stream, other_til
             g, cl = groups[tile[0]], classes[tile[5]]
             if tile[5] >= n_stream:
                 cost = panel_cost(g[0], g[1], cl, tile[3])
-                panel[slot % W] += (cost if parts == 1 else cost // parts + 1020000) + start
+                panel[slot % W] += (cost if parts == 1 else cost // parts + (500000 if cl[1] == 128 else 1020000)) + start
             else:
                 wide = tile[4] * (2 if len(g) > 3 and g[3] else 1)
                 cost = g[1] * (6 * wide + (2 * cl[1] if cl[1] >= 32 else 0))
                 stream[slot % W] += cost if parts == 1 else cost // parts + 24 * cl[1] * wide
         return panel, stream
 
-    panel, stream = loads(other_classes, other_n_stream, other_tiles, other_order, 600000)
+    panel, stream = loads(other_classes, other_n_stream, other_tiles, other_order, 900000)
     other = max(a + b for a, b in zip(panel, stream))
     n_stream = len(block_classes) - 1
     _, _, _, tiles = plan_groups([g[:3] for g in groups], block_classes)
     order = schedule_tiles(groups, block_classes, n_stream, tiles, W, n_xcd, panel_m, panel_n)
     panel, stream = loads(block_classes, n_stream, tiles, order, 0)
     finish = max(panel) + (max(stream) + 400000 if any(t[5] < n_stream for t in tiles) else 0)
-    return finish < other - other // 15, tiles, order, finish
+    return finish < other, tiles, order, finish
 
 
 def chain_waits(producer_tiles, counter_base, producer):

@@ -23,8 +23,27 @@ namespace {
 constexpr int BLOCK_RING = 4;                                    // pairs in flight or being read
 constexpr int BLOCK_LDS_BYTES = BLOCK_RING * 128 * 128;          // 64 KiB; the epilogue parks the tile's outputs in the same place
 
+// Split block tiles: three of them per slot of the panel tiles' workspace (four parts of 64 KiB each), their counters behind.
+constexpr int BLOCK_PART_BYTES = 65536, BLOCK_TILES_PER_SLOT = EPARA_BLOCK_TILES_PER_SLOT;
+constexpr int BLOCK_SLOT_BYTES = SPLIT_MAX_PARTS * PANEL_SPLIT_STRIDE;
+static_assert(BLOCK_TILES_PER_SLOT * SPLIT_MAX_PARTS * BLOCK_PART_BYTES + BLOCK_TILES_PER_SLOT * 4 <= BLOCK_SLOT_BYTES, "a slot is too small");
+__device__ __forceinline__ char* block_partials(const split_ctx& sp, int tile)
+{
+    return panel_partials(sp) + static_cast<size_t>(tile / BLOCK_TILES_PER_SLOT) * BLOCK_SLOT_BYTES +
+           (tile % BLOCK_TILES_PER_SLOT) * (SPLIT_MAX_PARTS * BLOCK_PART_BYTES);
+}
+__device__ __forceinline__ uint32_t* block_counter(const split_ctx& sp, int tile)
+{
+    return reinterpret_cast<uint32_t*>(panel_partials(sp) + static_cast<size_t>(tile / BLOCK_TILES_PER_SLOT) * BLOCK_SLOT_BYTES +
+                                       BLOCK_TILES_PER_SLOT * (SPLIT_MAX_PARTS * BLOCK_PART_BYTES)) + tile % BLOCK_TILES_PER_SLOT;
+}
+
+// entry: the visit; a tile of a long K may be visited in parts (EPARA_BLOCK_SPLIT_K).  A part leaves its raw sums in the
+// workspace, lane by lane as they sit in the registers, written through to memory, and counts itself at the tile; whoever
+// counts last adds the parts in index order (its own too: the order does not depend on who it is), runs the epilogue and
+// puts the counter back to zero.  Nobody waits for another workgroup.
 template <int DT, bool GATED, int FM>
-__device__ __forceinline__ void block_tile(const epara_group_args& ga, const epara_tile& tl, int out_dtype, char* lds)
+__device__ __forceinline__ void block_tile(const epara_group_args& ga, const epara_tile& tl, int entry, int out_dtype, char* lds, const split_ctx& sp)
 {
     constexpr int ESZ = DT == EPARA_BF16 ? 2 : 1;
     constexpr int EPC = 16 / ESZ;                                // elements per 16-byte chunk
@@ -39,12 +58,21 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
     ldsptr l3 = (ldsptr)lds;
     const int K = ga.K, N = ga.N, rows = tl.rows, cols = tl.cols;
     const int KSP = ((K + KF - 1) / KF + 3) & ~3;
-    const int n_pairs = KSP >> 1;                                // even
+    const int parts = order_parts(entry), part = order_part(entry);
+    const int slot_tile = parts > 1 ? ga.reserved + (tl.m0 >> 7) * ((N + (GATED ? 63 : 127)) / (GATED ? 64 : 128)) + tl.n0 / (GATED ? 64 : 128) : 0;
+    // parts without a workspace, or more of them than it holds: not an order that the library's planner writes; the visit is
+    // dropped rather than let it write outside
+    if (parts > 1 && (sp.ws == nullptr || parts > SPLIT_MAX_PARTS || ga.reserved < 0 || slot_tile >= sp.n_panel * BLOCK_TILES_PER_SLOT)) return;
+    // this visit's pairs: whole units of two
+    const uint32_t units = static_cast<uint32_t>(KSP >> 2);
+    const int first_pair = 2 * static_cast<int>(units * part / parts), n_pairs = 2 * static_cast<int>(units * (part + 1) / parts) - first_pair;
+    if (n_pairs < 2) return;                                     // fewer units than parts: likewise
 
     // ---- activations: instruction j of a pair covers rows 8 (4 j + wave) .. + 7; lane l writes chunk l % 8 of row l / 8
     // and fetches the chunk that belongs there (chunk ^ (row / 2) % 8: fragment reads are free of bank conflicts)
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char*>(static_cast<const char*>(ga.X)) + static_cast<size_t>(tl.m0) * K * ESZ, 0, -1, 0x00020000);
+        const_cast<char*>(static_cast<const char*>(ga.X)) + static_cast<size_t>(tl.m0) * K * ESZ + first_pair * 128, 0, -1, 0x00020000);
+    const int K_left = K - first_pair * 2 * KF;                  // of the visit; its first chunk is inside K
     const int x_chunk = (lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7);
     uint32_t x_off[FM];
 #pragma unroll
@@ -53,11 +81,12 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
     // ---- weights: lane (r32, h) takes chunk 2 s2 + h of column r32 % 16 of one of the wave's two packed column blocks
     const int NB = (N + 15) >> 4, nb0 = (tl.n0 >> 4) + (GATED ? wave : 2 * wave);
     const int nb = min(GATED ? nb0 : nb0 + (r32 >> 4), NB - 1);  // a block past N only feeds columns that are not stored
-    gcptr wp = as_global<char>((GATED && r32 >= 16) ? ga.W2 : ga.W) + static_cast<size_t>(nb) * KSP * 1024 + (h * 16 + (r32 & 15)) * 16;
+    gcptr wp = as_global<char>((GATED && r32 >= 16) ? ga.W2 : ga.W) + static_cast<size_t>(nb) * KSP * 1024 +
+               static_cast<size_t>(first_pair) * 2048 + (h * 16 + (r32 & 15)) * 16;
 
     v4i w[BLOCK_RING][4];                                        // [pair % 4][2 stage + half of its K]
     auto x_issue = [&](int p, int slot, int j) {
-        const int left = K - p * 2 * KF;                         // elements of K from this pair on
+        const int left = K_left - p * 2 * KF;                    // elements of K from this pair on
         uint32_t off = x_off[j];
         int so = p * 128;
         if (left < 2 * KF) {                                     // last pair(s) of a ragged K: chunks past K come from chunk 0
@@ -209,6 +238,53 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
     // then through the LDS, so that a store instruction covers whole row pieces of 256 bytes.  16-byte chunk c of a
     // row sits at c ^ (row % chunks per row).
     __syncthreads();                                             // the ring has been read
+    if (parts > 1) {
+        char* slab = block_partials(sp, slot_tile);
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(slab, 0, -1, 0x00020000);
+        const int at = wave * 16384 + lane * 16;
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const v4f q = {acc[fm][4 * g], acc[fm][4 * g + 1], acc[fm][4 * g + 2], acc[fm][4 * g + 3]};
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, q), rsrc, at, part * BLOCK_PART_BYTES + (fm * 4 + g) * 1024, 16);   // 16: device scope (sc1)
+            }
+        asm volatile("" ::: "memory");
+        wait_vmcnt<0>();
+        __syncthreads();                                         // every wave's sums are in memory
+        __attribute__((address_space(3))) uint32_t* box = (__attribute__((address_space(3))) uint32_t*)l3;
+        uint32_t* counter = block_counter(sp, slot_tile);
+        if (tid == 0) *box = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        const bool last = *box == static_cast<uint32_t>(parts - 1);
+        __syncthreads();                                         // the box's place in the LDS is free again
+        if (!last) return;
+        if (tid == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        auto add = [&](auto n_tag) {
+            constexpr int P = decltype(n_tag)::value;
+#pragma unroll
+            for (int fm = 0; fm < FM; ++fm) {
+                v4i in[4][P];
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                    for (int j = 0; j < P; ++j)
+                        in[g][j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, j * BLOCK_PART_BYTES + (fm * 4 + g) * 1024, 16);
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    v4f sum = __builtin_bit_cast(v4f, in[g][0]);
+#pragma unroll
+                    for (int j = 1; j < P; ++j) sum += __builtin_bit_cast(v4f, in[g][j]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[fm][4 * g + i] = sum[i];
+                }
+
+            }
+        };
+        if (parts == 2)      add(act_tag<2>{});
+        else if (parts == 3) add(act_tag<3>{});
+        else                 add(act_tag<4>{});
+    }
     auto finish = [&](auto out_tag, auto act) {
         constexpr int OUT = decltype(out_tag)::value, ACT = decltype(act)::value;
         constexpr int OSZ = OUT == EPARA_BF16 ? 2 : 1;
@@ -288,8 +364,10 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
 
 template <int DT, bool GATED>
 __global__ __launch_bounds__(NT, 2) void grouped_block_kernel(const epara_group_args* __restrict__ args, const epara_tile* __restrict__ tiles,
-                                                              const int32_t* __restrict__ order, long n_slots, int out_dtype)
+                                                              const int32_t* __restrict__ order, long n_slots, int out_dtype,
+                                                              uint32_t* split_ws, int n_split, int n_panel_split)
 {
+    const split_ctx sp = {split_ws, n_split, n_panel_split, 0};
     extern __shared__ __attribute__((aligned(16))) char lds[];
     for (long s = blockIdx.x; s < n_slots; s += gridDim.x) {
         const int t = order[s];
@@ -298,21 +376,21 @@ __global__ __launch_bounds__(NT, 2) void grouped_block_kernel(const epara_group_
         if (tl.cls < N_STREAM_CLASSES) continue;                 // the streaming tiles of the launch have a kernel of their own
         const epara_group_args ga = args[tl.group];
         const int fm = (tl.rows + 31) >> 5;
-        if (fm > 3)       block_tile<DT, GATED, 4>(ga, tl, out_dtype, lds);
-        else if (fm == 3) block_tile<DT, GATED, 3>(ga, tl, out_dtype, lds);
-        else if (fm == 2) block_tile<DT, GATED, 2>(ga, tl, out_dtype, lds);
-        else              block_tile<DT, GATED, 1>(ga, tl, out_dtype, lds);
+        if (fm > 3)       block_tile<DT, GATED, 4>(ga, tl, t, out_dtype, lds, sp);
+        else if (fm == 3) block_tile<DT, GATED, 3>(ga, tl, t, out_dtype, lds, sp);
+        else if (fm == 2) block_tile<DT, GATED, 2>(ga, tl, t, out_dtype, lds, sp);
+        else              block_tile<DT, GATED, 1>(ga, tl, t, out_dtype, lds, sp);
     }
 }
 
 template <int DT, bool GATED>
 hipError_t enqueue_block(unsigned grid, hipStream_t stream, const epara_group_args* args, const epara_tile* tiles,
-                         const int32_t* order, long n_slots, int out_dtype)
+                         const int32_t* order, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_panel_split)
 {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_block_kernel<DT, GATED>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, BLOCK_LDS_BYTES);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((grouped_block_kernel<DT, GATED>), dim3(grid), dim3(NT), BLOCK_LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype);
+    hipLaunchKernelGGL((grouped_block_kernel<DT, GATED>), dim3(grid), dim3(NT), BLOCK_LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, split_ws, n_split, n_panel_split);
     return hipGetLastError();
 }
 

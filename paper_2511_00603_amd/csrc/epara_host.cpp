@@ -6,6 +6,7 @@
 // puts several services into one launch, and the tile class picked per group is the
 // "parallel mode" that group runs in.
 #include "epara.h"
+#include "epara_plan.h"
 
 #include <algorithm>
 #include <climits>
@@ -106,7 +107,7 @@ int32_t panel_split_of(const epara_group_desc* groups, int32_t G, const epara_ti
         const epara_group_desc& d = groups[g];
         if (d.M <= 0) continue;
         const int32_t c = class_of(d.M, classes, n_classes);
-        if (c < n_stream_classes || d.act == EPARA_ACT_SWIGLU) return 0;
+        if (c < n_stream_classes || d.act == EPARA_ACT_SWIGLU || classes[c].BM == EPARA_BLOCK_ROWS) return 0;
         if (cls >= 0 && (c != cls || d.K != K)) return 0;
         if (classes[c].split_K <= 0 || d.K < classes[c].split_K) return 0;
         cls = c; K = d.K;
@@ -114,6 +115,83 @@ int32_t panel_split_of(const epara_group_desc* groups, int32_t G, const epara_ti
     }
     if (cls < 0 || n > 0xFFFFFF) return 0;
     return panel_split_choice(n, W, static_cast<int64_t>(EPARA_COST_PANEL) * K, parts, n_more);
+}
+
+// Workgroups by (load, index): the smallest on top, costs added to it.
+class least_loaded {
+public:
+    least_loaded(int64_t n, const int64_t* load)                 // load: null = all level
+    {
+        heap_.reserve(static_cast<size_t>(n));
+        for (int64_t i = 0; i < n; ++i) heap_.push_back({load ? load[i] : 0, i});
+        std::make_heap(heap_.begin(), heap_.end(), std::greater<std::pair<int64_t, int64_t>>());
+    }
+    int64_t top() const { return heap_[0].second; }
+    int64_t add_to_top(int64_t cost)                             // back into place with one walk down; returns its new load
+    {
+        std::pair<int64_t, int64_t> moved = heap_[0];
+        moved.first += cost;
+        size_t i = 0;
+        for (const size_t n = heap_.size();;) {
+            size_t child = 2 * i + 1;
+            if (child >= n) break;
+            if (child + 1 < n && heap_[child + 1] < heap_[child]) ++child;
+            if (!(heap_[child] < moved)) break;
+            heap_[i] = heap_[child];
+            i = child;
+        }
+        heap_[i] = moved;
+        return moved.first;
+    }
+private:
+    std::vector<std::pair<int64_t, int64_t>> heap_;
+};
+
+// Block tiles of a launch: is group d (with rows) one of the block class, and visited in parts of K if the launch's are
+inline bool block_group(const epara_group_desc& d, const epara_tile_class* classes, int32_t n_classes, int32_t n_stream_classes)
+{
+    const int32_t c = class_of(d.M, classes, n_classes);
+    return c >= n_stream_classes && classes[c].BM == EPARA_BLOCK_ROWS;
+}
+inline bool block_splits(const epara_group_desc& d, const epara_tile_class& c) { return c.split_K > 0 && d.K >= c.split_K; }
+inline int64_t block_visit_cost(int64_t cost, int32_t parts) { return parts == 1 ? cost : cost / parts + EPARA_COST_BLOCK_PARTIAL; }
+
+// In how many parts of K a launch visits its block tiles of a long K ("Block tiles of a long K" in the header).
+int32_t block_parts(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
+                    int32_t n_stream_classes, int64_t W)
+{
+    std::vector<int32_t> members;
+    int64_t n = 0, n_split = 0;
+    for (int32_t g = 0; g < G; ++g)
+        if (groups[g].M > 0 && block_group(groups[g], classes, n_classes, n_stream_classes)) {
+            const epara_tile_class& c = classes[class_of(groups[g].M, classes, n_classes)];
+            const int64_t tiles = ceil_div(groups[g].M, c.BM) * ceil_div(groups[g].N, c.BN);
+            members.push_back(g);
+            n += tiles;
+            if (block_splits(groups[g], c)) n_split += tiles;
+        }
+    if (n_split == 0 || n > EPARA_BLOCK_SPLIT_MAX_PER_LIST * W) return 1;
+    auto class_at = [&](int32_t g) -> const epara_tile_class& { return classes[class_of(groups[g].M, classes, n_classes)]; };
+    std::stable_sort(members.begin(), members.end(), [&](int32_t a, int32_t b) {
+        return panel_cost(groups[a], class_at(a), groups[a].M) > panel_cost(groups[b], class_at(b), groups[b].M);
+    });
+    int32_t best_parts = 1;
+    int64_t best = -1;
+    for (int32_t P = 1; P <= EPARA_SPLIT_MAX_PARTS; ++P) {
+        least_loaded bins(W, nullptr);
+        int64_t finish = 0;
+        for (int32_t g : members) {
+            const epara_tile_class& c = class_at(g);
+            const int32_t parts = block_splits(groups[g], c) ? P : 1;
+            const int64_t TN = ceil_div(groups[g].N, c.BN);
+            for (int64_t m0 = 0; m0 < groups[g].M; m0 += c.BM) {
+                const int64_t each = block_visit_cost(panel_cost(groups[g], c, groups[g].M - m0), parts);
+                for (int64_t i = 0; i < TN * parts; ++i) finish = std::max(finish, bins.add_to_top(each));
+            }
+        }
+        if (best < 0 || finish < best) { best = finish; best_parts = P; }
+    }
+    return best_parts;
 }
 
 int32_t gated_of(const epara_group_desc* groups, int32_t G, int32_t* gated)
@@ -133,11 +211,28 @@ inline int32_t split_parts(const epara_group_desc& d, const epara_tile_class& c)
 inline int64_t visit_cost(int64_t cost, int32_t parts, const epara_group_desc& d, const epara_tile& t, const epara_tile_class& c, bool panel = false)
 {
     if (parts == 1) return cost;
-    if (panel) return cost / parts + EPARA_COST_PANEL_PARTIAL;
+    if (panel) return cost / parts + (c.BM == EPARA_BLOCK_ROWS ? EPARA_COST_BLOCK_PARTIAL : EPARA_COST_PANEL_PARTIAL);
     return cost / parts + static_cast<int64_t>(EPARA_COST_PARTIAL) * c.BM * t.cols * (d.act == EPARA_ACT_SWIGLU ? 2 : 1);
 }
 
 }  // namespace
+
+int32_t epara_block_split(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
+                          int32_t n_stream_classes, int64_t W, int32_t* base, int32_t* parts)
+{
+    *parts = block_parts(groups, G, classes, n_classes, n_stream_classes, W);
+    if (*parts == 1) return 0;
+    int64_t n = 0;
+    for (int32_t g = 0; g < G; ++g) {
+        const epara_group_desc& d = groups[g];
+        if (d.M <= 0 || !block_group(d, classes, n_classes, n_stream_classes)) continue;
+        const epara_tile_class& c = classes[class_of(d.M, classes, n_classes)];
+        if (!block_splits(d, c)) continue;
+        if (base) base[g] = static_cast<int32_t>(n);
+        n += ceil_div(d.M, c.BM) * ceil_div(d.N, c.BN);
+    }
+    return static_cast<int32_t>(ceil_div(n, EPARA_BLOCK_TILES_PER_SLOT));
+}
 
 extern "C" {
 
@@ -532,35 +627,6 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 
 namespace {
 
-// Workgroups by (load, index): the smallest on top, costs added to it.
-class least_loaded {
-public:
-    least_loaded(int64_t n, const int64_t* load)                 // load: null = all level
-    {
-        heap_.reserve(static_cast<size_t>(n));
-        for (int64_t i = 0; i < n; ++i) heap_.push_back({load ? load[i] : 0, i});
-        std::make_heap(heap_.begin(), heap_.end(), std::greater<std::pair<int64_t, int64_t>>());
-    }
-    int64_t top() const { return heap_[0].second; }
-    void add_to_top(int64_t cost)                                // back into place with one walk down
-    {
-        std::pair<int64_t, int64_t> moved = heap_[0];
-        moved.first += cost;
-        size_t i = 0;
-        for (const size_t n = heap_.size();;) {
-            size_t child = 2 * i + 1;
-            if (child >= n) break;
-            if (child + 1 < n && heap_[child + 1] < heap_[child]) ++child;
-            if (!(heap_[child] < moved)) break;
-            heap_[i] = heap_[child];
-            i = child;
-        }
-        heap_[i] = moved;
-    }
-private:
-    std::vector<std::pair<int64_t, int64_t>> heap_;
-};
-
 // epara_schedule_chain; keep (n_phases vectors, or null): receives the orders whatever their size, so that a planner that
 // does not know the size yet schedules once.
 int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workgroups, int32_t n_xcd, int32_t panel_m, int32_t panel_n,
@@ -620,6 +686,10 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
     int32_t panel_parts = 1, panel_more = 0;
     const int64_t n_panel_split = n_phases == 1 ? panel_split_of(phases[0].groups, phases[0].G, phases[0].classes, phases[0].n_classes,
                                                                  phases[0].n_stream_classes, W, &panel_parts, &panel_more) : 0;
+    // and a single launch its block tiles of a long K
+    const int32_t n_block_parts = n_phases == 1 ? block_parts(phases[0].groups, phases[0].G, phases[0].classes, phases[0].n_classes,
+                                                              phases[0].n_stream_classes, W) : 1;
+    if (n_block_parts > 1 && phases[0].n_tiles > 0xFFFFFF) return EPARA_ERR_SHAPE;
     for (int32_t p = 0; p < n_phases; ++p) {
         const epara_phase_schedule& ph = phases[p];
         visits[p].reserve(static_cast<size_t>(ph.n_tiles));
@@ -645,7 +715,10 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
                             for (int64_t tm = pm; tm < std::min<int64_t>(pm + panel_m, TM); ++tm) {
                                 const int64_t tile = first[p][g] + tm * TN + tn;
                                 if (tile >= ph.n_tiles - n_panel_split) continue;      // visited in parts, after the whole tiles
-                                to_panel_workgroup(p, static_cast<int32_t>(tile), panel_cost(ph.groups[g], ph.classes[c], ph.groups[g].M - tm * BM));
+                                const int64_t cost = panel_cost(ph.groups[g], ph.classes[c], ph.groups[g].M - tm * BM);
+                                const int32_t parts = BM == EPARA_BLOCK_ROWS && block_splits(ph.groups[g], ph.classes[c]) ? n_block_parts : 1;
+                                for (int32_t j = 0; j < parts; ++j)
+                                    to_panel_workgroup(p, EPARA_ORDER_ENTRY(static_cast<int32_t>(tile), j, parts), block_visit_cost(cost, parts));
                             }
             }
         }
@@ -816,13 +889,14 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
     for (size_t i = 0; i < order.size(); ++i)
         if (order[i] >= 0) {
             const epara_tile& tl = o.tiles[EPARA_ORDER_TILE(order[i])];
-            const int64_t cost = visit_cost(tile_cost(groups[tl.group], tl, o.classes, o.n_stream), (order[i] >> 28) + 1, groups[tl.group], tl, o.classes[tl.cls]);
+            const int64_t cost = visit_cost(tile_cost(groups[tl.group], tl, o.classes, o.n_stream), (order[i] >> 28) + 1, groups[tl.group], tl, o.classes[tl.cls],
+                                            tl.cls >= o.n_stream);
             if (tl.cls >= o.n_stream) load[i % W] += cost;
             else { stream[i % W] += cost; any_stream = true; }
         }
     *finish = *std::max_element(load.begin(), load.end()) +
               (any_stream ? *std::max_element(stream.begin(), stream.end()) + EPARA_COST_KERNEL : 0);
-    *take = *finish < other - other / 15;
+    *take = *finish < other;
     return EPARA_OK;
 }
 
@@ -962,6 +1036,8 @@ int32_t epara_plan_launch(const epara_group_desc* groups, int32_t G, int32_t in_
                                         &plan->n_split_tiles, &plan->workspace_bytes)) return s3;
     int32_t panel_parts = 1, panel_more = 0;
     plan->n_panel_split_tiles = panel_split_of(groups, G, plan->classes, plan->n_classes, plan->n_stream_classes, n_workgroups, &panel_parts, &panel_more);
+    if (plan->narrow == EPARA_TABLE_BLOCK)
+        plan->n_panel_split_tiles = epara_block_split(groups, G, plan->classes, plan->n_classes, plan->n_stream_classes, n_workgroups, split_base, &panel_parts);
     plan->workspace_bytes = epara_split_workspace_bytes(plan->n_split_tiles, plan->n_panel_split_tiles);
     if (row_off || x_off || y_off) {
         int64_t n = 0;
@@ -1054,14 +1130,15 @@ int64_t epara_workspace_bytes(const epara_group_desc* groups, int32_t G, int32_t
     int32_t gated = 0;
     if (gated_of(groups, G, &gated) != EPARA_OK) return -1;
     int64_t worst = 0;
-    for (int narrow = 0; narrow < 2; ++narrow) {
+    for (int narrow = 0; narrow < 3; ++narrow) {
         epara_tile_class classes[4];
         int32_t nc = 0, ns = 0, n_split = 0;
         int64_t bytes = 0;
         if (epara_kernel_classes(in_dtype, gated, narrow, classes, 4, &nc, &ns) != EPARA_OK) return -1;
         if (epara_split_layout(groups, G, classes, nc, ns, nullptr, &n_split, &bytes) != EPARA_OK) return -1;
         int32_t parts = 1, more = 0;
-        const int32_t n_panel = panel_split_of(groups, G, classes, nc, ns, n_workgroups, &parts, &more);
+        const int32_t n_panel = narrow == EPARA_TABLE_BLOCK ? epara_block_split(groups, G, classes, nc, ns, n_workgroups, nullptr, &parts)
+                                                            : panel_split_of(groups, G, classes, nc, ns, n_workgroups, &parts, &more);
         worst = std::max(worst, epara_split_workspace_bytes(n_split, n_panel));
     }
     return worst;
@@ -1086,7 +1163,7 @@ int32_t epara_kernel_classes(int32_t in_dtype, int32_t gated, int32_t narrow,
         table[n++] = {32, 32, gated ? 32 : 64, split_K};
         table[n++] = {64, 64, (gated ? 64 : 128) >> (narrow ? 1 : 0), split_K};
         ns = 3;
-        if (narrow == EPARA_TABLE_BLOCK) table[n++] = {INT32_MAX, EPARA_BLOCK_ROWS, gated ? 64 : 128, 0};
+        if (narrow == EPARA_TABLE_BLOCK) table[n++] = {INT32_MAX, EPARA_BLOCK_ROWS, gated ? 64 : 128, EPARA_BLOCK_SPLIT_K};
         else table[n++] = {INT32_MAX, 256, gated ? 128 : 256, (gated || in_dtype != EPARA_BF16) ? 0 : EPARA_PANEL_SPLIT_K};  // matrix-core class
     } else {
         return EPARA_ERR_DTYPE;

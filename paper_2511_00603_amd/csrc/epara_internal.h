@@ -7,8 +7,7 @@
 #include <stdint.h>
 
 #include "epara.h"
-
-#define EPARA_HIDDEN __attribute__((visibility("hidden")))
+#include "epara_plan.h"
 
 // `narrow` of a grouped kernel: 0 / 1, or this: the streaming tiles of the narrow table, tiles of other classes are passed over.
 #define EPARA_STREAM_TILES_ONLY 3
@@ -36,8 +35,8 @@ EPARA_HIDDEN hipError_t epara_enqueue_fp8_gated(int panel_only, unsigned grid, h
 EPARA_HIDDEN hipError_t epara_enqueue_f32(unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots);
 
 // One grouped launch of block tiles (the block table of epara_kernel_classes).
-EPARA_HIDDEN hipError_t epara_enqueue_block_bf16(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype);
-EPARA_HIDDEN hipError_t epara_enqueue_block_fp8(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype);
+EPARA_HIDDEN hipError_t epara_enqueue_block_bf16(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_panel_split);
+EPARA_HIDDEN hipError_t epara_enqueue_block_fp8(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_panel_split);
 
 // Chain kernels.  resident != NULL: no launch, *resident = workgroups of that kernel the current device holds at once.
 EPARA_HIDDEN hipError_t epara_chain_bf16_plain(const epara_chain_tables&, const epara_chain_scalars&, unsigned grid, hipStream_t, int64_t* resident);

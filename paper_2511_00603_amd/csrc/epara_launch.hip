@@ -61,6 +61,7 @@ int32_t check_split(const epara_launch* L, int32_t in_dtype, int narrow)
     for (int32_t g = 0; g < L->G; ++g) d[g] = {L->h_args[g].M, L->h_args[g].K, L->h_args[g].N, L->h_args[g].act, 0, 0};
     if (int32_t st = epara_split_layout(d.data(), L->G, cls, ncls, nstream, base.data(), &n_split, &bytes)) return st;
     if (int32_t st = epara_panel_split(d.data(), L->G, cls, ncls, nstream, L->n_workgroups, &n_panel, &parts, &more)) return st;
+    if (narrow == EPARA_TABLE_BLOCK) n_panel = epara_block_split(d.data(), L->G, cls, ncls, nstream, L->n_workgroups, base.data(), &parts);
     if (n_split != L->n_split_tiles || n_panel != L->n_panel_split_tiles) return EPARA_ERR_SHAPE;
     for (int32_t g = 0; g < L->G; ++g)
         if (base[g] >= 0 && L->h_args[g].reserved != base[g]) return EPARA_ERR_SHAPE;
@@ -149,10 +150,11 @@ int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int 
             e = (in_dtype == EPARA_BF16 ? (gated ? epara_enqueue_bf16_gated : epara_enqueue_bf16_plain)
                                         : (gated ? epara_enqueue_fp8_gated : epara_enqueue_fp8_plain))(
                 0, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype, EPARA_STREAM_TILES_ONLY, static_cast<uint32_t*>(L->d_workspace),
-                L->n_split_tiles, 0, 0);
+                L->n_split_tiles, L->n_panel_split_tiles, 0);
             if (e != hipSuccess) return EPARA_ERR_HIP;
         }
-        e = (in_dtype == EPARA_BF16 ? epara_enqueue_block_bf16 : epara_enqueue_block_fp8)(gated, 2 * grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype);
+        e = (in_dtype == EPARA_BF16 ? epara_enqueue_block_bf16 : epara_enqueue_block_fp8)(gated, 2 * grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype,
+                                                                                           static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, L->n_panel_split_tiles);
         return e == hipSuccess ? EPARA_OK : EPARA_ERR_HIP;
     }
     if (in_dtype == EPARA_F32)       e = epara_enqueue_f32(grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots);

@@ -106,7 +106,7 @@ class LaunchPlan:
             self.groups, in_dtype, n_workgroups, n_xcd, panel_m, panel_n)
         self.n_split_tiles, self.workspace_bytes = int(info.n_split_tiles), int(info.workspace_bytes)
         self.n_panel_split_tiles = int(info.n_panel_split_tiles)
-        if self.n_split_tiles:                               # where each group's split tiles meet in the workspace
+        if self.workspace_bytes:                             # where each group's split tiles meet in the workspace
             self.args["reserved"] = split_base
         self.makespan, self.narrow, self.classes, self.n_stream_classes = info.makespan, bool(info.narrow), info.class_table(), info.n_stream_classes
         self.plan_seconds = time.perf_counter() - t0

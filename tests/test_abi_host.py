@@ -553,7 +553,7 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
             best = (max(loads), cls, ns, rt, ro)
     bc, bn = B.epara_kernel_classes(dtype, gated, 2)
     bc = [tuple(int(v) for v in c) for c in bc]
-    assert bc[3] == (P.INT32_MAX, 128, 64 if gated else 128, 0) and bn == 3
+    assert bc[3] == (P.INT32_MAX, 128, 64 if gated else 128, 1024) and bn == 3
     assert bc[:3] == [tuple(int(v) for v in c) for c in B.epara_kernel_classes(dtype, gated, 1)[0][:3]]
     taken, rt, ro, finish = P.block_choice(ref, bc, *best[1:], W, 8, 1, 4)
     assert bool(taken) == block
@@ -563,8 +563,14 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
         for t in tiles:
             cover[int(t["group"])][t["m0"]: t["m0"] + t["rows"], t["n0"]: t["n0"] + t["cols"]] += 1
         assert all(np.all(c == 1) for c in cover.values())
-        base, n_split, nbytes = P.split_layout(shapes, bc, bn)
-        assert (split_base.tolist(), info.n_split_tiles, info.workspace_bytes, info.n_panel_split_tiles) == (base, n_split, nbytes, 0)
+        base, n_split, _ = P.split_layout(shapes, bc, bn)
+        parts, block_base, slots = P.block_split(ref, bc, bn, W)
+        base = [b if k is None else k for b, k in zip(base, block_base)]
+        assert (split_base.tolist(), info.n_split_tiles, info.n_panel_split_tiles) == (base, n_split, slots)
+        assert info.workspace_bytes == P.split_workspace_bytes(n_split, slots) <= B.epara_workspace_bytes(_desc(shapes, act), dtype, W)
+        seen = sorted(P.order_decode(int(e)) for e in order if e >= 0)
+        want = lambda t: (P.split_parts(shapes[t[0]][1], bc[t[5]]) if t[5] < bn else parts if block_base[t[0]] is not None else 1)
+        assert seen == sorted((i, j, want(t)) for i, t in enumerate(rt) for j in range(want(t)))
     assert B.epara_plan_launch(_desc(shapes, act), dtype, 120, 8, 1, 4)[0].narrow != 2
     if shapes and not gated:
         _, phases = B.epara_plan_chain([_desc(shapes, act), _desc(shapes, act)], [None, None], dtype, W, 8, 1, 4)

@@ -229,11 +229,41 @@ def test_block_tiles_at_the_edges_of_their_range(dtype_name, out_name):
 
 
 @pytest.mark.parametrize("dtype_name", ["bf16", "fp8"])
-@pytest.mark.parametrize("rows,d,ffn", [([3, 40, 300], 128, 352), ([20, 200], 256, 8224), ([75, 130, 237], 272, 208), ([97, 1], 48, 80)])
+def test_block_tiles_visited_in_parts(dtype_name):
+    """Block tiles of a long K: every number of parts (by the number of tiles of the launch), parts that cover two pairs only
+    and ones that go round the ring, ragged K, rows and columns, next to a streaming batch that is split itself.
+    Integer-valued operands: bit for bit, three calls in a row (the counters return to zero), then new activations at
+    the same addresses (a part of an earlier call must not be read)."""
+    rng = np.random.default_rng(31)
+    seen = set()
+    for shapes in ([(75, 1040, 130), (130, 2064, 200), (200, 4112, 72), (40, 8208, 136), (66, 512, 40)],
+                   [(300, 1552, 264), (97, 1024, 17)], [(1100, 3088, 1290)], [(600, 4112, 1900)]):
+        specs = []
+        for M, K, N in shapes:
+            specs.append({"X": rng.integers(-3, 4, (M, K)).astype(np.float32), "W": rng.integers(-2, 3, (K, N)).astype(np.float32),
+                          "b": rng.integers(-8, 9, N).astype(np.float32), "act": "relu" if M % 2 else "none", "s_x": 0.125, "s_w": 0.25})
+        G = U.Groups(specs, dtype_name)
+        assert int(G.plan.classes[-1][1]) == 128
+        seen |= {int(e >> 28) + 1 for e in G.plan.order if e >= 0 and G.plan.tiles[e & 0xFFFFFF]["cls"] == 3}
+        want = [ref.bf16_decode(ref.bf16_encode(y)) for y in G.expected()]
+        for rep in range(3):
+            for (M, K, N), y, yref in zip(shapes, G.run(), want):
+                assert np.array_equal(y, yref), (dtype_name, rep, M, K, N)
+        if dtype_name == "bf16":
+            for i, sp in enumerate(specs):
+                G.keep[3 * i].mul_(-2.0)
+                G.bits[i]["X"] = casts.bf16_bits(-2.0 * sp["X"])
+            for (M, K, N), y, yref in zip(shapes, G.run(), [ref.bf16_decode(ref.bf16_encode(y)) for y in G.expected()]):
+                assert np.array_equal(y, yref), ("rescaled", M, K, N)
+    assert seen == {1, 2, 3, 4}
+
+
+@pytest.mark.parametrize("dtype_name", ["bf16", "fp8"])
+@pytest.mark.parametrize("rows,d,ffn", [([3, 40, 300], 128, 352), ([20, 200], 256, 8224), ([70, 200], 2064, 80), ([75, 130, 237], 272, 208), ([97, 1], 48, 80)])
 def test_gated_block_tiles(dtype_name, rows, d, ffn):
     mix = make_mix(4, d=d, ffn=ffn, rows=rows)
     staged = StagedMix(mix, dtype_name, U.DEV, s_h=[1.0] * len(rows) if dtype_name == "fp8" else None)
-    assert int(staged.plans()[-1].classes[-1][1]) == 128 and (ffn > 8192 or int(staged.plans()[0].classes[-1][1]) == 128)
+    assert int(staged.plans()[-1].classes[-1][1]) == 128 == int(staged.plans()[0].classes[-1][1])
     check_mix(mix, dtype_name)
 
 
