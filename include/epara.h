@@ -369,11 +369,11 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * EPARA_COST_BLOCK_START.
  * Measured, bf16, 512 tiles at a time: K = 4096, own weights: 94 / 100 / 114 us for f = 1 / 2 / 4; weights shared by many row
  * tiles: 8.0 ns (K = 3072, N = 768) to 9.3 ns (K = 5120, N = 13824) per K and compute unit for f = 4, against 5.9 ns for a quarter of
- * a panel tile, which moves fewer bytes per product and so runs at higher clocks.  But a panel tile costs about 10 us of
+ * a panel tile, which moves fewer bytes per product and so runs at higher clocks.  But a panel tile costs about 9 us of
  * start and finish (EPARA_COST_PANEL_START), which one wave per SIMD cannot overlap with anything and two workgroups
  * per unit hide from each other.  The constants are fitted to both kernels' times on 112 launches (SwiGLU batches of 1
  * .. 2048 rows, K = 1120 .. 13824, bf16 and fp8; layers of vision transformers of 192 .. 1024 columns): where the model takes
- * block tiles they were 1.0 .. 4.3 times as fast, where it does not at most 1.3 times.
+ * block tiles they were 1.0 .. 4.3 times as fast, where it does not at most 1.4 times.
  *
  * Block tiles of a long K.  Few tiles of a long K (a down projection) leave units idle, so the tiles of the groups with
  * K >= EPARA_BLOCK_SPLIT_K (the block class's split_K) are visited in P = 1 .. EPARA_SPLIT_MAX_PARTS parts of K, the same P for the
@@ -389,11 +389,11 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 #define EPARA_TABLE_BLOCK 2               /* `narrow` of the block table */
 #define EPARA_BLOCK_ROWS 128
 #define EPARA_BLOCK_MIN_WORKGROUPS 128    /* smaller grids leave units free, where workgroups do not pair up */
-#define EPARA_COST_BLOCK_STREAM 1300
-#define EPARA_COST_BLOCK_STREAM_PER_32 90
-#define EPARA_COST_BLOCK_PER_32 210
-#define EPARA_COST_BLOCK_START 40000
-#define EPARA_COST_PANEL_START 900000
+#define EPARA_COST_BLOCK_STREAM 1200
+#define EPARA_COST_BLOCK_STREAM_PER_32 120
+#define EPARA_COST_BLOCK_PER_32 180
+#define EPARA_COST_BLOCK_START 80000
+#define EPARA_COST_PANEL_START 800000
 #define EPARA_BLOCK_SPLIT_K 1024
 #define EPARA_BLOCK_SPLIT_MAX_PER_LIST 3
 #define EPARA_BLOCK_TILES_PER_SLOT 3
@@ -530,7 +530,7 @@ typedef struct {
  * bf16 / fp8 launches with a batch of more than 64 rows and n_workgroups >= EPARA_BLOCK_MIN_WORKGROUPS, when its makespan T
  * (the largest load of block tiles, plus the largest load of streaming tiles and EPARA_COST_KERNEL if there are any) is
  * below U, the largest load of a workgroup in the order of the other choice with
- * EPARA_COST_PANEL_START added to every visit to a panel tile -- then plans
+ * EPARA_COST_PANEL_START added to every visit to a whole panel tile -- then plans
  * (epara_plan_groups) and schedules (epara_schedule_tiles) with it.  The groups must be all
  * EPARA_ACT_SWIGLU or none (ERR_DTYPE).  (A chain, epara_plan_chain with more than one phase, has no block tiles.)  *plan is always written (sizes included); tiles / order are
  * written when given and large enough, else ERR_CAPACITY (give NULL and 0 to ask for the sizes only;

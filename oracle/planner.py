@@ -212,11 +212,11 @@ def plan_groups(groups, classes):
 
 def panel_cost(M, K, cls, rows):
     """Cost of a tile of a panel class cls = (max_M, BM, BN[, split_K]) with `rows` rows of a group of M: 2040 * K, or for
-    a class of 128 rows (block tiles, f = ceil(rows / 32), s = ceil(M / 128)) K * max(1300 // s + 90 f, 210 f) + 40000."""
+    a class of 128 rows (block tiles, f = ceil(rows / 32), s = ceil(M / 128)) K * max(1200 // s + 120 f, 180 f) + 80000."""
     if cls[1] != 128:
         return 2040 * K
     f, s = -(-min(rows, 128) // 32), -(-M // 128)
-    return K * max(1300 // s + 90 * f, 210 * f) + 40000
+    return K * max(1200 // s + 120 * f, 180 * f) + 80000
 
 
 def split_parts(K, cls):
@@ -482,7 +482,7 @@ def block_choice(groups, block_classes, other_classes, other_n_stream, other_til
     and visit order of which are given) -> (taken, tiles, order, finish).  Considered when a batch has more than 64 rows
     and W >= 128.  finish = the largest load of
     a list in block tiles, plus the largest load in streaming tiles and 400000 if there are any; taken if that is below the largest load of
-    a workgroup in the other order where every visit to a panel tile costs 900000 more."""
+    a workgroup in the other order where every visit to a whole panel tile costs 800000 more."""
     W = n_workgroups
     if max((g[0] for g in groups), default=0) <= 64 or W < 128:
         return False, None, None, None
@@ -497,14 +497,14 @@ def block_choice(groups, block_classes, other_classes, other_n_stream, other_til
             g, cl = groups[tile[0]], classes[tile[5]]
             if tile[5] >= n_stream:
                 cost = panel_cost(g[0], g[1], cl, tile[3])
-                panel[slot % W] += (cost if parts == 1 else cost // parts + (500000 if cl[1] == 128 else 1020000)) + start
+                panel[slot % W] += cost + start if parts == 1 else cost // parts + (500000 if cl[1] == 128 else 1020000)
             else:
                 wide = tile[4] * (2 if len(g) > 3 and g[3] else 1)
                 cost = g[1] * (6 * wide + (2 * cl[1] if cl[1] >= 32 else 0))
                 stream[slot % W] += cost if parts == 1 else cost // parts + 24 * cl[1] * wide
         return panel, stream
 
-    panel, stream = loads(other_classes, other_n_stream, other_tiles, other_order, 900000)
+    panel, stream = loads(other_classes, other_n_stream, other_tiles, other_order, 800000)
     other = max(a + b for a, b in zip(panel, stream))
     n_stream = len(block_classes) - 1
     _, _, _, tiles = plan_groups([g[:3] for g in groups], block_classes)

@@ -873,7 +873,7 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
             const epara_tile& tl = best.tiles[EPARA_ORDER_TILE(best_order[i])];
             const bool panel = tl.cls >= best.n_stream;
             load[i % W] += visit_cost(tile_cost(groups[tl.group], tl, best.classes, best.n_stream), (best_order[i] >> 28) + 1, groups[tl.group], tl,
-                                      best.classes[tl.cls], panel) + (panel ? EPARA_COST_PANEL_START : 0);
+                                      best.classes[tl.cls], panel) + (panel && best_order[i] >> 28 == 0 ? EPARA_COST_PANEL_START : 0);
         }
     const int64_t other = *std::max_element(load.begin(), load.end());
     if (int32_t st = make_option(groups, G, in_dtype, gated, EPARA_TABLE_BLOCK, o)) return st;
