@@ -384,7 +384,7 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * sums (64 KiB) in the workspace and counts itself at the tile; whoever counts last adds the parts in index order and
  * runs the epilogue.  Three split tiles share a slot of a split panel tile: epara_launch.n_panel_split_tiles =
  * ceil(split block tiles / EPARA_BLOCK_TILES_PER_SLOT), and split_base[g] = index of the group's first tile among them.
- * Measured, bf16, 75 rows, K = 11008, N = 4096 (32 tiles): 106 -> 34 us in four parts; 563 rows, K = 2416, N = 2192 (90 tiles): 21 us in
+ * Measured, bf16, 74 rows, K = 11008, N = 4096 (32 tiles): 34 us in four parts (panel tiles in parts: 73); 563 rows, K = 2416, N = 2192 (90 tiles): 21 us in
  * three (panel tiles: 51). */
 #define EPARA_TABLE_BLOCK 2               /* `narrow` of the block table */
 #define EPARA_BLOCK_ROWS 128
