@@ -384,6 +384,7 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * sums (64 KiB) in the workspace and counts itself at the tile; whoever counts last adds the parts in index order and
  * runs the epilogue.  Three split tiles share a slot of a split panel tile: epara_launch.n_panel_split_tiles =
  * ceil(split block tiles / EPARA_BLOCK_TILES_PER_SLOT), and split_base[g] = index of the group's first tile among them.
+ * EPARA_BLOCK_TILES_PER_COUNTER of them share a counter, 4 bits each.
  * Measured, bf16, 74 rows, K = 11008, N = 4096 (32 tiles): 34 us in four parts (panel tiles in parts: 73); 563 rows, K = 2416, N = 2192 (90 tiles): 21 us in
  * three (panel tiles: 51). */
 #define EPARA_TABLE_BLOCK 2               /* `narrow` of the block table */
@@ -397,6 +398,7 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 #define EPARA_BLOCK_SPLIT_K 1024
 #define EPARA_BLOCK_SPLIT_MAX_PER_LIST 3
 #define EPARA_BLOCK_TILES_PER_SLOT 3
+#define EPARA_BLOCK_TILES_PER_COUNTER 8
 #define EPARA_COST_BLOCK_PARTIAL 500000
 #define EPARA_COST_KERNEL 400000          /* a second kernel: about 5 us */
 
@@ -444,7 +446,7 @@ int32_t epara_panel_split(const epara_group_desc* groups, int32_t G,
                           int32_t n_workgroups, int32_t* n_panel_split_tiles, int32_t* parts, int32_t* n_more);
 
 /* Bytes of the workspace of a launch with n_split_tiles split streaming tiles and n_panel_split_tiles split
- * panel tiles: 4 bytes of counter per split tile, rounded up to 256, then EPARA_SPLIT_MAX_PARTS parts of
+ * panel tiles (or slots of split block tiles): 4 bytes of counter per split tile, rounded up to 256, then EPARA_SPLIT_MAX_PARTS parts of
  * EPARA_SPLIT_STRIDE bytes per streaming tile, then EPARA_SPLIT_MAX_PARTS parts of EPARA_PANEL_SPLIT_STRIDE bytes
  * per panel tile; 0 if both counts are 0, -1 if one is negative. */
 int64_t epara_split_workspace_bytes(int32_t n_split_tiles, int32_t n_panel_split_tiles);
@@ -458,6 +460,10 @@ int64_t epara_split_workspace_bytes(int32_t n_split_tiles, int32_t n_panel_split
  * n_panel_split_tiles from epara_panel_split) and provides a workspace of
  * epara_split_workspace_bytes(n_split_tiles, n_panel_split_tiles) bytes, zeroed once with epara_workspace_init
  * (a launch leaves its counters zero).  epara_plan_launch does all of this.
+ * A launch's partial sums follow its counters, rounded up to 256 bytes, so launches that run one after the other may
+ * share a workspace if their counters take the same room: ceil(c / 64) is the same, with c = n_split_tiles +
+ * n_panel_split_tiles (block table: n_split_tiles + ceil(3 n_panel_split_tiles / 8)).  Otherwise each needs its own, or
+ * the workspace is zeroed in between: the sums of the one would lie where the other counts.
  * More than 2^24 tiles -> ERR_SHAPE. */
 int32_t epara_split_layout(const epara_group_desc* groups, int32_t G,
                            const epara_tile_class* classes, int32_t n_classes, int32_t n_stream_classes,

@@ -23,19 +23,16 @@ namespace {
 constexpr int BLOCK_RING = 4;                                    // pairs in flight or being read
 constexpr int BLOCK_LDS_BYTES = BLOCK_RING * 128 * 128;          // 64 KiB; the epilogue parks the tile's outputs in the same place
 
-// Split block tiles: three of them per slot of the panel tiles' workspace (four parts of 64 KiB each), their counters behind.
-constexpr int BLOCK_PART_BYTES = 65536, BLOCK_TILES_PER_SLOT = EPARA_BLOCK_TILES_PER_SLOT;
-constexpr int BLOCK_SLOT_BYTES = SPLIT_MAX_PARTS * PANEL_SPLIT_STRIDE;
-static_assert(BLOCK_TILES_PER_SLOT * SPLIT_MAX_PARTS * BLOCK_PART_BYTES + BLOCK_TILES_PER_SLOT * 4 <= BLOCK_SLOT_BYTES, "a slot is too small");
+// Split block tiles: three of them per slot of the panel tiles' workspace (four parts of 64 KiB each).  They count in
+// front of all partial sums like every other split tile, eight tiles to a counter: partial sums never land on the counters of
+// a launch that uses the same workspace later, unless those take more room.  sp.n_panel: the counters, sp.first_panel: the tiles.
+constexpr int BLOCK_PART_BYTES = 65536, BLOCK_TILES_PER_SLOT = EPARA_BLOCK_TILES_PER_SLOT, BLOCK_COUNTER_BITS = 32 / EPARA_BLOCK_TILES_PER_COUNTER;
+static_assert(BLOCK_TILES_PER_SLOT * SPLIT_MAX_PARTS * BLOCK_PART_BYTES <= SPLIT_MAX_PARTS * PANEL_SPLIT_STRIDE, "a slot is too small");
+static_assert(SPLIT_MAX_PARTS < (1 << BLOCK_COUNTER_BITS), "a tile's bits of a counter hold its parts");
 __device__ __forceinline__ char* block_partials(const split_ctx& sp, int tile)
 {
-    return panel_partials(sp) + static_cast<size_t>(tile / BLOCK_TILES_PER_SLOT) * BLOCK_SLOT_BYTES +
+    return panel_partials(sp) + static_cast<size_t>(tile / BLOCK_TILES_PER_SLOT) * (SPLIT_MAX_PARTS * PANEL_SPLIT_STRIDE) +
            (tile % BLOCK_TILES_PER_SLOT) * (SPLIT_MAX_PARTS * BLOCK_PART_BYTES);
-}
-__device__ __forceinline__ uint32_t* block_counter(const split_ctx& sp, int tile)
-{
-    return reinterpret_cast<uint32_t*>(panel_partials(sp) + static_cast<size_t>(tile / BLOCK_TILES_PER_SLOT) * BLOCK_SLOT_BYTES +
-                                       BLOCK_TILES_PER_SLOT * (SPLIT_MAX_PARTS * BLOCK_PART_BYTES)) + tile % BLOCK_TILES_PER_SLOT;
 }
 
 // entry: the visit; a tile of a long K may be visited in parts (EPARA_BLOCK_SPLIT_K).  A part leaves its raw sums in the
@@ -62,7 +59,7 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
     const int slot_tile = parts > 1 ? ga.reserved + (tl.m0 >> 7) * ((N + (GATED ? 63 : 127)) / (GATED ? 64 : 128)) + tl.n0 / (GATED ? 64 : 128) : 0;
     // parts without a workspace, or more of them than it holds: not an order that the library's planner writes; the visit is
     // dropped rather than let it write outside
-    if (parts > 1 && (sp.ws == nullptr || parts > SPLIT_MAX_PARTS || ga.reserved < 0 || slot_tile >= sp.n_panel * BLOCK_TILES_PER_SLOT)) return;
+    if (parts > 1 && (sp.ws == nullptr || parts > SPLIT_MAX_PARTS || ga.reserved < 0 || slot_tile >= sp.first_panel)) return;
     // this visit's pairs: whole units of two
     const uint32_t units = static_cast<uint32_t>(KSP >> 2);
     const int first_pair = 2 * static_cast<int>(units * part / parts), n_pairs = 2 * static_cast<int>(units * (part + 1) / parts) - first_pair;
@@ -253,13 +250,14 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
         wait_vmcnt<0>();
         __syncthreads();                                         // every wave's sums are in memory
         __attribute__((address_space(3))) uint32_t* box = (__attribute__((address_space(3))) uint32_t*)l3;
-        uint32_t* counter = block_counter(sp, slot_tile);
-        if (tid == 0) *box = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t* counter = sp.ws + sp.n_split + slot_tile / EPARA_BLOCK_TILES_PER_COUNTER;
+        const int shift = slot_tile % EPARA_BLOCK_TILES_PER_COUNTER * BLOCK_COUNTER_BITS;
+        if (tid == 0) *box = (__hip_atomic_fetch_add(counter, 1u << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> shift) & ((1u << BLOCK_COUNTER_BITS) - 1);
         __syncthreads();
         const bool last = *box == static_cast<uint32_t>(parts - 1);
         __syncthreads();                                         // the box's place in the LDS is free again
         if (!last) return;
-        if (tid == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) (void)__hip_atomic_fetch_sub(counter, static_cast<uint32_t>(parts) << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         auto add = [&](auto n_tag) {
             constexpr int P = decltype(n_tag)::value;
 #pragma unroll
@@ -365,9 +363,9 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
 template <int DT, bool GATED>
 __global__ __launch_bounds__(NT, 2) void grouped_block_kernel(const epara_group_args* __restrict__ args, const epara_tile* __restrict__ tiles,
                                                               const int32_t* __restrict__ order, long n_slots, int out_dtype,
-                                                              uint32_t* split_ws, int n_split, int n_panel_split)
+                                                              uint32_t* split_ws, int n_split, int n_counters, int n_tiles)
 {
-    const split_ctx sp = {split_ws, n_split, n_panel_split, 0};
+    const split_ctx sp = {split_ws, n_split, n_counters, n_tiles};
     extern __shared__ __attribute__((aligned(16))) char lds[];
     for (long s = blockIdx.x; s < n_slots; s += gridDim.x) {
         const int t = order[s];
@@ -385,12 +383,12 @@ __global__ __launch_bounds__(NT, 2) void grouped_block_kernel(const epara_group_
 
 template <int DT, bool GATED>
 hipError_t enqueue_block(unsigned grid, hipStream_t stream, const epara_group_args* args, const epara_tile* tiles,
-                         const int32_t* order, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_panel_split)
+                         const int32_t* order, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles)
 {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_block_kernel<DT, GATED>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, BLOCK_LDS_BYTES);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((grouped_block_kernel<DT, GATED>), dim3(grid), dim3(NT), BLOCK_LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, split_ws, n_split, n_panel_split);
+    hipLaunchKernelGGL((grouped_block_kernel<DT, GATED>), dim3(grid), dim3(NT), BLOCK_LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, split_ws, n_split, n_counters, n_tiles);
     return hipGetLastError();
 }
 

@@ -34,9 +34,10 @@ EPARA_HIDDEN hipError_t epara_enqueue_fp8_plain(int panel_only, unsigned grid, h
 EPARA_HIDDEN hipError_t epara_enqueue_fp8_gated(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split);
 EPARA_HIDDEN hipError_t epara_enqueue_f32(unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots);
 
-// One grouped launch of block tiles (the block table of epara_kernel_classes).
-EPARA_HIDDEN hipError_t epara_enqueue_block_bf16(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_panel_split);
-EPARA_HIDDEN hipError_t epara_enqueue_block_fp8(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_panel_split);
+// One grouped launch of block tiles (the block table of epara_kernel_classes).  n_counters: of the split ones, behind the n_split
+// of the streaming tiles; n_tiles: how many of them the workspace holds.
+EPARA_HIDDEN hipError_t epara_enqueue_block_bf16(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles);
+EPARA_HIDDEN hipError_t epara_enqueue_block_fp8(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles);
 
 // Chain kernels.  resident != NULL: no launch, *resident = workgroups of that kernel the current device holds at once.
 EPARA_HIDDEN hipError_t epara_chain_bf16_plain(const epara_chain_tables&, const epara_chain_scalars&, unsigned grid, hipStream_t, int64_t* resident);

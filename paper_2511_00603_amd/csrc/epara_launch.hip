@@ -145,16 +145,18 @@ int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int 
     (void)hipGetLastError();
     hipError_t e;
     if (narrow == EPARA_TABLE_BLOCK) {
+        const int n_tiles = EPARA_BLOCK_TILES_PER_SLOT * L->n_panel_split_tiles;
+        const int n_counters = (n_tiles + EPARA_BLOCK_TILES_PER_COUNTER - 1) / EPARA_BLOCK_TILES_PER_COUNTER;
         // streaming tiles first, in a kernel that passes over the block tiles; then those, two workgroups per compute unit
         if (n_stream > 0) {
             e = (in_dtype == EPARA_BF16 ? (gated ? epara_enqueue_bf16_gated : epara_enqueue_bf16_plain)
                                         : (gated ? epara_enqueue_fp8_gated : epara_enqueue_fp8_plain))(
                 0, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype, EPARA_STREAM_TILES_ONLY, static_cast<uint32_t*>(L->d_workspace),
-                L->n_split_tiles, L->n_panel_split_tiles, 0);
+                L->n_split_tiles, n_counters, 0);
             if (e != hipSuccess) return EPARA_ERR_HIP;
         }
         e = (in_dtype == EPARA_BF16 ? epara_enqueue_block_bf16 : epara_enqueue_block_fp8)(gated, 2 * grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype,
-                                                                                           static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, L->n_panel_split_tiles);
+                                                                                           static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, n_counters, n_tiles);
         return e == hipSuccess ? EPARA_OK : EPARA_ERR_HIP;
     }
     if (in_dtype == EPARA_F32)       e = epara_enqueue_f32(grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots);

@@ -258,6 +258,32 @@ def test_block_tiles_visited_in_parts(dtype_name):
     assert seen == {1, 2, 3, 4}
 
 
+def test_launches_with_split_tiles_take_turns_on_one_workspace():
+    """Panel tiles in four parts, streaming tiles in two, block tiles in parts and both kinds in one launch, all on one
+    workspace that is zeroed once: the counters lie in front of every launch's partial sums, so each launch finds its own
+    at zero whatever ran before it.  Integer-valued operands: bit for bit, in three different orders."""
+    rng = np.random.default_rng(37)
+    groups = []
+    for shapes, W_, kind in (([(300, 2064, 500), (600, 2064, 300)], 8, 256), ([(40, 8208, 200), (17, 8192, 70)], None, None),
+                             ([(300, 1552, 264), (97, 1024, 17)], None, 128), ([(75, 1040, 130), (200, 4112, 72), (40, 8208, 136)], None, 128)):
+        specs = [{"X": rng.integers(-3, 4, (M, K)).astype(np.float32), "W": rng.integers(-2, 3, (K, N)).astype(np.float32),
+                  "b": rng.integers(-8, 9, N).astype(np.float32), "act": "relu" if M % 2 else "none"} for M, K, N in shapes]
+        G = U.Groups(specs, "bf16", n_workgroups=W_)
+        assert kind is None or int(G.plan.classes[-1][1]) == kind
+        assert 0 < G.plan.n_split_tiles + G.plan.n_panel_split_tiles <= 64          # as many counters as share a workspace
+        assert max(int(e >> 28) + 1 for e in G.plan.order if e >= 0) == (2 if kind is None else 4)
+        groups.append((shapes, G, [ref.bf16_decode(ref.bf16_encode(y)) for y in G.expected()]))
+    ws = torch.empty(max(G.plan.workspace_bytes for _, G, _ in groups), dtype=torch.uint8, device=U.DEV)
+    B.epara_workspace_init(ws.data_ptr(), ws.numel(), R.current_stream_handle())
+    for _, G, _ in groups:
+        G.plan.c.d_workspace, G.plan.c.workspace_bytes = ws.data_ptr(), ws.numel()
+    for turn in ([0, 2, 1, 3], [3, 0, 3, 2], [2, 1, 0, 2, 3, 0]):
+        for i in turn:
+            shapes, G, want = groups[i]
+            for sh, y, yref in zip(shapes, G.run(), want):
+                assert np.array_equal(y, yref), (turn, i, sh)
+
+
 @pytest.mark.parametrize("dtype_name", ["bf16", "fp8"])
 @pytest.mark.parametrize("rows,d,ffn", [([3, 40, 300], 128, 352), ([20, 200], 256, 8224), ([70, 200], 2064, 80), ([75, 130, 237], 272, 208), ([97, 1], 48, 80)])
 def test_gated_block_tiles(dtype_name, rows, d, ffn):
