@@ -437,7 +437,8 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * A visit leaves its 256 x 256 fp32 sums (EPARA_PANEL_SPLIT_STRIDE bytes) in the workspace, behind the streaming
  * tiles' slots; counting and the addition in index order work as for streaming tiles.  epara_panel_split states
  * the decision (*parts = P of the first tiles, *n_more = how many of the last tiles get P + 1); it depends on the
- * grid size. */
+ * grid size.  For a class table with block tiles it states theirs: *n_panel_split_tiles = the slots they need
+ * (0 if they are not split), *parts = P, *n_more = 0. */
 #define EPARA_PANEL_SPLIT_STRIDE 262144   /* bytes of partial sums per (split panel tile, part) */
 #define EPARA_PANEL_SPLIT_K 1024          /* every part then holds whole units of four stages, bf16 or fp8 */
 #define EPARA_COST_PANEL_PARTIAL 1020000  /* a part's trip through memory, in cost units (about 500 elements of K) */
@@ -454,8 +455,9 @@ int64_t epara_split_workspace_bytes(int32_t n_split_tiles, int32_t n_panel_split
 #define EPARA_ORDER_TILE(entry) ((entry) & 0xFFFFFF)
 
 /* Where the split tiles of a launch meet: split_base[g] (G entries) = index of the first split tile of
- * group g among all split tiles of the launch (its tiles follow in n0 order), or -1 if the tiles of g are
- * not split; *n_split_tiles = their number; *workspace_bytes = epara_split_workspace_bytes(n_split_tiles, 0).
+ * group g among all split streaming tiles of the launch (its tiles follow in n0 order), or -1 if the tiles of g are
+ * not split; *n_split_tiles = their number; a group of block tiles that may be split (K >= the class's split_K) gets the index
+ * of its first tile among those, which means something only if epara_panel_split splits them; *workspace_bytes = epara_split_workspace_bytes(n_split_tiles, 0).
  * The caller writes split_base[g] into epara_group_args.reserved, sets epara_launch.n_split_tiles (and
  * n_panel_split_tiles from epara_panel_split) and provides a workspace of
  * epara_split_workspace_bytes(n_split_tiles, n_panel_split_tiles) bytes, zeroed once with epara_workspace_init

@@ -235,8 +235,9 @@ def order_decode(entry):
 
 
 def split_layout(groups, classes, n_stream_classes):
-    """-> (split_base per group, number of split tiles, workspace bytes): see epara_split_layout in the header."""
-    base, n = [], 0
+    """-> (split_base per group, number of split streaming tiles, their workspace bytes): see epara_split_layout in the
+    header.  Groups of block tiles that may be split are numbered on their own, and not counted."""
+    base, n, n_block = [], 0, 0
     for M, K, N in (g[:3] for g in groups):
         b = -1
         if M > 0:
@@ -244,6 +245,9 @@ def split_layout(groups, classes, n_stream_classes):
             if c < n_stream_classes and split_parts(K, classes[c]) > 1:
                 b = n
                 n += -(-M // classes[c][1]) * -(-N // classes[c][2])
+            elif c >= n_stream_classes and classes[c][1] == 128 and len(classes[c]) > 3 and 0 < classes[c][3] <= K:
+                b = n_block
+                n_block += -(-M // 128) * -(-N // classes[c][2])
         base.append(b)
     return base, n, (0 if n == 0 else (n * 4 + 255) // 256 * 256 + n * 4 * 32768)
 

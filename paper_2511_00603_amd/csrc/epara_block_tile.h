@@ -55,15 +55,18 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
     ldsptr l3 = (ldsptr)lds;
     const int K = ga.K, N = ga.N, rows = tl.rows, cols = tl.cols;
     const int KSP = ((K + KF - 1) / KF + 3) & ~3;
-    const int parts = order_parts(entry), part = order_part(entry);
+    const uint32_t units = static_cast<uint32_t>(KSP >> 2);      // a visit covers whole units of two pairs
+    const int part = order_part(entry);
+    int parts = order_parts(entry);
     const int slot_tile = parts > 1 ? ga.reserved + (tl.m0 >> 7) * ((N + (GATED ? 63 : 127)) / (GATED ? 64 : 128)) + tl.n0 / (GATED ? 64 : 128) : 0;
-    // parts without a workspace, or more of them than it holds: not an order that the library's planner writes; the visit is
-    // dropped rather than let it write outside
-    if (parts > 1 && (sp.ws == nullptr || parts > SPLIT_MAX_PARTS || ga.reserved < 0 || slot_tile >= sp.first_panel)) return;
-    // this visit's pairs: whole units of two
-    const uint32_t units = static_cast<uint32_t>(KSP >> 2);
+    // the launch brought no room for the parts' sums (or holds more parts than there are units): the first visit multiplies
+    // the whole K
+    if (parts > 1 && (sp.ws == nullptr || parts > SPLIT_MAX_PARTS || ga.reserved < 0 || slot_tile >= sp.first_panel || static_cast<uint32_t>(parts) > units)) {
+        if (part != 0) return;
+        parts = 1;
+    }
+    if (part >= parts) return;                                   // no entry of a planner
     const int first_pair = 2 * static_cast<int>(units * part / parts), n_pairs = 2 * static_cast<int>(units * (part + 1) / parts) - first_pair;
-    if (n_pairs < 2) return;                                     // fewer units than parts: likewise
 
     // ---- activations: instruction j of a pair covers rows 8 (4 j + wave) .. + 7; lane l writes chunk l % 8 of row l / 8
     // and fetches the chunk that belongs there (chunk ^ (row / 2) % 8: fragment reads are free of bank conflicts)

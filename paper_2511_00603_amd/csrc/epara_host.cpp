@@ -218,7 +218,7 @@ inline int64_t visit_cost(int64_t cost, int32_t parts, const epara_group_desc& d
 }  // namespace
 
 int32_t epara_block_split(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
-                          int32_t n_stream_classes, int64_t W, int32_t* base, int32_t* parts)
+                          int32_t n_stream_classes, int64_t W, int32_t* parts)
 {
     *parts = block_parts(groups, G, classes, n_classes, n_stream_classes, W);
     if (*parts == 1) return 0;
@@ -227,9 +227,7 @@ int32_t epara_block_split(const epara_group_desc* groups, int32_t G, const epara
         const epara_group_desc& d = groups[g];
         if (d.M <= 0 || !block_group(d, classes, n_classes, n_stream_classes)) continue;
         const epara_tile_class& c = classes[class_of(d.M, classes, n_classes)];
-        if (!block_splits(d, c)) continue;
-        if (base) base[g] = static_cast<int32_t>(n);
-        n += ceil_div(d.M, c.BM) * ceil_div(d.N, c.BN);
+        if (block_splits(d, c)) n += ceil_div(d.M, c.BM) * ceil_div(d.N, c.BN);
     }
     return static_cast<int32_t>(ceil_div(n, EPARA_BLOCK_TILES_PER_SLOT));
 }
@@ -1035,9 +1033,8 @@ int32_t epara_plan_launch(const epara_group_desc* groups, int32_t G, int32_t in_
     if (int32_t s3 = epara_split_layout(groups, G, plan->classes, plan->n_classes, plan->n_stream_classes, split_base,
                                         &plan->n_split_tiles, &plan->workspace_bytes)) return s3;
     int32_t panel_parts = 1, panel_more = 0;
-    plan->n_panel_split_tiles = panel_split_of(groups, G, plan->classes, plan->n_classes, plan->n_stream_classes, n_workgroups, &panel_parts, &panel_more);
-    if (plan->narrow == EPARA_TABLE_BLOCK)
-        plan->n_panel_split_tiles = epara_block_split(groups, G, plan->classes, plan->n_classes, plan->n_stream_classes, n_workgroups, split_base, &panel_parts);
+    if (int32_t s4 = epara_panel_split(groups, G, plan->classes, plan->n_classes, plan->n_stream_classes, n_workgroups,
+                                       &plan->n_panel_split_tiles, &panel_parts, &panel_more)) return s4;
     plan->workspace_bytes = epara_split_workspace_bytes(plan->n_split_tiles, plan->n_panel_split_tiles);
     if (row_off || x_off || y_off) {
         int64_t n = 0;
@@ -1076,7 +1073,7 @@ int32_t epara_split_layout(const epara_group_desc* groups, int32_t G,
     if (!n_split_tiles || !workspace_bytes || (G > 0 && !groups)) return EPARA_ERR_NULL;
     if (int32_t st = check_classes(classes, n_classes)) return st;
     if (n_stream_classes < 0 || n_stream_classes > n_classes) return EPARA_ERR_SHAPE;
-    int64_t n = 0;
+    int64_t n = 0, n_block = 0;
     for (int32_t g = 0; g < G; ++g) {
         const epara_group_desc& d = groups[g];
         if (d.M < 0 || d.K <= 0 || d.N <= 0) return EPARA_ERR_SHAPE;
@@ -1087,6 +1084,9 @@ int32_t epara_split_layout(const epara_group_desc* groups, int32_t G,
             if (c < n_stream_classes && split_parts(d, classes[c]) > 1) {
                 base = static_cast<int32_t>(n);
                 n += ceil_div(d.M, classes[c].BM) * ceil_div(d.N, classes[c].BN);
+            } else if (c >= n_stream_classes && classes[c].BM == EPARA_BLOCK_ROWS && block_splits(d, classes[c])) {
+                base = n_block > 0xFFFFFF ? -1 : static_cast<int32_t>(n_block);      // so many are never split
+                n_block += ceil_div(d.M, classes[c].BM) * ceil_div(d.N, classes[c].BN);
             }
         }
         if (split_base) split_base[g] = base;
@@ -1119,6 +1119,8 @@ int32_t epara_panel_split(const epara_group_desc* groups, int32_t G,
         if (groups[g].M > 0 && class_of(groups[g].M, classes, n_classes) < 0) return EPARA_ERR_SHAPE;
     }
     *n_panel_split_tiles = panel_split_of(groups, G, classes, n_classes, n_stream_classes, n_workgroups, parts, n_more);
+    for (int32_t c = n_stream_classes; c < n_classes; ++c)
+        if (classes[c].BM == EPARA_BLOCK_ROWS) *n_panel_split_tiles = epara_block_split(groups, G, classes, n_classes, n_stream_classes, n_workgroups, parts);
     return EPARA_OK;
 }
 
@@ -1137,7 +1139,7 @@ int64_t epara_workspace_bytes(const epara_group_desc* groups, int32_t G, int32_t
         if (epara_kernel_classes(in_dtype, gated, narrow, classes, 4, &nc, &ns) != EPARA_OK) return -1;
         if (epara_split_layout(groups, G, classes, nc, ns, nullptr, &n_split, &bytes) != EPARA_OK) return -1;
         int32_t parts = 1, more = 0;
-        const int32_t n_panel = narrow == EPARA_TABLE_BLOCK ? epara_block_split(groups, G, classes, nc, ns, n_workgroups, nullptr, &parts)
+        const int32_t n_panel = narrow == EPARA_TABLE_BLOCK ? epara_block_split(groups, G, classes, nc, ns, n_workgroups, &parts)
                                                             : panel_split_of(groups, G, classes, nc, ns, n_workgroups, &parts, &more);
         worst = std::max(worst, epara_split_workspace_bytes(n_split, n_panel));
     }

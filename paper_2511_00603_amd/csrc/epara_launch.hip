@@ -61,10 +61,10 @@ int32_t check_split(const epara_launch* L, int32_t in_dtype, int narrow)
     for (int32_t g = 0; g < L->G; ++g) d[g] = {L->h_args[g].M, L->h_args[g].K, L->h_args[g].N, L->h_args[g].act, 0, 0};
     if (int32_t st = epara_split_layout(d.data(), L->G, cls, ncls, nstream, base.data(), &n_split, &bytes)) return st;
     if (int32_t st = epara_panel_split(d.data(), L->G, cls, ncls, nstream, L->n_workgroups, &n_panel, &parts, &more)) return st;
-    if (narrow == EPARA_TABLE_BLOCK) n_panel = epara_block_split(d.data(), L->G, cls, ncls, nstream, L->n_workgroups, base.data(), &parts);
+    if (narrow == EPARA_TABLE_BLOCK) n_panel = epara_block_split(d.data(), L->G, cls, ncls, nstream, L->n_workgroups, &parts);
     if (n_split != L->n_split_tiles || n_panel != L->n_panel_split_tiles) return EPARA_ERR_SHAPE;
     for (int32_t g = 0; g < L->G; ++g)
-        if (base[g] >= 0 && L->h_args[g].reserved != base[g]) return EPARA_ERR_SHAPE;
+        if (base[g] >= 0 && (n_panel > 0 || d[g].M <= cls[nstream - 1].max_M) && L->h_args[g].reserved != base[g]) return EPARA_ERR_SHAPE;
     if (!L->d_workspace) return EPARA_ERR_NULL;
     if (reinterpret_cast<uintptr_t>(L->d_workspace) % 256 != 0) return EPARA_ERR_ALIGN;
     if (L->workspace_bytes < epara_split_workspace_bytes(n_split, n_panel)) return EPARA_ERR_CAPACITY;

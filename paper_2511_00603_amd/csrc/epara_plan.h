@@ -9,8 +9,8 @@
 #define EPARA_HIDDEN __attribute__((visibility("hidden")))
 
 // Block tiles visited in parts of K ("Block tiles" in the header): *parts, and the slots (three tiles each) they need in the
-// workspace; base[g] = first split block tile of group g (other entries are left alone).  Shapes and classes are valid.
+// workspace.  Shapes and classes are valid.
 EPARA_HIDDEN int32_t epara_block_split(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
-                                       int32_t n_stream_classes, int64_t W, int32_t* base, int32_t* parts);
+                                       int32_t n_stream_classes, int64_t W, int32_t* parts);
 
 #endif

@@ -577,6 +577,25 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
         assert all(ph["info"].narrow != 2 for ph in phases)
 
 
+@pytest.mark.parametrize("shapes", [[(100, 4096, 4096)], [(75, 1040, 130), (130, 2064, 200), (40, 8208, 136)], [(66, 512, 40)]])
+def test_a_block_launch_can_be_composed_from_the_single_calls(shapes):
+    """Class table, tiles, visit order, split layout and number of split tiles asked for one by one: whenever the order visits
+    block tiles in parts, the other calls say where the parts meet, as epara_plan_launch does for the same groups."""
+    g, W = _desc(shapes), 256
+    cls, ns = B.epara_kernel_classes(B.EPARA_BF16, 0, 2)
+    tiles = B.epara_plan_groups(g, cls)[3]
+    order = B.epara_schedule_tiles(g, cls, ns, tiles, W, 8, 1, 4)
+    base, n_split, _ = B.epara_split_layout(g, cls, ns)
+    slots, parts, more = B.epara_panel_split(g, cls, ns, W)
+    table = [tuple(int(v) for v in c) for c in cls]
+    assert (list(base), n_split) == P.split_layout(shapes, table, ns)[:2]
+    assert (parts, slots) == P.block_split(shapes, table, ns, W)[::2] and more == 0
+    assert {P.order_decode(int(e))[2] for e in order if e >= 0 and tiles[P.order_decode(int(e))[0]]["cls"] >= ns} == {parts} | ({1} if len(shapes) > 1 and shapes[0][1] < 1024 else set())
+    info, _, _, _, t2, o2, base2 = B.epara_plan_launch(g, B.EPARA_BF16, W)
+    assert info.narrow == 2 and (info.n_split_tiles, info.n_panel_split_tiles) == (n_split, slots)
+    assert t2.tolist() == tiles.tolist() and o2.tolist() == order.tolist() and base2.tolist() == list(base)
+
+
 def test_plan_chain_picks_tables_jointly_and_writes_waits():
     """epara_plan_chain on the decode FFN (gate/up then down): both phases may take either table; whatever it
     picks, the plan is valid, the waits are those of epara_chain_waits, and no other combination finishes

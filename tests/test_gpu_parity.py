@@ -258,6 +258,18 @@ def test_block_tiles_visited_in_parts(dtype_name):
     assert seen == {1, 2, 3, 4}
 
 
+def test_block_tiles_in_parts_without_a_workspace_are_still_computed():
+    """An order with parts in a launch that states no split tiles: the first visit of a tile multiplies the whole K."""
+    rng = np.random.default_rng(41)
+    specs = [{"X": rng.integers(-3, 4, (M, K)).astype(np.float32), "W": rng.integers(-2, 3, (K, N)).astype(np.float32),
+              "b": rng.integers(-8, 9, N).astype(np.float32), "act": "none"} for M, K, N in ((100, 1040, 200), (300, 2064, 72))]
+    G = U.Groups(specs, "bf16")
+    assert int(G.plan.classes[-1][1]) == 128 and G.plan.n_split_tiles == 0 and max(int(e >> 28) for e in G.plan.order if e >= 0) > 0
+    G.plan.c.n_panel_split_tiles, G.plan.c.d_workspace, G.plan.c.workspace_bytes = 0, None, 0
+    for y, yref in zip(G.run(), G.expected()):
+        assert np.array_equal(y, ref.bf16_decode(ref.bf16_encode(yref)))
+
+
 def test_launches_with_split_tiles_take_turns_on_one_workspace():
     """Panel tiles in four parts, streaming tiles in two, block tiles in parts and both kinds in one launch, all on one
     workspace that is zeroed once: the counters lie in front of every launch's partial sums, so each launch finds its own
