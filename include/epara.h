@@ -376,7 +376,8 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * block tiles they were 1.0 .. 4.3 times as fast, where it does not at most 1.4 times.
  *
  * Block tiles of a long K.  Few tiles of a long K (a down projection) leave units idle, so the tiles of the groups with
- * K >= EPARA_BLOCK_SPLIT_K (the block class's split_K) are visited in P = 1 .. EPARA_SPLIT_MAX_PARTS parts of K, the same P for the
+ * K >= the block class's split_K > 0 (EPARA_BLOCK_SPLIT_K for plain bf16 launches; 0 for gated and fp8 ones, whose results do not
+ * depend on the grid or on the other groups) are visited in P = 1 .. EPARA_SPLIT_MAX_PARTS parts of K, the same P for the
  * whole launch: part j covers the units floor(U j / P) .. floor(U (j+1) / P) - 1 of the U = ceil(ceil(K / stage) / 4) units of
  * four 64-byte stages.  P is the one whose visits, the groups by descending cost of their first tile (ties: lower group), tiles
  * in table order, part by part, each to the least loaded of W lists, finish first (ties: fewer parts); 1 if the launch has more than
@@ -633,8 +634,10 @@ int32_t epara_pack_weights(const void* d_W, int32_t K, int32_t N, int32_t dtype,
  * pre-placement, epara_pack_weights).
  * Y_g = act_g(s_g X_g W_g + b_g) for all groups of the launch, in one persistent kernel
  * that walks the device tile table in the scheduled order; bias, activation, SwiGLU gating
- * and the output cast are fused in the epilogue.  Accumulation is fp32 in a fixed order
- * (bit-reproducible, independent of n_workgroups).
+ * and the output cast are fused in the epilogue.  Accumulation is fp32 in a fixed order (bit-reproducible).  The order
+ * does not depend on n_workgroups or on the other groups, except in plain bf16 launches with batches of more than 64 rows and
+ * K >= 1024: how many parts of K their panel or block tiles are visited in follows from the whole launch and its grid
+ * ("Splitting K", "Block tiles").
  * in_dtype / out_dtype: F32 -> F32; BF16 -> BF16; FP8_E4M3 -> BF16 or FP8_E4M3.
  * n_tiles = 0 enqueues nothing.  Validates h_args / h_tiles first: ERR_NULL, ERR_SHAPE,
  * ERR_DTYPE, ERR_ALIGN as described at the top; ERR_HIP if the launch fails. */

@@ -35,7 +35,7 @@ __device__ __forceinline__ char* block_partials(const split_ctx& sp, int tile)
            (tile % BLOCK_TILES_PER_SLOT) * (SPLIT_MAX_PARTS * BLOCK_PART_BYTES);
 }
 
-// entry: the visit; a tile of a long K may be visited in parts (EPARA_BLOCK_SPLIT_K).  A part leaves its raw sums in the
+// entry: the visit; in plain bf16 launches a tile of a long K may be visited in parts (EPARA_BLOCK_SPLIT_K).  A part leaves its raw sums in the
 // workspace, lane by lane as they sit in the registers, written through to memory, and counts itself at the tile; whoever
 // counts last adds the parts in index order (its own too: the order does not depend on who it is), runs the epilogue and
 // puts the counter back to zero.  Nobody waits for another workgroup.
@@ -56,12 +56,13 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
     const int K = ga.K, N = ga.N, rows = tl.rows, cols = tl.cols;
     const int KSP = ((K + KF - 1) / KF + 3) & ~3;
     const uint32_t units = static_cast<uint32_t>(KSP >> 2);      // a visit covers whole units of two pairs
+    constexpr bool HAS_SPLIT = DT == EPARA_BF16 && !GATED;
     const int part = order_part(entry);
     int parts = order_parts(entry);
-    const int slot_tile = parts > 1 ? ga.reserved + (tl.m0 >> 7) * ((N + (GATED ? 63 : 127)) / (GATED ? 64 : 128)) + tl.n0 / (GATED ? 64 : 128) : 0;
+    const int slot_tile = HAS_SPLIT && parts > 1 ? ga.reserved + (tl.m0 >> 7) * ((N + 127) >> 7) + (tl.n0 >> 7) : 0;
     // the launch brought no room for the parts' sums (or holds more parts than there are units): the first visit multiplies
     // the whole K
-    if (parts > 1 && (sp.ws == nullptr || parts > SPLIT_MAX_PARTS || ga.reserved < 0 || slot_tile >= sp.first_panel || static_cast<uint32_t>(parts) > units)) {
+    if (parts > 1 && (!HAS_SPLIT || sp.ws == nullptr || parts > SPLIT_MAX_PARTS || ga.reserved < 0 || slot_tile >= sp.first_panel || static_cast<uint32_t>(parts) > units)) {
         if (part != 0) return;
         parts = 1;
     }
@@ -238,7 +239,7 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
     // then through the LDS, so that a store instruction covers whole row pieces of 256 bytes.  16-byte chunk c of a
     // row sits at c ^ (row % chunks per row).
     __syncthreads();                                             // the ring has been read
-    if (parts > 1) {
+    if constexpr (HAS_SPLIT) if (parts > 1) {
         char* slab = block_partials(sp, slot_tile);
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(slab, 0, -1, 0x00020000);
         const int at = wave * 16384 + lane * 16;

@@ -1165,7 +1165,7 @@ int32_t epara_kernel_classes(int32_t in_dtype, int32_t gated, int32_t narrow,
         table[n++] = {32, 32, gated ? 32 : 64, split_K};
         table[n++] = {64, 64, (gated ? 64 : 128) >> (narrow ? 1 : 0), split_K};
         ns = 3;
-        if (narrow == EPARA_TABLE_BLOCK) table[n++] = {INT32_MAX, EPARA_BLOCK_ROWS, gated ? 64 : 128, EPARA_BLOCK_SPLIT_K};
+        if (narrow == EPARA_TABLE_BLOCK) table[n++] = {INT32_MAX, EPARA_BLOCK_ROWS, gated ? 64 : 128, (gated || in_dtype != EPARA_BF16) ? 0 : EPARA_BLOCK_SPLIT_K};
         else table[n++] = {INT32_MAX, 256, gated ? 128 : 256, (gated || in_dtype != EPARA_BF16) ? 0 : EPARA_PANEL_SPLIT_K};  // matrix-core class
     } else {
         return EPARA_ERR_DTYPE;

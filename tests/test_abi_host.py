@@ -553,7 +553,7 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
             best = (max(loads), cls, ns, rt, ro)
     bc, bn = B.epara_kernel_classes(dtype, gated, 2)
     bc = [tuple(int(v) for v in c) for c in bc]
-    assert bc[3] == (P.INT32_MAX, 128, 64 if gated else 128, 1024) and bn == 3
+    assert bc[3] == (P.INT32_MAX, 128, 64 if gated else 128, 1024 if dtype == B.EPARA_BF16 and not gated else 0) and bn == 3
     assert bc[:3] == [tuple(int(v) for v in c) for c in B.epara_kernel_classes(dtype, gated, 1)[0][:3]]
     taken, rt, ro, finish = P.block_choice(ref, bc, *best[1:], W, 8, 1, 4)
     assert bool(taken) == block
