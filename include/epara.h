@@ -541,7 +541,7 @@ typedef struct {
  * below U, the largest load of a workgroup in the order of the other choice with
  * EPARA_COST_PANEL_START added to every visit to a whole panel tile -- then plans
  * (epara_plan_groups) and schedules (epara_schedule_tiles) with it.  The groups must be all
- * EPARA_ACT_SWIGLU or none (ERR_DTYPE).  (A chain, epara_plan_chain with more than one phase, has no block tiles.)  *plan is always written (sizes included); tiles / order are
+ * EPARA_ACT_SWIGLU or none (ERR_DTYPE).  (A chain, epara_plan_chain, has no block tiles, not even one of a single phase.)  *plan is always written (sizes included); tiles / order are
  * written when given and large enough, else ERR_CAPACITY (give NULL and 0 to ask for the sizes only;
  * that returns EPARA_OK).  row_off / x_off / y_off and split_base (G entries, epara_split_layout) may be NULL.
  * plan->n_split_tiles, n_panel_split_tiles and workspace_bytes say what the launch needs for tiles visited in

@@ -906,10 +906,10 @@ void fill_plan(epara_launch_plan& plan, const phase_option& o, int32_t gated, in
     plan.n_tiles = static_cast<int64_t>(o.tiles.size()); plan.n_slots = n_slots; plan.makespan = makespan;
 }
 
-}  // namespace
-
-int32_t epara_plan_chain(epara_chain_plan_phase* phases, int32_t n_phases, int32_t in_dtype,
-                         int32_t n_workgroups, int32_t n_xcd, int32_t panel_m, int32_t panel_n, int64_t* finish)
+// epara_plan_chain, and with one phase and `blocks` the plan of a single launch, which may use the block table (a chain has no
+// kernel for it, however many phases it has).
+int32_t plan_phases(epara_chain_plan_phase* phases, int32_t n_phases, int32_t in_dtype,
+                    int32_t n_workgroups, int32_t n_xcd, int32_t panel_m, int32_t panel_n, int64_t* finish, bool blocks)
 {
     if (n_phases < 1 || n_phases > EPARA_MAX_CHAIN_PHASES) return EPARA_ERR_SHAPE;
     if (!phases) return EPARA_ERR_NULL;
@@ -972,7 +972,7 @@ int32_t epara_plan_chain(epara_chain_plan_phase* phases, int32_t n_phases, int32
     // a single launch may do better with block tiles
     phase_option block;
     bool use_block = false;
-    if (n_phases == 1) {
+    if (blocks) {
         std::vector<int32_t> order;
         int64_t fin = 0;
         if (int32_t st = block_option(phases[0].groups, phases[0].G, in_dtype, gated[0], W, n_xcd, panel_m, panel_n, options[0][best_pick[0]],
@@ -1017,6 +1017,14 @@ int32_t epara_plan_chain(epara_chain_plan_phase* phases, int32_t n_phases, int32
     return EPARA_OK;
 }
 
+}  // namespace
+
+int32_t epara_plan_chain(epara_chain_plan_phase* phases, int32_t n_phases, int32_t in_dtype,
+                         int32_t n_workgroups, int32_t n_xcd, int32_t panel_m, int32_t panel_n, int64_t* finish)
+{
+    return plan_phases(phases, n_phases, in_dtype, n_workgroups, n_xcd, panel_m, panel_n, finish, false);
+}
+
 int32_t epara_plan_launch(const epara_group_desc* groups, int32_t G, int32_t in_dtype,
                           int32_t n_workgroups, int32_t n_xcd, int32_t panel_m, int32_t panel_n,
                           int64_t* row_off, int64_t* x_off, int64_t* y_off,
@@ -1027,7 +1035,7 @@ int32_t epara_plan_launch(const epara_group_desc* groups, int32_t G, int32_t in_
     epara_chain_plan_phase ph;
     std::memset(&ph, 0, sizeof ph);
     ph.groups = groups; ph.G = G; ph.tiles = tiles; ph.tiles_cap = tiles_cap; ph.order = order; ph.order_cap = order_cap;
-    const int32_t st = epara_plan_chain(&ph, 1, in_dtype, n_workgroups, n_xcd, panel_m, panel_n, nullptr);
+    const int32_t st = plan_phases(&ph, 1, in_dtype, n_workgroups, n_xcd, panel_m, panel_n, nullptr, true);
     if (st != EPARA_OK && st != EPARA_ERR_CAPACITY) return st;
     *plan = ph.plan;
     if (int32_t s3 = epara_split_layout(groups, G, plan->classes, plan->n_classes, plan->n_stream_classes, split_base,

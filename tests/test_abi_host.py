@@ -577,6 +577,14 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
         assert all(ph["info"].narrow != 2 for ph in phases)
 
 
+def test_a_chain_of_one_phase_is_planned_without_block_tiles():
+    """epara_grouped_chain has no kernel for block tiles, so epara_plan_chain must not choose them where epara_plan_launch does."""
+    for groups, dtype in (([(200, 512, 512)], B.EPARA_BF16), ([(300, 2048, 400), (7, 512, 64)], B.EPARA_FP8_E4M3)):
+        assert B.epara_plan_launch(_desc(groups), dtype, 256)[0].narrow == 2
+        _, phases = B.epara_plan_chain([_desc(groups)], [None], dtype, 256)
+        assert phases[0]["info"].narrow in (0, 1) and [int(v) for v in phases[0]["info"].class_table()[-1]][1] == 256
+
+
 @pytest.mark.parametrize("shapes", [[(100, 4096, 4096)], [(75, 1040, 130), (130, 2064, 200), (40, 8208, 136)], [(66, 512, 40)]])
 def test_a_block_launch_can_be_composed_from_the_single_calls(shapes):
     """Class table, tiles, visit order, split layout and number of split tiles asked for one by one: whenever the order visits

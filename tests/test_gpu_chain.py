@@ -132,6 +132,22 @@ def test_chain_sees_fresh_activations_when_the_inputs_change_between_passes(inde
         prev = _raw(ch)
 
 
+@pytest.mark.parametrize("dtype_name,shapes", [("bf16", [(200, 512, 512)]), ("bf16", [(300, 768, 200), (9, 64, 40)]), ("f32", [(100, 64, 70)])])
+def test_a_chain_of_one_phase_equals_the_launch(dtype_name, shapes):
+    """Also where the launch is planned with block tiles, for which the chain has no kernel (K below the split tiles')."""
+    rng = np.random.default_rng(43)
+    G = U.Groups([U.rand_spec(rng, M, K, N, "relu") for M, K, N in shapes], dtype_name)
+    G.run()
+    want = [y.cpu().numpy() if dtype_name == "f32" else y.view(torch.int16).cpu().numpy() for y in G.raw()]
+    chain = R.ChainPlan([G.args], [G.out_dtype], [None], B.DTYPE_BY_NAME[dtype_name], U.DEV)
+    for y in G.Y:
+        y.zero_()
+    R.grouped_chain(chain)
+    assert R.chain_status(chain) == 0
+    for y, w in zip(G.raw(), want):
+        assert np.array_equal(y.cpu().numpy() if dtype_name == "f32" else y.view(torch.int16).cpu().numpy(), w)
+
+
 def test_device_copies_of_the_chain_plan_are_the_reference_planners():
     from oracle import planner as P
     staged = StagedMix(make_mix(4), "bf16", U.DEV, chained=True)
