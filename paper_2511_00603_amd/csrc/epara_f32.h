@@ -9,14 +9,16 @@ namespace {
 // An fp32 tile belongs to a small model: a handful of workgroups, and what a launch takes is the chain of dependent
 // memory latencies in one of them.  So a workgroup has sixteen waves and cuts K into pieces of 16 that are dealt to them
 // contiguously (16-row class: sixteen parts of K; 64-row class: eight parts for each half of the rows); a wave asks for
-// several pieces at once and the partial tiles are added in the order of K: the result depends on nothing but the
+// several pieces at once and the partial tiles are added in a fixed order (see f32_do_tile): the result depends on nothing but the
 // operands.  Operands go from memory straight into v_mfma_f32_16x16x4_f32 (products and sums in fp32): lane (i, q) loads
 // X[row i][k + 4 q .. + 3] and W[k + 4 q + e][column 4 i .. 4 i + 3] as 16-byte pieces; product e of a piece pairs the k
 // = 4 q + e of both, and the four columns of a lane belong to four accumulators, so that a lane ends with 4 rows x 4
 // consecutive columns.  Measured, three
 // launches of two MLPs (256-512-512-10, 4 and 16 rows): 37 -> 21 us a pass; one of 64 rows, 512-512-64: 71 -> 36 us (four waves that
 // staged 16 or 64 k at a time through the LDS and multiplied on the vector units).
-constexpr int F32_WAVES = 16, F32_NT = F32_WAVES * 64, F32_BN = 64;
+// A chain whose grid does not fit the chip with one such workgroup per unit runs workgroups of eight waves, two per unit, in
+// which a wave takes two of the sixteen shares one after the other: the same sums in the same order.
+constexpr int F32_WAVES = 16, F32_NT = F32_WAVES * 64, F32_BN = 64, F32_HALF_NT = F32_NT / 2;
 
 // A piece of 16 k: RB blocks of 16 rows x 64 columns of one wave.
 template <int RB>
@@ -81,31 +83,35 @@ __device__ __forceinline__ void f32_multiply(const f32_tile& t, int p0, int p1, 
 }
 
 // A tile of RB x 16 x HALVES rows; PARTS = F32_WAVES / HALVES parts of K.  At most 64 KiB of partial sums meet in the LDS at a
-// time: with eight parts of 64 rows the upper four are added to the lower four first.
-template <bool CHAIN, int RB, int HALVES>
+// time: with eight parts of 64 rows part s + 4 is added to part s first, then the four sums in the order of s; the sixteen
+// parts of a 16-row tile are added in the order of K.  WAVES: of the workgroup, which hold F32_WAVES / WAVES shares each.
+template <bool CHAIN, int WAVES, int RB, int HALVES>
 __device__ __forceinline__ void f32_do_tile(const epara_group_args& ga, const epara_tile& tl, v4f* lds)
 {
-    constexpr int PARTS = F32_WAVES / HALVES, ROWS = RB * 16 * HALVES;
+    constexpr int PARTS = F32_WAVES / HALVES, ROWS = RB * 16 * HALVES, ROUNDS = F32_WAVES / WAVES;
     constexpr int MEET = 65536 / (ROWS * F32_BN * 4) < PARTS ? 65536 / (ROWS * F32_BN * 4) : PARTS;      // parts that fit the LDS
     static_assert(MEET == PARTS || 2 * MEET == PARTS, "parts meet in one or two steps");
+    static_assert(ROUNDS == 1 || ROUNDS == 2, "a wave takes one or two shares");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int part = wave / HALVES, half = wave % HALVES;
+    const int half = wave % HALVES;                              // the same for both shares
     const int i = lane & 15, q = lane >> 4;
     const int K = ga.K, N = ga.N, row0 = half * RB * 16;
-    v4f acc[RB][4];
-#pragma unroll
-    for (int b = 0; b < RB; ++b)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[b][c] = v4f{0.f, 0.f, 0.f, 0.f};
     const int pieces = (K + 15) >> 4;
-    // contiguous shares; products of 32 bits: a K that overflows them has more pieces than memory holds weights
-    const int p0 = static_cast<int>(static_cast<int64_t>(pieces) * part / PARTS), p1 = static_cast<int>(static_cast<int64_t>(pieces) * (part + 1) / PARTS);
-    if (row0 < tl.rows) {
-        const f32_tile t = {as_global<float>(ga.X) + static_cast<size_t>(tl.m0 + row0) * K, as_global<float>(ga.W) + tl.n0, K, N,
-                            tl.rows - row0, tl.cols, (K & 3) == 0, (N & 3) == 0};
-        f32_multiply<RB, RB == 1 ? 3 : 1>(t, p0, p1, lane, acc);
-    }
+    v4f acc[RB][4];
+    auto multiply = [&](int part) {                              // contiguous shares of the pieces of K
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[b][c] = v4f{0.f, 0.f, 0.f, 0.f};
+        const int p0 = static_cast<int>(static_cast<int64_t>(pieces) * part / PARTS), p1 = static_cast<int>(static_cast<int64_t>(pieces) * (part + 1) / PARTS);
+        if (row0 < tl.rows) {
+            const f32_tile t = {as_global<float>(ga.X) + static_cast<size_t>(tl.m0 + row0) * K, as_global<float>(ga.W) + tl.n0, K, N,
+                                tl.rows - row0, tl.cols, (K & 3) == 0, (N & 3) == 0};
+            // (two shares: one piece less ahead, or the kernel needs more than the 128 registers of two workgroups per unit)
+            f32_multiply<RB, RB == 1 ? (ROUNDS == 2 ? 2 : 3) : 1>(t, p0, p1, lane, acc);
+        }
+    };
     // quad (row, column quad) of part s at [s][row][quad]; a lane holds rows 4 q + v of each block, columns 4 i .. 4 i + 3
     auto at = [&](int s, int row, int quad) -> v4f& { return lds[(s * ROWS + row) * 16 + quad]; };
     auto dump = [&](int s) {
@@ -114,6 +120,12 @@ __device__ __forceinline__ void f32_do_tile(const epara_group_args& ga, const ep
 #pragma unroll
             for (int v = 0; v < 4; ++v) at(s, row0 + 16 * b + 4 * q + v, i) = v4f{acc[b][0][v], acc[b][1][v], acc[b][2][v], acc[b][3][v]};
     };
+    const int part = wave / HALVES;
+    if constexpr (ROUNDS == 2) {                                 // the upper share first: its sums wait in the LDS
+        multiply(part + PARTS / 2);
+        dump(MEET < PARTS ? part : part + PARTS / 2);
+    }
+    multiply(part);
     if constexpr (MEET < PARTS) {
         if (part >= MEET) dump(part - MEET);
         __syncthreads();
@@ -131,7 +143,7 @@ __device__ __forceinline__ void f32_do_tile(const epara_group_args& ga, const ep
     }
     if (part < MEET) dump(part);
     __syncthreads();
-    for (int u = threadIdx.x; u < ROWS * 16; u += F32_NT) {
+    for (int u = threadIdx.x; u < ROWS * 16; u += WAVES * 64) {
         const int row = u >> 4, col = (u & 15) * 4;
         if (row >= tl.rows || col >= tl.cols) continue;
         v4f sum = at(0, row, u & 15);
@@ -157,7 +169,7 @@ __device__ __forceinline__ void f32_do_tile(const epara_group_args& ga, const ep
     __syncthreads();                                             // the partial tiles are free again
 }
 
-template <bool CHAIN>
+template <bool CHAIN, int WAVES>
 __device__ __forceinline__ void f32_body(const epara_group_args* __restrict__ args, const epara_tile* __restrict__ tiles,
                                          const int32_t* __restrict__ order, long n_slots, chain_ctx* chain)
 {
@@ -168,8 +180,8 @@ __device__ __forceinline__ void f32_body(const epara_group_args* __restrict__ ar
         const epara_tile tl = tiles[t];
         if constexpr (CHAIN) chain_wait(*chain, tl.group);
         const epara_group_args ga = args[tl.group];
-        if (tl.cls == 0) f32_do_tile<CHAIN, 1, 1>(ga, tl, lds);  // class 0 of the fp32 table: at most 16 rows
-        else             f32_do_tile<CHAIN, 2, 2>(ga, tl, lds);
+        if (tl.cls == 0) f32_do_tile<CHAIN, WAVES, 1, 1>(ga, tl, lds);  // class 0 of the fp32 table: at most 16 rows
+        else             f32_do_tile<CHAIN, WAVES, 2, 2>(ga, tl, lds);
         if constexpr (CHAIN) chain_done(*chain, tl.group);
     }
 }

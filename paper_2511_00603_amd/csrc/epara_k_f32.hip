@@ -8,14 +8,15 @@ __global__ __launch_bounds__(F32_NT) void grouped_kernel_f32(const epara_group_a
                                                              const epara_tile* __restrict__ tiles,
                                                              const int32_t* __restrict__ order, long n_slots)
 {
-    f32_body<false>(args, tiles, order, n_slots, nullptr);
+    f32_body<false, F32_WAVES>(args, tiles, order, n_slots, nullptr);
 }
 
 #define CHAIN_TABLES(i) const epara_group_args* __restrict__ a##i, const epara_tile* __restrict__ t##i, \
                         const int32_t* __restrict__ o##i, const epara_chain_wait* __restrict__ w##i
 #define CHAIN_PICK(p, x) ((p) == 0 ? x##0 : (p) == 1 ? x##1 : (p) == 2 ? x##2 : x##3)
 
-__global__ __launch_bounds__(F32_NT) void grouped_chain_kernel_f32(CHAIN_TABLES(0), CHAIN_TABLES(1), CHAIN_TABLES(2), CHAIN_TABLES(3),
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 4) void grouped_chain_kernel_f32(CHAIN_TABLES(0), CHAIN_TABLES(1), CHAIN_TABLES(2), CHAIN_TABLES(3),
                                                                    const epara_chain_scalars S)
 {
     chain_ctx c;
@@ -26,7 +27,7 @@ __global__ __launch_bounds__(F32_NT) void grouped_chain_kernel_f32(CHAIN_TABLES(
         c.waits = CHAIN_PICK(p, w);
         c.counter_base = S.counter_base[p];
         c.ok_group = -1;
-        f32_body<true>(CHAIN_PICK(p, a), CHAIN_PICK(p, t), CHAIN_PICK(p, o), S.n_slots[p], &c);
+        f32_body<true, WAVES>(CHAIN_PICK(p, a), CHAIN_PICK(p, t), CHAIN_PICK(p, o), S.n_slots[p], &c);
     }
     chain_exit(c, S.n_counters);
 }
@@ -78,18 +79,23 @@ hipError_t epara_enqueue_f32(unsigned grid, hipStream_t stream, const epara_grou
 
 hipError_t epara_chain_f32(const epara_chain_tables& T, const epara_chain_scalars& S, unsigned grid, hipStream_t stream, int64_t* resident)
 {
-    const void* fn = reinterpret_cast<const void*>(&grouped_chain_kernel_f32);
+    // sixteen waves per workgroup where that fits (every unit holds one such workgroup), else eight, of which a unit holds two
+    int cus = 0, dev = 0;
+    if (hipError_t e = hipGetDevice(&dev)) return e;
+    if (hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) return e;
     if (resident) {
-        int per_cu = 0, cus = 0, dev = 0;
-        if (hipError_t e = hipGetDevice(&dev)) return e;
-        if (hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) return e;
-        if (hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, F32_NT, 0)) return e;
+        int per_cu = 0;
+        if (hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&grouped_chain_kernel_f32<F32_WAVES / 2>), F32_HALF_NT, 0)) return e;
         *resident = static_cast<int64_t>(per_cu) * cus;
         return hipSuccess;
     }
-    hipLaunchKernelGGL(grouped_chain_kernel_f32, dim3(grid), dim3(F32_NT), 0, stream,
-                       T.args[0], T.tiles[0], T.order[0], T.waits[0], T.args[1], T.tiles[1], T.order[1], T.waits[1],
-                       T.args[2], T.tiles[2], T.order[2], T.waits[2], T.args[3], T.tiles[3], T.order[3], T.waits[3], S);
+    auto launch = [&](auto fn, int threads) {
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), 0, stream,
+                           T.args[0], T.tiles[0], T.order[0], T.waits[0], T.args[1], T.tiles[1], T.order[1], T.waits[1],
+                           T.args[2], T.tiles[2], T.order[2], T.waits[2], T.args[3], T.tiles[3], T.order[3], T.waits[3], S);
+    };
+    if (grid <= static_cast<unsigned>(cus)) launch(grouped_chain_kernel_f32<F32_WAVES>, F32_NT);
+    else                                    launch(grouped_chain_kernel_f32<F32_WAVES / 2>, F32_HALF_NT);
     return hipGetLastError();
 }
 

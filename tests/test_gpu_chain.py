@@ -148,6 +148,33 @@ def test_a_chain_of_one_phase_equals_the_launch(dtype_name, shapes):
         assert np.array_equal(y.cpu().numpy() if dtype_name == "f32" else y.view(torch.int16).cpu().numpy(), w)
 
 
+@pytest.mark.parametrize("n_workgroups", [256, 264, 512])
+def test_fp32_chain_on_more_workgroups_than_compute_units(n_workgroups):
+    """fp32 chains run on up to two workgroups per compute unit, with the bits of the separate launches: both tile classes,
+    K of less than a piece per share up to several, ragged rows and columns, the second layer reading the first."""
+    rng = np.random.default_rng(47)
+    shapes = [(4, 7, 200), (16, 256, 520), (17, 64, 65), (64, 300, 130), (150, 520, 260), (33, 1040, 64)]
+    X = [torch.from_numpy(rng.uniform(-1, 1, (M, K)).astype(np.float32)).to(U.DEV) for M, K, _ in shapes]
+    W = [R.pack_weights(torch.from_numpy((rng.standard_normal((K, N)) / np.sqrt(K)).astype(np.float32)).to(U.DEV), B.EPARA_F32)
+         for _, a, b in shapes for K, N in ((a, b), (b, a))]
+    H = [torch.zeros((M * N + 63) // 32 * 32, dtype=torch.float32, device=U.DEV)[: M * N].view(M, N) for M, _, N in shapes]
+    Y = [torch.zeros((M, K), dtype=torch.float32, device=U.DEV) for M, K, _ in shapes]
+    up = np.array([R.group_args(X[g], W[2 * g], H[g], M, K, N, "relu") for g, (M, K, N) in enumerate(shapes)], dtype=B.GROUP_ARGS)
+    down = np.array([R.group_args(H[g], W[2 * g + 1], Y[g], M, N, K, "none") for g, (M, K, N) in enumerate(shapes)], dtype=B.GROUP_ARGS)
+    for args in (up, down):
+        R.grouped_forward(R.LaunchPlan(args, B.EPARA_F32, U.DEV), B.EPARA_F32)
+    torch.cuda.synchronize()
+    want = [t.cpu().numpy().copy() for t in H + Y]
+    chain = R.ChainPlan([up, down], [B.EPARA_F32] * 2, [None, np.arange(len(shapes), dtype=np.int32)], B.EPARA_F32, U.DEV, n_workgroups)
+    for rep in range(2):
+        for t in H + Y:
+            t.zero_()
+        R.grouped_chain(chain)
+        assert R.chain_status(chain) == 0
+        for t, w in zip(H + Y, want):
+            assert np.array_equal(t.cpu().numpy(), w), (rep, tuple(t.shape))
+
+
 def test_device_copies_of_the_chain_plan_are_the_reference_planners():
     from oracle import planner as P
     staged = StagedMix(make_mix(4), "bf16", U.DEV, chained=True)
