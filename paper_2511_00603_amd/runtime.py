@@ -106,7 +106,8 @@ class LaunchPlan:
             self.groups, in_dtype, n_workgroups, n_xcd, panel_m, panel_n)
         self.n_split_tiles, self.workspace_bytes = int(info.n_split_tiles), int(info.workspace_bytes)
         self.n_panel_split_tiles = int(info.n_panel_split_tiles)
-        if self.workspace_bytes:                             # where each group's split tiles meet in the workspace
+        if self.workspace_bytes:                             # where each group's split tiles meet in this plan's workspace
+            self.args = self.args.copy()                     # the caller's array may serve other plans
             self.args["reserved"] = split_base
         self.makespan, self.narrow, self.classes, self.n_stream_classes = info.makespan, bool(info.narrow), info.class_table(), info.n_stream_classes
         self.plan_seconds = time.perf_counter() - t0

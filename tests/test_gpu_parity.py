@@ -270,6 +270,27 @@ def test_block_tiles_in_parts_without_a_workspace_are_still_computed():
         assert np.array_equal(y, ref.bf16_decode(ref.bf16_encode(yref)))
 
 
+def test_two_plans_of_one_argument_array_do_not_disturb_each_other():
+    """The split tiles of a plan meet at places of its own: making a second plan, for another grid, from the same array of
+    arguments changes neither the array nor the first plan."""
+    rng = np.random.default_rng(53)
+    specs = [{"X": rng.integers(-3, 4, (M, K)).astype(np.float32), "W": rng.integers(-2, 3, (K, N)).astype(np.float32),
+              "b": None, "act": "none"} for M, K, N in ((75, 1040, 130), (200, 4112, 72), (40, 8208, 136))]
+    G = U.Groups(specs, "bf16")
+    before = G.args.copy()
+    plans = [R.LaunchPlan(G.args, B.EPARA_BF16, U.DEV, W) for W in (256, 120, 256)]
+    assert plans[0].workspace_bytes and plans[1].workspace_bytes and plans[0].args["reserved"].tolist() != plans[1].args["reserved"].tolist()
+    assert np.array_equal(G.args, before)
+    want = [ref.bf16_decode(ref.bf16_encode(y)) for y in G.expected()]
+    for plan in (plans[0], plans[1], plans[2], plans[0]):
+        for y in G.Y:
+            y.zero_()
+        R.grouped_forward(plan, B.EPARA_BF16)
+        torch.cuda.synchronize()
+        for y, w in zip(G.Y, want):
+            assert np.array_equal(U.fetch(y), w)
+
+
 def test_launches_with_split_tiles_take_turns_on_one_workspace():
     """Panel tiles in four parts, streaming tiles in two, block tiles in parts and both kinds in one launch, all on one
     workspace that is zeroed once: the counters lie in front of every launch's partial sums, so each launch finds its own
