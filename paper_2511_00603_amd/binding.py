@@ -39,6 +39,7 @@ ATTN_ARGS = np.dtype([("QKV", "<u8"), ("O", "<u8"), ("M", "<i4"), ("tokens", "<i
                       ("first_item", "<i4"), ("reserved", "<i4")])
 assert NORM_ARGS.itemsize == 64 and ATTN_ARGS.itemsize == 40
 EPARA_NORM_MAX_D, EPARA_ATTN_MAX_TOKENS, EPARA_ATTN_HEAD_DIM = 8192, 224, 64
+EPARA_TABLE_BLOCK = 2
 SIM_REQUEST = np.dtype([("arrival_us", "<i8"), ("slo_us", "<i8"), ("service", "<i4"), ("origin", "<i4"), ("frames", "<i4"), ("fps_milli", "<i4")])
 assert SIM_REQUEST.itemsize == 32
 EPARA_MAX_CHAIN_PHASES = 4
@@ -570,7 +571,7 @@ def epara_chain_status(d_workspace, stream):
 
 
 def epara_kernel_classes(in_dtype, gated, narrow=False):
-    """-> (classes, n_stream_classes)."""
+    """-> (classes, n_stream_classes).  narrow: 0, 1 or EPARA_TABLE_BLOCK."""
     n = np.zeros(2, dtype=np.int32)
     classes = np.zeros(8, dtype=TILE_CLASS)
     _check(lib().epara_kernel_classes(int(in_dtype), int(bool(gated)), int(narrow), _ptr(classes), len(classes),

@@ -109,7 +109,7 @@ class LaunchPlan:
         if self.workspace_bytes:                             # where each group's split tiles meet in this plan's workspace
             self.args = self.args.copy()                     # the caller's array may serve other plans
             self.args["reserved"] = split_base
-        self.makespan, self.narrow, self.classes, self.n_stream_classes = info.makespan, bool(info.narrow), info.class_table(), info.n_stream_classes
+        self.makespan, self.narrow, self.classes, self.n_stream_classes = info.makespan, int(info.narrow), info.class_table(), info.n_stream_classes
         self.plan_seconds = time.perf_counter() - t0
         t0 = time.perf_counter()
         self.d_args, self.d_tiles, self.d_order = _upload_all([self.args, self.tiles, self.order], device)
@@ -153,7 +153,7 @@ class ChainPlan:
             ph = _Phase()
             ph.args, ph.groups, ph.in_dtype, ph.n_workgroups = args[p], groups[p], in_dtype, n_workgroups
             info = planned[p]["info"]
-            ph.narrow, ph.classes, ph.n_stream_classes = bool(info.narrow), info.class_table(), info.n_stream_classes
+            ph.narrow, ph.classes, ph.n_stream_classes = int(info.narrow), info.class_table(), info.n_stream_classes
             ph.tiles, ph.order, ph.waits, ph.counter_base = planned[p]["tiles"], planned[p]["order"], planned[p]["waits"], planned[p]["counter_base"]
             self.phases.append(ph)
         self.n_counters = sum(len(a) for a in args)

@@ -577,6 +577,20 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
         assert all(ph["info"].narrow != 2 for ph in phases)
 
 
+def test_a_plan_says_which_class_table_it_was_made_with(monkeypatch):
+    """LaunchPlan.narrow is the number of the table (wide, narrow, block), with which epara_kernel_classes returns it; the
+    arrays stay on the host here."""
+    from paper_2511_00603_amd import runtime as R
+    monkeypatch.setattr(R, "_require_gpu", lambda: None)
+    monkeypatch.setattr(R.torch.cuda, "synchronize", lambda *a: None)
+    for shape, table in (((300, 512, 512), B.EPARA_TABLE_BLOCK), ((64, 512, 512), 1), ((8, 512, 512), 0)):
+        args = np.zeros(1, dtype=B.GROUP_ARGS)
+        args["M"], args["K"], args["N"] = shape
+        plan = R.LaunchPlan(args, B.EPARA_BF16, "cpu", 256)
+        classes, n_stream = B.epara_kernel_classes(B.EPARA_BF16, 0, plan.narrow)
+        assert plan.narrow == table and plan.classes.tolist() == classes.tolist() and plan.n_stream_classes == n_stream
+
+
 def test_a_chain_of_one_phase_is_planned_without_block_tiles():
     """epara_grouped_chain has no kernel for block tiles, so epara_plan_chain must not choose them where epara_plan_launch does."""
     for groups, dtype in (([(200, 512, 512)], B.EPARA_BF16), ([(300, 2048, 400), (7, 512, 64)], B.EPARA_FP8_E4M3)):
