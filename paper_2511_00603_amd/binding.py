@@ -402,7 +402,7 @@ def epara_plan_launch(groups, in_dtype, n_workgroups, n_xcd=8, panel_m=1, panel_
     split_base = np.full(G, -1, dtype=np.int32)
     # The sizes of a plan are known when it is made, so it is made into arrays that hold what most launches need (some
     # thousand tiles, lists of sixteen) and once more, into arrays of the right size, where that was not enough.
-    n_tiles, n_slots = 4096, 16 * n_workgroups
+    n_tiles, n_slots = 4096, 16 * min(max(int(n_workgroups), 1), 4096)       # the library checks n_workgroups
     while True:
         tiles, order = np.empty(n_tiles, dtype=TILE), np.empty(n_slots, dtype=np.int32)
         status = lib().epara_plan_launch(gp, G, int(in_dtype), n_workgroups, n_xcd, panel_m, panel_n, _ptr(row_off), _ptr(x_off), _ptr(y_off),

@@ -577,6 +577,13 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
         assert all(ph["info"].narrow != 2 for ph in phases)
 
 
+def test_plan_launch_reports_a_bad_grid_as_the_library_does():
+    for kw in (dict(n_workgroups=-8), dict(n_workgroups=0), dict(n_workgroups=250), dict(n_workgroups=256, n_xcd=0), dict(n_workgroups=256, panel_m=0)):
+        with pytest.raises(B.EparaError) as e:
+            B.epara_plan_launch(_desc([(100, 64, 64)]), B.EPARA_BF16, **kw)
+        assert e.value.status == B.EPARA_ERR_SHAPE, kw
+
+
 def test_a_plan_says_which_class_table_it_was_made_with(monkeypatch):
     """LaunchPlan.narrow is the number of the table (wide, narrow, block), with which epara_kernel_classes returns it; the
     arrays stay on the host here."""
