@@ -116,19 +116,20 @@ int32_t validate_launch(const epara_launch* L, int32_t in_dtype, int32_t out_dty
     }
     // The table the launch was cut with, by its tiles and its split counts.  One that fits several of them gives the same
     // results with each; block tiles come first, where the caller has a kernel for them.
-    int32_t first_error = EPARA_OK;
+    // What a launch is refused for: the objection to its split tiles of the first table that its tiles fit (to their workspace
+    // rather than to their counts), else that of the last table to its tiles.
+    int32_t tiles_error = EPARA_OK, split_error = EPARA_OK;
     static const int tables[3] = {EPARA_TABLE_BLOCK, 0, 1};
     for (int i = (f32 || !blocks || !any_panel(L)) ? 1 : 0; i < (f32 ? 2 : 3); ++i) {
-        int32_t st = check_tiles(L, in_dtype, tables[i]);
-        if (st == EPARA_OK) st = check_split(L, in_dtype, tables[i]);
+        if (int32_t st = check_tiles(L, in_dtype, tables[i])) { tiles_error = st; continue; }
+        const int32_t st = check_split(L, in_dtype, tables[i]);
         if (st == EPARA_OK) {
             if (narrow_out) *narrow_out = tables[i];
             return EPARA_OK;
         }
-        // what a launch is refused for: the wide table's objection to its split, else the last table's to its tiles
-        if (tables[i] != EPARA_TABLE_BLOCK && (first_error == EPARA_OK || first_error == EPARA_ERR_SHAPE)) first_error = st;
+        if (split_error == EPARA_OK || split_error == EPARA_ERR_SHAPE) split_error = st;
     }
-    return first_error;
+    return split_error != EPARA_OK ? split_error : tiles_error;
 }
 
 int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int narrow, hipStream_t stream)

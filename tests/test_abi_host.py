@@ -724,6 +724,35 @@ def test_split_launch_validation_without_a_gpu():
     assert lib.epara_workspace_init(ctypes.c_void_p(0x7000004), 256, None) == B.EPARA_ERR_ALIGN
 
 
+@pytest.mark.parametrize("groups", [[(74, 11008, 4096)], [(40, 11008, 520), (300, 2048, 520), (70, 512, 40)]])
+def test_split_block_launch_validation_without_a_gpu(groups):
+    """The same for a launch of block tiles in parts, alone and next to split streaming tiles: what is wrong is named."""
+    from paper_2511_00603_amd.runtime import group_args
+    lib = B.lib()
+
+    class T:
+        def __init__(self, p): self.p = p
+        def data_ptr(self): return self.p
+    info, _, _, _, tiles, order, base = B.epara_plan_launch(_desc(groups), B.EPARA_BF16, 256)
+    assert info.narrow == 2 and info.n_panel_split_tiles > 0
+    args = np.array([group_args(T(0x100000), T(0x200000), T(0x300000), M, K, N, "none") for M, K, N in groups], dtype=B.GROUP_ARGS)
+    args["reserved"] = base
+
+    def fwd(ws=0x7000000, ws_bytes=info.workspace_bytes, n_split=info.n_split_tiles, n_panel=info.n_panel_split_tiles, a=args, t=tiles):
+        L = B.Launch(a.ctypes.data, 0x1000, t.ctypes.data, 0x2000, 0x3000, len(t), len(order), 256, len(a), ws, ws_bytes, n_split, n_panel)
+        return lib.epara_grouped_forward(ctypes.addressof(L), B.EPARA_BF16, B.EPARA_BF16, None)
+    assert fwd(ws=None) == B.EPARA_ERR_NULL
+    assert fwd(ws=0x7000010) == B.EPARA_ERR_ALIGN
+    assert fwd(ws_bytes=info.workspace_bytes - 1) == B.EPARA_ERR_CAPACITY
+    for bad in (dict(n_panel=info.n_panel_split_tiles + 1), dict(n_panel=info.n_panel_split_tiles - 1) if info.n_panel_split_tiles > 1 else dict(n_panel=-1),
+                dict(n_panel=-1), dict(n_split=info.n_split_tiles + 1), dict(n_split=-1)):
+        assert fwd(**bad) == B.EPARA_ERR_SHAPE, bad
+    moved = args.copy(); moved["reserved"][1 if len(groups) > 1 else 0] += 1
+    assert fwd(a=moved) == B.EPARA_ERR_SHAPE
+    cut = tiles.copy(); cut["cols"][0] -= 1
+    assert fwd(t=cut) == B.EPARA_ERR_SHAPE
+
+
 def test_panel_split_decision_and_its_error_paths():
     """epara_panel_split against the reference on the launches of the mixes and on shapes around the rule's edges
     (a full last round, a K below the class's split_K, gated groups, two different K, a streaming group next to
