@@ -217,11 +217,8 @@ inline int64_t visit_cost(int64_t cost, int32_t parts, const epara_group_desc& d
 
 }  // namespace
 
-int32_t epara_block_split(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
-                          int32_t n_stream_classes, int64_t W, int32_t* parts)
+int32_t epara_block_slots(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes, int32_t n_stream_classes)
 {
-    *parts = block_parts(groups, G, classes, n_classes, n_stream_classes, W);
-    if (*parts == 1) return 0;
     int64_t n = 0;
     for (int32_t g = 0; g < G; ++g) {
         const epara_group_desc& d = groups[g];
@@ -229,8 +226,20 @@ int32_t epara_block_split(const epara_group_desc* groups, int32_t G, const epara
         const epara_tile_class& c = classes[class_of(d.M, classes, n_classes)];
         if (block_splits(d, c)) n += ceil_div(d.M, c.BM) * ceil_div(d.N, c.BN);
     }
-    return static_cast<int32_t>(ceil_div(n, EPARA_BLOCK_TILES_PER_SLOT));
+    return n > 0xFFFFFF ? 0 : static_cast<int32_t>(ceil_div(n, EPARA_BLOCK_TILES_PER_SLOT));      // so many are never split
 }
+
+namespace {
+
+// Slots of the block tiles of a launch that are visited in *parts parts of K; 0 if they are not.
+int32_t block_split_of(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
+                       int32_t n_stream_classes, int64_t W, int32_t* parts)
+{
+    *parts = block_parts(groups, G, classes, n_classes, n_stream_classes, W);
+    return *parts == 1 ? 0 : epara_block_slots(groups, G, classes, n_classes, n_stream_classes);
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -1128,7 +1137,7 @@ int32_t epara_panel_split(const epara_group_desc* groups, int32_t G,
     }
     *n_panel_split_tiles = panel_split_of(groups, G, classes, n_classes, n_stream_classes, n_workgroups, parts, n_more);
     for (int32_t c = n_stream_classes; c < n_classes; ++c)
-        if (classes[c].BM == EPARA_BLOCK_ROWS) *n_panel_split_tiles = epara_block_split(groups, G, classes, n_classes, n_stream_classes, n_workgroups, parts);
+        if (classes[c].BM == EPARA_BLOCK_ROWS) *n_panel_split_tiles = block_split_of(groups, G, classes, n_classes, n_stream_classes, n_workgroups, parts);
     return EPARA_OK;
 }
 
@@ -1147,7 +1156,7 @@ int64_t epara_workspace_bytes(const epara_group_desc* groups, int32_t G, int32_t
         if (epara_kernel_classes(in_dtype, gated, narrow, classes, 4, &nc, &ns) != EPARA_OK) return -1;
         if (epara_split_layout(groups, G, classes, nc, ns, nullptr, &n_split, &bytes) != EPARA_OK) return -1;
         int32_t parts = 1, more = 0;
-        const int32_t n_panel = narrow == EPARA_TABLE_BLOCK ? epara_block_split(groups, G, classes, nc, ns, n_workgroups, &parts)
+        const int32_t n_panel = narrow == EPARA_TABLE_BLOCK ? block_split_of(groups, G, classes, nc, ns, n_workgroups, &parts)
                                                             : panel_split_of(groups, G, classes, nc, ns, n_workgroups, &parts, &more);
         worst = std::max(worst, epara_split_workspace_bytes(n_split, n_panel));
     }

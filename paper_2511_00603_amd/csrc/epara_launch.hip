@@ -60,8 +60,13 @@ int32_t check_split(const epara_launch* L, int32_t in_dtype, int narrow)
     std::vector<int32_t> base(static_cast<size_t>(L->G));
     for (int32_t g = 0; g < L->G; ++g) d[g] = {L->h_args[g].M, L->h_args[g].K, L->h_args[g].N, L->h_args[g].act, 0, 0};
     if (int32_t st = epara_split_layout(d.data(), L->G, cls, ncls, nstream, base.data(), &n_split, &bytes)) return st;
-    if (int32_t st = epara_panel_split(d.data(), L->G, cls, ncls, nstream, L->n_workgroups, &n_panel, &parts, &more)) return st;
-    if (narrow == EPARA_TABLE_BLOCK) n_panel = epara_block_split(d.data(), L->G, cls, ncls, nstream, L->n_workgroups, &parts);
+    // block tiles: all that may be visited in parts have slots, or none has (into how many parts the order cuts them, if at all,
+    // is its own affair: the kernel takes any number up to EPARA_SPLIT_MAX_PARTS)
+    if (narrow != EPARA_TABLE_BLOCK) {
+        if (int32_t st = epara_panel_split(d.data(), L->G, cls, ncls, nstream, L->n_workgroups, &n_panel, &parts, &more)) return st;
+    } else if (L->n_panel_split_tiles != 0) {
+        n_panel = epara_block_slots(d.data(), L->G, cls, ncls, nstream);
+    }
     if (n_split != L->n_split_tiles || n_panel != L->n_panel_split_tiles) return EPARA_ERR_SHAPE;
     for (int32_t g = 0; g < L->G; ++g)
         if (base[g] >= 0 && (n_panel > 0 || d[g].M <= cls[nstream - 1].max_M) && L->h_args[g].reserved != base[g]) return EPARA_ERR_SHAPE;

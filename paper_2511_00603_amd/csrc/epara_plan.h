@@ -8,9 +8,8 @@
 
 #define EPARA_HIDDEN __attribute__((visibility("hidden")))
 
-// Block tiles visited in parts of K ("Block tiles" in the header): *parts, and the slots (three tiles each) they need in the
-// workspace.  Shapes and classes are valid.
-EPARA_HIDDEN int32_t epara_block_split(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
-                                       int32_t n_stream_classes, int64_t W, int32_t* parts);
+// Slots (three tiles each) of the block tiles of a launch that may be visited in parts of K ("Block tiles" in the header); how
+// many parts, or whether at all, is a search that only the planner makes.  Shapes and classes are valid.
+EPARA_HIDDEN int32_t epara_block_slots(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes, int32_t n_stream_classes);
 
 #endif

@@ -753,6 +753,26 @@ def test_split_block_launch_validation_without_a_gpu(groups):
     assert fwd(t=cut) == B.EPARA_ERR_SHAPE
 
 
+def test_a_call_does_not_repeat_the_search_for_the_parts_of_block_tiles():
+    """Host time of the checks of a call (the launch is refused for its workspace after all of them): 3 + 40 + 1501 rows of a
+    down projection take some 5 us; the search that a call used to repeat takes 150."""
+    import time
+    groups = [(3, 11008, 4096), (40, 11008, 4096), (1501, 11008, 4096)]
+    info, _, _, _, tiles, order, base = B.epara_plan_launch(_desc(groups), B.EPARA_BF16, 256)
+    assert info.narrow == 2 and info.n_panel_split_tiles > 0
+    args = np.zeros(3, dtype=B.GROUP_ARGS)
+    args["M"], args["K"], args["N"] = zip(*groups)
+    args["X"], args["W"], args["Y"], args["reserved"] = 0x100000, 0x200000, 0x300000, base
+    L = B.Launch(args.ctypes.data, 0x1000, tiles.ctypes.data, 0x2000, 0x3000, len(tiles), len(order), 256, 3, 0x7000000, info.workspace_bytes - 1,
+                 info.n_split_tiles, info.n_panel_split_tiles)
+    best = 1.0
+    for _ in range(100):
+        t0 = time.perf_counter()
+        assert B.lib().epara_grouped_forward(ctypes.addressof(L), B.EPARA_BF16, B.EPARA_BF16, None) == B.EPARA_ERR_CAPACITY
+        best = min(best, time.perf_counter() - t0)
+    assert best < 50e-6
+
+
 def test_panel_split_decision_and_its_error_paths():
     """epara_panel_split against the reference on the launches of the mixes and on shapes around the rule's edges
     (a full last round, a K below the class's split_K, gated groups, two different K, a streaming group next to
