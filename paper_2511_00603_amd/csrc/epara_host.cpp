@@ -12,6 +12,7 @@
 #include <climits>
 #include <cstring>
 #include <functional>
+#include <map>
 #include <queue>
 #include <utility>
 #include <vector>
@@ -147,6 +148,27 @@ private:
     std::vector<std::pair<int64_t, int64_t>> heap_;
 };
 
+// How many of the workgroups carry which load, for the finish of a schedule whose order nobody needs: equal items are placed a
+// level at a time instead of one by one.
+class load_levels {
+public:
+    explicit load_levels(int64_t n) { levels_[0] = n; }
+    void place(int64_t count, int64_t cost)                      // `count` items, each to one of the least loaded
+    {
+        while (count > 0) {
+            const auto lowest = levels_.begin();
+            const int64_t k = std::min(count, lowest->second);
+            levels_[lowest->first + cost] += k;
+            if (k == lowest->second) levels_.erase(lowest);
+            else lowest->second -= k;
+            count -= k;
+        }
+    }
+    int64_t most() const { return levels_.rbegin()->first; }
+private:
+    std::map<int64_t, int64_t> levels_;
+};
+
 // Block tiles of a launch: is group d (with rows) one of the block class, and visited in parts of K if the launch's are
 inline bool block_group(const epara_group_desc& d, const epara_tile_class* classes, int32_t n_classes, int32_t n_stream_classes)
 {
@@ -178,17 +200,15 @@ int32_t block_parts(const epara_group_desc* groups, int32_t G, const epara_tile_
     int32_t best_parts = 1;
     int64_t best = -1;
     for (int32_t P = 1; P <= EPARA_SPLIT_MAX_PARTS; ++P) {
-        least_loaded bins(W, nullptr);
-        int64_t finish = 0;
+        load_levels bins(W);
         for (int32_t g : members) {
             const epara_tile_class& c = class_at(g);
             const int32_t parts = block_splits(groups[g], c) ? P : 1;
             const int64_t TN = ceil_div(groups[g].N, c.BN);
-            for (int64_t m0 = 0; m0 < groups[g].M; m0 += c.BM) {
-                const int64_t each = block_visit_cost(panel_cost(groups[g], c, groups[g].M - m0), parts);
-                for (int64_t i = 0; i < TN * parts; ++i) finish = std::max(finish, bins.add_to_top(each));
-            }
+            for (int64_t m0 = 0; m0 < groups[g].M; m0 += c.BM)
+                bins.place(TN * parts, block_visit_cost(panel_cost(groups[g], c, groups[g].M - m0), parts));
         }
+        const int64_t finish = bins.most();
         if (best < 0 || finish < best) { best = finish; best_parts = P; }
     }
     return best_parts;
@@ -742,15 +762,13 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
 
     // 2. streaming tiles of every phase together, longest first onto the least loaded workgroup.  A group has at most two
     // different costs (its last column of tiles may be narrower), so equal costs are gathered instead of sorting items.
-    struct bucket { int64_t cost; std::vector<std::pair<int32_t, int32_t>> items; };       // (phase, entry), in the order of ties
-    std::vector<bucket> buckets;
-    size_t last = 0;
-    auto bucket_of = [&](int64_t cost) -> bucket& {
-        if (last < buckets.size() && buckets[last].cost == cost) return buckets[last];
-        for (last = 0; last < buckets.size(); ++last)
-            if (buckets[last].cost == cost) return buckets[last];
-        buckets.push_back({cost, {}});
-        return buckets[last];
+    typedef std::vector<std::pair<int32_t, int32_t>> items;      // (phase, entry), in the order of ties
+    std::map<int64_t, items, std::greater<int64_t>> buckets;     // by cost, the largest first
+    items* last = nullptr;
+    int64_t last_cost = -1;
+    auto bucket_of = [&](int64_t cost) -> items& {
+        if (cost != last_cost) { last = &buckets[cost]; last_cost = cost; }
+        return *last;
     };
     for (int32_t p = 0; p < n_phases; ++p) {
         const epara_phase_schedule& ph = phases[p];
@@ -760,23 +778,22 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
                 const epara_tile_class& c = ph.classes[ph.tiles[t].cls];
                 const int64_t cost = tile_cost(d, ph.tiles[t], ph.classes, ph.n_stream_classes);
                 const int32_t parts = n_phases == 1 ? split_parts(d, c) : 1;       // the phases of a chain are not split
-                if (parts == 1) { bucket_of(cost).items.push_back({p, static_cast<int32_t>(t)}); continue; }
+                if (parts == 1) { bucket_of(cost).push_back({p, static_cast<int32_t>(t)}); continue; }
                 if (ph.n_tiles > 0xFFFFFF) return EPARA_ERR_SHAPE;
-                bucket& bk = bucket_of(visit_cost(cost, parts, d, ph.tiles[t], c));
-                for (int32_t j = 0; j < parts; ++j) bk.items.push_back({p, EPARA_ORDER_ENTRY(static_cast<int32_t>(t), j, parts)});
+                items& same = bucket_of(visit_cost(cost, parts, d, ph.tiles[t], c));
+                for (int32_t j = 0; j < parts; ++j) same.push_back({p, EPARA_ORDER_ENTRY(static_cast<int32_t>(t), j, parts)});
             }
     }
     if (!buckets.empty()) {
-        std::sort(buckets.begin(), buckets.end(), [](const bucket& a, const bucket& b) { return a.cost > b.cost; });
         // next to block tiles they run in a kernel of their own, on level workgroups
         bool apart = false;
         if (n_phases == 1)
             for (int32_t c = phases[0].n_stream_classes; c < phases[0].n_classes; ++c) apart = apart || phases[0].classes[c].BM == EPARA_BLOCK_ROWS;
         least_loaded bins(W, apart ? nullptr : load.data());
-        for (const bucket& bk : buckets)
-            for (const auto& it : bk.items) {
+        for (const auto& same : buckets)
+            for (const auto& it : same.second) {
                 visits[it.first].push_back({static_cast<int32_t>(bins.top()), it.second});
-                bins.add_to_top(bk.cost);
+                bins.add_to_top(same.first);
             }
     }
 
@@ -865,7 +882,58 @@ int32_t phase_options(const epara_group_desc* groups, int32_t G, int32_t in_dtyp
     return EPARA_OK;
 }
 
-// The block table of a single launch (see epara_plan_launch): schedules it into `order` and says whether it is expected to finish earlier than `best`, the choice among the other tables with its order.
+// The finish of a single launch's block tiles and streaming tiles under the cost model (see epara_plan_launch), without
+// their order: the same sequences of costs as in schedule().
+int64_t block_finish(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes, int32_t n_stream,
+                     int64_t W, int32_t panel_m, int32_t panel_n)
+{
+    const int32_t block_class = n_classes - 1, split = block_parts(groups, G, classes, n_classes, n_stream, W);
+    const epara_tile_class& c = classes[block_class];
+    std::vector<int32_t> members;
+    std::map<int64_t, int64_t, std::greater<int64_t>> stream;    // cost -> how many visits
+    for (int32_t g = 0; g < G; ++g) {
+        const epara_group_desc& d = groups[g];
+        if (d.M <= 0) continue;
+        const int32_t k = class_of(d.M, classes, n_classes);
+        if (k == block_class) { members.push_back(g); continue; }
+        epara_tile tl = {g, 0, 0, d.M, classes[k].BN, k};
+        const int32_t parts = split_parts(d, classes[k]);
+        for (const int64_t cols : {static_cast<int64_t>(classes[k].BN), static_cast<int64_t>(d.N % classes[k].BN)}) {
+            tl.cols = static_cast<int32_t>(cols);
+            const int64_t tiles = (cols == classes[k].BN ? d.N / classes[k].BN : cols > 0) * ceil_div(d.M, classes[k].BM);
+            if (tiles > 0) stream[visit_cost(tile_cost(d, tl, classes, n_stream), parts, d, tl, classes[k])] += tiles * parts;
+        }
+    }
+    std::stable_sort(members.begin(), members.end(), [&](int32_t a, int32_t b) {
+        return panel_cost(groups[a], c, groups[a].M) > panel_cost(groups[b], c, groups[b].M);
+    });
+    load_levels blocks(W), streams(W);
+    int64_t count = 0, each = 0;                                 // a run of equal items that is not placed yet
+    for (int32_t g : members) {
+        const epara_group_desc& d = groups[g];
+        const int64_t TM = ceil_div(d.M, c.BM), TN = ceil_div(d.N, c.BN);
+        const int32_t parts = block_splits(d, c) ? split : 1;
+        const int64_t whole = block_visit_cost(panel_cost(d, c, c.BM), parts), bottom = block_visit_cost(panel_cost(d, c, d.M - (TM - 1) * c.BM), parts);
+        auto run = [&](int64_t n, int64_t cost) {
+            if (cost != each) { blocks.place(count, each); count = 0; each = cost; }
+            count += n * parts;
+        };
+        for (int64_t pn = 0; pn < TN; pn += panel_n) {
+            const int64_t cols = std::min<int64_t>(panel_n, TN - pn), upper = (TM - 1) / panel_m * panel_m;      // rows of the panels above the last
+            run(cols * upper, whole);
+            if (whole == bottom) run(cols * (TM - upper), whole);
+            else
+                for (int64_t tn = 0; tn < cols; ++tn) { run(TM - 1 - upper, whole); run(1, bottom); }
+        }
+    }
+    blocks.place(count, each);
+    if (stream.empty()) return blocks.most();
+    for (const auto& same : stream) streams.place(same.second, same.first);
+    return blocks.most() + streams.most() + EPARA_COST_KERNEL;
+}
+
+// The block table of a single launch (see epara_plan_launch): whether it is expected to finish earlier than `best`, the choice
+// among the other tables with its order; if so it is cut and scheduled into `order`.
 int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype, int32_t gated, int64_t W, int32_t n_xcd,
                      int32_t panel_m, int32_t panel_n, const phase_option& best, const std::vector<int32_t>& best_order,
                      phase_option& o, std::vector<int32_t>& order, int64_t* finish, bool* take)
@@ -883,28 +951,27 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
                                       best.classes[tl.cls], panel) + (panel && best_order[i] >> 28 == 0 ? EPARA_COST_PANEL_START : 0);
         }
     const int64_t other = *std::max_element(load.begin(), load.end());
+    if (int32_t st = epara_kernel_classes(in_dtype, gated, EPARA_TABLE_BLOCK, o.classes, 4, &o.n_classes, &o.n_stream)) return st;
+    // no schedule of the block tiles finishes before their level load
+    int64_t total = 0;
+    for (int32_t g = 0; g < G; ++g)
+        if (groups[g].M > 0 && block_group(groups[g], o.classes, o.n_classes, o.n_stream)) {
+            const epara_tile_class& c = o.classes[o.n_classes - 1];
+            const int64_t TM = ceil_div(groups[g].M, c.BM);
+            total += ceil_div(groups[g].N, c.BN) * ((TM - 1) * panel_cost(groups[g], c, c.BM) + panel_cost(groups[g], c, groups[g].M - (TM - 1) * c.BM));
+        }
+    if (total / W >= other) return EPARA_OK;
+    *finish = block_finish(groups, G, o.classes, o.n_classes, o.n_stream, W, panel_m, panel_n);
+    if (*finish >= other) return EPARA_OK;
     if (int32_t st = make_option(groups, G, in_dtype, gated, EPARA_TABLE_BLOCK, o)) return st;
+    if (o.tiles.size() > 0xFFFFFF) return EPARA_OK;              // more than an entry of an order with parts can name
+    *take = true;
     epara_phase_schedule ph;
     std::memset(&ph, 0, sizeof ph);
     ph.groups = groups; ph.classes = o.classes; ph.tiles = o.tiles.data();
     ph.n_tiles = static_cast<int64_t>(o.tiles.size());
     ph.G = G; ph.n_classes = o.n_classes; ph.n_stream_classes = o.n_stream;
-    if (int32_t st = schedule(&ph, 1, static_cast<int32_t>(W), n_xcd, panel_m, panel_n, &order)) return st;
-    load.assign(static_cast<size_t>(W), 0);
-    std::vector<int64_t> stream(static_cast<size_t>(W), 0);
-    bool any_stream = false;
-    for (size_t i = 0; i < order.size(); ++i)
-        if (order[i] >= 0) {
-            const epara_tile& tl = o.tiles[EPARA_ORDER_TILE(order[i])];
-            const int64_t cost = visit_cost(tile_cost(groups[tl.group], tl, o.classes, o.n_stream), (order[i] >> 28) + 1, groups[tl.group], tl, o.classes[tl.cls],
-                                            tl.cls >= o.n_stream);
-            if (tl.cls >= o.n_stream) load[i % W] += cost;
-            else { stream[i % W] += cost; any_stream = true; }
-        }
-    *finish = *std::max_element(load.begin(), load.end()) +
-              (any_stream ? *std::max_element(stream.begin(), stream.end()) + EPARA_COST_KERNEL : 0);
-    *take = *finish < other;
-    return EPARA_OK;
+    return schedule(&ph, 1, static_cast<int32_t>(W), n_xcd, panel_m, panel_n, &order);
 }
 
 void fill_plan(epara_launch_plan& plan, const phase_option& o, int32_t gated, int64_t n_slots, int64_t makespan)

@@ -598,6 +598,42 @@ def test_a_plan_says_which_class_table_it_was_made_with(monkeypatch):
         assert plan.narrow == table and plan.classes.tolist() == classes.tolist() and plan.n_stream_classes == n_stream
 
 
+@pytest.mark.parametrize("panels", [(1, 4), (2, 3), (8, 4), (3, 1)])
+@pytest.mark.parametrize("shapes,act,dtype", [([(75, 4096, 11008), (130, 4096, 11008), (237, 4096, 11008)], 5, B.EPARA_BF16),
+                                              ([(3, 11008, 4096), (40, 11008, 4096), (1501, 11008, 4096)], 0, B.EPARA_BF16),
+                                              ([(700, 3072, 768), (50, 900, 333), (1000, 768, 2304), (129, 1024, 130)], 0, B.EPARA_BF16),
+                                              ([(600, 2048, 700), (17, 640, 100)], 0, B.EPARA_FP8_E4M3)])
+def test_the_finish_that_block_tiles_are_chosen_by_is_that_of_their_order(shapes, act, dtype, panels):
+    """The choice is made from the finish of the block tiles, which is computed without their order: it must be the one of the
+    order that the plan then holds, for every shape of the panels of tiles."""
+    W = 256
+    info, _, _, _, tiles, order, _ = B.epara_plan_launch(_desc(shapes, act), dtype, W, 8, *panels)
+    assert info.narrow == 2
+    classes = [tuple(int(v) for v in c) for c in info.class_table()]
+    block, stream = [0] * W, [0] * W
+    for slot, e in enumerate(order):
+        if e >= 0:
+            t, _, parts = P.order_decode(int(e))
+            tl = tuple(int(v) for v in tiles[t])
+            if tl[5] == 3:
+                cost = P.panel_cost(shapes[tl[0]][0], shapes[tl[0]][1], classes[3], tl[3])
+                block[slot % W] += cost if parts == 1 else cost // parts + 500000
+            else:
+                stream[slot % W] += _ref_cost(shapes[tl[0]], tl, classes, 3, act == 5, parts)
+    assert info.makespan == max(block) + (max(stream) + 400000 if max(stream) else 0)
+
+
+def test_planning_a_launch_that_keeps_its_panel_tiles_is_quick():
+    """4 x 600 rows in fp8: the block tiles lose before they are cut and scheduled (50 us; 980 when they were)."""
+    import time
+    g, best = _desc([(600, 11008, 4096)] * 4), 1.0
+    for _ in range(40):
+        t0 = time.perf_counter()
+        info = B.epara_plan_launch(g, B.EPARA_FP8_E4M3, 256)[0]
+        best = min(best, time.perf_counter() - t0)
+    assert info.narrow == 0 and best < 400e-6
+
+
 def test_a_chain_of_one_phase_is_planned_without_block_tiles():
     """epara_grouped_chain has no kernel for block tiles, so epara_plan_chain must not choose them where epara_plan_launch does."""
     for groups, dtype in (([(200, 512, 512)], B.EPARA_BF16), ([(300, 2048, 400), (7, 512, 64)], B.EPARA_FP8_E4M3)):
