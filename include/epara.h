@@ -462,7 +462,8 @@ int64_t epara_split_workspace_bytes(int32_t n_split_tiles, int32_t n_panel_split
  * The caller writes split_base[g] into epara_group_args.reserved, sets epara_launch.n_split_tiles (and
  * n_panel_split_tiles from epara_panel_split) and provides a workspace of
  * epara_split_workspace_bytes(n_split_tiles, n_panel_split_tiles) bytes, zeroed once with epara_workspace_init
- * (a launch leaves its counters zero).  epara_plan_launch does all of this.
+ * (a launch leaves its counters zero; the partial sums behind them are written before they are read, so the first
+ * 4 (n_split_tiles + n_panel_split_tiles) bytes, rounded up to 256, are enough).  epara_plan_launch does all of this.
  * A launch's partial sums follow its counters, rounded up to 256 bytes, so launches that run one after the other may
  * share a workspace if their counters take the same room: ceil(c / 64) is the same, with c = n_split_tiles +
  * n_panel_split_tiles (block table: n_split_tiles + ceil(3 n_panel_split_tiles / 8)).  Otherwise each needs its own, or
@@ -472,7 +473,7 @@ int32_t epara_split_layout(const epara_group_desc* groups, int32_t G,
                            const epara_tile_class* classes, int32_t n_classes, int32_t n_stream_classes,
                            int32_t* split_base, int32_t* n_split_tiles, int64_t* workspace_bytes);
 
-/* Zeroes a launch workspace (one small kernel on `stream`). */
+/* Zeroes a launch workspace, or its first `bytes` bytes (one small kernel on `stream`). */
 int32_t epara_workspace_init(void* d_workspace, int64_t bytes, void* stream);
 
 /* Visit order of the persistent workgroups.  Workgroup b of W = n_workgroups visits slots

@@ -116,7 +116,8 @@ class LaunchPlan:
         self.d_workspace = None
         if self.workspace_bytes:
             self.d_workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=device)
-            B.epara_workspace_init(self.d_workspace.data_ptr(), self.workspace_bytes, current_stream_handle())
+            counters = 4 * (self.n_split_tiles + self.n_panel_split_tiles)       # the rest is written before it is read
+            B.epara_workspace_init(self.d_workspace.data_ptr(), (counters + 255) // 256 * 256, current_stream_handle())
         torch.cuda.synchronize(device)
         self.upload_seconds = time.perf_counter() - t0
         self.c = B.Launch(self.args.ctypes.data, self.d_args.data_ptr(), self.tiles.ctypes.data, self.d_tiles.data_ptr(),

@@ -577,6 +577,20 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
         assert all(ph["info"].narrow != 2 for ph in phases)
 
 
+def test_a_plan_zeroes_the_counters_of_its_workspace_only(monkeypatch):
+    """A down projection of 3 + 40 + 1501 rows has 142 MB of workspace and 192 counters."""
+    from paper_2511_00603_amd import runtime as R
+    zeroed = []
+    monkeypatch.setattr(R, "_require_gpu", lambda: None)
+    monkeypatch.setattr(R, "current_stream_handle", lambda: 0)
+    monkeypatch.setattr(R.torch.cuda, "synchronize", lambda *a: None)
+    monkeypatch.setattr(B, "epara_workspace_init", lambda ws, nbytes, stream=0: zeroed.append(nbytes))
+    args = np.zeros(3, dtype=B.GROUP_ARGS)
+    args["M"], args["K"], args["N"] = (3, 40, 1501), 11008, 4096
+    plan = R.LaunchPlan(args, B.EPARA_BF16, "cpu", 256)
+    assert plan.workspace_bytes > 1 << 27 and zeroed == [-(-4 * (plan.n_split_tiles + plan.n_panel_split_tiles) // 256) * 256]
+
+
 def test_plan_launch_reports_a_bad_grid_as_the_library_does():
     for kw in (dict(n_workgroups=-8), dict(n_workgroups=0), dict(n_workgroups=250), dict(n_workgroups=256, n_xcd=0), dict(n_workgroups=256, panel_m=0)):
         with pytest.raises(B.EparaError) as e:

@@ -270,6 +270,22 @@ def test_block_tiles_in_parts_without_a_workspace_are_still_computed():
         assert np.array_equal(y, ref.bf16_decode(ref.bf16_encode(yref)))
 
 
+@pytest.mark.parametrize("shapes,W_", [([(300, 2064, 500), (600, 2064, 300)], 8), ([(40, 8208, 200), (17, 8192, 70)], None),
+                                       ([(75, 1040, 130), (200, 4112, 72), (40, 8208, 136)], None)])
+def test_only_the_counters_of_a_workspace_have_to_be_zero(shapes, W_):
+    """Panel, streaming and block tiles in parts on a workspace whose partial sums start as NaN: bit for bit."""
+    rng = np.random.default_rng(59)
+    specs = [{"X": rng.integers(-3, 4, (M, K)).astype(np.float32), "W": rng.integers(-2, 3, (K, N)).astype(np.float32),
+              "b": None, "act": "none"} for M, K, N in shapes]
+    G = U.Groups(specs, "bf16", n_workgroups=W_)
+    counters = 4 * (G.plan.n_split_tiles + G.plan.n_panel_split_tiles)
+    assert counters > 0
+    G.plan.d_workspace.fill_(255)
+    B.epara_workspace_init(G.plan.d_workspace.data_ptr(), -(-counters // 256) * 256, R.current_stream_handle())
+    for sh, y, yref in zip(shapes, G.run(), G.expected()):
+        assert np.array_equal(y, ref.bf16_decode(ref.bf16_encode(yref))), sh
+
+
 def test_two_plans_of_one_argument_array_do_not_disturb_each_other():
     """The split tiles of a plan meet at places of its own: making a second plan, for another grid, from the same array of
     arguments changes neither the array nor the first plan."""
