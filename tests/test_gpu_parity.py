@@ -61,10 +61,26 @@ def check_mix(mix, dtype_name, rows=None, h_scales=None, host_bits=None):
     return worst
 
 
+# A launch with batches of more than 64 rows runs them as block tiles (128 rows) where the planner expects those to finish
+# earlier, as it does on a whole chip for the small launches below, and as panel tiles (256 rows) otherwise, always on fewer
+# than 128 workgroups: what is said of either kind of tile is tested on a grid that has it.
+TALL = {"block": (None, 128), "panel": (64, 256)}
+
+
+def tall_groups(specs, dtype_name, tiles):
+    """Groups on a grid that runs the batches of more than 64 rows as `tiles` ("block", "panel"; fp32: None)."""
+    if tiles is None:
+        return U.Groups(specs, dtype_name)
+    n_workgroups, rows = TALL[tiles]
+    G = U.Groups(specs, dtype_name, n_workgroups=n_workgroups)
+    assert int(G.plan.classes[-1][1]) == rows and any(int(c) == len(G.plan.classes) - 1 for c in G.plan.tiles["cls"])
+    return G
+
+
 # ---- exactness on integer-valued inputs (layout, indexing, tails) -----------------------------
 
-@pytest.mark.parametrize("dtype_name", ["f32", "bf16", "fp8"])
-def test_small_integers_are_bit_exact(dtype_name):
+@pytest.mark.parametrize("dtype_name,tiles", [("f32", None), ("bf16", "block"), ("bf16", "panel"), ("fp8", "block"), ("fp8", "panel")])
+def test_small_integers_are_bit_exact(dtype_name, tiles):
     """Small integers: every product and sum is exact in fp32, so the output must be the oracle's, bit for bit,
     after the cast.  fp8 runs with power-of-two per-tensor scales (1/8 for X, 1/4 for W), under which the
     codes, their products and the scale product 2^-5 are all exact."""
@@ -76,7 +92,7 @@ def test_small_integers_are_bit_exact(dtype_name):
         W = rng.integers(-3, 4, (K, N)).astype(np.float32)
         b = rng.integers(-8, 9, N).astype(np.float32)
         specs.append({"X": X, "W": W, "b": b, "act": "relu", "s_x": 0.125, "s_w": 0.25})
-    G = U.Groups(specs, dtype_name)
+    G = tall_groups(specs, dtype_name, tiles)
     got, want = G.run(), G.expected()
     for (M, K, N), y, yref in zip(shapes, got, want):
         if dtype_name != "f32":
@@ -371,8 +387,8 @@ def test_linearity_in_x(dtype_name):
 
 
 def test_fp32_small_batches_with_awkward_shapes():
-    """Batches of at most 16 rows take the fp32 path that cuts K into four quarters: K smaller than the number of
-    quarters, K not a multiple of the staging step, ragged column tiles, every activation, next to a group of
+    """Batches of at most 16 rows take the fp32 path that cuts K into sixteen shares of pieces of 16: K of less than a
+    piece, of fewer pieces than shares, not a multiple of a piece, ragged column tiles, every activation, next to a group of
     the 64-row class in the same launch."""
     rng = np.random.default_rng(21)
     acts = ["none", "relu", "gelu_erf", "gelu_tanh", "silu"]
@@ -453,15 +469,15 @@ def test_gated_and_fp8_outputs_do_not_depend_on_the_grid_or_the_other_services(d
 
 # ---- edge cases -------------------------------------------------------------------------------------
 
-@pytest.mark.parametrize("dtype_name", ["f32", "bf16", "fp8"])
-def test_ragged_and_degenerate_groups(dtype_name):
+@pytest.mark.parametrize("dtype_name,tiles", [("f32", None), ("bf16", "block"), ("bf16", "panel"), ("fp8", "block"), ("fp8", "panel")])
+def test_ragged_and_degenerate_groups(dtype_name, tiles):
     rng = np.random.default_rng(15)
     kmul = 16 if dtype_name == "fp8" else 8
     shapes = [(0, 64, 32, "none"), (1, kmul, 1, "none"), (1, 64, 10, "relu"), (64, 5 * kmul, 33, "gelu_erf"),
               (65, 3 * kmul, 31, "silu"), (255, 7 * kmul, 255, "gelu_tanh"), (256, 128, 256, "none"),
               (257, 64 + kmul, 257, "relu"), (0, 32, 8, "none"), (513, 2 * kmul, 7, "none")]
     specs = [U.rand_spec(rng, M, K, N, act) for M, K, N, act in shapes]
-    G = U.Groups(specs, dtype_name)
+    G = tall_groups(specs, dtype_name, tiles)
     got, want = G.run(), G.expected()
     for sh, y, yref in zip(shapes, got, want):
         assert y.shape == yref.shape
@@ -469,10 +485,11 @@ def test_ragged_and_degenerate_groups(dtype_name):
             assert_close(y, yref, TOL[dtype_name], str(sh))
 
 
+@pytest.mark.parametrize("tiles", ["panel", "block"])
 @pytest.mark.parametrize("dtype_name", ["bf16", "fp8"])
-def test_every_activation_on_whole_and_ragged_panel_tiles(dtype_name):
-    """The matrix-core kernels use the hardware's exp / reciprocal and a rational erf in their epilogue;
-    whole 256 x 256 tiles run an unrolled epilogue, ragged ones a loop: both against the fp64 oracle, with
+def test_every_activation_on_whole_and_ragged_tall_tiles(dtype_name, tiles):
+    """The matrix-core kernels use the hardware's exp / reciprocal and a rational erf in their epilogue; whole 256 x 256
+    tiles run an unrolled epilogue, ragged ones a loop, block tiles one of their own: all against the fp64 oracle, with
     bias, K of one to five stages incl. an odd stage count and a ragged last stage."""
     rng = np.random.default_rng(16)
     kmul = 16 if dtype_name == "fp8" else 8
@@ -481,15 +498,16 @@ def test_every_activation_on_whole_and_ragged_panel_tiles(dtype_name):
     specs = [U.rand_spec(rng, M, K, N, act) for M, K, N, act in shapes]
     for sp in specs:                                                     # activations need arguments of both signs and sizes
         sp["X"] *= 2.0
-    G = U.Groups(specs, dtype_name)
+    G = tall_groups(specs, dtype_name, tiles)
     got, want = G.run(), G.expected()
     for sh, y, yref in zip(shapes, got, want):
         assert_close(y, yref, TOL[dtype_name], str(sh))
 
 
-def test_output_beyond_four_gibibytes_is_addressed_with_64_bits():
+@pytest.mark.parametrize("tiles", ["panel", "block"])
+def test_output_beyond_four_gibibytes_is_addressed_with_64_bits(tiles):
     """One group whose output has more than 2^32 bytes (and its last rows more than 2^31 elements in): rows
-    sampled from the start, the 4 GiB boundary and the end against the oracle, panel tiles whole and ragged."""
+    sampled from the start, the 4 GiB boundary and the end against the oracle, tiles whole and ragged."""
     rng = np.random.default_rng(17)
     M, K, N = 36100, 16, 60040
     sp = U.rand_spec(rng, M, K, N, "relu")
@@ -499,7 +517,9 @@ def test_output_beyond_four_gibibytes_is_addressed_with_64_bits():
     db = torch.from_numpy(sp["b"]).to(U.DEV)
     dY = torch.zeros((M, N), dtype=torch.bfloat16, device=U.DEV)
     assert dY.numel() * 2 > 2 ** 32
-    plan = R.LaunchPlan(np.array([R.group_args(dX, dW, dY, M, K, N, "relu", bias=db)], dtype=B.GROUP_ARGS), B.EPARA_BF16, U.DEV)
+    plan = R.LaunchPlan(np.array([R.group_args(dX, dW, dY, M, K, N, "relu", bias=db)], dtype=B.GROUP_ARGS), B.EPARA_BF16, U.DEV,
+                        TALL[tiles][0])
+    assert int(plan.classes[-1][1]) == TALL[tiles][1]
     R.grouped_forward(plan, B.EPARA_BF16)
     torch.cuda.synchronize()
     edge = 2 ** 32 // (2 * N)                                            # the row that straddles byte 2^32
