@@ -55,19 +55,25 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
     ldsptr l3 = (ldsptr)lds;
     const int K = ga.K, N = ga.N, rows = tl.rows, cols = tl.cols;
     const int KSP = ((K + KF - 1) / KF + 3) & ~3;
-    const uint32_t units = static_cast<uint32_t>(KSP >> 2);      // a visit covers whole units of two pairs
+    // a visit to the whole tile, or to a part of its K: whole units of two pairs.  Where the launch brought no room for the parts'
+    // sums (or an entry is none of a planner's), the first visit multiplies the whole K.
     constexpr bool HAS_SPLIT = DT == EPARA_BF16 && !GATED;
-    const int part = order_part(entry);
-    int parts = order_parts(entry);
-    const int slot_tile = HAS_SPLIT && parts > 1 ? ga.reserved + (tl.m0 >> 7) * ((N + 127) >> 7) + (tl.n0 >> 7) : 0;
-    // the launch brought no room for the parts' sums (or holds more parts than there are units): the first visit multiplies
-    // the whole K
-    if (parts > 1 && (!HAS_SPLIT || sp.ws == nullptr || parts > SPLIT_MAX_PARTS || ga.reserved < 0 || slot_tile >= sp.first_panel || static_cast<uint32_t>(parts) > units)) {
-        if (part != 0) return;
-        parts = 1;
+    int parts = order_parts(entry), part = 0, slot_tile = 0, first_pair = 0, n_pairs = KSP >> 1;
+    if (parts > 1) {
+        bool room = false;
+        part = order_part(entry);
+        if constexpr (HAS_SPLIT) {
+            const uint32_t units = static_cast<uint32_t>(KSP >> 2);
+            slot_tile = ga.reserved + (tl.m0 >> 7) * ((N + 127) >> 7) + (tl.n0 >> 7);
+            room = sp.ws != nullptr && parts <= SPLIT_MAX_PARTS && ga.reserved >= 0 && slot_tile < sp.first_panel && static_cast<uint32_t>(parts) <= units;
+            if (room) {
+                first_pair = 2 * static_cast<int>(units * part / parts);
+                n_pairs = 2 * static_cast<int>(units * (part + 1) / parts) - first_pair;
+            }
+        }
+        if (!room) parts = 1;
+        if (part >= parts) return;
     }
-    if (part >= parts) return;                                   // no entry of a planner
-    const int first_pair = 2 * static_cast<int>(units * part / parts), n_pairs = 2 * static_cast<int>(units * (part + 1) / parts) - first_pair;
 
     // ---- activations: instruction j of a pair covers rows 8 (4 j + wave) .. + 7; lane l writes chunk l % 8 of row l / 8
     // and fetches the chunk that belongs there (chunk ^ (row / 2) % 8: fragment reads are free of bank conflicts)
@@ -286,6 +292,9 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
         if (parts == 2)      add(act_tag<2>{});
         else if (parts == 3) add(act_tag<3>{});
         else                 add(act_tag<4>{});
+        // nothing is in flight here; said, because a load that the compiler takes for pending on some path makes the K loop of
+        // every later tile wait for all its loads once a round (2 us per launch)
+        wait_vmcnt<0>();
     }
     auto finish = [&](auto out_tag, auto act) {
         constexpr int OUT = decltype(out_tag)::value, ACT = decltype(act)::value;
