@@ -64,8 +64,8 @@ typedef enum { EPARA_CAT_LATENCY = 0, EPARA_CAT_FREQUENCY = 1 } epara_category;
 typedef struct { int32_t M, K, N; int32_t act; int32_t has_bias; int32_t category; } epara_group_desc;
 
 /* A group with M <= max_M (first such class wins) is cut into BM x BN output tiles.  split_K: 0, or the K
- * from which a single launch may visit a tile of this class in parts of K (see "Splitting K" below): a
- * weight-streaming tile in two, the panel tiles of a launch's last round in two to four. */
+ * from which a single launch may visit a tile of this class in parts of K (see "Splitting K" and "Block tiles" below): a
+ * weight-streaming tile in two, the panel tiles of a launch's last round in two to four, block tiles in up to four. */
 typedef struct { int32_t max_M; int32_t BM, BN; int32_t split_K; } epara_tile_class;
 
 /* One output tile: rows [m0, m0+rows) x columns [n0, n0+cols) of group `group`. 24 bytes. */
@@ -102,7 +102,7 @@ typedef struct {
     void*   d_workspace;              /* device, 256-byte aligned, zeroed once (epara_workspace_init); NULL if nothing is split */
     int64_t workspace_bytes;          /* at least epara_split_workspace_bytes(n_split_tiles, n_panel_split_tiles) */
     int32_t n_split_tiles;            /* streaming tiles whose K is split over several visits (epara_split_layout) */
-    int32_t n_panel_split_tiles;      /* panel tiles, the last ones of the tile table, likewise (epara_panel_split) */
+    int32_t n_panel_split_tiles;      /* panel tiles (the last ones of the tile table), or slots of block tiles, likewise (epara_panel_split) */
 } epara_launch;
 
 /* ---- chains of launches in one kernel -----------------------------------------------------
@@ -371,9 +371,10 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * tiles: 8.0 ns (K = 3072, N = 768) to 9.3 ns (K = 5120, N = 13824) per K and compute unit for f = 4, against 5.9 ns for a quarter of
  * a panel tile, which moves fewer bytes per product and so runs at higher clocks.  But a panel tile costs about 9 us of
  * start and finish (EPARA_COST_PANEL_START), which one wave per SIMD cannot overlap with anything and two workgroups
- * per unit hide from each other.  The constants are fitted to both kernels' times on 112 launches (SwiGLU batches of 1
- * .. 2048 rows, K = 1120 .. 13824, bf16 and fp8; layers of vision transformers of 192 .. 1024 columns): where the model takes
- * block tiles they were 1.0 .. 4.3 times as fast, where it does not at most 1.4 times.
+ * per unit hide from each other.  The constants were fitted to both kernels' times on such launches (SwiGLU batches of 1
+ * .. 2048 rows, K = 1120 .. 13824, bf16 and fp8; layers of vision transformers of 192 .. 1024 columns).  On the 123 of
+ * profiles/block_tile_launches.txt they are 0.98 .. 3.7 times as fast where the model takes block tiles (74) and would be
+ * 0.72 .. 1.5 times as fast where it does not.
  *
  * Block tiles of a long K.  Few tiles of a long K (a down projection) leave units idle, so the tiles of the groups with
  * K >= the block class's split_K > 0 (EPARA_BLOCK_SPLIT_K for plain bf16 launches; 0 for gated and fp8 ones, whose results do not
@@ -386,8 +387,8 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * runs the epilogue.  Three split tiles share a slot of a split panel tile: epara_launch.n_panel_split_tiles =
  * ceil(split block tiles / EPARA_BLOCK_TILES_PER_SLOT), and split_base[g] = index of the group's first tile among them.
  * EPARA_BLOCK_TILES_PER_COUNTER of them share a counter, 4 bits each.
- * Measured, bf16, 74 rows, K = 11008, N = 4096 (32 tiles): 34 us in four parts (panel tiles in parts: 73); 563 rows, K = 2416, N = 2192 (90 tiles): 21 us in
- * three (panel tiles: 51). */
+ * Measured, bf16, 74 rows, K = 11008, N = 4096 (32 tiles): 33 us in four parts (panel tiles in parts: 69); 563 rows, K = 2416, N = 2192
+ * (90 tiles): 19 us in two (panel tiles: 50). */
 #define EPARA_TABLE_BLOCK 2               /* `narrow` of the block table */
 #define EPARA_BLOCK_ROWS 128
 #define EPARA_BLOCK_MIN_WORKGROUPS 128    /* smaller grids leave units free, where workgroups do not pair up */
@@ -613,7 +614,7 @@ int32_t epara_ffn_swiglu_args(const epara_ffn_desc* ffn, int32_t G, int32_t in_d
 /* ---- device side -------------------------------------------------------------------- */
 
 /* An upper bound of the device workspace a launch of these groups on n_workgroups workgroups needs, whichever
- * class table the plan picks (epara_plan_launch reports the exact size): the larger of the two tables' needs;
+ * class table the plan picks (epara_plan_launch reports the exact size): the largest of the three tables' needs;
  * 0 when no tile would be split (fp32 launches, batches of at most 16 rows, short K, full last rounds).  -1 for
  * a bad dtype, G < 0, n_workgroups <= 0 or a mixture of EPARA_ACT_SWIGLU and other groups. */
 int64_t epara_workspace_bytes(const epara_group_desc* groups, int32_t G, int32_t in_dtype, int32_t n_workgroups);

@@ -13,9 +13,9 @@ namespace {
 // operands.  Operands go from memory straight into v_mfma_f32_16x16x4_f32 (products and sums in fp32): lane (i, q) loads
 // X[row i][k + 4 q .. + 3] and W[k + 4 q + e][column 4 i .. 4 i + 3] as 16-byte pieces; product e of a piece pairs the k
 // = 4 q + e of both, and the four columns of a lane belong to four accumulators, so that a lane ends with 4 rows x 4
-// consecutive columns.  Measured, three
-// launches of two MLPs (256-512-512-10, 4 and 16 rows): 37 -> 21 us a pass; one of 64 rows, 512-512-64: 71 -> 36 us (four waves that
-// staged 16 or 64 k at a time through the LDS and multiplied on the vector units).
+// consecutive columns.  Measured, three launches of two MLPs (256-512-512-10, 4 and 16 rows): 38.5 -> 23.7 us a pass; one launch of
+// 256 rows, 1024 x 1024, five times: 130 -> 69 us, 4096 rows: 257 -> 129 us (four waves that staged 16 or 64 k at a time through
+// the LDS and multiplied on the vector units).
 // A chain whose grid does not fit the chip with one such workgroup per unit runs workgroups of eight waves, two per unit, in
 // which a wave takes two of the sixteen shares one after the other: the same sums in the same order.
 constexpr int F32_WAVES = 16, F32_NT = F32_WAVES * 64, F32_BN = 64, F32_HALF_NT = F32_NT / 2;

@@ -405,6 +405,21 @@ def test_fp32_small_batches_with_awkward_shapes():
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("M,K", [(16, 256), (16, 1024), (64, 256), (64, 1024), (200, 4096)])
+def test_fp32_error_against_64_bits(M, K):
+    """fp32 tiles add K in sixteen (64 rows: eight) shares, so the error is that of sums of n = K / 16 (K / 8) products: a
+    rounding errs by about 0.4 u (u = 2^-24) of a partial sum that grows like the root of its length, 0.4 sqrt(n / 2) u = 0.29 sqrt(n) u in all,
+    and adding the shares by another u.  Bound: (0.33 sqrt(n) + 1.2) u, below what one sum over K shows (64 rows, K = 1024:
+    5.7e-7, here 2.1e-7, bound 2.9e-7)."""
+    rng = np.random.default_rng(61)
+    X = rng.uniform(-1, 1, (M, K)).astype(np.float32)
+    W = (rng.standard_normal((K, 512)) / np.sqrt(K)).astype(np.float32)
+    y = U.Groups([{"X": X, "W": W, "b": None, "act": "none"}], "f32").run()[0]
+    want = X.astype(np.float64) @ W.astype(np.float64)
+    n = K / (16 if M <= 16 else 8)
+    assert np.linalg.norm(y - want) <= (0.33 * np.sqrt(n) + 1.2) * 2.0 ** -24 * np.linalg.norm(want)
+
+
 # ---- independence and determinism ------------------------------------------------------------------
 
 def test_group_order_row_order_and_grid_size_do_not_change_a_single_bit():
