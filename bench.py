@@ -7,7 +7,7 @@ resident in HBM.  The headline workload is the prefill mix (two 13B-shaped SwiGL
 requests/s and the roofline fraction of every other mix (decode mix against HBM bandwidth; each mix
 also timed as one chained kernel), the
 roofline object of the headline mix's dominant kernel, and the CPU oracle timed on a bounded
-sample of the same workload.
+sample of the same workload; what is known of every launch goes to stderr.
 
     python bench.py [--steps K] [--warmup W] [--mixes 5,4] [--no-cpu-baseline]
 """
@@ -469,6 +469,27 @@ def cpu_baseline(mix, budget_s=15.0):
             "sample": "%d rows of service 0 of the prefill mix (SwiGLU FFN d=%d f=%d), fp64 triple loop, %.1f s" % (rows, d, f, dt)}
 
 
+def rounded(v):
+    """The same structure with floats of six significant digits."""
+    if isinstance(v, dict):
+        return {k: rounded(x) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [rounded(x) for x in v]
+    return float("%.6g" % v) if isinstance(v, float) else v
+
+
+# What the line carries of every mix; its launches and how they were timed go to stderr.
+MIX_KEYS = ("dtype", "ms_per_step", "ms_per_step_median", "ms_per_step_min", "tflops", "requests_per_s", "requests", "rows", "launches",
+            "plan_us", "plan_upload_us", "warm_cache_ms_per_step", "graph_replay_ms_per_step", "chained")
+
+
+def mix_summary(r):
+    out = {k: r[k] for k in MIX_KEYS if k in r}
+    out["roofline"] = {k: r["roofline"][k] for k in ("bound", "frac", "traffic") if k in r["roofline"]}
+    out["pass_frac"], out["two_streams_ms_per_step"] = r["pass_roofline"]["frac"], r["two_streams"]["ms_per_step"]
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -535,8 +556,10 @@ def main():
                 head["name"], head["dtype"], head["rows"], head["requests"], head["launches"])},
             "requests_per_s": head["requests_per_s"], "measured_peaks": peaks,
             "roofline": head["roofline"], "cpu_baseline": cpu, "pass_roofline": head["pass_roofline"], "batch_forming": forming, "vit_block_pieces": pieces,
-            "mixes": {("%s_%s" % (r["name"], r["dtype"])): r for r in results}}
-    print(json.dumps(line))
+            "mixes": {("%s_%s" % (r["name"], r["dtype"])): mix_summary(r) for r in results}}
+    for r in results:
+        print("# details " + json.dumps(rounded(r)), file=sys.stderr, flush=True)
+    print(json.dumps(rounded(line)))
 
 
 if __name__ == "__main__":
