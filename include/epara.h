@@ -369,20 +369,33 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * EPARA_COST_BLOCK_START.
  * Measured, bf16, 512 tiles at a time: K = 4096, own weights: 94 / 100 / 114 us for f = 1 / 2 / 4; weights shared by many row
  * tiles: 8.0 ns (K = 3072, N = 768) to 9.3 ns (K = 5120, N = 13824) per K and compute unit for f = 4, against 5.9 ns for a quarter of
- * a panel tile, which moves fewer bytes per product and so runs at higher clocks.  But a panel tile costs about 9 us of
- * start and finish (EPARA_COST_PANEL_START), which one wave per SIMD cannot overlap with anything and two workgroups
- * per unit hide from each other.  The constants were fitted to both kernels' times on such launches (SwiGLU batches of 1
- * .. 2048 rows, K = 1120 .. 13824, bf16 and fp8; layers of vision transformers of 192 .. 1024 columns).  On the 123 of
- * profiles/block_tile_launches.txt they are 0.98 .. 3.7 times as fast where the model takes block tiles (74) and would be
- * 0.72 .. 1.5 times as fast where it does not.
+ * a panel tile, which moves fewer bytes per product and so runs at higher clocks.
+ * The lists take the groups by descending cost of their first tile, groups of one row tile after the others (they stream weights
+ * for themselves alone and fill the gaps: 75 + 130 + 237 rows, K = 4096, N = 11008 gated: 157 -> 144 us, fp8 76 -> 62 us).  Inside a group
+ * the tiles go strip by strip and row by row; with at most EPARA_BLOCK_COLUMN_TILES row tiles and K >= EPARA_BLOCK_COLUMN_K column by
+ * column, so that the row tiles of a column run together on a die, whose L2 then fetches their weights once (600 + 700 rows, fp8 gated, K = 4096:
+ * 123 -> 114 us; 12 row tiles 241 -> 251, K = 768 65 -> 75: rows first).
+ *
+ * Which table.  Block tiles are taken where their estimate, and the streaming tiles' kernel next to them, is below the load
+ * of the most loaded workgroup under the other table, in which every visit to a whole panel tile costs EPARA_COST_PANEL_START more,
+ * every part of one EPARA_COST_PANEL_PART_START and the launch EPARA_COST_PANEL_LAUNCH (start and finish, which one wave per SIMD
+ * cannot overlap with anything and two workgroups per unit hide from each other).  The estimate is the larger of
+ *   the most loaded of W lists, when the visits, EPARA_COST_BLOCK_PER_32 * f * K / P + EPARA_COST_BLOCK_VISIT (P > 1: +
+ *     EPARA_COST_BLOCK_PART), groups by descending M, the ragged row tile of a group last, each go to the least loaded one, and of
+ *   the weights' way to the chip, sum of K * N * (2 for EPARA_ACT_SWIGLU) * (2 TM + 1) / EPARA_COST_BLOCK_STREAMED over the groups: fetched
+ *     once for the first of TM row tiles and two thirds of a time for each other one, at 5.3 TB/s.
+ * For fp8 the two constants of a visit count twice (a K is half the bytes).  Fitted to what either kernel takes on 500 launches of 65 .. 2500 rows, K = 384 .. 13824
+ * and N = 192 .. 13824: on 2600 others the choice (and that of P) is on average 0.6 % slower than the best of all, where the rule
+ * before it, of one list cost per tile, lost 9 %.
  *
  * Block tiles of a long K.  Few tiles of a long K (a down projection) leave units idle, so the tiles of the groups with
  * K >= the block class's split_K > 0 (EPARA_BLOCK_SPLIT_K for plain bf16 launches; 0 for gated and fp8 ones, whose results do not
  * depend on the grid or on the other groups) are visited in P = 1 .. EPARA_SPLIT_MAX_PARTS parts of K, the same P for the
  * whole launch: part j covers the units floor(U j / P) .. floor(U (j+1) / P) - 1 of the U = ceil(ceil(K / stage) / 4) units of
- * four 64-byte stages.  P is the one whose visits, the groups by descending cost of their first tile (ties: lower group), tiles
- * in table order, part by part, each to the least loaded of W lists, finish first (ties: fewer parts); 1 if the launch has more than
- * EPARA_BLOCK_SPLIT_MAX_PER_LIST * W block tiles.  A visit costs cost / P + EPARA_COST_BLOCK_PARTIAL.  Every visit leaves its raw
+ * four 64-byte stages.  P is the one of the smallest estimate (ties: fewer parts); 1 if the launch has more than
+ * EPARA_BLOCK_SPLIT_MAX_PER_LIST * W block tiles.  In the lists a visit costs cost / P + EPARA_COST_BLOCK_PARTIAL, and a group's first parts come
+ * before all its second ones: what runs together reads the same piece of the activations (1501 rows, K = 11008, N = 4096 in two parts:
+ * tile by tile 158 us, part by part 134; 75 + 130 + 237 rows in three: 94 -> 84).  Every visit leaves its raw
  * sums (64 KiB) in the workspace and counts itself at the tile; whoever counts last adds the parts in index order and
  * runs the epilogue.  Three split tiles share a slot of a split panel tile: epara_launch.n_panel_split_tiles =
  * ceil(split block tiles / EPARA_BLOCK_TILES_PER_SLOT), and split_base[g] = index of the group's first tile among them.
@@ -397,6 +410,13 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 #define EPARA_COST_BLOCK_PER_32 180
 #define EPARA_COST_BLOCK_START 80000
 #define EPARA_COST_PANEL_START 800000
+#define EPARA_COST_PANEL_PART_START 1980000
+#define EPARA_COST_PANEL_LAUNCH 1100000
+#define EPARA_COST_BLOCK_VISIT 200000
+#define EPARA_COST_BLOCK_PART 800000
+#define EPARA_COST_BLOCK_STREAMED 80
+#define EPARA_BLOCK_COLUMN_TILES 8
+#define EPARA_BLOCK_COLUMN_K 4096
 #define EPARA_BLOCK_SPLIT_K 1024
 #define EPARA_BLOCK_SPLIT_MAX_PER_LIST 3
 #define EPARA_BLOCK_TILES_PER_SLOT 3
@@ -538,10 +558,9 @@ typedef struct {
 /* The whole planning decision of one launch (Sec. 3.1: the parallel mode of each task): picks the class
  * table -- the wide one, or the narrow one when some batch has more than 32 rows and the narrow
  * table's schedule has the smaller makespan under the cost model (ties: wide); or the block table ("Block tiles"), for
- * bf16 / fp8 launches with a batch of more than 64 rows and n_workgroups >= EPARA_BLOCK_MIN_WORKGROUPS, when its makespan T
- * (the largest load of block tiles, plus the largest load of streaming tiles and EPARA_COST_KERNEL if there are any) is
- * below U, the largest load of a workgroup in the order of the other choice with
- * EPARA_COST_PANEL_START added to every visit to a whole panel tile -- then plans
+ * bf16 / fp8 launches with a batch of more than 64 rows and n_workgroups >= EPARA_BLOCK_MIN_WORKGROUPS, when its estimate
+ * (plus the largest load of streaming tiles and EPARA_COST_KERNEL if there are any) is below that of the other choice ("Which table");
+ * its makespan is the largest load of block tiles plus the same for streaming tiles -- then plans
  * (epara_plan_groups) and schedules (epara_schedule_tiles) with it.  The groups must be all
  * EPARA_ACT_SWIGLU or none (ERR_DTYPE).  (A chain, epara_plan_chain, has no block tiles, not even one of a single phase.)  *plan is always written (sizes included); tiles / order are
  * written when given and large enough, else ERR_CAPACITY (give NULL and 0 to ask for the sizes only;

@@ -313,13 +313,31 @@ def panel_split(groups, classes, n_stream_classes, n_workgroups):
     return (m, parts, more) if parts > 1 else (0, 1, 0)
 
 
+def block_estimate(groups, classes, n_stream_classes, n_workgroups, parts, unit):
+    """What a launch's block tiles take when those that may be split are visited in `parts` parts of K: the larger of
+    the most loaded of W lists, when the visits (180 K f // P + 200000 unit, in parts 800000 unit more; f = ceil(rows / 32)), groups by
+    descending M, whole row tiles before the last one, each go to the least loaded list, and of
+    sum K N (2 if gated) (2 TM + 1) // 80 (weights fetched (2 TM + 1) / 3 times).  unit: 2 for fp8, 1 for bf16."""
+    import heapq
+    bins, streamed = [0] * n_workgroups, 0
+    members = [g for g, gr in enumerate(groups) if gr[0] > 0 and pick_class(gr[0], classes) >= n_stream_classes]
+    for g in sorted(members, key=lambda g: -groups[g][0]):
+        M, K, N = groups[g][:3]
+        cl = classes[pick_class(M, classes)]
+        p = parts if len(cl) > 3 and cl[3] > 0 and K >= cl[3] else 1
+        for m0 in range(0, M, 128):
+            each = 180 * -(-min(128, M - m0) // 32) * K // p + unit * (200000 + (800000 if p > 1 else 0))
+            for _ in range(-(-N // cl[2]) * p):
+                heapq.heapreplace(bins, bins[0] + each)
+        streamed += K * N * (2 if len(groups[g]) > 3 and groups[g][3] else 1) * (2 * -(-M // 128) + 1)
+    return max(max(bins), streamed // 80)
+
+
 def block_split(groups, classes, n_stream_classes, n_workgroups):
     """-> (P, split_base per group or None, slots): in how many parts of K a single launch visits the block tiles (a panel
     class of 128 rows with split_K > 0) of the groups with K >= split_K, where they meet, and how many slots of three tiles
-    that takes.  P = 1 with more than 3 W block tiles or none to split; otherwise the P = 1 .. 4 whose visits (cost of a
-    tile, or cost // P + 500000), groups by descending cost of the first tile, tiles in table order, each to the least
-    loaded of W lists, finish first; fewer parts on ties."""
-    import heapq
+    that takes.  P = 1 with more than 3 W block tiles or none to split; otherwise the P = 1 .. 4 of the smallest block_estimate;
+    fewer parts on ties."""
     W = n_workgroups
     members, n, n_split, base, at = [], 0, 0, [None] * len(groups), 0
     for g, gr in enumerate(groups):
@@ -339,20 +357,11 @@ def block_split(groups, classes, n_stream_classes, n_workgroups):
             at += count
     if n_split == 0 or n > 3 * W:
         return 1, [None] * len(groups), 0
-    members.sort(key=lambda m: -panel_cost(groups[m[0]][0], groups[m[0]][1], m[1], groups[m[0]][0]))
     best = None
     for P in (1, 2, 3, 4):
-        bins = [0] * W
-        for g, cl in members:
-            M, K, N = groups[g][:3]
-            p = P if base[g] is not None else 1
-            for m0 in range(0, M, cl[1]):
-                cost = panel_cost(M, K, cl, M - m0)
-                each = cost if p == 1 else cost // p + 500000
-                for _ in range(-(-N // cl[2]) * p):
-                    heapq.heapreplace(bins, bins[0] + each)
-        if best is None or max(bins) < best[0]:
-            best = (max(bins), P)
+        finish = block_estimate(groups, classes, n_stream_classes, W, P, 1)
+        if best is None or finish < best[0]:
+            best = (finish, P)
     if best[1] == 1:
         return 1, [None] * len(groups), 0
     return best[1], base, -(-n_split // 3)
@@ -368,9 +377,11 @@ def schedule_tiles(groups, classes, n_stream_classes, tiles, n_workgroups, n_xcd
     n_stream_classes classes are weight-streaming classes, the others panel classes.
 
     1. Panel tiles.  Classes by descending BM*BN (ties: lower class first); inside a class the
-       groups by descending cost of their first tile (panel_cost; tiles of 256 rows: by descending
-       K; ties: lower group first); inside a group the tile grid TM x TN is cut into panels of panel_m x panel_n tiles, panels taken with the n-panel index
-       outermost, and inside a panel the m index runs fastest.  Each tile of that sequence goes to the
+       groups by descending cost of their first tile (panel_cost; tiles of 256 rows: by descending K; ties: lower group first), block
+       tiles (128 rows) of groups with a single row tile after all others; inside a group the tile grid TM x TN is cut into
+       panels of panel_m x panel_n tiles (block tiles of TM <= 8 and K >= 4096: TM x panel_n), panels taken with the n-panel index
+       outermost, and inside a panel the m index runs fastest; block tiles in parts of K once per part, the first parts of all
+       tiles first.  Each tile of that sequence goes to the
        workgroup with the smallest accumulated cost (panel_cost); among equally loaded
        workgroups the one of smallest die-major rank, rank r standing for workgroup (r mod (W/X)) * X + r div (W/X).
        Tiles of equal cost therefore go round robin, the l-th to rank l mod W, and the W/X tiles that run
@@ -417,27 +428,26 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
             first.setdefault(tile[0], t)
         panel_classes = sorted(range(n_stream_classes, len(classes)), key=lambda c: (-classes[c][1] * classes[c][2], c))
         for c in panel_classes:
-            members = sorted({t[0] for t in tiles if t[5] == c}, key=lambda g: (-panel_cost(groups[g][0], groups[g][1], classes[c], groups[g][0]), g))
             bm, bn = classes[c][1], classes[c][2]
+            members = sorted({t[0] for t in tiles if t[5] == c}, key=lambda g: (bm == 128 and groups[g][0] <= 128, -panel_cost(groups[g][0], groups[g][1], classes[c], groups[g][0]), g))
             for g in members:
                 M, K, N = groups[g][:3]
                 TM, TN = -(-M // bm), -(-N // bn)
-                for pn in range(0, TN, panel_n):
-                    for pm in range(0, TM, panel_m):
-                        for tn in range(pn, min(pn + panel_n, TN)):
-                            for tm in range(pm, min(pm + panel_m, TM)):
-                                t = first[g] + tm * TN + tn
-                                if t >= len(tiles) - n_panel_split:      # visited in parts, after the whole tiles
-                                    continue
-                                cost = panel_cost(M, K, classes[c], M - tm * bm)
-                                parts = block_parts if block_base[g] is not None else 1
-                                for j in range(parts):
-                                    _, r = heapq.heappop(rank_heap)
-                                    x, i = divmod(r, per)
-                                    b = i * X + x
-                                    lists[p][b].append(order_entry(t, j, parts))
-                                    load[b] += cost if parts == 1 else cost // parts + 500000
-                                    heapq.heappush(rank_heap, (load[b], r))
+                rows = TM if bm == 128 and TM <= 8 and K >= 4096 else panel_m
+                parts = block_parts if block_base[g] is not None else 1
+                for j, pn, pm in ((j, pn, pm) for j in range(parts) for pn in range(0, TN, panel_n) for pm in range(0, TM, rows)):
+                    for tn in range(pn, min(pn + panel_n, TN)):
+                        for tm in range(pm, min(pm + rows, TM)):
+                            t = first[g] + tm * TN + tn
+                            if t >= len(tiles) - n_panel_split:      # visited in parts, after the whole tiles
+                                continue
+                            cost = panel_cost(M, K, classes[c], M - tm * bm)
+                            _, r = heapq.heappop(rank_heap)
+                            x, i = divmod(r, per)
+                            b = i * X + x
+                            lists[p][b].append(order_entry(t, j, parts))
+                            load[b] += cost if parts == 1 else cost // parts + 500000
+                            heapq.heappush(rank_heap, (load[b], r))
         for t in range(len(tiles) - n_panel_split, len(tiles)):    # the parts: tile by tile, part by part, same rule
             parts_t = panel_parts + (1 if t >= len(tiles) - panel_more else 0)      # the last panel_more tiles: one part more
             each = 2040 * groups[tiles[t][0]][1] // parts_t + 1020000
@@ -484,14 +494,16 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
 def block_choice(groups, block_classes, other_classes, other_n_stream, other_tiles, other_order, n_workgroups, n_xcd, panel_m, panel_n):
     """Whether a single bf16 / fp8 launch takes the block table instead of the best of the other tables (class table, tiles
     and visit order of which are given) -> (taken, tiles, order, finish).  Considered when a batch has more than 64 rows
-    and W >= 128.  finish = the largest load of
-    a list in block tiles, plus the largest load in streaming tiles and 400000 if there are any; taken if that is below the largest load of
-    a workgroup in the other order where every visit to a whole panel tile costs 800000 more."""
+    and W >= 128.  Taken if block_estimate, plus the largest load of a list in streaming tiles and 400000 if there are any, is below the
+    largest load of a workgroup in the other order where every visit to a whole panel tile costs 800000 more and every part
+    1980000 more, plus 1100000.  finish = the largest load of a list in block tiles plus the same for streaming tiles."""
     W = n_workgroups
     if max((g[0] for g in groups), default=0) <= 64 or W < 128:
         return False, None, None, None
+    fp8 = block_classes[1][3] == 0                           # the streaming classes of bf16 tables name a K to split from
+    unit = 2 if fp8 else 1
 
-    def loads(classes, n_stream, tiles, order, start):
+    def loads(classes, n_stream, tiles, order, start, part_start):
         panel, stream = [0] * W, [0] * W
         for slot, e in enumerate(order):
             if e < 0:
@@ -501,21 +513,22 @@ def block_choice(groups, block_classes, other_classes, other_n_stream, other_til
             g, cl = groups[tile[0]], classes[tile[5]]
             if tile[5] >= n_stream:
                 cost = panel_cost(g[0], g[1], cl, tile[3])
-                panel[slot % W] += cost + start if parts == 1 else cost // parts + (500000 if cl[1] == 128 else 1020000)
+                panel[slot % W] += cost + start if parts == 1 else cost // parts + (500000 if cl[1] == 128 else 1020000) + part_start
             else:
                 wide = tile[4] * (2 if len(g) > 3 and g[3] else 1)
                 cost = g[1] * (6 * wide + (2 * cl[1] if cl[1] >= 32 else 0))
                 stream[slot % W] += cost if parts == 1 else cost // parts + 24 * cl[1] * wide
         return panel, stream
 
-    panel, stream = loads(other_classes, other_n_stream, other_tiles, other_order, 800000)
-    other = max(a + b for a, b in zip(panel, stream))
+    panel, stream = loads(other_classes, other_n_stream, other_tiles, other_order, 800000, 1980000)
+    other = max(a + b for a, b in zip(panel, stream)) + 1100000
     n_stream = len(block_classes) - 1
     _, _, _, tiles = plan_groups([g[:3] for g in groups], block_classes)
     order = schedule_tiles(groups, block_classes, n_stream, tiles, W, n_xcd, panel_m, panel_n)
-    panel, stream = loads(block_classes, n_stream, tiles, order, 0)
-    finish = max(panel) + (max(stream) + 400000 if any(t[5] < n_stream for t in tiles) else 0)
-    return finish < other, tiles, order, finish
+    panel, stream = loads(block_classes, n_stream, tiles, order, 0, 0)
+    streaming = max(stream) + 400000 if any(t[5] < n_stream for t in tiles) else 0
+    parts = block_split(groups, block_classes, n_stream, W)[0]
+    return block_estimate(groups, block_classes, n_stream, W, parts, unit) + streaming < other, tiles, order, max(panel) + streaming
 
 
 def chain_waits(producer_tiles, counter_base, producer):

@@ -178,37 +178,49 @@ inline bool block_group(const epara_group_desc& d, const epara_tile_class* class
 inline bool block_splits(const epara_group_desc& d, const epara_tile_class& c) { return c.split_K > 0 && d.K >= c.split_K; }
 inline int64_t block_visit_cost(int64_t cost, int32_t parts) { return parts == 1 ? cost : cost / parts + EPARA_COST_BLOCK_PARTIAL; }
 
+// What a launch's block tiles take when those of a long K are visited in `parts` parts ("Which table" in the header).  unit: what a
+// constant of time is multiplied by, 1, or 2 where an element has one byte (the costs per K are then of half the bytes).
+int64_t block_estimate(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
+                       int32_t n_stream_classes, int64_t W, int32_t parts, int64_t unit)
+{
+    std::vector<int32_t> members;
+    for (int32_t g = 0; g < G; ++g)
+        if (groups[g].M > 0 && block_group(groups[g], classes, n_classes, n_stream_classes)) members.push_back(g);
+    std::stable_sort(members.begin(), members.end(), [&](int32_t a, int32_t b) { return groups[a].M > groups[b].M; });
+    load_levels lists(W);
+    double streamed = 0;                                         // exact below 2^53, which is beyond any memory
+    for (int32_t g : members) {
+        const epara_group_desc& d = groups[g];
+        const epara_tile_class& c = classes[class_of(d.M, classes, n_classes)];
+        const int64_t TN = ceil_div(d.N, c.BN), TM = ceil_div(d.M, c.BM), p = block_splits(d, c) ? parts : 1;
+        auto visits = [&](int64_t tiles, int64_t rows) {
+            const int64_t cost = EPARA_COST_BLOCK_PER_32 * ceil_div(rows, 32) * d.K;
+            lists.place(tiles * p, cost / p + unit * (EPARA_COST_BLOCK_VISIT + (p > 1 ? EPARA_COST_BLOCK_PART : 0)));
+        };
+        visits(TN * (TM - 1), c.BM);
+        visits(TN, d.M - (TM - 1) * c.BM);
+        streamed += static_cast<double>(d.K) * d.N * (d.act == EPARA_ACT_SWIGLU ? 2 : 1) * static_cast<double>(2 * TM + 1);
+    }
+    return std::max(lists.most(), static_cast<int64_t>(std::min(streamed / EPARA_COST_BLOCK_STREAMED, 4e18)));
+}
+
 // In how many parts of K a launch visits its block tiles of a long K ("Block tiles of a long K" in the header).
 int32_t block_parts(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
                     int32_t n_stream_classes, int64_t W)
 {
-    std::vector<int32_t> members;
     int64_t n = 0, n_split = 0;
     for (int32_t g = 0; g < G; ++g)
         if (groups[g].M > 0 && block_group(groups[g], classes, n_classes, n_stream_classes)) {
             const epara_tile_class& c = classes[class_of(groups[g].M, classes, n_classes)];
             const int64_t tiles = ceil_div(groups[g].M, c.BM) * ceil_div(groups[g].N, c.BN);
-            members.push_back(g);
             n += tiles;
             if (block_splits(groups[g], c)) n_split += tiles;
         }
     if (n_split == 0 || n > EPARA_BLOCK_SPLIT_MAX_PER_LIST * W) return 1;
-    auto class_at = [&](int32_t g) -> const epara_tile_class& { return classes[class_of(groups[g].M, classes, n_classes)]; };
-    std::stable_sort(members.begin(), members.end(), [&](int32_t a, int32_t b) {
-        return panel_cost(groups[a], class_at(a), groups[a].M) > panel_cost(groups[b], class_at(b), groups[b].M);
-    });
     int32_t best_parts = 1;
     int64_t best = -1;
     for (int32_t P = 1; P <= EPARA_SPLIT_MAX_PARTS; ++P) {
-        load_levels bins(W);
-        for (int32_t g : members) {
-            const epara_tile_class& c = class_at(g);
-            const int32_t parts = block_splits(groups[g], c) ? P : 1;
-            const int64_t TN = ceil_div(groups[g].N, c.BN);
-            for (int64_t m0 = 0; m0 < groups[g].M; m0 += c.BM)
-                bins.place(TN * parts, block_visit_cost(panel_cost(groups[g], c, groups[g].M - m0), parts));
-        }
-        const int64_t finish = bins.most();
+        const int64_t finish = block_estimate(groups, G, classes, n_classes, n_stream_classes, W, P, 1);      // only bf16 tiles are split
         if (best < 0 || finish < best) { best = finish; best_parts = P; }
     }
     return best_parts;
@@ -729,24 +741,31 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
             members.clear();
             for (int32_t g = 0; g < ph.G; ++g)
                 if (cls[p][g] == c) members.push_back(g);
-            // by descending cost of a group's first tile (panel tiles of 256 rows: by descending K)
-            std::stable_sort(members.begin(), members.end(), [&](int32_t a, int32_t b) {
-                return panel_cost(ph.groups[a], ph.classes[c], ph.groups[a].M) > panel_cost(ph.groups[b], ph.classes[c], ph.groups[b].M);
-            });
+            // by descending cost of a group's first tile (panel tiles of 256 rows: by descending K); block tiles of a single row tile
+            // last: they stream weights for themselves alone, into the gaps of those that share them
             const int64_t BM = ph.classes[c].BM, BN = ph.classes[c].BN;
+            const bool block = BM == EPARA_BLOCK_ROWS;
+            std::stable_sort(members.begin(), members.end(), [&](int32_t a, int32_t b) {
+                const epara_group_desc &x = ph.groups[a], &y = ph.groups[b];
+                if (block && (x.M <= BM) != (y.M <= BM)) return y.M <= BM;
+                return panel_cost(x, ph.classes[c], x.M) > panel_cost(y, ph.classes[c], y.M);
+            });
             for (int32_t g : members) {
                 const int64_t TM = ceil_div(ph.groups[g].M, BM), TN = ceil_div(ph.groups[g].N, BN);
-                for (int64_t pn = 0; pn < TN; pn += panel_n)
-                    for (int64_t pm = 0; pm < TM; pm += panel_m)
-                        for (int64_t tn = pn; tn < std::min<int64_t>(pn + panel_n, TN); ++tn)
-                            for (int64_t tm = pm; tm < std::min<int64_t>(pm + panel_m, TM); ++tm) {
-                                const int64_t tile = first[p][g] + tm * TN + tn;
-                                if (tile >= ph.n_tiles - n_panel_split) continue;      // visited in parts, after the whole tiles
-                                const int64_t cost = panel_cost(ph.groups[g], ph.classes[c], ph.groups[g].M - tm * BM);
-                                const int32_t parts = BM == EPARA_BLOCK_ROWS && block_splits(ph.groups[g], ph.classes[c]) ? n_block_parts : 1;
-                                for (int32_t j = 0; j < parts; ++j)
+                // block tiles of a long K: the row tiles of a column next to each other, so that they run together on a die and its L2
+                // fetches their weights once, as long as they are few
+                const int64_t rows = block && TM <= EPARA_BLOCK_COLUMN_TILES && ph.groups[g].K >= EPARA_BLOCK_COLUMN_K ? TM : panel_m;
+                const int32_t parts = block && block_splits(ph.groups[g], ph.classes[c]) ? n_block_parts : 1;
+                for (int32_t j = 0; j < parts; ++j)
+                    for (int64_t pn = 0; pn < TN; pn += panel_n)
+                        for (int64_t pm = 0; pm < TM; pm += rows)
+                            for (int64_t tn = pn; tn < std::min<int64_t>(pn + panel_n, TN); ++tn)
+                                for (int64_t tm = pm; tm < std::min<int64_t>(pm + rows, TM); ++tm) {
+                                    const int64_t tile = first[p][g] + tm * TN + tn;
+                                    if (tile >= ph.n_tiles - n_panel_split) continue;      // visited in parts, after the whole tiles
+                                    const int64_t cost = panel_cost(ph.groups[g], ph.classes[c], ph.groups[g].M - tm * BM);
                                     to_panel_workgroup(p, EPARA_ORDER_ENTRY(static_cast<int32_t>(tile), j, parts), block_visit_cost(cost, parts));
-                            }
+                                }
             }
         }
     }
@@ -882,20 +901,15 @@ int32_t phase_options(const epara_group_desc* groups, int32_t G, int32_t in_dtyp
     return EPARA_OK;
 }
 
-// The finish of a single launch's block tiles and streaming tiles under the cost model (see epara_plan_launch), without
-// their order: the same sequences of costs as in schedule().
-int64_t block_finish(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes, int32_t n_stream,
-                     int64_t W, int32_t panel_m, int32_t panel_n)
+// The largest load of a list in streaming tiles, which are scheduled on level workgroups next to block tiles, without their order.
+int64_t stream_finish(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes, int32_t n_stream, int64_t W)
 {
-    const int32_t block_class = n_classes - 1, split = block_parts(groups, G, classes, n_classes, n_stream, W);
-    const epara_tile_class& c = classes[block_class];
-    std::vector<int32_t> members;
     std::map<int64_t, int64_t, std::greater<int64_t>> stream;    // cost -> how many visits
     for (int32_t g = 0; g < G; ++g) {
         const epara_group_desc& d = groups[g];
         if (d.M <= 0) continue;
         const int32_t k = class_of(d.M, classes, n_classes);
-        if (k == block_class) { members.push_back(g); continue; }
+        if (k >= n_stream) continue;
         epara_tile tl = {g, 0, 0, d.M, classes[k].BN, k};
         const int32_t parts = split_parts(d, classes[k]);
         for (const int64_t cols : {static_cast<int64_t>(classes[k].BN), static_cast<int64_t>(d.N % classes[k].BN)}) {
@@ -904,32 +918,9 @@ int64_t block_finish(const epara_group_desc* groups, int32_t G, const epara_tile
             if (tiles > 0) stream[visit_cost(tile_cost(d, tl, classes, n_stream), parts, d, tl, classes[k])] += tiles * parts;
         }
     }
-    std::stable_sort(members.begin(), members.end(), [&](int32_t a, int32_t b) {
-        return panel_cost(groups[a], c, groups[a].M) > panel_cost(groups[b], c, groups[b].M);
-    });
-    load_levels blocks(W), streams(W);
-    int64_t count = 0, each = 0;                                 // a run of equal items that is not placed yet
-    for (int32_t g : members) {
-        const epara_group_desc& d = groups[g];
-        const int64_t TM = ceil_div(d.M, c.BM), TN = ceil_div(d.N, c.BN);
-        const int32_t parts = block_splits(d, c) ? split : 1;
-        const int64_t whole = block_visit_cost(panel_cost(d, c, c.BM), parts), bottom = block_visit_cost(panel_cost(d, c, d.M - (TM - 1) * c.BM), parts);
-        auto run = [&](int64_t n, int64_t cost) {
-            if (cost != each) { blocks.place(count, each); count = 0; each = cost; }
-            count += n * parts;
-        };
-        for (int64_t pn = 0; pn < TN; pn += panel_n) {
-            const int64_t cols = std::min<int64_t>(panel_n, TN - pn), upper = (TM - 1) / panel_m * panel_m;      // rows of the panels above the last
-            run(cols * upper, whole);
-            if (whole == bottom) run(cols * (TM - upper), whole);
-            else
-                for (int64_t tn = 0; tn < cols; ++tn) { run(TM - 1 - upper, whole); run(1, bottom); }
-        }
-    }
-    blocks.place(count, each);
-    if (stream.empty()) return blocks.most();
-    for (const auto& same : stream) streams.place(same.second, same.first);
-    return blocks.most() + streams.most() + EPARA_COST_KERNEL;
+    load_levels lists(W);
+    for (const auto& same : stream) lists.place(same.second, same.first);
+    return lists.most();
 }
 
 // The block table of a single launch (see epara_plan_launch): whether it is expected to finish earlier than `best`, the choice
@@ -942,27 +933,20 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
     int32_t max_M = 0;
     for (int32_t g = 0; g < G; ++g) max_M = std::max(max_M, groups[g].M);
     if (in_dtype == EPARA_F32 || max_M <= 64 || W < EPARA_BLOCK_MIN_WORKGROUPS) return EPARA_OK;
+    const int64_t unit = in_dtype == EPARA_FP8_E4M3 ? 2 : 1;
     std::vector<int64_t> load(static_cast<size_t>(W), 0);
     for (size_t i = 0; i < best_order.size(); ++i)
         if (best_order[i] >= 0) {
             const epara_tile& tl = best.tiles[EPARA_ORDER_TILE(best_order[i])];
-            const bool panel = tl.cls >= best.n_stream;
+            const bool panel = tl.cls >= best.n_stream, whole = best_order[i] >> 28 == 0;
             load[i % W] += visit_cost(tile_cost(groups[tl.group], tl, best.classes, best.n_stream), (best_order[i] >> 28) + 1, groups[tl.group], tl,
-                                      best.classes[tl.cls], panel) + (panel && best_order[i] >> 28 == 0 ? EPARA_COST_PANEL_START : 0);
+                                      best.classes[tl.cls], panel) + (panel ? (whole ? EPARA_COST_PANEL_START : EPARA_COST_PANEL_PART_START) : 0);
         }
-    const int64_t other = *std::max_element(load.begin(), load.end());
+    const int64_t other = *std::max_element(load.begin(), load.end()) + EPARA_COST_PANEL_LAUNCH;
     if (int32_t st = epara_kernel_classes(in_dtype, gated, EPARA_TABLE_BLOCK, o.classes, 4, &o.n_classes, &o.n_stream)) return st;
-    // no schedule of the block tiles finishes before their level load
-    int64_t total = 0;
-    for (int32_t g = 0; g < G; ++g)
-        if (groups[g].M > 0 && block_group(groups[g], o.classes, o.n_classes, o.n_stream)) {
-            const epara_tile_class& c = o.classes[o.n_classes - 1];
-            const int64_t TM = ceil_div(groups[g].M, c.BM);
-            total += ceil_div(groups[g].N, c.BN) * ((TM - 1) * panel_cost(groups[g], c, c.BM) + panel_cost(groups[g], c, groups[g].M - (TM - 1) * c.BM));
-        }
-    if (total / W >= other) return EPARA_OK;
-    *finish = block_finish(groups, G, o.classes, o.n_classes, o.n_stream, W, panel_m, panel_n);
-    if (*finish >= other) return EPARA_OK;
+    const int32_t parts = block_parts(groups, G, o.classes, o.n_classes, o.n_stream, W);
+    const int64_t stream = stream_finish(groups, G, o.classes, o.n_classes, o.n_stream, W);
+    if (block_estimate(groups, G, o.classes, o.n_classes, o.n_stream, W, parts, unit) + (stream > 0 ? stream + EPARA_COST_KERNEL : 0) >= other) return EPARA_OK;
     if (int32_t st = make_option(groups, G, in_dtype, gated, EPARA_TABLE_BLOCK, o)) return st;
     if (o.tiles.size() > 0xFFFFFF) return EPARA_OK;              // more than an entry of an order with parts can name
     *take = true;
@@ -971,7 +955,15 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
     ph.groups = groups; ph.classes = o.classes; ph.tiles = o.tiles.data();
     ph.n_tiles = static_cast<int64_t>(o.tiles.size());
     ph.G = G; ph.n_classes = o.n_classes; ph.n_stream_classes = o.n_stream;
-    return schedule(&ph, 1, static_cast<int32_t>(W), n_xcd, panel_m, panel_n, &order);
+    if (int32_t st = schedule(&ph, 1, static_cast<int32_t>(W), n_xcd, panel_m, panel_n, &order)) return st;
+    std::vector<int64_t> blocks(static_cast<size_t>(W), 0);
+    for (size_t i = 0; i < order.size(); ++i)
+        if (order[i] >= 0) {
+            const epara_tile& tl = o.tiles[EPARA_ORDER_TILE(order[i])];
+            if (tl.cls >= o.n_stream) blocks[i % W] += block_visit_cost(tile_cost(groups[tl.group], tl, o.classes, o.n_stream), (order[i] >> 28) + 1);
+        }
+    *finish = *std::max_element(blocks.begin(), blocks.end()) + (stream > 0 ? stream + EPARA_COST_KERNEL : 0);
+    return EPARA_OK;
 }
 
 void fill_plan(epara_launch_plan& plan, const phase_option& o, int32_t gated, int64_t n_slots, int64_t makespan)

@@ -577,6 +577,17 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
         assert all(ph["info"].narrow != 2 for ph in phases)
 
 
+@pytest.mark.parametrize("shapes,act,dtype,block", [
+    ([(1024, 4096, 512), (1025, 4096, 320), (128, 4096, 200), (129, 4096, 136)], 5, B.EPARA_BF16, True),     # 8 and 9 row tiles, 1 and 2, columns first from K = 4096
+    ([(1024, 4088, 512), (1025, 4088, 320), (128, 4088, 200)], 0, B.EPARA_BF16, True),                       # rows first below it; parts
+    ([(300, 4096, 520), (100, 4096, 520), (40, 4096, 64)], 5, B.EPARA_FP8_E4M3, True),
+    ([(1000, 11008, 4096)], 0, B.EPARA_BF16, True), ([(300, 5504, 2048), (1200, 5504, 2048)], 0, B.EPARA_BF16, True),   # one block tile a unit
+    ([(600, 11008, 4096), (700, 11008, 4096)], 0, B.EPARA_BF16, True), ([(4426, 13824, 5120)], 0, B.EPARA_BF16, False)])
+def test_block_tiles_in_the_order_and_where_the_estimate_says(shapes, act, dtype, block):
+    """The same comparison with the reference planner where the order of block tiles changes and on either side of the choice."""
+    test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype, block)
+
+
 def test_a_plan_zeroes_the_counters_of_its_workspace_only(monkeypatch):
     """A down projection of 3 + 40 + 1501 rows has 142 MB of workspace and 192 counters."""
     from paper_2511_00603_amd import runtime as R
