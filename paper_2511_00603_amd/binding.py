@@ -57,7 +57,7 @@ class LaunchPlanInfo(ctypes.Structure):
                 ("n_panel_split_tiles", ctypes.c_int32)]
 
     def class_table(self):
-        return np.array(list(self.classes), dtype=np.int32)[: 4 * self.n_classes].view(TILE_CLASS).copy()
+        return np.frombuffer(self.classes, dtype=np.int32, count=4 * self.n_classes).view(TILE_CLASS).copy()
 
 
 class ChainPlanPhase(ctypes.Structure):
@@ -398,20 +398,22 @@ def epara_plan_launch(groups, in_dtype, n_workgroups, n_xcd=8, panel_m=1, panel_
     G = len(groups)
     gp = _ptr(groups) if G else None
     info = LaunchPlanInfo()
-    row_off, x_off, y_off = (np.empty(G + 1, dtype=np.int64) for _ in range(3))
-    split_base = np.full(G, -1, dtype=np.int32)
+    row_off, x_off, y_off = offsets = np.empty((3, G + 1), dtype=np.int64)
+    split_base = np.empty(G, dtype=np.int32)
+    at = _ptr(offsets)
     # The sizes of a plan are known when it is made, so it is made into arrays that hold what most launches need (some
     # thousand tiles, lists of sixteen) and once more, into arrays of the right size, where that was not enough.
     n_tiles, n_slots = 4096, 16 * min(max(int(n_workgroups), 1), 4096)       # the library checks n_workgroups
     while True:
-        tiles, order = np.empty(n_tiles, dtype=TILE), np.empty(n_slots, dtype=np.int32)
-        status = lib().epara_plan_launch(gp, G, int(in_dtype), n_workgroups, n_xcd, panel_m, panel_n, _ptr(row_off), _ptr(x_off), _ptr(y_off),
+        tiles, order = np.empty(TILE.itemsize * n_tiles, dtype=np.uint8), np.empty(n_slots, dtype=np.int32)
+        status = lib().epara_plan_launch(gp, G, int(in_dtype), n_workgroups, n_xcd, panel_m, panel_n, at, at + 8 * (G + 1), at + 16 * (G + 1),
                                          _ptr(tiles), n_tiles, _ptr(order), n_slots, _ptr(split_base) if G else None, ctypes.addressof(info))
         if status != EPARA_ERR_CAPACITY or (info.n_tiles <= n_tiles and info.n_slots <= n_slots):
             break
         n_tiles, n_slots = max(n_tiles, info.n_tiles), max(n_slots, info.n_slots)
     _check(status, "epara_plan_launch")
-    tiles, order = tiles[: info.n_tiles].copy(), order[: info.n_slots].copy()
+    # (copied as bytes: numpy copies an array of records field by field, ten times as slowly)
+    tiles, order = tiles[: TILE.itemsize * info.n_tiles].copy().view(TILE), order[: info.n_slots].copy()
     return info, row_off, x_off, y_off, tiles, order, split_base
 
 

@@ -128,6 +128,23 @@ public:
         std::make_heap(heap_.begin(), heap_.end(), std::greater<std::pair<int64_t, int64_t>>());
     }
     int64_t top() const { return heap_[0].second; }
+    // `rounds` items of the same cost for every workgroup, if all are equally loaded (in index order then, which is the heap's)
+    bool level() const
+    {
+        for (const auto& h : heap_)
+            if (h.first != heap_[0].first) return false;
+        return true;
+    }
+    void add_to_all(int64_t cost)
+    {
+        for (size_t i = 0; i < heap_.size(); ++i) heap_[i] = {heap_[0].first + (i == 0 ? cost : 0), static_cast<int64_t>(i)};
+    }
+    int64_t most() const
+    {
+        int64_t m = 0;
+        for (const auto& h : heap_) m = std::max(m, h.first);
+        return m;
+    }
     int64_t add_to_top(int64_t cost)                             // back into place with one walk down; returns its new load
     {
         std::pair<int64_t, int64_t> moved = heap_[0];
@@ -667,9 +684,9 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 namespace {
 
 // epara_schedule_chain; keep (n_phases vectors, or null): receives the orders whatever their size, so that a planner that
-// does not know the size yet schedules once.
+// does not know the size yet schedules once.  most (or null): the largest load of a workgroup over all phases.
 int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workgroups, int32_t n_xcd, int32_t panel_m, int32_t panel_n,
-                 std::vector<int32_t>* keep)
+                 std::vector<int32_t>* keep, int64_t* most = nullptr)
 {
     if (n_phases < 0) return EPARA_ERR_SHAPE;
     if (n_phases > 0 && !phases) return EPARA_ERR_NULL;
@@ -809,11 +826,21 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
         if (n_phases == 1)
             for (int32_t c = phases[0].n_stream_classes; c < phases[0].n_classes; ++c) apart = apart || phases[0].classes[c].BM == EPARA_BLOCK_ROWS;
         least_loaded bins(W, apart ? nullptr : load.data());
-        for (const auto& same : buckets)
-            for (const auto& it : same.second) {
-                visits[it.first].push_back({static_cast<int32_t>(bins.top()), it.second});
+        for (const auto& same : buckets) {
+            size_t i = 0;
+            if (same.second.size() >= static_cast<size_t>(W) && bins.level())      // whole rounds: one each, no search
+                for (; i + W <= same.second.size(); i += W) {
+                    for (int64_t b = 0; b < W; ++b) visits[same.second[i + b].first].push_back({static_cast<int32_t>(b), same.second[i + b].second});
+                    bins.add_to_all(same.first);
+                }
+            for (; i < same.second.size(); ++i) {
+                visits[same.second[i].first].push_back({static_cast<int32_t>(bins.top()), same.second[i].second});
                 bins.add_to_top(same.first);
             }
+        }
+        if (most) *most = bins.most();
+    } else if (most) {
+        *most = *std::max_element(load.begin(), load.end());
     }
 
     int32_t status = EPARA_OK;
@@ -1010,10 +1037,11 @@ int32_t plan_phases(epara_chain_plan_phase* phases, int32_t n_phases, int32_t in
             ph.n_tiles = static_cast<int64_t>(o.tiles.size());
             ph.G = phases[p].G; ph.n_classes = o.n_classes; ph.n_stream_classes = o.n_stream;
         }
-        if (int32_t st = schedule(sched.data(), n_phases, n_workgroups, n_xcd, panel_m, panel_n, order.data())) return st;
-        // replay under the cost model, waits included
+        int64_t fin = 0;
+        if (int32_t st = schedule(sched.data(), n_phases, n_workgroups, n_xcd, panel_m, panel_n, order.data(), &fin)) return st;
+        // replay under the cost model, waits included (a single phase has none)
         std::vector<int64_t> clock(static_cast<size_t>(W), 0), ready_prev;
-        for (int32_t p = 0; p < n_phases; ++p) {
+        for (int32_t p = 0; n_phases > 1 && p < n_phases; ++p) {
             const phase_option& o = options[p][pick[p]];
             std::vector<int64_t> ready(static_cast<size_t>(phases[p].G), 0);
             const int64_t rows = sched[p].n_slots / W;
@@ -1031,8 +1059,8 @@ int32_t plan_phases(epara_chain_plan_phase* phases, int32_t n_phases, int32_t in
                 }
             ready_prev.swap(ready);
         }
-        const int64_t fin = *std::max_element(clock.begin(), clock.end());
-        if (best_finish < 0 || fin < best_finish) { best_finish = fin; best_pick = pick; best_order = order; }
+        if (n_phases > 1) fin = *std::max_element(clock.begin(), clock.end());
+        if (best_finish < 0 || fin < best_finish) { best_finish = fin; best_pick = pick; best_order.swap(order); }
         int32_t p = n_phases - 1;
         while (p >= 0 && ++pick[p] == static_cast<int>(options[p].size())) pick[p--] = 0;
         if (p < 0) break;
@@ -1053,16 +1081,15 @@ int32_t plan_phases(epara_chain_plan_phase* phases, int32_t n_phases, int32_t in
         const phase_option& o = use_block ? block : options[p][best_pick[p]];
         epara_chain_plan_phase& ph = phases[p];
         // a phase's own makespan: its workgroups' costs in this phase alone
-        std::vector<int64_t> load(static_cast<size_t>(W), 0);
-        for (size_t i = 0; i < best_order[p].size(); ++i)
+        std::vector<int64_t> load(static_cast<size_t>(W), n_phases == 1 ? best_finish : 0);
+        for (size_t i = 0; n_phases > 1 && i < best_order[p].size(); ++i)
             if (best_order[p][i] >= 0) {
                 const int32_t e = best_order[p][i];
                 const epara_tile& tl = o.tiles[EPARA_ORDER_TILE(e)];
                 load[i % W] += visit_cost(tile_cost(ph.groups[tl.group], tl, o.classes, o.n_stream), (e >> 28) + 1, ph.groups[tl.group], tl,
                                           o.classes[tl.cls], tl.cls >= o.n_stream);
             }
-        fill_plan(ph.plan, o, gated[p], static_cast<int64_t>(best_order[p].size()),
-                  use_block ? best_finish : *std::max_element(load.begin(), load.end()));
+        fill_plan(ph.plan, o, gated[p], static_cast<int64_t>(best_order[p].size()), *std::max_element(load.begin(), load.end()));
         ph.counter_base = base;
         base += ph.G;
         if (ph.tiles) {

@@ -25,17 +25,15 @@ def _upload(a, device):
 
 
 def _upload_all(arrays, device):
-    """numpy arrays -> one uint8 device tensor per array holding the same bytes, all with one copy: they are pieces of one
-    buffer, each at a multiple of 256 bytes and never empty."""
-    sizes = [max(a.nbytes, 16) for a in arrays]
-    starts = [0]
-    for n in sizes:
-        starts.append(starts[-1] + (n + 255) // 256 * 256)
-    raw = np.zeros(starts[-1], dtype=np.uint8)
-    for a, at in zip(arrays, starts):
+    """numpy arrays (contiguous) -> one uint8 device tensor per array that begins with the same bytes, all with one copy: they are
+    pieces of one buffer, of whole 256 bytes each and never empty."""
+    sizes = [(max(a.nbytes, 16) + 255) // 256 * 256 for a in arrays]
+    raw = np.zeros(sum(sizes), dtype=np.uint8)
+    at = 0
+    for a, n in zip(arrays, sizes):
         raw[at: at + a.nbytes] = a.view(np.uint8).reshape(-1)
-    whole = torch.from_numpy(raw).to(device)
-    return [whole[at: at + n] for at, n in zip(starts, sizes)]
+        at += n
+    return torch.from_numpy(raw).to(device).split_with_sizes(sizes)
 
 
 def current_stream_handle():
@@ -118,9 +116,9 @@ class LaunchPlan:
             self.d_workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=device)
             counters = 4 * (self.n_split_tiles + self.n_panel_split_tiles)       # the rest is written before it is read
             B.epara_workspace_init(self.d_workspace.data_ptr(), (counters + 255) // 256 * 256, current_stream_handle())
-        torch.cuda.synchronize(device)
+            torch.cuda.synchronize(device)                   # (the upload of pageable memory has waited for itself)
         self.upload_seconds = time.perf_counter() - t0
-        self.c = B.Launch(self.args.ctypes.data, self.d_args.data_ptr(), self.tiles.ctypes.data, self.d_tiles.data_ptr(),
+        self.c = B.Launch(B._ptr(self.args), self.d_args.data_ptr(), B._ptr(self.tiles), self.d_tiles.data_ptr(),
                           self.d_order.data_ptr(), len(self.tiles), len(self.order), n_workgroups, G,
                           None if self.d_workspace is None else self.d_workspace.data_ptr(), self.workspace_bytes, self.n_split_tiles,
                           self.n_panel_split_tiles)
