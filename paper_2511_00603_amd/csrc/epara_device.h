@@ -176,6 +176,18 @@ __device__ __forceinline__ void store4(void* Y, int out_dtype, size_t m, int n, 
     }
 }
 
+// The same with the quad's four bias values in hand.
+template <int ACT, bool WT>
+__device__ __forceinline__ void finish_plain_quad(const epara_group_args& ga, int out_dtype, const v4f& a, const v4f& b,
+                                                  int m0, int ml, int rows, int n0, int nl, int cols, bool vec_ok)
+{
+    if (ml >= rows || nl >= cols) return;
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = act_fast<ACT>(ga.scale * a[i] + b[i]) * ga.out_inv_scale;
+    store4<WT>(ga.Y, out_dtype, static_cast<size_t>(m0 + ml), n0 + nl, ga.N, v, cols - nl, vec_ok);
+}
+
 // Epilogue of one accumulator quad (plain groups): the lane holds columns nl..nl+3 of row ml.
 // `bias` points at the bias of column n0 (global memory for streaming tiles; panel tiles stage the
 // tile's 256 bias values in LDS first, because a global load inside the store loop would make

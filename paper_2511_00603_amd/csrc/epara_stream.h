@@ -175,6 +175,12 @@ struct skinny_shape {
     static constexpr int UPW = (UNITS + 3) / 4;                  // units per wave and pass
     static constexpr int BN = (GATED ? NFR / 2 : NFR) * 16;      // output columns of a tile
     static_assert(QUADS * 1024 <= SPLIT_STRIDE, "a tile's partial sums do not fit their workspace slot");
+    // Where the partial sums leave room below the rings, a tile's bias comes into the LDS while its weights stream (two tiles' worth:
+    // a wave may start the next tile while another one still finishes this one).  A load of it in the epilogue would wait for
+    // every load of the next tile, which are in flight by then, and leave the ring without any for a whole latency: sixteen
+    // models of 256 .. 1024 columns, a pass of two launches 41.7 -> 41.0 us.
+    static constexpr bool EARLY_BIAS = !GATED && PASSES * NP * MB * 4096 + 2 * BN * 4 <= RING_LDS_OFFSET;
+    static constexpr int BIAS_LDS_OFFSET = RING_LDS_OFFSET - 2 * BN * 4;
     // does the unit hold rows and columns of the group at all
     static __device__ __forceinline__ bool live(int pass, int unit, int M, int cols)
     {
@@ -184,9 +190,10 @@ struct skinny_shape {
 };
 
 // Epilogue of one unit: the lane's quad of the sums (gated: gate and up) becomes four stored outputs.
+// bias_lds: the tile's bias if it is in the LDS already, else null.
 template <class ActTag, bool GATED, int MB, int NFR, bool WT>
 __device__ __forceinline__ void skinny_finish_unit(const epara_group_args& ga, int out_dtype, int n0, int cols, int pass, int unit,
-                                                   const v4f& a, const v4f& b, int lane, bool vec_ok)
+                                                   const v4f& a, const v4f& b, int lane, bool vec_ok, const char* bias_lds = nullptr)
 {
     typedef skinny_shape<GATED, MB, NFR> S;
     const int r = lane & 15, q = lane >> 4;
@@ -194,8 +201,14 @@ __device__ __forceinline__ void skinny_finish_unit(const epara_group_args& ga, i
     if constexpr (GATED) {
         finish_gated<WT>(ga, out_dtype, a, b, 0, fm * 16 + r, ga.M, n0, (pass * (S::NP / 2) + hi) * 16 + 4 * q, cols, vec_ok);
     } else {
-        finish_plain<ActTag::value, WT>(ga, out_dtype, a, ga.bias ? as_global<float>(ga.bias) + n0 : nullptr, 0,
-                                        fm * 16 + r, ga.M, n0, (pass * S::NP + hi) * 16 + 4 * q, cols, vec_ok);
+        const int nl = (pass * S::NP + hi) * 16 + 4 * q;
+        if (S::EARLY_BIAS && bias_lds != nullptr) {
+            const v4f quad = ga.bias ? *reinterpret_cast<const v4f*>(bias_lds + nl * 4) : v4f{0.f, 0.f, 0.f, 0.f};
+            finish_plain_quad<ActTag::value, WT>(ga, out_dtype, a, quad, 0, fm * 16 + r, ga.M, n0, nl, cols, vec_ok);
+        } else {
+            finish_plain<ActTag::value, WT>(ga, out_dtype, a, ga.bias ? as_global<float>(ga.bias) + n0 : nullptr, 0,
+                                            fm * 16 + r, ga.M, n0, nl, cols, vec_ok);
+        }
     }
 }
 
@@ -204,7 +217,7 @@ __device__ __forceinline__ void skinny_finish_unit(const epara_group_args& ga, i
 // is noted in `pend`.  Returns whether the output tile was stored.
 template <int DT, bool GATED, int MB, int NFR, bool WT>
 __device__ __forceinline__ bool skinny_finish(const epara_group_args& ga, int out_dtype, int n0, int cols,
-                                              v4f (&acc)[NFR][MB], int wave, int lane, char* lds,
+                                              v4f (&acc)[NFR][MB], int wave, int lane, char* lds, const char* bias_lds,
                                               const split_ctx* sp, int entry, split_pending* pend)
 {
     typedef skinny_shape<GATED, MB, NFR> S;
@@ -270,7 +283,7 @@ __device__ __forceinline__ bool skinny_finish(const epara_group_args& ga, int ou
                 if (!S::live(pass, unit, M, cols)) continue;
                 v4f a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
                 sum(unit, a, b);
-                skinny_finish_unit<decltype(tag), GATED, MB, NFR, WT>(ga, out_dtype, n0, cols, pass, unit, a, b, lane, vec_ok);
+                skinny_finish_unit<decltype(tag), GATED, MB, NFR, WT>(ga, out_dtype, n0, cols, pass, unit, a, b, lane, vec_ok, bias_lds);
             }
         }
     };
@@ -383,7 +396,19 @@ __device__ __forceinline__ long skinny_run(const epara_group_args* __restrict__ 
     for (int u = 0; u < U; ++u) skinny_load<DT, MB, NFR>(cur, u, wave, lane, ring[u], xring + u * XSLOT_BYTES);
     __builtin_amdgcn_sched_barrier(0);
 
+    typedef skinny_shape<GATED, MB, NFR> S;
+    char* bias_lds = S::EARLY_BIAS ? lds + S::BIAS_LDS_OFFSET : nullptr;
     for (;;) {
+        if constexpr (S::EARLY_BIAS) {
+            if (ga.bias && wave == 0) {                          // (columns past the tile's last one repeat it: they are not stored)
+                const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(ga.bias) + tl.n0, 0, -1, 0x00020000);
+#pragma unroll
+                for (int b = 0; b < S::BN; b += 64)
+                    if (b + lane < S::BN)
+                        __builtin_amdgcn_raw_ptr_buffer_load_lds(brsrc, (__attribute__((address_space(3))) void*)((ldsptr)bias_lds + b * 4), 4,
+                                                                 min(b + lane, tl.cols - 1) * 4, 0, 0, 0);
+            }
+        }
         // What follows this tile in the workgroup's list (a list has no holes, so an idle slot ends
         // it) is found by three dependent scalar loads: order -> tile -> group arguments.  Each
         // link is issued after one chunk of the tile and read after the next, so that its latency
@@ -436,7 +461,7 @@ __device__ __forceinline__ long skinny_run(const epara_group_args* __restrict__ 
         } else {                                                 // nothing follows: the ring drains
             skinny_drain<DT, MB, NFR, U, 0>(cur, c_last, wave, lane, ring, xring, acc);
         }
-        const bool stored = skinny_finish<DT, GATED, MB, NFR, CHAIN>(ga, out_dtype, tl.n0, tl.cols, acc, wave, lane, lds, sp, entry, pend);
+        const bool stored = skinny_finish<DT, GATED, MB, NFR, CHAIN>(ga, out_dtype, tl.n0, tl.cols, acc, wave, lane, lds, bias_lds, sp, entry, pend);
         if constexpr (CHAIN) { if (stored) chain_done(*chain, tl.group); }
         if (slot_next < 0) {                                     // the run ends here: hand over what is known of the next slot
             following.known = t_next >= 0;
@@ -446,6 +471,7 @@ __device__ __forceinline__ long skinny_run(const epara_group_args* __restrict__ 
             slot = t_next >= 0 ? slot + stride : n_slots;
             break;
         }
+        if constexpr (S::EARLY_BIAS) bias_lds = lds + S::BIAS_LDS_OFFSET + (lds + S::BIAS_LDS_OFFSET + S::BN * 4 - bias_lds);
         slot = slot_next;
         entry = t_next;
         tl = tl_next;
