@@ -136,7 +136,13 @@ __global__ __launch_bounds__(NT) void quantize_segments_kernel(const epara_segme
     constexpr int ESZ = SRC == EPARA_F32 ? 4 : 2;
     if (blockIdx.x == 0)
         for (int g = threadIdx.x; g < G; g += NT) scale[g] = scale_of(amax[g]);
-    for (int64_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
+    const int64_t rounded = (n_chunks + 7) & ~static_cast<int64_t>(7);
+    for (int64_t i = blockIdx.x; i < rounded; i += gridDim.x) {
+        // Backwards in eights: up to 32 MB that the maxima kernel has read last are still in the L2 of the die that read them, which is
+        // this one (chunk c of both kernels runs on a workgroup that is c modulo 8).  8192 x 5120 bf16 quantised and sent back:
+        // 82.7 -> 80.7 us.
+        const int64_t c = rounded - 8 - (i & ~static_cast<int64_t>(7)) + (i & 7);
+        if (c >= n_chunks) continue;
         const epara_segment sg = segs[find_segment(segs, n, c)];
         const float inv = 1.f / scale_of(amax[sg.group]);      // codes = RNE(x * (1 / scale)), as the forward path's epilogue does
         const int64_t base = (c - sg.first_chunk) * CHUNK;
