@@ -9,7 +9,7 @@
 // once for the maximum, once for the codes) and every destination byte written once.  A
 // workgroup of 256 threads moves 16-KiB chunks with 16-byte accesses per lane (a wave
 // instruction covers 1 KiB of consecutive memory); chunk c belongs to the last segment whose
-// first_chunk is <= c, found by bisection (the value is the same for all lanes: scalar loads).
+// first_chunk is <= c (find_segment; the value is the same for all lanes).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -26,8 +26,17 @@ constexpr int NT = 256;
 constexpr int64_t CHUNK = 16384;
 constexpr int MAX_GRID = 256 * 16;       // workgroups: enough waves to keep every HBM channel busy
 
-__device__ __forceinline__ int64_t find_segment(const epara_segment* __restrict__ segs, int64_t n, int64_t c)
+// The segment of chunk c: the last one whose first_chunk is <= c.  Up to 64 segments: lane i has read the first chunk of segment i once
+// (first_chunks) and the wave counts, where halving costs a chain of loads in front of every chunk; more: bisection.  Nine requests, 8192 x 5120 bf16
+// quantised and sent back: 80.7 -> 78.4 us.
+__device__ __forceinline__ int64_t first_chunks(const epara_segment* __restrict__ segs, int64_t n)
 {
+    const int lane = threadIdx.x & 63;
+    return n <= 64 && lane < n ? segs[lane].first_chunk : INT64_MAX;
+}
+__device__ __forceinline__ int64_t find_segment(const epara_segment* __restrict__ segs, int64_t n, int64_t c, int64_t first)
+{
+    if (n <= 64) return __builtin_popcountll(__ballot(first <= c)) - 1;      // first_chunk never decreases, segment 0 starts at 0
     int64_t lo = 0, hi = n - 1;            // invariant: first_chunk[lo] <= c
     while (lo < hi) {
         const int64_t mid = (lo + hi + 1) >> 1;
@@ -38,8 +47,9 @@ __device__ __forceinline__ int64_t find_segment(const epara_segment* __restrict_
 
 __global__ __launch_bounds__(NT) void copy_segments_kernel(const epara_segment* __restrict__ segs, int64_t n, int64_t n_chunks)
 {
+    const int64_t first = first_chunks(segs, n);
     for (int64_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-        const epara_segment sg = segs[find_segment(segs, n, c)];
+        const epara_segment sg = segs[find_segment(segs, n, c, first)];
         const int64_t base = (c - sg.first_chunk) * CHUNK;
         const EPARA_GLOBAL char* src = (const EPARA_GLOBAL char*)sg.src + base;
         EPARA_GLOBAL char* dst = (EPARA_GLOBAL char*)sg.dst + base;
@@ -100,8 +110,9 @@ __global__ __launch_bounds__(NT) void amax_segments_kernel(const epara_segment* 
         __syncthreads();
         m = 0;
     };
+    const int64_t first = first_chunks(segs, n);
     for (int64_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-        const epara_segment sg = segs[find_segment(segs, n, c)];
+        const epara_segment sg = segs[find_segment(segs, n, c, first)];
         if (sg.group != group) {
             if (group >= 0) publish();
             group = sg.group;
@@ -136,6 +147,7 @@ __global__ __launch_bounds__(NT) void quantize_segments_kernel(const epara_segme
     constexpr int ESZ = SRC == EPARA_F32 ? 4 : 2;
     if (blockIdx.x == 0)
         for (int g = threadIdx.x; g < G; g += NT) scale[g] = scale_of(amax[g]);
+    const int64_t first = first_chunks(segs, n);
     const int64_t rounded = (n_chunks + 7) & ~static_cast<int64_t>(7);
     for (int64_t i = blockIdx.x; i < rounded; i += gridDim.x) {
         // Backwards in eights: up to 32 MB that the maxima kernel has read last are still in the L2 of the die that read them, which is
@@ -143,7 +155,7 @@ __global__ __launch_bounds__(NT) void quantize_segments_kernel(const epara_segme
         // 82.7 -> 80.7 us.
         const int64_t c = rounded - 8 - (i & ~static_cast<int64_t>(7)) + (i & 7);
         if (c >= n_chunks) continue;
-        const epara_segment sg = segs[find_segment(segs, n, c)];
+        const epara_segment sg = segs[find_segment(segs, n, c, first)];
         const float inv = 1.f / scale_of(amax[sg.group]);      // codes = RNE(x * (1 / scale)), as the forward path's epilogue does
         const int64_t base = (c - sg.first_chunk) * CHUNK;
         const EPARA_GLOBAL char* src = (const EPARA_GLOBAL char*)sg.src + base;

@@ -103,6 +103,14 @@ def test_dynamic_quantisation_gives_the_reference_scales_and_codes(layout, src):
             assert np.array_equal(codes[g].cpu().numpy(), RW.quantize_e4m3(x, s)), g
 
 
+@pytest.mark.parametrize("n", [63, 64, 65])
+def test_copies_and_codes_around_64_segments(n):
+    """A wave's lanes hold the first chunks of up to 64 segments; with more the segment is found by halving.  Empty requests, the last one too."""
+    layout = [(512, [(0, 1, 17, 33)[(i + n) % 4] for i in range(n - 3)]), (512, [2, 40, 0])]
+    test_gather_and_scatter_move_every_byte_where_the_reference_puts_it(layout, torch.bfloat16)
+    test_dynamic_quantisation_gives_the_reference_scales_and_codes(layout, "bf16")
+
+
 def test_scales_from_device_memory_reach_the_group_arguments():
     G = 5
     rng = np.random.default_rng(43)
