@@ -72,6 +72,13 @@ def test_add_layernorm_mixed_groups(with_r, with_s):
     check_norm(groups, want, "mixed")
 
 
+@pytest.mark.parametrize("n", [63, 64, 65])
+def test_add_layernorm_around_64_groups(n):
+    """A wave's lanes hold the first rows of up to 64 groups; with more the group is found by halving.  Some groups have no rows, the last one too."""
+    groups, want = norm_case(np.random.default_rng(34), [((0, 1, 3, 0, 2)[(i + n) % 5] if i < n - 1 else 0, 64) for i in range(n)], True, True)
+    check_norm(groups, want, "%d groups" % n)
+
+
 def test_add_layernorm_vit_sizes_and_exact_sums():
     rng = np.random.default_rng(32)
     groups, want = norm_case(rng, [(197 * 8, 768), (197, 768), (197 * 3, 768)])
