@@ -32,7 +32,7 @@ EPARA_HIDDEN hipError_t epara_enqueue_bf16_plain(int panel_only, unsigned grid, 
 EPARA_HIDDEN hipError_t epara_enqueue_bf16_gated(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split);
 EPARA_HIDDEN hipError_t epara_enqueue_fp8_plain(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split);
 EPARA_HIDDEN hipError_t epara_enqueue_fp8_gated(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split);
-EPARA_HIDDEN hipError_t epara_enqueue_f32(unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots);
+EPARA_HIDDEN hipError_t epara_enqueue_f32(unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int G, long n_tiles);
 
 // One grouped launch of block tiles (the block table of epara_kernel_classes).  n_counters: of the split ones, behind the n_split
 // of the streaming tiles; n_tiles: how many of them the workspace holds.

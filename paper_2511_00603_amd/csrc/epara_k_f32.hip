@@ -6,8 +6,9 @@ namespace {
 
 __global__ __launch_bounds__(F32_NT) void grouped_kernel_f32(const epara_group_args* __restrict__ args,
                                                              const epara_tile* __restrict__ tiles,
-                                                             const int32_t* __restrict__ order, long n_slots)
+                                                             const int32_t* __restrict__ order, long n_slots, uint32_t args_bytes, uint32_t tile_bytes)
 {
+    if (tile_bytes > 0) f32_warm(args, args_bytes, tiles, tile_bytes, order, n_slots);
     f32_body<false, F32_WAVES>(args, tiles, order, n_slots, nullptr);
 }
 
@@ -71,9 +72,13 @@ __global__ void pack_kernel(const char* __restrict__ W, int K, int N, char* __re
 }  // namespace
 
 hipError_t epara_enqueue_f32(unsigned grid, hipStream_t stream, const epara_group_args* args, const epara_tile* tiles,
-                             const int32_t* order, long n_slots)
+                             const int32_t* order, long n_slots, int G, long n_tiles)
 {
-    hipLaunchKernelGGL(grouped_kernel_f32, dim3(grid), dim3(F32_NT), 0, stream, args, tiles, order, n_slots);
+    // both tables within the lines that the sixteen waves ask for; larger ones are looked up record by record
+    const long args_bytes = static_cast<long>(G) * static_cast<long>(sizeof(epara_group_args)), tile_bytes = n_tiles * static_cast<long>(sizeof(epara_tile));
+    const bool warm = args_bytes <= F32_WARM_BYTES && tile_bytes <= F32_WARM_BYTES;
+    hipLaunchKernelGGL(grouped_kernel_f32, dim3(grid), dim3(F32_NT), 0, stream, args, tiles, order, n_slots,
+                       warm ? static_cast<uint32_t>(args_bytes) : 0u, warm ? static_cast<uint32_t>(tile_bytes) : 0u);
     return hipGetLastError();
 }
 

@@ -386,6 +386,15 @@ def test_linearity_in_x(dtype_name):
     assert_close(lhs, rhs, 3 * TOL[dtype_name], "linearity")
 
 
+@pytest.mark.parametrize("shapes", [[(3, 20, 64 * 42)], [(3, 20, 64 * 43)], [(2, 24, 12)] * 14, [(2, 24, 12)] * 15])
+def test_fp32_launches_around_the_tables_that_are_read_ahead(shapes):
+    """Launches whose tables of tiles (42 x 24 bytes) or arguments (14 x 72 bytes) just fit what a workgroup asks for ahead, and the next ones."""
+    rng = np.random.default_rng(22)
+    G = U.Groups([U.rand_spec(rng, M, K, N) for M, K, N in shapes], "f32")
+    for y, yref in zip(G.run(), G.expected()):
+        assert_close(y, yref, TOL["f32"], "fp32 tables %d" % len(shapes))
+
+
 def test_fp32_small_batches_with_awkward_shapes():
     """Batches of at most 16 rows take the fp32 path that cuts K into sixteen shares of pieces of 16: K of less than a
     piece, of fewer pieces than shares, not a multiple of a piece, ragged column tiles, every activation, next to a group of
