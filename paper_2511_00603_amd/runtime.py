@@ -85,7 +85,10 @@ def _group_desc(args):
 
 class LaunchPlan:
     """Host plan + its device copy for one grouped launch (epara_launch).  The plan itself -- class table, tiles,
-    visit order -- is the library's (epara_plan_launch); this class only keeps the arrays and uploads them."""
+    visit order -- is the library's (epara_plan_launch); this class only keeps the arrays and uploads them.
+
+    The constructor waits for the whole device, with or without a workspace: the plan can be launched on any stream, and what
+    was enqueued before, on any stream (weights packed on a side stream, say), is finished when it returns."""
 
     def __init__(self, args, in_dtype, device, n_workgroups=None, n_xcd=8, panel_m=1, panel_n=4):
         # panel 1 x 4: panel tiles are visited strip by strip (4 tile columns), row by row, so the 32
@@ -116,7 +119,7 @@ class LaunchPlan:
             self.d_workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=device)
             counters = 4 * (self.n_split_tiles + self.n_panel_split_tiles)       # the rest is written before it is read
             B.epara_workspace_init(self.d_workspace.data_ptr(), (counters + 255) // 256 * 256, current_stream_handle())
-            torch.cuda.synchronize(device)                   # (the upload of pageable memory has waited for itself)
+        torch.cuda.synchronize(device)
         self.upload_seconds = time.perf_counter() - t0
         self.c = B.Launch(B._ptr(self.args), self.d_args.data_ptr(), B._ptr(self.tiles), self.d_tiles.data_ptr(),
                           self.d_order.data_ptr(), len(self.tiles), len(self.order), n_workgroups, G,

@@ -602,6 +602,22 @@ def test_a_plan_zeroes_the_counters_of_its_workspace_only(monkeypatch):
     assert plan.workspace_bytes > 1 << 27 and zeroed == [-(-4 * (plan.n_split_tiles + plan.n_panel_split_tiles) // 256) * 256]
 
 
+@pytest.mark.parametrize("shape,workspace", [((8, 512, 512), False), ((300, 512, 512), False), ((1501, 11008, 4096), True)])
+def test_making_a_plan_waits_for_the_device(shape, workspace, monkeypatch):
+    """With or without a workspace, and once everything that the constructor enqueues has been enqueued."""
+    from paper_2511_00603_amd import runtime as R
+    calls, upload = [], R._upload_all
+    monkeypatch.setattr(R, "_require_gpu", lambda: None)
+    monkeypatch.setattr(R, "current_stream_handle", lambda: 0)
+    monkeypatch.setattr(R, "_upload_all", lambda *a: calls.append("upload") or upload(*a))
+    monkeypatch.setattr(R.torch.cuda, "synchronize", lambda *a: calls.append("wait"))
+    monkeypatch.setattr(B, "epara_workspace_init", lambda *a: calls.append("init"))
+    args = np.zeros(1, dtype=B.GROUP_ARGS)
+    args["M"], args["K"], args["N"] = shape
+    plan = R.LaunchPlan(args, B.EPARA_BF16, "cpu", 256)
+    assert (plan.workspace_bytes > 0) == workspace and calls == ["upload"] + ["init"] * workspace + ["wait"]
+
+
 def test_plan_launch_reports_a_bad_grid_as_the_library_does():
     for kw in (dict(n_workgroups=-8), dict(n_workgroups=0), dict(n_workgroups=250), dict(n_workgroups=256, n_xcd=0), dict(n_workgroups=256, panel_m=0)):
         with pytest.raises(B.EparaError) as e:

@@ -5,6 +5,8 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2511_00603_amd import binding as B
+from paper_2511_00603_amd import runtime as R
 from paper_2511_00603_amd.mixrun import StagedMix
 from workloads import make_mix
 
@@ -81,3 +83,22 @@ def test_passes_on_two_streams_equal_the_passes_one_after_the_other():
         for la, lb in zip(want[c], raw(c)):
             for a, b in zip(la, lb):
                 assert np.array_equal(a, b)
+
+
+def test_a_plan_made_while_another_stream_is_busy_can_be_launched_on_any_stream():
+    """Making a plan (here one without a workspace) waits for the whole device, so weights packed on a side stream are there when
+    it returns, and a launch on a third stream finds both them and the plan's tables."""
+    rng = np.random.default_rng(51)
+    G = U.Groups([U.rand_spec(rng, M, 256, 512) for M in (3, 40)], "bf16")
+    want = G.run()
+    side, third = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(50_000_000)              # some twenty milliseconds
+    plan = R.LaunchPlan(G.args, B.EPARA_BF16, U.DEV)
+    assert side.query() and plan.workspace_bytes == 0
+    for y in G.Y:
+        y.zero_()
+    torch.cuda.synchronize()
+    R.grouped_forward(plan, B.EPARA_BF16, third.cuda_stream)
+    torch.cuda.synchronize()
+    assert all(np.array_equal(U.fetch(y), w) for y, w in zip(G.Y, want))
