@@ -15,6 +15,7 @@
 
 #include "epara.h"
 #include "epara_cast.h"
+#include "epara_rows.h"
 
 namespace {
 
@@ -24,7 +25,7 @@ typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 
 constexpr int NT = 256;
 constexpr int64_t CHUNK = 16384;
-constexpr int MAX_GRID = 256 * 16;       // workgroups: enough waves to keep every HBM channel busy (the same pass with 256 * 4: 80.3 us, * 8: 79.4, * 16: 79.0)
+constexpr int MAX_GRID = ROWS_MAX_GRID;  // workgroups: enough waves to keep every HBM channel busy (the same pass with 256 * 4: 80.3 us, * 8: 79.4, * 16: 79.0)
 
 // The segment of chunk c: the last one whose first_chunk is <= c.  Up to 64 segments: lane i has read the first chunk of segment i once
 // (first_chunks) and the wave counts, where halving costs a chain of loads in front of every chunk; more: bisection.  Nine requests, 8192 x 5120 bf16
@@ -148,12 +149,8 @@ __global__ __launch_bounds__(NT) void quantize_segments_kernel(const epara_segme
     if (blockIdx.x == 0)
         for (int g = threadIdx.x; g < G; g += NT) scale[g] = scale_of(amax[g]);
     const int64_t first = first_chunks(segs, n);
-    const int64_t rounded = (n_chunks + 7) & ~static_cast<int64_t>(7);
-    for (int64_t i = blockIdx.x; i < rounded; i += gridDim.x) {
-        // Backwards in eights: up to 32 MB that the maxima kernel has read last are still in the L2 of the die that read them, which is
-        // this one (chunk c of both kernels runs on a workgroup that is c modulo 8).  8192 x 5120 bf16 quantised and sent back:
-        // 82.7 -> 80.7 us.
-        const int64_t c = rounded - 8 - (i & ~static_cast<int64_t>(7)) + (i & 7);
+    for (int64_t i = blockIdx.x; i < quantize_span(n_chunks); i += gridDim.x) {
+        const int64_t c = quantize_chunk(i, n_chunks);           // backwards: 8192 x 5120 bf16 quantised and sent back 82.7 -> 80.7 us
         if (c >= n_chunks) continue;
         const epara_segment sg = segs[find_segment(segs, n, c, first)];
         const float inv = 1.f / scale_of(amax[sg.group]);      // codes = RNE(x * (1 / scale)), as the forward path's epilogue does
@@ -270,7 +267,7 @@ int32_t epara_quantize_segments_e4m3(const epara_segment* h_segments, const epar
                                reinterpret_cast<unsigned int*>(d_amax));
     }
     // the quantising kernel also writes the scales (workgroup 0); with no data it runs for that alone
-    const dim3 qgrid(n_chunks > 0 ? grid_for(n_chunks) : 1);
+    const dim3 qgrid(static_cast<unsigned>(quantize_grid(n_chunks)));
     if (src_dtype == EPARA_F32)
         hipLaunchKernelGGL(quantize_segments_kernel<EPARA_F32>, qgrid, dim3(NT), 0, s, d_segments, n_segments, n_chunks, d_amax, d_scale, G);
     else

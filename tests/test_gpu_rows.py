@@ -111,6 +111,12 @@ def test_copies_and_codes_around_64_segments(n):
     test_dynamic_quantisation_gives_the_reference_scales_and_codes(layout, "bf16")
 
 
+@pytest.mark.parametrize("chunks", [1, 7, 9, 1023, 4095, 4097])
+def test_codes_of_batches_around_whole_eights_of_chunks(chunks):
+    """Chunks of 16 KiB (sixteen rows of 512 bf16) are quantised backwards in eights by up to 4096 workgroups; the last one is cut short."""
+    test_dynamic_quantisation_gives_the_reference_scales_and_codes([(512, [16 * chunks - 5])], "bf16")
+
+
 def test_scales_from_device_memory_reach_the_group_arguments():
     G = 5
     rng = np.random.default_rng(43)

@@ -1,6 +1,8 @@
 """Batch forming (the step before and after the grouped forward): pins of the numpy reference
 (oracle/rows.py, oracle/planner.request_segments) and the host half of the library against it."""
 import ctypes
+import os
+import subprocess
 
 import numpy as np
 import pytest
@@ -143,3 +145,41 @@ def test_segment_launches_validate_before_they_enqueue():
     assert L.epara_patch_scales(None, 2, fake_dev, fake_dev, None, None, None) == B.EPARA_ERR_NULL
     assert L.epara_patch_scales(fake_dev, -1, fake_dev, fake_dev, None, None, None) == B.EPARA_ERR_SHAPE
     assert L.epara_patch_scales(None, 0, None, None, None, None, None) == B.EPARA_OK
+
+
+CHUNK_ORDER = r"""
+#include <cstdio>
+#include <vector>
+#include "epara_rows.h"
+int main()
+{
+    const int64_t most = ROWS_MAX_GRID;
+    for (int64_t n : {int64_t(0), int64_t(1), int64_t(7), int64_t(8), int64_t(9), int64_t(1023), most - 9, most - 1, most, most + 1, 3 * most + 5}) {
+        const int64_t grid = quantize_grid(n);
+        std::vector<int> seen(n, 0);
+        for (int64_t b = 0; b < grid; ++b) {
+            int rounds = 0;
+            for (int64_t i = b; i < quantize_span(n); i += grid, ++rounds) {
+                const int64_t c = quantize_chunk(i, n);
+                if (c < 0 || c >= quantize_span(n)) return std::printf("n %lld: chunk %lld\n", (long long)n, (long long)c), 1;
+                if (c % 8 != b % 8) return std::printf("n %lld: chunk %lld on workgroup %lld\n", (long long)n, (long long)c, (long long)b), 1;
+                if (c < n) ++seen[c];
+            }
+            if (n <= most && rounds > 1) return std::printf("n %lld: workgroup %lld has %d rounds\n", (long long)n, (long long)b, rounds), 1;
+        }
+        if (grid < 1 || grid > most) return std::printf("n %lld: grid %lld\n", (long long)n, (long long)grid), 1;
+        for (int64_t c = 0; c < n; ++c) if (seen[c] != 1) return std::printf("n %lld: chunk %lld %d times\n", (long long)n, (long long)c, seen[c]), 1;
+    }
+    return 0;
+}
+"""
+
+
+def test_chunks_are_quantised_once_on_their_die_and_in_one_round(tmp_path):
+    """The order in which the quantising kernel takes the chunks: every chunk once, on a workgroup of the same residue modulo
+    the eight dies (the maxima kernel read it there), and none on a second round while the grid could still grow."""
+    (tmp_path / "order.cpp").write_text(CHUNK_ORDER)
+    csrc = os.path.join(os.path.dirname(B.__file__), "csrc")
+    subprocess.check_call(["g++", "-std=c++17", "-I" + csrc, str(tmp_path / "order.cpp"), "-o", str(tmp_path / "order")])
+    r = subprocess.run([str(tmp_path / "order")], stdout=subprocess.PIPE, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout
