@@ -372,9 +372,9 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * a panel tile, which moves fewer bytes per product and so runs at higher clocks.
  * The lists take the groups by descending cost of their first tile, groups of one row tile after the others (they stream weights
  * for themselves alone and fill the gaps: 75 + 130 + 237 rows, K = 4096, N = 11008 gated: 157 -> 144 us, fp8 76 -> 62 us).  Inside a group
- * the tiles go strip by strip and row by row; with at most EPARA_BLOCK_COLUMN_TILES row tiles and K >= EPARA_BLOCK_COLUMN_K column by
- * column, so that the row tiles of a column run together on a die, whose L2 then fetches their weights once (600 + 700 rows, fp8 gated, K = 4096:
- * 123 -> 114 us; 12 row tiles 241 -> 251, K = 768 65 -> 75: rows first).
+ * the tiles go strip by strip and row by row, so that the 32 tiles that run together on a die are eight rows of four columns.  (Column by
+ * column for up to eight row tiles of a long K, 1.00 .. 1.18 times as long on launches of one group of 2 .. 12 row tiles, K = 512 .. 8192,
+ * and 0.90 .. 1.19 times, 1.006 on average, on 335 mixed ones: no K and no number of row tiles from which it pays.)
  *
  * Which table.  Block tiles are taken where their estimate, and the streaming tiles' kernel next to them, is below the load
  * of the most loaded workgroup under the other table, in which every visit to a whole panel tile costs EPARA_COST_PANEL_START more,
@@ -415,8 +415,6 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 #define EPARA_COST_BLOCK_VISIT 200000
 #define EPARA_COST_BLOCK_PART 800000
 #define EPARA_COST_BLOCK_STREAMED 80
-#define EPARA_BLOCK_COLUMN_TILES 8
-#define EPARA_BLOCK_COLUMN_K 4096
 #define EPARA_BLOCK_SPLIT_K 1024
 #define EPARA_BLOCK_SPLIT_MAX_PER_LIST 3
 #define EPARA_BLOCK_TILES_PER_SLOT 3

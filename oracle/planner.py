@@ -379,7 +379,7 @@ def schedule_tiles(groups, classes, n_stream_classes, tiles, n_workgroups, n_xcd
     1. Panel tiles.  Classes by descending BM*BN (ties: lower class first); inside a class the
        groups by descending cost of their first tile (panel_cost; tiles of 256 rows: by descending K; ties: lower group first), block
        tiles (128 rows) of groups with a single row tile after all others; inside a group the tile grid TM x TN is cut into
-       panels of panel_m x panel_n tiles (block tiles of TM <= 8 and K >= 4096: TM x panel_n), panels taken with the n-panel index
+       panels of panel_m x panel_n tiles, panels taken with the n-panel index
        outermost, and inside a panel the m index runs fastest; block tiles in parts of K once per part, the first parts of all
        tiles first.  Each tile of that sequence goes to the
        workgroup with the smallest accumulated cost (panel_cost); among equally loaded
@@ -433,11 +433,10 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
             for g in members:
                 M, K, N = groups[g][:3]
                 TM, TN = -(-M // bm), -(-N // bn)
-                rows = TM if bm == 128 and TM <= 8 and K >= 4096 else panel_m
                 parts = block_parts if block_base[g] is not None else 1
-                for j, pn, pm in ((j, pn, pm) for j in range(parts) for pn in range(0, TN, panel_n) for pm in range(0, TM, rows)):
+                for j, pn, pm in ((j, pn, pm) for j in range(parts) for pn in range(0, TN, panel_n) for pm in range(0, TM, panel_m)):
                     for tn in range(pn, min(pn + panel_n, TN)):
-                        for tm in range(pm, min(pm + rows, TM)):
+                        for tm in range(pm, min(pm + panel_m, TM)):
                             t = first[g] + tm * TN + tn
                             if t >= len(tiles) - n_panel_split:      # visited in parts, after the whole tiles
                                 continue

@@ -769,15 +769,12 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
             });
             for (int32_t g : members) {
                 const int64_t TM = ceil_div(ph.groups[g].M, BM), TN = ceil_div(ph.groups[g].N, BN);
-                // block tiles of a long K: the row tiles of a column next to each other, so that they run together on a die and its L2
-                // fetches their weights once, as long as they are few
-                const int64_t rows = block && TM <= EPARA_BLOCK_COLUMN_TILES && ph.groups[g].K >= EPARA_BLOCK_COLUMN_K ? TM : panel_m;
                 const int32_t parts = block && block_splits(ph.groups[g], ph.classes[c]) ? n_block_parts : 1;
                 for (int32_t j = 0; j < parts; ++j)
                     for (int64_t pn = 0; pn < TN; pn += panel_n)
-                        for (int64_t pm = 0; pm < TM; pm += rows)
+                        for (int64_t pm = 0; pm < TM; pm += panel_m)
                             for (int64_t tn = pn; tn < std::min<int64_t>(pn + panel_n, TN); ++tn)
-                                for (int64_t tm = pm; tm < std::min<int64_t>(pm + rows, TM); ++tm) {
+                                for (int64_t tm = pm; tm < std::min<int64_t>(pm + panel_m, TM); ++tm) {
                                     const int64_t tile = first[p][g] + tm * TN + tn;
                                     if (tile >= ph.n_tiles - n_panel_split) continue;      // visited in parts, after the whole tiles
                                     const int64_t cost = panel_cost(ph.groups[g], ph.classes[c], ph.groups[g].M - tm * BM);

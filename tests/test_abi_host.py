@@ -578,14 +578,25 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
 
 
 @pytest.mark.parametrize("shapes,act,dtype,block", [
-    ([(1024, 4096, 512), (1025, 4096, 320), (128, 4096, 200), (129, 4096, 136)], 5, B.EPARA_BF16, True),     # 8 and 9 row tiles, 1 and 2, columns first from K = 4096
-    ([(1024, 4088, 512), (1025, 4088, 320), (128, 4088, 200)], 0, B.EPARA_BF16, True),                       # rows first below it; parts
+    ([(1024, 4096, 512), (1025, 4096, 320), (128, 4096, 200), (129, 4096, 136)], 5, B.EPARA_BF16, True),     # 8 and 9 row tiles, 1 and 2
+    ([(1024, 4088, 512), (1025, 4088, 320), (128, 4088, 200)], 0, B.EPARA_BF16, True),                       # parts
     ([(300, 4096, 520), (100, 4096, 520), (40, 4096, 64)], 5, B.EPARA_FP8_E4M3, True),
     ([(1000, 11008, 4096)], 0, B.EPARA_BF16, True), ([(300, 5504, 2048), (1200, 5504, 2048)], 0, B.EPARA_BF16, True),   # one block tile a unit
     ([(600, 11008, 4096), (700, 11008, 4096)], 0, B.EPARA_BF16, True), ([(4426, 13824, 5120)], 0, B.EPARA_BF16, False)])
 def test_block_tiles_in_the_order_and_where_the_estimate_says(shapes, act, dtype, block):
     """The same comparison with the reference planner where the order of block tiles changes and on either side of the choice."""
     test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype, block)
+
+
+@pytest.mark.parametrize("M", [256, 640, 1024, 1152])
+def test_the_order_of_block_tiles_inside_a_group_does_not_depend_on_k(M):
+    """Strip by strip and row by row, whatever the length of K."""
+    orders = []
+    cls, ns = B.epara_kernel_classes(B.EPARA_FP8_E4M3, 1, B.EPARA_TABLE_BLOCK)
+    for K in (768, 4080, 4096, 11008):
+        g = _desc([(M, K, 11008)], 5)
+        orders.append(B.epara_schedule_tiles(g, cls, ns, B.epara_plan_groups(g, cls)[3], 256, 8, 1, 4).tolist())
+    assert all(o == orders[0] for o in orders)
 
 
 def test_a_plan_zeroes_the_counters_of_its_workspace_only(monkeypatch):
