@@ -370,8 +370,11 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * Measured, bf16, 512 tiles at a time: K = 4096, own weights: 94 / 100 / 114 us for f = 1 / 2 / 4; weights shared by many row
  * tiles: 8.0 ns (K = 3072, N = 768) to 9.3 ns (K = 5120, N = 13824) per K and compute unit for f = 4, against 5.9 ns for a quarter of
  * a panel tile, which moves fewer bytes per product and so runs at higher clocks.
- * The lists take the groups by descending cost of their first tile, groups of one row tile after the others (they stream weights
- * for themselves alone and fill the gaps: 75 + 130 + 237 rows, K = 4096, N = 11008 gated: 157 -> 144 us, fp8 76 -> 62 us).  Inside a group
+ * The lists take the groups by descending cost of their first tile; groups of one row tile after the others (they stream weights for
+ * themselves alone and fill the gaps) in a single launch of n whole block tiles of one K with n <= W or 4 n >= EPARA_BLOCK_SINGLE_LAST_QUARTERS * W.
+ * Measured, such groups last against by cost, 600 launches of 2 .. 6 groups, K = 512 .. 13824: n <= W 0.989 times as long (247 launches), W .. 1.5 W
+ * 1.068 (81; the lists with a second tile get one more stream at the end), 1.5 .. 1.75 W 1.012, 1.75 .. 7 W 0.964 (249); in parts
+ * of K 1.10 for W .. 1.5 W visits, 1.00 otherwise; of several K 1.012.  75 + 130 + 237 rows, K = 4096, N = 11008 gated: 156 -> 141 us, fp8 79 -> 71.  Inside a group
  * the tiles go strip by strip and row by row, so that the 32 tiles that run together on a die are eight rows of four columns.  (Column by
  * column for up to eight row tiles of a long K, 1.00 .. 1.18 times as long on launches of one group of 2 .. 12 row tiles, K = 512 .. 8192,
  * and 0.90 .. 1.19 times, 1.006 on average, on 335 mixed ones: no K and no number of row tiles from which it pays.)
@@ -415,6 +418,7 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 #define EPARA_COST_BLOCK_VISIT 200000
 #define EPARA_COST_BLOCK_PART 800000
 #define EPARA_COST_BLOCK_STREAMED 80
+#define EPARA_BLOCK_SINGLE_LAST_QUARTERS 7
 #define EPARA_BLOCK_SPLIT_K 1024
 #define EPARA_BLOCK_SPLIT_MAX_PER_LIST 3
 #define EPARA_BLOCK_TILES_PER_SLOT 3

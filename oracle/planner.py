@@ -378,7 +378,8 @@ def schedule_tiles(groups, classes, n_stream_classes, tiles, n_workgroups, n_xcd
 
     1. Panel tiles.  Classes by descending BM*BN (ties: lower class first); inside a class the
        groups by descending cost of their first tile (panel_cost; tiles of 256 rows: by descending K; ties: lower group first), block
-       tiles (128 rows) of groups with a single row tile after all others; inside a group the tile grid TM x TN is cut into
+       tiles (128 rows) of groups with a single row tile after all others in a single launch whose block tiles have one K, are not
+       visited in parts, and are at most W or at least 7/4 W; inside a group the tile grid TM x TN is cut into
        panels of panel_m x panel_n tiles, panels taken with the n-panel index
        outermost, and inside a panel the m index runs fastest; block tiles in parts of K once per part, the first parts of all
        tiles first.  Each tile of that sequence goes to the
@@ -429,7 +430,10 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
         panel_classes = sorted(range(n_stream_classes, len(classes)), key=lambda c: (-classes[c][1] * classes[c][2], c))
         for c in panel_classes:
             bm, bn = classes[c][1], classes[c][2]
-            members = sorted({t[0] for t in tiles if t[5] == c}, key=lambda g: (bm == 128 and groups[g][0] <= 128, -panel_cost(groups[g][0], groups[g][1], classes[c], groups[g][0]), g))
+            own = {t[0] for t in tiles if t[5] == c}
+            n = sum(t[5] == c for t in tiles)
+            single_last = bm == 128 and len(phases) == 1 and block_parts == 1 and len({groups[g][1] for g in own}) <= 1 and (n <= W or 4 * n >= 7 * W)
+            members = sorted(own, key=lambda g: (single_last and groups[g][0] <= 128, -panel_cost(groups[g][0], groups[g][1], classes[c], groups[g][0]), g))
             for g in members:
                 M, K, N = groups[g][:3]
                 TM, TN = -(-M // bm), -(-N // bn)

@@ -759,12 +759,19 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
             for (int32_t g = 0; g < ph.G; ++g)
                 if (cls[p][g] == c) members.push_back(g);
             // by descending cost of a group's first tile (panel tiles of 256 rows: by descending K); block tiles of a single row tile
-            // last: they stream weights for themselves alone, into the gaps of those that share them
+            // last where the header says so: they stream weights for themselves alone, into the gaps of those that share them
             const int64_t BM = ph.classes[c].BM, BN = ph.classes[c].BN;
             const bool block = BM == EPARA_BLOCK_ROWS;
+            int64_t n_block = 0;
+            bool single_last = block && n_phases == 1 && n_block_parts == 1;
+            for (int32_t g : members) {
+                n_block += ceil_div(ph.groups[g].M, BM) * ceil_div(ph.groups[g].N, BN);
+                single_last = single_last && ph.groups[g].K == ph.groups[members[0]].K;
+            }
+            single_last = single_last && (n_block <= W || 4 * n_block >= EPARA_BLOCK_SINGLE_LAST_QUARTERS * W);
             std::stable_sort(members.begin(), members.end(), [&](int32_t a, int32_t b) {
                 const epara_group_desc &x = ph.groups[a], &y = ph.groups[b];
-                if (block && (x.M <= BM) != (y.M <= BM)) return y.M <= BM;
+                if (single_last && (x.M <= BM) != (y.M <= BM)) return y.M <= BM;
                 return panel_cost(x, ph.classes[c], x.M) > panel_cost(y, ph.classes[c], y.M);
             });
             for (int32_t g : members) {

@@ -588,6 +588,24 @@ def test_block_tiles_in_the_order_and_where_the_estimate_says(shapes, act, dtype
     test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype, block)
 
 
+@pytest.mark.parametrize("shapes,act,last", [
+    ([(100, 4096, 4096), (300, 4096, 4096)], 5, True),                               # 64 + 192 tiles: one a list
+    ([(100, 4096, 4160), (300, 4096, 4160)], 5, False),                              # 65 + 195
+    ([(100, 4096, 7104), (300, 4096, 7104)], 5, False),                              # 111 + 333, just below 7/4 a list
+    ([(100, 4096, 7168), (300, 4096, 7168)], 5, True),                               # 112 + 336
+    ([(100, 4096, 1024), (300, 2048, 1024)], 5, False),                              # a long K of its own goes first
+    ([(100, 2048, 1024), (300, 2048, 1024)], 0, False),                              # in parts of K
+    ([(100, 768, 1024), (300, 768, 1024)], 0, True)])
+def test_block_tiles_of_a_single_row_tile_go_last_where_the_header_says(shapes, act, last):
+    cls, ns = B.epara_kernel_classes(B.EPARA_BF16, int(act == 5), B.EPARA_TABLE_BLOCK)
+    g, W = _desc(shapes, act), 256
+    tiles = B.epara_plan_groups(g, cls)[3]
+    order = B.epara_schedule_tiles(g, cls, ns, tiles, W, 8, 1, 4)
+    table = [tuple(int(v) for v in c) for c in cls]
+    assert order.tolist() == P.schedule_tiles([s + (act == 5,) for s in shapes], table, ns, P.plan_groups(shapes, table)[3], W, 8, 1, 4)
+    assert int(tiles[P.order_decode(int(order[0]))[0]]["group"]) == int(last)        # workgroup 0 gets the first tile
+
+
 @pytest.mark.parametrize("M", [256, 640, 1024, 1152])
 def test_the_order_of_block_tiles_inside_a_group_does_not_depend_on_k(M):
     """Strip by strip and row by row, whatever the length of K."""
