@@ -381,8 +381,8 @@ def schedule_tiles(groups, classes, n_stream_classes, tiles, n_workgroups, n_xcd
        tiles (128 rows) of groups with a single row tile after all others in a single launch whose block tiles have one K, are not
        visited in parts, and are at most W or at least 7/4 W; inside a group the tile grid TM x TN is cut into
        panels of panel_m x panel_n tiles, panels taken with the n-panel index
-       outermost, and inside a panel the m index runs fastest; block tiles in parts of K once per part, the first parts of all
-       tiles first.  Each tile of that sequence goes to the
+       outermost, and inside a panel the m index runs fastest; block tiles in parts of K tile by tile up to 5/4 W visits, above that once per part,
+       the first parts of all tiles first.  Each tile of that sequence goes to the
        workgroup with the smallest accumulated cost (panel_cost); among equally loaded
        workgroups the one of smallest die-major rank, rank r standing for workgroup (r mod (W/X)) * X + r div (W/X).
        Tiles of equal cost therefore go round robin, the l-th to rank l mod W, and the W/X tiles that run
@@ -432,25 +432,28 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
             bm, bn = classes[c][1], classes[c][2]
             own = {t[0] for t in tiles if t[5] == c}
             n = sum(t[5] == c for t in tiles)
+            visits = sum(block_parts if block_base[t[0]] is not None else 1 for t in tiles if t[5] == c)
             single_last = bm == 128 and len(phases) == 1 and block_parts == 1 and len({groups[g][1] for g in own}) <= 1 and (n <= W or 4 * n >= 7 * W)
             members = sorted(own, key=lambda g: (single_last and groups[g][0] <= 128, -panel_cost(groups[g][0], groups[g][1], classes[c], groups[g][0]), g))
             for g in members:
                 M, K, N = groups[g][:3]
                 TM, TN = -(-M // bm), -(-N // bn)
                 parts = block_parts if block_base[g] is not None else 1
-                for j, pn, pm in ((j, pn, pm) for j in range(parts) for pn in range(0, TN, panel_n) for pm in range(0, TM, panel_m)):
+                rounds = parts if 4 * visits > 5 * W else 1
+                for k, pn, pm in ((k, pn, pm) for k in range(rounds) for pn in range(0, TN, panel_n) for pm in range(0, TM, panel_m)):
                     for tn in range(pn, min(pn + panel_n, TN)):
                         for tm in range(pm, min(pm + panel_m, TM)):
                             t = first[g] + tm * TN + tn
                             if t >= len(tiles) - n_panel_split:      # visited in parts, after the whole tiles
                                 continue
                             cost = panel_cost(M, K, classes[c], M - tm * bm)
-                            _, r = heapq.heappop(rank_heap)
-                            x, i = divmod(r, per)
-                            b = i * X + x
-                            lists[p][b].append(order_entry(t, j, parts))
-                            load[b] += cost if parts == 1 else cost // parts + 500000
-                            heapq.heappush(rank_heap, (load[b], r))
+                            for j in (k,) if rounds > 1 else range(parts):
+                                _, r = heapq.heappop(rank_heap)
+                                x, i = divmod(r, per)
+                                b = i * X + x
+                                lists[p][b].append(order_entry(t, j, parts))
+                                load[b] += cost if parts == 1 else cost // parts + 500000
+                                heapq.heappush(rank_heap, (load[b], r))
         for t in range(len(tiles) - n_panel_split, len(tiles)):    # the parts: tile by tile, part by part, same rule
             parts_t = panel_parts + (1 if t >= len(tiles) - panel_more else 0)      # the last panel_more tiles: one part more
             each = 2040 * groups[tiles[t][0]][1] // parts_t + 1020000

@@ -762,10 +762,12 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
             // last where the header says so: they stream weights for themselves alone, into the gaps of those that share them
             const int64_t BM = ph.classes[c].BM, BN = ph.classes[c].BN;
             const bool block = BM == EPARA_BLOCK_ROWS;
-            int64_t n_block = 0;
+            int64_t n_block = 0, n_visits = 0;
             bool single_last = block && n_phases == 1 && n_block_parts == 1;
             for (int32_t g : members) {
-                n_block += ceil_div(ph.groups[g].M, BM) * ceil_div(ph.groups[g].N, BN);
+                const int64_t n = ceil_div(ph.groups[g].M, BM) * ceil_div(ph.groups[g].N, BN);
+                n_block += n;
+                n_visits += n * (block && block_splits(ph.groups[g], ph.classes[c]) ? n_block_parts : 1);
                 single_last = single_last && ph.groups[g].K == ph.groups[members[0]].K;
             }
             single_last = single_last && (n_block <= W || 4 * n_block >= EPARA_BLOCK_SINGLE_LAST_QUARTERS * W);
@@ -777,7 +779,9 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
             for (int32_t g : members) {
                 const int64_t TM = ceil_div(ph.groups[g].M, BM), TN = ceil_div(ph.groups[g].N, BN);
                 const int32_t parts = block && block_splits(ph.groups[g], ph.classes[c]) ? n_block_parts : 1;
-                for (int32_t j = 0; j < parts; ++j)
+                // parts of K: all first parts before all second ones, or tile by tile (see the header)
+                const int32_t rounds = 4 * n_visits > EPARA_BLOCK_PART_ORDER_QUARTERS * W ? parts : 1;
+                for (int32_t round = 0; round < rounds; ++round)
                     for (int64_t pn = 0; pn < TN; pn += panel_n)
                         for (int64_t pm = 0; pm < TM; pm += panel_m)
                             for (int64_t tn = pn; tn < std::min<int64_t>(pn + panel_n, TN); ++tn)
@@ -785,7 +789,8 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
                                     const int64_t tile = first[p][g] + tm * TN + tn;
                                     if (tile >= ph.n_tiles - n_panel_split) continue;      // visited in parts, after the whole tiles
                                     const int64_t cost = panel_cost(ph.groups[g], ph.classes[c], ph.groups[g].M - tm * BM);
-                                    to_panel_workgroup(p, EPARA_ORDER_ENTRY(static_cast<int32_t>(tile), j, parts), block_visit_cost(cost, parts));
+                                    for (int32_t j = rounds > 1 ? round : 0; j < (rounds > 1 ? round + 1 : parts); ++j)
+                                        to_panel_workgroup(p, EPARA_ORDER_ENTRY(static_cast<int32_t>(tile), j, parts), block_visit_cost(cost, parts));
                                 }
             }
         }

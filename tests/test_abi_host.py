@@ -606,6 +606,23 @@ def test_block_tiles_of_a_single_row_tile_go_last_where_the_header_says(shapes, 
     assert int(tiles[P.order_decode(int(order[0]))[0]]["group"]) == int(last)        # workgroup 0 gets the first tile
 
 
+@pytest.mark.parametrize("shapes,together", [
+    ([(300, 11008, 1280)], True), ([(300, 11008, 4096)], True),                      # 30 tiles in four parts, 96 in three
+    ([(300, 11008, 2560), (640, 512, 2048)], True),                                  # 60 in four and 80 whole ones: 320 visits
+    ([(300, 11008, 2688), (384, 768, 2944)], False),                                 # 63 in four and 69: 321
+    ([(1501, 11008, 4096)], False)])
+def test_the_parts_of_block_tiles_are_visited_side_by_side_up_to_five_quarters_of_a_visit_per_list(shapes, together):
+    cls, ns = B.epara_kernel_classes(B.EPARA_BF16, 0, B.EPARA_TABLE_BLOCK)
+    g, W = _desc(shapes), 256
+    tiles = B.epara_plan_groups(g, cls)[3]
+    order = B.epara_schedule_tiles(g, cls, ns, tiles, W, 8, 1, 4)
+    table = [tuple(int(v) for v in c) for c in cls]
+    assert order.tolist() == P.schedule_tiles([s + (False,) for s in shapes], table, ns, P.plan_groups(shapes, table)[3], W, 8, 1, 4)
+    visits = [P.order_decode(int(e)) for e in order if e >= 0]
+    assert max(v[2] for v in visits) > 1 and (4 * len(visits) <= 5 * W) == together
+    assert (visits[0][0] == P.order_decode(int(order[8]))[0]) == together            # workgroups 0 and 8: the first two of a die
+
+
 @pytest.mark.parametrize("M", [256, 640, 1024, 1152])
 def test_the_order_of_block_tiles_inside_a_group_does_not_depend_on_k(M):
     """Strip by strip and row by row, whatever the length of K."""
