@@ -387,7 +387,7 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  *     EPARA_COST_BLOCK_PART), groups by descending M, the ragged row tile of a group last, each go to the least loaded one, and of
  *   the weights' way to the chip, sum of K * N * (2 for EPARA_ACT_SWIGLU) * (2 TM + 1) / EPARA_COST_BLOCK_STREAMED over the groups: fetched
  *     once for the first of TM row tiles and two thirds of a time for each other one, at 5.3 TB/s.
- * For fp8 the two constants of a visit count twice (a K is half the bytes).  Fitted to what either kernel takes on 500 launches of 65 .. 2500 rows, K = 384 .. 13824
+ * Fitted to what either kernel takes on 500 launches of 65 .. 2500 rows, K = 384 .. 13824
  * and N = 192 .. 13824: on 2600 others the choice (and that of P) is on average 0.6 % slower than the best of all, where the rule
  * before it, of one list cost per tile, lost 9 %.
  *

@@ -313,11 +313,11 @@ def panel_split(groups, classes, n_stream_classes, n_workgroups):
     return (m, parts, more) if parts > 1 else (0, 1, 0)
 
 
-def block_estimate(groups, classes, n_stream_classes, n_workgroups, parts, unit):
+def block_estimate(groups, classes, n_stream_classes, n_workgroups, parts):
     """What a launch's block tiles take when those that may be split are visited in `parts` parts of K: the larger of
-    the most loaded of W lists, when the visits (180 K f // P + 200000 unit, in parts 800000 unit more; f = ceil(rows / 32)), groups by
+    the most loaded of W lists, when the visits (180 K f // P + 200000, in parts 800000 more; f = ceil(rows / 32)), groups by
     descending M, whole row tiles before the last one, each go to the least loaded list, and of
-    sum K N (2 if gated) (2 TM + 1) // 80 (weights fetched (2 TM + 1) / 3 times).  unit: 2 for fp8, 1 for bf16."""
+    sum K N (2 if gated) (2 TM + 1) // 80 (weights fetched (2 TM + 1) / 3 times)."""
     import heapq
     bins, streamed = [0] * n_workgroups, 0
     members = [g for g, gr in enumerate(groups) if gr[0] > 0 and pick_class(gr[0], classes) >= n_stream_classes]
@@ -326,7 +326,7 @@ def block_estimate(groups, classes, n_stream_classes, n_workgroups, parts, unit)
         cl = classes[pick_class(M, classes)]
         p = parts if len(cl) > 3 and cl[3] > 0 and K >= cl[3] else 1
         for m0 in range(0, M, 128):
-            each = 180 * -(-min(128, M - m0) // 32) * K // p + unit * (200000 + (800000 if p > 1 else 0))
+            each = 180 * -(-min(128, M - m0) // 32) * K // p + 200000 + (800000 if p > 1 else 0)
             for _ in range(-(-N // cl[2]) * p):
                 heapq.heapreplace(bins, bins[0] + each)
         streamed += K * N * (2 if len(groups[g]) > 3 and groups[g][3] else 1) * (2 * -(-M // 128) + 1)
@@ -359,7 +359,7 @@ def block_split(groups, classes, n_stream_classes, n_workgroups):
         return 1, [None] * len(groups), 0
     best = None
     for P in (1, 2, 3, 4):
-        finish = block_estimate(groups, classes, n_stream_classes, W, P, 1)
+        finish = block_estimate(groups, classes, n_stream_classes, W, P)
         if best is None or finish < best[0]:
             best = (finish, P)
     if best[1] == 1:
@@ -506,8 +506,6 @@ def block_choice(groups, block_classes, other_classes, other_n_stream, other_til
     W = n_workgroups
     if max((g[0] for g in groups), default=0) <= 64 or W < 128:
         return False, None, None, None
-    fp8 = block_classes[1][3] == 0                           # the streaming classes of bf16 tables name a K to split from
-    unit = 2 if fp8 else 1
 
     def loads(classes, n_stream, tiles, order, start, part_start):
         panel, stream = [0] * W, [0] * W
@@ -534,7 +532,7 @@ def block_choice(groups, block_classes, other_classes, other_n_stream, other_til
     panel, stream = loads(block_classes, n_stream, tiles, order, 0, 0)
     streaming = max(stream) + 400000 if any(t[5] < n_stream for t in tiles) else 0
     parts = block_split(groups, block_classes, n_stream, W)[0]
-    return block_estimate(groups, block_classes, n_stream, W, parts, unit) + streaming < other, tiles, order, max(panel) + streaming
+    return block_estimate(groups, block_classes, n_stream, W, parts) + streaming < other, tiles, order, max(panel) + streaming
 
 
 def chain_waits(producer_tiles, counter_base, producer):

@@ -195,10 +195,9 @@ inline bool block_group(const epara_group_desc& d, const epara_tile_class* class
 inline bool block_splits(const epara_group_desc& d, const epara_tile_class& c) { return c.split_K > 0 && d.K >= c.split_K; }
 inline int64_t block_visit_cost(int64_t cost, int32_t parts) { return parts == 1 ? cost : cost / parts + EPARA_COST_BLOCK_PARTIAL; }
 
-// What a launch's block tiles take when those of a long K are visited in `parts` parts ("Which table" in the header).  unit: what a
-// constant of time is multiplied by, 1, or 2 where an element has one byte (the costs per K are then of half the bytes).
+// What a launch's block tiles take when those of a long K are visited in `parts` parts ("Which table" in the header).
 int64_t block_estimate(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
-                       int32_t n_stream_classes, int64_t W, int32_t parts, int64_t unit)
+                       int32_t n_stream_classes, int64_t W, int32_t parts)
 {
     std::vector<int32_t> members;
     for (int32_t g = 0; g < G; ++g)
@@ -212,7 +211,7 @@ int64_t block_estimate(const epara_group_desc* groups, int32_t G, const epara_ti
         const int64_t TN = ceil_div(d.N, c.BN), TM = ceil_div(d.M, c.BM), p = block_splits(d, c) ? parts : 1;
         auto visits = [&](int64_t tiles, int64_t rows) {
             const int64_t cost = EPARA_COST_BLOCK_PER_32 * ceil_div(rows, 32) * d.K;
-            lists.place(tiles * p, cost / p + unit * (EPARA_COST_BLOCK_VISIT + (p > 1 ? EPARA_COST_BLOCK_PART : 0)));
+            lists.place(tiles * p, cost / p + EPARA_COST_BLOCK_VISIT + (p > 1 ? EPARA_COST_BLOCK_PART : 0));
         };
         visits(TN * (TM - 1), c.BM);
         visits(TN, d.M - (TM - 1) * c.BM);
@@ -237,7 +236,7 @@ int32_t block_parts(const epara_group_desc* groups, int32_t G, const epara_tile_
     int32_t best_parts = 1;
     int64_t best = -1;
     for (int32_t P = 1; P <= EPARA_SPLIT_MAX_PARTS; ++P) {
-        const int64_t finish = block_estimate(groups, G, classes, n_classes, n_stream_classes, W, P, 1);      // only bf16 tiles are split
+        const int64_t finish = block_estimate(groups, G, classes, n_classes, n_stream_classes, W, P);
         if (best < 0 || finish < best) { best = finish; best_parts = P; }
     }
     return best_parts;
@@ -969,7 +968,6 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
     int32_t max_M = 0;
     for (int32_t g = 0; g < G; ++g) max_M = std::max(max_M, groups[g].M);
     if (in_dtype == EPARA_F32 || max_M <= 64 || W < EPARA_BLOCK_MIN_WORKGROUPS) return EPARA_OK;
-    const int64_t unit = in_dtype == EPARA_FP8_E4M3 ? 2 : 1;
     std::vector<int64_t> load(static_cast<size_t>(W), 0);
     for (size_t i = 0; i < best_order.size(); ++i)
         if (best_order[i] >= 0) {
@@ -982,7 +980,7 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
     if (int32_t st = epara_kernel_classes(in_dtype, gated, EPARA_TABLE_BLOCK, o.classes, 4, &o.n_classes, &o.n_stream)) return st;
     const int32_t parts = block_parts(groups, G, o.classes, o.n_classes, o.n_stream, W);
     const int64_t stream = stream_finish(groups, G, o.classes, o.n_classes, o.n_stream, W);
-    if (block_estimate(groups, G, o.classes, o.n_classes, o.n_stream, W, parts, unit) + (stream > 0 ? stream + EPARA_COST_KERNEL : 0) >= other) return EPARA_OK;
+    if (block_estimate(groups, G, o.classes, o.n_classes, o.n_stream, W, parts) + (stream > 0 ? stream + EPARA_COST_KERNEL : 0) >= other) return EPARA_OK;
     if (int32_t st = make_option(groups, G, in_dtype, gated, EPARA_TABLE_BLOCK, o)) return st;
     if (o.tiles.size() > 0xFFFFFF) return EPARA_OK;              // more than an entry of an order with parts can name
     *take = true;
