@@ -379,7 +379,8 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * column for up to eight row tiles of a long K, 1.00 .. 1.18 times as long on launches of one group of 2 .. 12 row tiles, K = 512 .. 8192,
  * and 0.90 .. 1.19 times, 1.006 on average, on 335 mixed ones: no K and no number of row tiles from which it pays.)
  *
- * Which table.  Block tiles are taken where their estimate, and the streaming tiles' kernel next to them, is below the load
+ * Which table.  Block tiles are taken where their estimate, plus, if there are streaming tiles, the largest load of a list in those and
+ * EPARA_COST_BLOCK_BEHIND_STREAM (their kernel runs before, and what a chip full of streams would have hidden is not), is below the load
  * of the most loaded workgroup under the other table, in which every visit to a whole panel tile costs EPARA_COST_PANEL_START more,
  * every part of one EPARA_COST_PANEL_PART_START and the launch EPARA_COST_PANEL_LAUNCH (start and finish, which one wave per SIMD
  * cannot overlap with anything and two workgroups per unit hide from each other).  The estimate is the larger of
@@ -420,6 +421,7 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 #define EPARA_COST_BLOCK_VISIT 200000
 #define EPARA_COST_BLOCK_PART 800000
 #define EPARA_COST_BLOCK_STREAMED 80
+#define EPARA_COST_BLOCK_BEHIND_STREAM 1200000
 #define EPARA_BLOCK_SINGLE_LAST_QUARTERS 7
 #define EPARA_BLOCK_PART_ORDER_QUARTERS 5
 #define EPARA_BLOCK_SPLIT_K 1024
@@ -564,8 +566,8 @@ typedef struct {
  * table -- the wide one, or the narrow one when some batch has more than 32 rows and the narrow
  * table's schedule has the smaller makespan under the cost model (ties: wide); or the block table ("Block tiles"), for
  * bf16 / fp8 launches with a batch of more than 64 rows and n_workgroups >= EPARA_BLOCK_MIN_WORKGROUPS, when its estimate
- * (plus the largest load of streaming tiles and EPARA_COST_KERNEL if there are any) is below that of the other choice ("Which table");
- * its makespan is the largest load of block tiles plus the same for streaming tiles -- then plans
+ * is below that of the other choice ("Which table"); its makespan is the largest load of block tiles, plus the largest load of streaming
+ * tiles and EPARA_COST_KERNEL if there are any (a figure of the lists, not of the estimate: it is not comparable with the makespan of the other tables) -- then plans
  * (epara_plan_groups) and schedules (epara_schedule_tiles) with it.  The groups must be all
  * EPARA_ACT_SWIGLU or none (ERR_DTYPE).  (A chain, epara_plan_chain, has no block tiles, not even one of a single phase.)  *plan is always written (sizes included); tiles / order are
  * written when given and large enough, else ERR_CAPACITY (give NULL and 0 to ask for the sizes only;

@@ -500,9 +500,10 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
 def block_choice(groups, block_classes, other_classes, other_n_stream, other_tiles, other_order, n_workgroups, n_xcd, panel_m, panel_n):
     """Whether a single bf16 / fp8 launch takes the block table instead of the best of the other tables (class table, tiles
     and visit order of which are given) -> (taken, tiles, order, finish).  Considered when a batch has more than 64 rows
-    and W >= 128.  Taken if block_estimate, plus the largest load of a list in streaming tiles and 400000 if there are any, is below the
+    and W >= 128.  Taken if block_estimate, plus the largest load of a list in streaming tiles and 1200000 if there are any, is below the
     largest load of a workgroup in the other order where every visit to a whole panel tile costs 800000 more and every part
-    1980000 more, plus 1100000.  finish = the largest load of a list in block tiles plus the same for streaming tiles."""
+    1980000 more, plus 1100000.  finish = the largest load of a list in block tiles, plus the largest load in streaming tiles and 400000
+    if there are any."""
     W = n_workgroups
     if max((g[0] for g in groups), default=0) <= 64 or W < 128:
         return False, None, None, None
@@ -532,7 +533,8 @@ def block_choice(groups, block_classes, other_classes, other_n_stream, other_til
     panel, stream = loads(block_classes, n_stream, tiles, order, 0, 0)
     streaming = max(stream) + 400000 if any(t[5] < n_stream for t in tiles) else 0
     parts = block_split(groups, block_classes, n_stream, W)[0]
-    return block_estimate(groups, block_classes, n_stream, W, parts) + streaming < other, tiles, order, max(panel) + streaming
+    behind = max(stream) + 1200000 if any(t[5] < n_stream for t in tiles) else 0
+    return block_estimate(groups, block_classes, n_stream, W, parts) + behind < other, tiles, order, max(panel) + streaming
 
 
 def chain_waits(producer_tiles, counter_base, producer):

@@ -980,7 +980,7 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
     if (int32_t st = epara_kernel_classes(in_dtype, gated, EPARA_TABLE_BLOCK, o.classes, 4, &o.n_classes, &o.n_stream)) return st;
     const int32_t parts = block_parts(groups, G, o.classes, o.n_classes, o.n_stream, W);
     const int64_t stream = stream_finish(groups, G, o.classes, o.n_classes, o.n_stream, W);
-    if (block_estimate(groups, G, o.classes, o.n_classes, o.n_stream, W, parts) + (stream > 0 ? stream + EPARA_COST_KERNEL : 0) >= other) return EPARA_OK;
+    if (block_estimate(groups, G, o.classes, o.n_classes, o.n_stream, W, parts) + (stream > 0 ? stream + EPARA_COST_BLOCK_BEHIND_STREAM : 0) >= other) return EPARA_OK;
     if (int32_t st = make_option(groups, G, in_dtype, gated, EPARA_TABLE_BLOCK, o)) return st;
     if (o.tiles.size() > 0xFFFFFF) return EPARA_OK;              // more than an entry of an order with parts can name
     *take = true;

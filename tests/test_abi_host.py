@@ -582,6 +582,8 @@ def test_plan_launch_takes_block_tiles_where_the_header_says(shapes, act, dtype,
     ([(1024, 4088, 512), (1025, 4088, 320), (128, 4088, 200)], 0, B.EPARA_BF16, True),                       # parts
     ([(300, 4096, 520), (100, 4096, 520), (40, 4096, 64)], 5, B.EPARA_FP8_E4M3, True),
     ([(3175, 192, 138), (6078, 16, 4902), (4039, 160, 16)], 5, B.EPARA_FP8_E4M3, True),                      # many short fp8 tiles
+    ([(64, 2592, 6102), (107, 480, 203), (5, 7312, 331), (18, 9376, 868)], 0, B.EPARA_BF16, False),          # two block tiles next to long streams
+    ([(18, 2544, 3484), (1080, 1024, 9524)], 5, B.EPARA_BF16, False),
     ([(1000, 11008, 4096)], 0, B.EPARA_BF16, True), ([(300, 5504, 2048), (1200, 5504, 2048)], 0, B.EPARA_BF16, True),   # one block tile a unit
     ([(600, 11008, 4096), (700, 11008, 4096)], 0, B.EPARA_BF16, True), ([(4426, 13824, 5120)], 0, B.EPARA_BF16, False)])
 def test_block_tiles_in_the_order_and_where_the_estimate_says(shapes, act, dtype, block):
