@@ -396,7 +396,8 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * K >= the block class's split_K > 0 (EPARA_BLOCK_SPLIT_K for plain bf16 launches; 0 for gated and fp8 ones, whose results do not
  * depend on the grid or on the other groups) are visited in P = 1 .. EPARA_SPLIT_MAX_PARTS parts of K, the same P for the
  * whole launch: part j covers the units floor(U j / P) .. floor(U (j+1) / P) - 1 of the U = ceil(ceil(K / stage) / 4) units of
- * four 64-byte stages.  P is the one of the smallest estimate (ties: fewer parts); 1 if the launch has more than
+ * four 64-byte stages.  P is the one whose lists finish first under "Which table" (ties: fewer parts; the weights' way is the same for every P and
+ * must not hide the difference: 80 + 68 rows, K = 13824, N = 5120 in two / three parts 73 / 59 us); 1 if the launch has more than
  * EPARA_BLOCK_SPLIT_MAX_PER_LIST * W block tiles.  In the lists a visit costs cost / P + EPARA_COST_BLOCK_PARTIAL, and with 4 n > EPARA_BLOCK_PART_ORDER_QUARTERS * W
  * visits n a group's first parts come before all its second ones: what runs together reads the same piece of the activations (1501 rows, K = 11008,
  * N = 4096 in two parts: tile by tile 158 us, part by part 134; 75 + 130 + 237 rows in three: 94 -> 84).  Fewer visits all run at once: tile by tile, so that the

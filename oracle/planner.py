@@ -314,10 +314,10 @@ def panel_split(groups, classes, n_stream_classes, n_workgroups):
 
 
 def block_estimate(groups, classes, n_stream_classes, n_workgroups, parts):
-    """What a launch's block tiles take when those that may be split are visited in `parts` parts of K: the larger of
-    the most loaded of W lists, when the visits (180 K f // P + 200000, in parts 800000 more; f = ceil(rows / 32)), groups by
-    descending M, whole row tiles before the last one, each go to the least loaded list, and of
-    sum K N (2 if gated) (2 TM + 1) // 80 (weights fetched (2 TM + 1) / 3 times)."""
+    """What a launch's block tiles take when those that may be split are visited in `parts` parts of K -> (lists, weights), of
+    which the larger counts: the most loaded of W lists, when the visits (180 K f // P + 200000, in parts 800000 more;
+    f = ceil(rows / 32)), groups by descending M, whole row tiles before the last one, each go to the least loaded list; and
+    sum K N (2 if gated) (2 TM + 1) // 80 (weights fetched (2 TM + 1) / 3 times), whatever the parts."""
     import heapq
     bins, streamed = [0] * n_workgroups, 0
     members = [g for g, gr in enumerate(groups) if gr[0] > 0 and pick_class(gr[0], classes) >= n_stream_classes]
@@ -330,14 +330,14 @@ def block_estimate(groups, classes, n_stream_classes, n_workgroups, parts):
             for _ in range(-(-N // cl[2]) * p):
                 heapq.heapreplace(bins, bins[0] + each)
         streamed += K * N * (2 if len(groups[g]) > 3 and groups[g][3] else 1) * (2 * -(-M // 128) + 1)
-    return max(max(bins), streamed // 80)
+    return max(bins), streamed // 80
 
 
 def block_split(groups, classes, n_stream_classes, n_workgroups):
     """-> (P, split_base per group or None, slots): in how many parts of K a single launch visits the block tiles (a panel
     class of 128 rows with split_K > 0) of the groups with K >= split_K, where they meet, and how many slots of three tiles
-    that takes.  P = 1 with more than 3 W block tiles or none to split; otherwise the P = 1 .. 4 of the smallest block_estimate;
-    fewer parts on ties."""
+    that takes.  P = 1 with more than 3 W block tiles or none to split; otherwise the P = 1 .. 4 whose lists finish first in
+    block_estimate; fewer parts on ties."""
     W = n_workgroups
     members, n, n_split, base, at = [], 0, 0, [None] * len(groups), 0
     for g, gr in enumerate(groups):
@@ -359,7 +359,7 @@ def block_split(groups, classes, n_stream_classes, n_workgroups):
         return 1, [None] * len(groups), 0
     best = None
     for P in (1, 2, 3, 4):
-        finish = block_estimate(groups, classes, n_stream_classes, W, P)
+        finish = block_estimate(groups, classes, n_stream_classes, W, P)[0]
         if best is None or finish < best[0]:
             best = (finish, P)
     if best[1] == 1:
@@ -534,7 +534,7 @@ def block_choice(groups, block_classes, other_classes, other_n_stream, other_til
     streaming = max(stream) + 400000 if any(t[5] < n_stream for t in tiles) else 0
     parts = block_split(groups, block_classes, n_stream, W)[0]
     behind = max(stream) + 1200000 if any(t[5] < n_stream for t in tiles) else 0
-    return block_estimate(groups, block_classes, n_stream, W, parts) + behind < other, tiles, order, max(panel) + streaming
+    return max(block_estimate(groups, block_classes, n_stream, W, parts)) + behind < other, tiles, order, max(panel) + streaming
 
 
 def chain_waits(producer_tiles, counter_base, producer):

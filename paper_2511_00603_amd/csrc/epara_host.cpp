@@ -195,9 +195,10 @@ inline bool block_group(const epara_group_desc& d, const epara_tile_class* class
 inline bool block_splits(const epara_group_desc& d, const epara_tile_class& c) { return c.split_K > 0 && d.K >= c.split_K; }
 inline int64_t block_visit_cost(int64_t cost, int32_t parts) { return parts == 1 ? cost : cost / parts + EPARA_COST_BLOCK_PARTIAL; }
 
-// What a launch's block tiles take when those of a long K are visited in `parts` parts ("Which table" in the header).
-int64_t block_estimate(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
-                       int32_t n_stream_classes, int64_t W, int32_t parts)
+// What a launch's block tiles take when those of a long K are visited in `parts` parts ("Which table" in the header): the most
+// loaded list; *weights (or null): the weights' way to the chip, whatever the parts.
+int64_t block_lists(const epara_group_desc* groups, int32_t G, const epara_tile_class* classes, int32_t n_classes,
+                    int32_t n_stream_classes, int64_t W, int32_t parts, int64_t* weights)
 {
     std::vector<int32_t> members;
     for (int32_t g = 0; g < G; ++g)
@@ -217,7 +218,8 @@ int64_t block_estimate(const epara_group_desc* groups, int32_t G, const epara_ti
         visits(TN, d.M - (TM - 1) * c.BM);
         streamed += static_cast<double>(d.K) * d.N * (d.act == EPARA_ACT_SWIGLU ? 2 : 1) * static_cast<double>(2 * TM + 1);
     }
-    return std::max(lists.most(), static_cast<int64_t>(std::min(streamed / EPARA_COST_BLOCK_STREAMED, 4e18)));
+    if (weights) *weights = static_cast<int64_t>(std::min(streamed / EPARA_COST_BLOCK_STREAMED, 4e18));
+    return lists.most();
 }
 
 // In how many parts of K a launch visits its block tiles of a long K ("Block tiles of a long K" in the header).
@@ -236,7 +238,7 @@ int32_t block_parts(const epara_group_desc* groups, int32_t G, const epara_tile_
     int32_t best_parts = 1;
     int64_t best = -1;
     for (int32_t P = 1; P <= EPARA_SPLIT_MAX_PARTS; ++P) {
-        const int64_t finish = block_estimate(groups, G, classes, n_classes, n_stream_classes, W, P);
+        const int64_t finish = block_lists(groups, G, classes, n_classes, n_stream_classes, W, P, nullptr);
         if (best < 0 || finish < best) { best = finish; best_parts = P; }
     }
     return best_parts;
@@ -980,7 +982,9 @@ int32_t block_option(const epara_group_desc* groups, int32_t G, int32_t in_dtype
     if (int32_t st = epara_kernel_classes(in_dtype, gated, EPARA_TABLE_BLOCK, o.classes, 4, &o.n_classes, &o.n_stream)) return st;
     const int32_t parts = block_parts(groups, G, o.classes, o.n_classes, o.n_stream, W);
     const int64_t stream = stream_finish(groups, G, o.classes, o.n_classes, o.n_stream, W);
-    if (block_estimate(groups, G, o.classes, o.n_classes, o.n_stream, W, parts) + (stream > 0 ? stream + EPARA_COST_BLOCK_BEHIND_STREAM : 0) >= other) return EPARA_OK;
+    int64_t weights = 0;
+    const int64_t lists = block_lists(groups, G, o.classes, o.n_classes, o.n_stream, W, parts, &weights);
+    if (std::max(lists, weights) + (stream > 0 ? stream + EPARA_COST_BLOCK_BEHIND_STREAM : 0) >= other) return EPARA_OK;
     if (int32_t st = make_option(groups, G, in_dtype, gated, EPARA_TABLE_BLOCK, o)) return st;
     if (o.tiles.size() > 0xFFFFFF) return EPARA_OK;              // more than an entry of an order with parts can name
     *take = true;

@@ -609,6 +609,16 @@ def test_block_tiles_of_a_single_row_tile_go_last_where_the_header_says(shapes, 
     assert int(tiles[P.order_decode(int(order[0]))[0]]["group"]) == int(last)        # workgroup 0 gets the first tile
 
 
+@pytest.mark.parametrize("rows,K,N,parts", [((80, 68), 13824, 5120, 3), ((66, 79, 215), 13824, 5120, 3), ((75, 130, 237), 11008, 4096, 2), ((136, 351), 13824, 5120, 3),
+                                            ((618, 137, 728), 11008, 4096, 2), ((1501,), 11008, 4096, 2)])
+def test_the_number_of_parts_is_chosen_by_the_lists_where_the_weights_take_longer(rows, K, N, parts):
+    """Launches whose estimate is the weights' way to the chip, the same for every number of parts, but whose lists differ."""
+    shapes = [(m, K, N) for m in rows]
+    cls, ns = B.epara_kernel_classes(B.EPARA_BF16, 0, B.EPARA_TABLE_BLOCK)
+    assert B.epara_panel_split(_desc(shapes), cls, ns, 256)[1] == parts
+    assert P.block_split([s + (False,) for s in shapes], [tuple(int(v) for v in c) for c in cls], ns, 256)[0] == parts
+
+
 @pytest.mark.parametrize("shapes,together", [
     ([(300, 11008, 1280)], True), ([(300, 11008, 4096)], True),                      # 30 tiles in four parts, 96 in three
     ([(300, 11008, 2560), (640, 512, 2048)], True),                                  # 60 in four and 80 whole ones: 320 visits
