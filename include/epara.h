@@ -398,11 +398,11 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * whole launch: part j covers the units floor(U j / P) .. floor(U (j+1) / P) - 1 of the U = ceil(ceil(K / stage) / 4) units of
  * four 64-byte stages.  P is the one whose lists finish first under "Which table" (ties: fewer parts; the weights' way is the same for every P and
  * must not hide the difference: 80 + 68 rows, K = 13824, N = 5120 in two / three parts 73 / 59 us); 1 if the launch has more than
- * EPARA_BLOCK_SPLIT_MAX_PER_LIST * W block tiles.  In the lists a visit costs cost / P + EPARA_COST_BLOCK_PARTIAL, and with 4 n > EPARA_BLOCK_PART_ORDER_QUARTERS * W
+ * EPARA_BLOCK_SPLIT_MAX_PER_LIST * W block tiles.  In the lists a visit costs cost / P + EPARA_COST_BLOCK_PARTIAL, and with 8 n > EPARA_BLOCK_PART_ORDER_EIGHTHS * W
  * visits n a group's first parts come before all its second ones: what runs together reads the same piece of the activations (1501 rows, K = 11008,
- * N = 4096 in two parts: tile by tile 158 us, part by part 134; 75 + 130 + 237 rows in three: 94 -> 84).  Fewer visits all run at once: tile by tile, so that the
- * parts of a tile meet on one die (2376 x 3008 x 247 in four: part by part 24.3 us, tile by tile 20.8).  Part by part against tile by tile, 267 launches in two, three and
- * four parts: up to W visits 1.010 times as long, .. 5/4 W 1.006, .. 3/2 W 0.981, .. 2 W 0.968, .. 3 W 0.948, .. 4 W 0.920, .. 6 W 0.892, above 0.842.  Every visit leaves its raw
+ * N = 4096 in two parts: tile by tile 158 us, part by part 134).  Fewer visits all run at once: tile by tile, so that the parts of a tile meet on one
+ * die (2376 x 3008 x 247 in four: part by part 24.3 us, tile by tile 20.8).  Part by part against tile by tile, 900 launches in the parts they are planned
+ * in: n <= W 1.006 times as long (683 launches), .. 1.1 W 1.038 (40), .. 1.2 W 0.990 (8), .. 1.3 W 0.967 (13), .. 1.75 W 0.929 (41), .. 2 W 0.933 (55), above 0.899 (60).  Every visit leaves its raw
  * sums (64 KiB) in the workspace and counts itself at the tile; whoever counts last adds the parts in index order and
  * runs the epilogue.  Three split tiles share a slot of a split panel tile: epara_launch.n_panel_split_tiles =
  * ceil(split block tiles / EPARA_BLOCK_TILES_PER_SLOT), and split_base[g] = index of the group's first tile among them.
@@ -424,7 +424,7 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 #define EPARA_COST_BLOCK_STREAMED 80
 #define EPARA_COST_BLOCK_BEHIND_STREAM 1200000
 #define EPARA_BLOCK_SINGLE_LAST_QUARTERS 7
-#define EPARA_BLOCK_PART_ORDER_QUARTERS 5
+#define EPARA_BLOCK_PART_ORDER_EIGHTHS 9
 #define EPARA_BLOCK_SPLIT_K 1024
 #define EPARA_BLOCK_SPLIT_MAX_PER_LIST 3
 #define EPARA_BLOCK_TILES_PER_SLOT 3

@@ -381,7 +381,7 @@ def schedule_tiles(groups, classes, n_stream_classes, tiles, n_workgroups, n_xcd
        tiles (128 rows) of groups with a single row tile after all others in a single launch whose block tiles have one K, are not
        visited in parts, and are at most W or at least 7/4 W; inside a group the tile grid TM x TN is cut into
        panels of panel_m x panel_n tiles, panels taken with the n-panel index
-       outermost, and inside a panel the m index runs fastest; block tiles in parts of K tile by tile up to 5/4 W visits, above that once per part,
+       outermost, and inside a panel the m index runs fastest; block tiles in parts of K tile by tile up to 9/8 W visits, above that once per part,
        the first parts of all tiles first.  Each tile of that sequence goes to the
        workgroup with the smallest accumulated cost (panel_cost); among equally loaded
        workgroups the one of smallest die-major rank, rank r standing for workgroup (r mod (W/X)) * X + r div (W/X).
@@ -439,7 +439,7 @@ def schedule_chain(phases, n_workgroups, n_xcd, panel_m, panel_n):
                 M, K, N = groups[g][:3]
                 TM, TN = -(-M // bm), -(-N // bn)
                 parts = block_parts if block_base[g] is not None else 1
-                rounds = parts if 4 * visits > 5 * W else 1
+                rounds = parts if 8 * visits > 9 * W else 1
                 for k, pn, pm in ((k, pn, pm) for k in range(rounds) for pn in range(0, TN, panel_n) for pm in range(0, TM, panel_m)):
                     for tn in range(pn, min(pn + panel_n, TN)):
                         for tm in range(pm, min(pm + panel_m, TM)):

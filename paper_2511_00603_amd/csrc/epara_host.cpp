@@ -781,7 +781,7 @@ int32_t schedule(epara_phase_schedule* phases, int32_t n_phases, int32_t n_workg
                 const int64_t TM = ceil_div(ph.groups[g].M, BM), TN = ceil_div(ph.groups[g].N, BN);
                 const int32_t parts = block && block_splits(ph.groups[g], ph.classes[c]) ? n_block_parts : 1;
                 // parts of K: all first parts before all second ones, or tile by tile (see the header)
-                const int32_t rounds = 4 * n_visits > EPARA_BLOCK_PART_ORDER_QUARTERS * W ? parts : 1;
+                const int32_t rounds = 8 * n_visits > EPARA_BLOCK_PART_ORDER_EIGHTHS * W ? parts : 1;
                 for (int32_t round = 0; round < rounds; ++round)
                     for (int64_t pn = 0; pn < TN; pn += panel_n)
                         for (int64_t pm = 0; pm < TM; pm += panel_m)
