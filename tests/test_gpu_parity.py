@@ -100,6 +100,27 @@ def test_small_integers_are_bit_exact(dtype_name, tiles):
         assert np.array_equal(y, yref), (dtype_name, M, K, N, np.argwhere(y != yref)[:5])
 
 
+@pytest.mark.parametrize("dtype_name", ["bf16", "fp8"])
+def test_streaming_tiles_in_a_row_add_their_own_bias(dtype_name):
+    """Small grid, so that a workgroup streams several tiles of a class one after the other: the bias of a bf16 tile comes into one of two
+    places in the LDS by turns while the one before may still be read.  Large integer biases, no two alike in a group, some groups
+    without, ragged last columns, K of one chunk and of several: bit for bit, twice."""
+    rng = np.random.default_rng(17)
+    shapes = [(16, 16, 1000), (32, 16, 900), (5, 208, 770), (20, 272, 1030), (1, 528, 333), (17, 1040, 520), (9, 1040, 1100), (31, 80, 640)]
+    specs = []
+    for i, (M, K, N) in enumerate(shapes):
+        b = (rng.permutation(4 * N)[:N] - 2 * N).astype(np.float32) if i not in (2, 5) else None
+        specs.append({"X": rng.integers(-4, 5, (M, K)).astype(np.float32), "W": rng.integers(-3, 4, (K, N)).astype(np.float32),
+                      "b": b, "act": "relu" if i % 2 else "none", "s_x": 0.125, "s_w": 0.25})
+    G = U.Groups(specs, dtype_name, n_workgroups=8)
+    cls = np.where(G.plan.order < 0, -1, G.plan.tiles["cls"][np.maximum(G.plan.order, 0) & 0xFFFFFF]).reshape(-1, 8)
+    for c in (0, 1):                                         # classes of 16 and 32 rows
+        assert any(np.all(cls[i: i + 4, w] == c) for w in range(8) for i in range(len(cls) - 3)), c
+    for rep in range(2):
+        for (M, K, N), y, yref in zip(shapes, G.run(), G.expected()):
+            assert np.array_equal(y, ref.bf16_decode(ref.bf16_encode(yref))), (dtype_name, rep, M, K, N)
+
+
 def test_long_k_tiles_visited_in_parts(dtype_name="bf16"):
     """Batches of 17 to 64 rows with K >= 8192 (bf16; fp8 tiles are not split): the launch visits each tile in two
     parts of K whose sums meet in the workspace.  Integer-valued operands make every order of addition exact, so the result must be
