@@ -376,21 +376,23 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  * 1.068 (81; the lists with a second tile get one more stream at the end), 1.5 .. 1.75 W 1.012, 1.75 .. 7 W 0.964 (249); in parts
  * of K 1.10 for W .. 1.5 W visits, 1.00 otherwise; of several K 1.012.  75 + 130 + 237 rows, K = 4096, N = 11008 gated: 156 -> 141 us, fp8 79 -> 71.  Inside a group
  * the tiles go strip by strip and row by row, so that the 32 tiles that run together on a die are eight rows of four columns.  (Column by
- * column for up to eight row tiles of a long K, 1.00 .. 1.18 times as long on launches of one group of 2 .. 12 row tiles, K = 512 .. 8192,
- * and 0.90 .. 1.19 times, 1.006 on average, on 335 mixed ones: no K and no number of row tiles from which it pays.)
+ * column: 0.97 .. 1.20 times as long on launches of one group of 2 .. 16 row tiles, K = 512 .. 8192, and, for up to eight row tiles and
+ * K >= 4096, 0.90 .. 1.19 times, 1.006 on average, on 335 mixed ones: no K and no number of row tiles from which it pays.)
  *
  * Which table.  Block tiles are taken where their estimate, plus, if there are streaming tiles, the largest load of a list in those and
- * EPARA_COST_BLOCK_BEHIND_STREAM (their kernel runs before, and what a chip full of streams would have hidden is not), is below the load
+ * EPARA_COST_BLOCK_BEHIND_STREAM (their kernel runs before, and what a chip full of streams would have hidden is not: of 327 such
+ * launches 3 lose more than 10 % by block tiles so priced, 13 with EPARA_COST_KERNEL), is below the load
  * of the most loaded workgroup under the other table, in which every visit to a whole panel tile costs EPARA_COST_PANEL_START more,
  * every part of one EPARA_COST_PANEL_PART_START and the launch EPARA_COST_PANEL_LAUNCH (start and finish, which one wave per SIMD
  * cannot overlap with anything and two workgroups per unit hide from each other).  The estimate is the larger of
  *   the most loaded of W lists, when the visits, EPARA_COST_BLOCK_PER_32 * f * K / P + EPARA_COST_BLOCK_VISIT (P > 1: +
  *     EPARA_COST_BLOCK_PART), groups by descending M, the ragged row tile of a group last, each go to the least loaded one, and of
  *   the weights' way to the chip, sum of K * N * (2 for EPARA_ACT_SWIGLU) * (2 TM + 1) / EPARA_COST_BLOCK_STREAMED over the groups: fetched
- *     once for the first of TM row tiles and two thirds of a time for each other one, at 5.3 TB/s.
- * Fitted to what either kernel takes on 500 launches of 65 .. 2500 rows, K = 384 .. 13824
- * and N = 192 .. 13824: on 2600 others the choice (and that of P) is on average 0.6 % slower than the best of all, where the rule
- * before it, of one list cost per tile, lost 9 %.
+ *     once for the first of TM row tiles and two thirds of a time for each other one, at 4.3 TB/s (80 units are a nanosecond of a list for
+ *     bf16, 160 for fp8, whose K are half the bytes, as under EPARA_COST_KERNEL; the constants of a visit are then half the time, which fits no worse).
+ * On 1196 launches drawn at random, none of them used to choose a constant, and 119 layers of language models and vision transformers
+ * (profiles/block_tile_launches.txt, every way timed) the plan takes 1.1 and 0.6 % longer than the best way on average, and more than 10 % in 56 and 3;
+ * panel tiles always 56 and 63 %, block tiles always 3.4 and 2.5 %; one list cost per tile instead of the estimate 4.6 and 4.5 %.
  *
  * Block tiles of a long K.  Few tiles of a long K (a down projection) leave units idle, so the tiles of the groups with
  * K >= the block class's split_K > 0 (EPARA_BLOCK_SPLIT_K for plain bf16 launches; 0 for gated and fp8 ones, whose results do not
@@ -430,7 +432,7 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
 #define EPARA_BLOCK_TILES_PER_SLOT 3
 #define EPARA_BLOCK_TILES_PER_COUNTER 8
 #define EPARA_COST_BLOCK_PARTIAL 500000
-#define EPARA_COST_KERNEL 400000          /* a second kernel: about 5 us */
+#define EPARA_COST_KERNEL 400000          /* a second kernel: about 5 us for bf16 */
 
 /* Splitting K.  A streaming tile of a class with BM >= 32 streams its weights while re-reading BM activation
  * rows per weight column, which is cheapest with wide tiles; wide tiles of a long K are too coarse to balance,

@@ -176,22 +176,10 @@ __device__ __forceinline__ void store4(void* Y, int out_dtype, size_t m, int n, 
     }
 }
 
-// The same with the quad's four bias values in hand.
-template <int ACT, bool WT>
-__device__ __forceinline__ void finish_plain_quad(const epara_group_args& ga, int out_dtype, const v4f& a, const v4f& b,
-                                                  int m0, int ml, int rows, int n0, int nl, int cols, bool vec_ok)
-{
-    if (ml >= rows || nl >= cols) return;
-    float v[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = act_fast<ACT>(ga.scale * a[i] + b[i]) * ga.out_inv_scale;
-    store4<WT>(ga.Y, out_dtype, static_cast<size_t>(m0 + ml), n0 + nl, ga.N, v, cols - nl, vec_ok);
-}
-
 // Epilogue of one accumulator quad (plain groups): the lane holds columns nl..nl+3 of row ml.
-// `bias` points at the bias of column n0 (global memory for streaming tiles; panel tiles stage the
-// tile's 256 bias values in LDS first, because a global load inside the store loop would make
-// every iteration wait for all earlier stores: loads and stores share one in-order counter).
+// `bias` points at the bias of column n0 (global memory for streaming tiles of fp8, of 64 rows and in parts of K, the others
+// have it in the LDS: finish_plain_quad; panel tiles stage the tile's 256 bias values in LDS first, because a global load inside the store
+// loop would make every iteration wait for all earlier stores: loads and stores share one in-order counter).
 template <int ACT, bool WT, class BiasPtr>
 __device__ __forceinline__ void finish_plain(const epara_group_args& ga, int out_dtype, const v4f& a, BiasPtr bias,
                                              int m0, int ml, int rows, int n0, int nl, int cols, bool vec_ok)
@@ -206,6 +194,18 @@ __device__ __forceinline__ void finish_plain(const epara_group_args& ga, int out
         v[i] = act_fast<ACT>(ga.scale * a[i] + b) * ga.out_inv_scale;
     }
     store4<WT>(ga.Y, out_dtype, static_cast<size_t>(m0 + ml), n0 + nl, ga.N, v, valid, vec_ok);
+}
+
+// finish_plain with the quad's four bias values in hand.
+template <int ACT, bool WT>
+__device__ __forceinline__ void finish_plain_quad(const epara_group_args& ga, int out_dtype, const v4f& a, const v4f& b,
+                                                  int m0, int ml, int rows, int n0, int nl, int cols, bool vec_ok)
+{
+    if (ml >= rows || nl >= cols) return;
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = act_fast<ACT>(ga.scale * a[i] + b[i]) * ga.out_inv_scale;
+    store4<WT>(ga.Y, out_dtype, static_cast<size_t>(m0 + ml), n0 + nl, ga.N, v, cols - nl, vec_ok);
 }
 
 // Epilogue of a gate/up fragment pair (EPARA_ACT_SWIGLU groups).

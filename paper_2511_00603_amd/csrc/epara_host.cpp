@@ -128,14 +128,13 @@ public:
         std::make_heap(heap_.begin(), heap_.end(), std::greater<std::pair<int64_t, int64_t>>());
     }
     int64_t top() const { return heap_[0].second; }
-    // `rounds` items of the same cost for every workgroup, if all are equally loaded (in index order then, which is the heap's)
-    bool level() const
+    bool level() const                                           // all carry the same load: the next n items of one cost go round in index order
     {
         for (const auto& h : heap_)
             if (h.first != heap_[0].first) return false;
         return true;
     }
-    void add_to_all(int64_t cost)
+    void add_to_all(int64_t cost)                                // of level workgroups; the heap is then in index order
     {
         for (size_t i = 0; i < heap_.size(); ++i) heap_[i] = {heap_[0].first + (i == 0 ? cost : 0), static_cast<int64_t>(i)};
     }
