@@ -25,15 +25,18 @@ def _upload(a, device):
 
 
 def _upload_all(arrays, device):
-    """numpy arrays (contiguous) -> one uint8 device tensor per array that begins with the same bytes, all with one copy: they are
-    pieces of one buffer, of whole 256 bytes each and never empty."""
-    sizes = [(max(a.nbytes, 16) + 255) // 256 * 256 for a in arrays]
+    """numpy arrays (contiguous) -> one uint8 device tensor per array holding the same bytes, all with one copy: they are
+    pieces of one buffer, each at a multiple of 256 bytes and never empty."""
+    sizes = []                                               # of a piece, of the gap behind it, of the next piece ...
+    for a in arrays:
+        n = max(a.nbytes, 16)
+        sizes += [n, -n % 256]
     raw = np.zeros(sum(sizes), dtype=np.uint8)
     at = 0
-    for a, n in zip(arrays, sizes):
+    for a, n, gap in zip(arrays, sizes[::2], sizes[1::2]):
         raw[at: at + a.nbytes] = a.view(np.uint8).reshape(-1)
-        at += n
-    return torch.from_numpy(raw).to(device).split_with_sizes(sizes)
+        at += n + gap
+    return torch.from_numpy(raw).to(device).split_with_sizes(sizes)[::2]
 
 
 def current_stream_handle():

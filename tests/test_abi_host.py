@@ -684,6 +684,23 @@ def test_plan_launch_reports_a_bad_grid_as_the_library_does():
         assert e.value.status == B.EPARA_ERR_SHAPE, kw
 
 
+@pytest.mark.parametrize("shape", [(8, 512, 512), (300, 512, 512), (1501, 11008, 4096), (0, 512, 512)])
+def test_the_device_copies_of_a_plan_have_the_size_of_its_tables(shape, monkeypatch):
+    """Pieces of one upload, but each as long as its table (16 bytes where that is empty), so that it can be viewed as records."""
+    from paper_2511_00603_amd import runtime as R
+    monkeypatch.setattr(R, "_require_gpu", lambda: None)
+    monkeypatch.setattr(R, "current_stream_handle", lambda: 0)
+    monkeypatch.setattr(R.torch.cuda, "synchronize", lambda *a: None)
+    monkeypatch.setattr(B, "epara_workspace_init", lambda *a: None)
+    args = np.zeros(1, dtype=B.GROUP_ARGS)
+    args["M"], args["K"], args["N"] = shape
+    plan = R.LaunchPlan(args, B.EPARA_BF16, "cpu", 256)
+    for d, table in ((plan.d_args, plan.args), (plan.d_tiles, plan.tiles), (plan.d_order, plan.order)):
+        assert d.numel() == max(table.nbytes, 16) and d.data_ptr() % 16 == 0
+        if len(table):
+            assert np.array_equal(d.numpy().view(table.dtype), table)
+
+
 def test_a_plan_says_which_class_table_it_was_made_with(monkeypatch):
     """LaunchPlan.narrow is the number of the table (wide, narrow, block), with which epara_kernel_classes returns it; the
     arrays stay on the host here."""
