@@ -39,6 +39,11 @@ EPARA_HIDDEN hipError_t epara_enqueue_f32(unsigned grid, hipStream_t, const epar
 EPARA_HIDDEN hipError_t epara_enqueue_block_bf16(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles);
 EPARA_HIDDEN hipError_t epara_enqueue_block_fp8(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles);
 
+// One launch of panel tiles alone, none of them in parts of K and no K above these, multiplied in halves by two workgroups per list (epara_half.h).
+#define EPARA_HALF_MAX_K 2560
+#define EPARA_HALF_MAX_K_GATED 1536
+EPARA_HIDDEN hipError_t epara_enqueue_half_bf16(int gated, unsigned n_lists, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype);
+
 // Chain kernels.  resident != NULL: no launch, *resident = workgroups of that kernel the current device holds at once.
 EPARA_HIDDEN hipError_t epara_chain_bf16_plain(const epara_chain_tables&, const epara_chain_scalars&, unsigned grid, hipStream_t, int64_t* resident);
 EPARA_HIDDEN hipError_t epara_chain_bf16_ffn(const epara_chain_tables&, const epara_chain_scalars&, unsigned grid, hipStream_t, int64_t* resident);

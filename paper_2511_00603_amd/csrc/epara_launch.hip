@@ -137,6 +137,21 @@ int32_t validate_launch(const epara_launch* L, int32_t in_dtype, int32_t out_dty
     return split_error != EPARA_OK ? split_error : tiles_error;
 }
 
+// Whether a bf16 launch of nothing but panel tiles multiplies each of them in halves by two workgroups (epara_half.h): where K is short the
+// start and the epilogue of a tile, which nothing hides when one workgroup has a unit to itself, are what the launch waits for; where it is long
+// the activations read by one workgroup more per tile cost power instead.  The same bits either way, so the line is drawn by time alone: 21 launches of
+// 256 .. 3564 tiles each, every K timed both ways, panel / half: plain K = 384 1.20 .. 1.37, 768 1.05 .. 1.31, 1024 1.07 .. 1.22, 1536
+// 1.05 .. 1.16, 2048 1.00 .. 1.12, 2560 1.00 .. 1.10, 3072 0.99 .. 1.07, 4096 0.98 .. 1.06, 5120 0.95 .. 1.04; gated K = 384 1.23 .. 1.42, 768 1.10 .. 1.24, 1024
+// 1.06 .. 1.17, 1536 1.02 .. 1.08, 2048 0.94 .. 1.06, 2560 0.94 .. 1.05, 5120 0.87 .. 1.01.  A launch with one longer K stays whole: 8 ViT services' QKV (768) next to
+// their FFN-down (3072) 129 us, in halves 134.
+bool halves(const epara_launch* L, int gated)
+{
+    if (L->n_panel_split_tiles != 0 || L->n_slots > INT32_MAX / 2) return false;
+    for (int32_t g = 0; g < L->G; ++g)
+        if (L->h_args[g].M > 0 && L->h_args[g].K > (gated ? EPARA_HALF_MAX_K_GATED : EPARA_HALF_MAX_K)) return false;
+    return true;
+}
+
 int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int narrow, hipStream_t stream)
 {
     if (L->n_tiles == 0) return EPARA_OK;
@@ -163,6 +178,10 @@ int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int 
         }
         e = (in_dtype == EPARA_BF16 ? epara_enqueue_block_bf16 : epara_enqueue_block_fp8)(gated, 2 * grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype,
                                                                                            static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, n_counters, n_tiles);
+        return e == hipSuccess ? EPARA_OK : EPARA_ERR_HIP;
+    }
+    if (in_dtype == EPARA_BF16 && panel_only && halves(L, gated)) {
+        e = epara_enqueue_half_bf16(gated, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype);
         return e == hipSuccess ? EPARA_OK : EPARA_ERR_HIP;
     }
     if (in_dtype == EPARA_F32)       e = epara_enqueue_f32(grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, L->G, static_cast<long>(L->n_tiles));

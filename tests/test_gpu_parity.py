@@ -707,3 +707,52 @@ def test_mix5_prefill_full_size_all_rows(mix5, dtype_name):
     """Every output element of the 8192-row prefill mix against the fp64 oracle (about a minute of oracle time
     per dtype on the host cores)."""
     check_mix(mix5, dtype_name)
+
+
+# ---- panel tiles in halves ---------------------------------------------------------------------
+
+@pytest.mark.parametrize("gated", [False, True])
+def test_panel_tiles_in_halves_give_the_bits_of_whole_ones(gated):
+    """bf16 launches of panel tiles multiply them in halves unless some K is above 2560 (gated 1536): the same groups alone and next to one such group give the
+    same bits, those of the fp64 oracle, as all sums are of small integers.  Row counts around the halves' fragments of 32 and around 128 and 256, so that
+    a half is missing, of one row or ragged; K of one pair of stages, of several and ragged; whole and ragged columns; with bias and without; a grid small
+    enough that a workgroup visits halves of several groups in a row."""
+    rng = np.random.default_rng(23)
+    limit = 1536 if gated else 2560
+    shapes = [(65, 8, 300), (96, 136, 256), (128, 64, 33), (129, 776, 520), (160, 256, 264), (161, 264, 512), (225, 384, 130), (256, 128, 256),
+              (257, 192, 257), (290, 320, 10), (384, 768, 384), (385, limit, 300), (512, 200, 700)]
+    keep, outs, want = [], [], []
+    def stage(M, K, N, i):
+        X = rng.integers(-2, 3, (M, K)).astype(np.float32)
+        Ws = [rng.integers(-1, 2, (K, N)).astype(np.float32) for _ in range(2 if gated else 1)]
+        b = None if gated or i % 3 == 2 else rng.integers(-8, 9, N).astype(np.float32)
+        dX = R.device_tensor_from_bits(casts.bf16_bits(X), B.EPARA_BF16, U.DEV)
+        dW = [R.pack_weights(R.device_tensor_from_bits(casts.bf16_bits(W), B.EPARA_BF16, U.DEV), B.EPARA_BF16) for W in Ws]
+        db = None if b is None else torch.from_numpy(b).to(U.DEV)
+        dY = torch.zeros((M, N), dtype=torch.bfloat16, device=U.DEV)
+        keep.extend([dX, db] + dW)
+        outs.append(dY)
+        if gated:
+            z, u = X.astype(np.float64) @ Ws[0], X.astype(np.float64) @ Ws[1]
+            want.append(z / (1 + np.exp(-z)) * u)
+            return R.group_args(dX, dW[0], dY, M, K, N, "swiglu", W2=dW[1])
+        want.append(ref.dense_forward(X.astype(np.float64), Ws[0].astype(np.float64), b, "relu"))
+        return R.group_args(dX, dW[0], dY, M, K, N, "relu", bias=db)
+    args = [stage(M, K, N, i) for i, (M, K, N) in enumerate(shapes)]
+    long = stage(70, limit + 8, 40, 0)
+    bits = []
+    for n_workgroups, groups in ((16, args), (64, args), (16, args + [long])):
+        plan = R.LaunchPlan(np.array(groups, dtype=B.GROUP_ARGS), B.EPARA_BF16, U.DEV, n_workgroups)
+        assert int(plan.classes[-1][1]) == 256 and plan.n_panel_split_tiles == 0
+        for rep in range(2):
+            for y in outs:
+                y.fill_(float("nan"))
+            R.grouped_forward(plan, B.EPARA_BF16)
+            torch.cuda.synchronize()
+        bits.append([y.view(torch.int16).clone() for y in outs[:len(shapes)]])
+    for sh, half, half64, whole, y, w in zip(shapes, *bits, outs, want):
+        assert torch.equal(half, whole) and torch.equal(half64, whole), sh
+        if gated:
+            assert_close(U.fetch(y), w, TOL["bf16"], str(sh))
+        else:
+            assert np.array_equal(U.fetch(y), ref.bf16_decode(ref.bf16_encode(w))), sh
