@@ -126,6 +126,8 @@ template <class T>
 __device__ __forceinline__ EPARA_GLOBAL T* as_global(void* p) { return (EPARA_GLOBAL T*)p; }
 
 __device__ __forceinline__ v4i ld16(gcptr p) { return *reinterpret_cast<const EPARA_GLOBAL v4i*>(p); }
+// The same for bytes that nobody reads again: they are the first to leave the die's L2.
+__device__ __forceinline__ v4i ld16_once(gcptr p) { return __builtin_nontemporal_load(reinterpret_cast<const EPARA_GLOBAL v4i*>(p)); }
 
 // Output stores.  WT ("write through"): the outputs of a chain are read by other workgroups of the
 // same kernel, possibly on another compute die with its own L2; stored as device-scope atomic

@@ -131,7 +131,7 @@ __device__ __forceinline__ void skinny_load(const skinny_tile_state<NFR>& st, in
     for (int e = 0; e < 2; ++e) {
         const int ks = min(2 * p + e, st.KS - 1);                // padding repeats the last fragment
 #pragma unroll
-        for (int f = 0; f < NFR; ++f) sl.w[e][f] = ld16(st.w[f] + static_cast<size_t>(ks) * 1024 + lane16);
+        for (int f = 0; f < NFR; ++f) sl.w[e][f] = ld16_once(st.w[f] + static_cast<size_t>(ks) * 1024 + lane16);
     }
 }
 
