@@ -9,7 +9,9 @@
 // once for the maximum, once for the codes) and every destination byte written once.  A
 // workgroup of 256 threads moves 16-KiB chunks with 16-byte accesses per lane (a wave
 // instruction covers 1 KiB of consecutive memory); chunk c belongs to the last segment whose
-// first_chunk is <= c (find_segment; the value is the same for all lanes).
+// first_chunk is <= c (find_segment; the value is the same for all lanes).  What a kernel does not read again is moved with the
+// non-temporal hint (copied bytes both ways, codes): 8192 x 5120 bf16 quantised and sent back 78.9 -> 71.2 us, 74.5 with the copies alone.
+// Not what is read for the maxima, which the codes are made from next (85.1 us), nor the source of the codes (82.9).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -59,12 +61,12 @@ __global__ __launch_bounds__(NT) void copy_segments_kernel(const epara_segment* 
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int64_t off = (i * NT + threadIdx.x) * 16;
-            if (off < left) v[i] = *reinterpret_cast<const EPARA_GLOBAL v4i*>(src + off);
+            if (off < left) v[i] = __builtin_nontemporal_load(reinterpret_cast<const EPARA_GLOBAL v4i*>(src + off));
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int64_t off = (i * NT + threadIdx.x) * 16;
-            if (off < left) *reinterpret_cast<EPARA_GLOBAL v4i*>(dst + off) = v[i];
+            if (off < left) __builtin_nontemporal_store(v[i], reinterpret_cast<EPARA_GLOBAL v4i*>(dst + off));
         }
     }
 }
@@ -189,7 +191,9 @@ __global__ __launch_bounds__(NT) void quantize_segments_kernel(const epara_segme
                 code[j] = epara_cast::f32x4_to_e4m3(f[0], f[1], f[2], f[3]);
             }
             EPARA_GLOBAL char* out = dst + off / ESZ;
-            if (off + 16 * PIECE <= left) *reinterpret_cast<EPARA_GLOBAL v4i*>(out) = v4i{static_cast<int>(code[0]), static_cast<int>(code[1]), static_cast<int>(code[2]), static_cast<int>(code[3])};
+            if (off + 16 * PIECE <= left)
+                __builtin_nontemporal_store(v4i{static_cast<int>(code[0]), static_cast<int>(code[1]), static_cast<int>(code[2]), static_cast<int>(code[3])},
+                                            reinterpret_cast<EPARA_GLOBAL v4i*>(out));
             else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)                    // the end of a run that is no multiple of 16 codes
