@@ -13,6 +13,11 @@
 // Two workgroups share a unit (64 KiB of LDS, at most 256 registers each), so nothing is pipelined across tiles:
 // while one workgroup waits for its first operands or stores, the other one multiplies.  Sums run over K in the
 // same order and with the same instructions as in a panel tile: the results agree bit for bit.
+//
+// Weights of a group of a single row tile are read by one workgroup once, with the non-temporal hint, so that they don't push the
+// activations out of the die's L2: three SwiGLU services of 75 rows, 4096 -> 11008, 120.6 -> 112.0 us, of 120 rows 134.4 -> 128.6,
+// four of 96 rows, 11008 -> 4096, 77.3 -> 69.8.  Where several row tiles share them the hint costs (75 + 130 + 237 rows, a pass
+// 236 -> 262 us), and so it does on activations (291).
 #ifndef EPARA_BLOCK_TILE_H
 #define EPARA_BLOCK_TILE_H
 
@@ -39,7 +44,8 @@ __device__ __forceinline__ char* block_partials(const split_ctx& sp, int tile)
 // workspace, lane by lane as they sit in the registers, written through to memory, and counts itself at the tile; whoever
 // counts last adds the parts in index order (its own too: the order does not depend on who it is), runs the epilogue and
 // puts the counter back to zero.  Nobody waits for another workgroup.
-template <int DT, bool GATED, int FM>
+// ONCE: no other tile reads the weights (a group of a single row tile).
+template <int DT, bool GATED, int FM, bool ONCE = false>
 __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epara_tile& tl, int entry, int out_dtype, char* lds, const split_ctx& sp)
 {
     constexpr int ESZ = DT == EPARA_BF16 ? 2 : 1;
@@ -91,6 +97,7 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
     gcptr wp = as_global<char>((GATED && r32 >= 16) ? ga.W2 : ga.W) + static_cast<size_t>(nb) * KSP * 1024 +
                static_cast<size_t>(first_pair) * 2048 + (h * 16 + (r32 & 15)) * 16;
 
+    auto w_load = [&](int i) -> v4i { return ONCE ? ld16_once(wp + i * 512) : ld16(wp + i * 512); };
     v4i w[BLOCK_RING][4];                                        // [pair % 4][2 stage + half of its K]
     auto x_issue = [&](int p, int slot, int j) {
         const int left = K_left - p * 2 * KF;                    // elements of K from this pair on
@@ -108,7 +115,7 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
 #pragma unroll
         for (int j = 0; j < NX; ++j) x_issue(p, slot, j);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) w[slot][i] = ld16(wp + i * 512);
+        for (int i = 0; i < 4; ++i) w[slot][i] = w_load(i);
         wp += 2048;
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -175,7 +182,7 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
             if constexpr (MODE == 0) {
                 if (fm == FM - 1) {
 #pragma unroll
-                    for (int e = 0; e < IPS; ++e) w[slot][S * IPS + e] = ld16(wp + (S * IPS + e) * 512);
+                    for (int e = 0; e < IPS; ++e) w[slot][S * IPS + e] = w_load(S * IPS + e);
                     if (LAST) wp += 2048;
                 }
             }
@@ -387,7 +394,11 @@ __global__ __launch_bounds__(NT, 2) void grouped_block_kernel(const epara_group_
         if (tl.cls < N_STREAM_CLASSES) continue;                 // the streaming tiles of the launch have a kernel of their own
         const epara_group_args ga = args[tl.group];
         const int fm = (tl.rows + 31) >> 5;
-        if (fm > 3)       block_tile<DT, GATED, 4>(ga, tl, t, out_dtype, lds, sp);
+        if (ga.M <= EPARA_BLOCK_ROWS) {                          // and more than 64
+            if (fm > 3)   block_tile<DT, GATED, 4, true>(ga, tl, t, out_dtype, lds, sp);
+            else          block_tile<DT, GATED, 3, true>(ga, tl, t, out_dtype, lds, sp);
+        }
+        else if (fm > 3)  block_tile<DT, GATED, 4>(ga, tl, t, out_dtype, lds, sp);
         else if (fm == 3) block_tile<DT, GATED, 3>(ga, tl, t, out_dtype, lds, sp);
         else if (fm == 2) block_tile<DT, GATED, 2>(ga, tl, t, out_dtype, lds, sp);
         else              block_tile<DT, GATED, 1>(ga, tl, t, out_dtype, lds, sp);
