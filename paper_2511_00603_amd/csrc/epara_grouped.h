@@ -11,6 +11,7 @@
 #include "epara_device.h"
 #include "epara_internal.h"
 #include "epara_panel.h"
+#include "epara_block_tile.h"
 #include "epara_stream.h"
 
 namespace {
@@ -66,6 +67,56 @@ __device__ __forceinline__ void split_flush(const epara_group_args* __restrict__
     pend.count = 0;
 }
 
+// The last round of a launch of panel tiles alone, where few of the lists have one: its tiles, those at slot tail_slot or later, are cut into
+// four block tiles (epara_block_tile.h: the same bits) that go to workgroups of their own, the four of a tile to units of one die, the
+// tiles to the dies in turn.  A unit with a quarter of a panel tile to itself takes a third of the tile's time, for which it waits on the
+// L2.  Every slot from tail_slot on is looked at (a ballot per 64 slots, kept in the LDS above a block tile's), so that no order loses a tile.
+template <int DT, bool GATED>
+__device__ __forceinline__ void panel_tail(const epara_group_args* __restrict__ args, const epara_tile* __restrict__ tiles,
+                                           const int32_t* __restrict__ order, long tail_slot, long n_slots, int out_dtype, char* lds)
+{
+    static_assert(BLOCK_LDS_BYTES + EPARA_TAIL_MAX_SLOTS / 8 <= LDS_BYTES, "the ballots do not fit");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = static_cast<int>(n_slots - tail_slot), ballots = (n + 63) >> 6;
+    typedef __attribute__((address_space(3))) unsigned long long* lds_u64;
+    const lds_u64 found = (lds_u64)((ldsptr)lds + BLOCK_LDS_BYTES);
+    __syncthreads();                                             // the operands and sums of the list have been read
+    for (int c = wave; c < ballots; c += NT / 64) {
+        const int t = c * 64 + lane < n ? order[tail_slot + c * 64 + lane] : -1;
+        const unsigned long long mask = __ballot(t >= 0 && order_parts(t) == 1);
+        if (lane == 0) found[c] = mask;
+    }
+    __syncthreads();
+    constexpr int BN = GATED ? 64 : 128;
+    const int die = blockIdx.x % EPARA_TAIL_DIES, per_die = gridDim.x / EPARA_TAIL_DIES;
+    for (int m = blockIdx.x / EPARA_TAIL_DIES; ; m += per_die) {
+        int left = EPARA_TAIL_DIES * (m >> 2) + die, at = -1;    // which of the tiles that were found
+        for (int c = 0; c < ballots; ++c) {
+            const unsigned long long v = found[c];
+            unsigned long long mask = (static_cast<unsigned long long>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32)))) << 32) |
+                                      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
+            const int here = __builtin_popcountll(mask);
+            if (left < here) {
+                for (; left > 0; --left) mask &= mask - 1;
+                at = c * 64 + __builtin_ctzll(mask);
+                break;
+            }
+            left -= here;
+        }
+        if (at < 0) break;
+        epara_tile tl = tiles[order_tile(order[tail_slot + at])];
+        const int m_half = (m & 1) * EPARA_BLOCK_ROWS, n_half = (m >> 1 & 1) * BN;
+        tl.m0 += m_half;
+        tl.n0 += n_half;
+        tl.rows = min(tl.rows - m_half, EPARA_BLOCK_ROWS);
+        tl.cols = min(tl.cols - n_half, BN);
+        if (tl.rows <= 0 || tl.cols <= 0) continue;
+        const epara_group_args ga = args[tl.group];
+        const split_ctx whole = {nullptr, 0, 0, 0};
+        block_tile<DT, GATED, 4>(ga, tl, 0, out_dtype, lds, whole);      // rows past the tile repeat its last one and are not stored
+    }
+}
+
 template <int DT, bool GATED, bool CHAIN, bool PANEL_ONLY>
 __device__ __forceinline__ void grouped_body(const epara_group_args* __restrict__ args, const epara_tile* __restrict__ tiles,
                                              const int32_t* __restrict__ order, long n_slots, int out_dtype, int narrow, char* lds,
@@ -104,32 +155,37 @@ __device__ __forceinline__ void grouped_body(const epara_group_args* __restrict_
     if constexpr (HAS_SPLIT) split_flush<DT, GATED, PANEL_ONLY>(args, tiles, out_dtype, narrow, lds, sp, pend);
 }
 
-template <int DT, bool GATED, bool PANEL_ONLY>
+// TAIL: the lists are visited up to slot tail_slot, what comes after it as panel_tail says.
+template <int DT, bool GATED, bool PANEL_ONLY, bool TAIL>
 __global__ __launch_bounds__(NT) void grouped_kernel(const epara_group_args* __restrict__ args,
                                                      const epara_tile* __restrict__ tiles,
                                                      const int32_t* __restrict__ order,
-                                                     long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split)
+                                                     long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const split_ctx sp = {split_ws, n_split, n_panel_split, first_panel_split};
-    grouped_body<DT, GATED, false, PANEL_ONLY>(args, tiles, order, n_slots, out_dtype, narrow, lds, nullptr, &sp);
+    grouped_body<DT, GATED, false, PANEL_ONLY>(args, tiles, order, TAIL ? tail_slot : n_slots, out_dtype, narrow, lds, nullptr, &sp);
+    if constexpr (TAIL) panel_tail<DT, GATED>(args, tiles, order, tail_slot, n_slots, out_dtype, lds);
+}
+
+template <int DT, bool GATED, bool PANEL_ONLY, bool TAIL>
+hipError_t enqueue_grouped_as(unsigned grid, hipStream_t stream, const epara_group_args* args, const epara_tile* tiles,
+                              const int32_t* order, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot)
+{
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_kernel<DT, GATED, PANEL_ONLY, TAIL>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL((grouped_kernel<DT, GATED, PANEL_ONLY, TAIL>), dim3(grid), dim3(NT), LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split, tail_slot);
+    return hipGetLastError();
 }
 
 template <int DT, bool GATED>
 hipError_t enqueue_grouped(int panel_only, unsigned grid, hipStream_t stream, const epara_group_args* args, const epara_tile* tiles,
-                           const int32_t* order, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split)
+                           const int32_t* order, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot)
 {
-    static const hipError_t attr0 = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_kernel<DT, GATED, false>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-    static const hipError_t attr1 = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_kernel<DT, GATED, true>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-    if (attr0 != hipSuccess) return attr0;
-    if (attr1 != hipSuccess) return attr1;
-    if (panel_only)
-        hipLaunchKernelGGL((grouped_kernel<DT, GATED, true>), dim3(grid), dim3(NT), LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split);
-    else
-        hipLaunchKernelGGL((grouped_kernel<DT, GATED, false>), dim3(grid), dim3(NT), LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split);
-    return hipGetLastError();
+    auto as = panel_only ? &enqueue_grouped_as<DT, GATED, true, false> : &enqueue_grouped_as<DT, GATED, false, false>;
+    if constexpr (GATED || DT != EPARA_BF16) { if (panel_only && tail_slot >= 0) as = &enqueue_grouped_as<DT, GATED, true, true>; }
+    return as(grid, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split, tail_slot);
 }
 
 // ---- a chain of launches as one kernel: the phases one after the other in every workgroup

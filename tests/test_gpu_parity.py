@@ -756,3 +756,56 @@ def test_panel_tiles_in_halves_give_the_bits_of_whole_ones(gated):
             assert_close(U.fetch(y), w, TOL["bf16"], str(sh))
         else:
             assert np.array_equal(U.fetch(y), ref.bf16_decode(ref.bf16_encode(w))), sh
+
+
+# ---- the last round of panel tiles in quarters --------------------------------------------------
+
+@pytest.mark.parametrize("dtype_name,gated", [("bf16", True), ("fp8", True), ("fp8", False)])
+def test_panel_tiles_of_a_last_round_in_quarters_give_the_bits_of_whole_ones(dtype_name, gated):
+    """Launches of panel tiles of one K with a few tiles more than whole rounds multiply those in quarters; the same groups next to one of another K do
+    not.  All sums are of small integers: the same bits, the oracle's.  The last tiles have a single row or column, one quarter, ragged ones or four
+    whole ones; one and two whole rounds, one tile left to three eighths of a round; K of one pair of stages, ragged, and beyond what is multiplied in halves."""
+    rng = np.random.default_rng(29)
+    W_, dt, u = 16, B.DTYPE_BY_NAME[dtype_name], 128 if gated else 256
+    launches = [[(257, 1552, 8 * u + 5)], [(600, 1552, 5 * u + u // 2 + 3), (130, 1552, 2 * u)], [(400, 2048, 8 * u), (100, 2048, 3 * u + 1)],
+                [(256, 1600, 16 * u + 17)], [(512, 1600, 18 * u + u // 2 + 1)], [(70, 1552, 22 * u)]]
+    if dtype_name == "fp8":
+        launches.append([(257, 16, 8 * u + 5)])
+    for shapes in launches:
+        tiles = sum(-(-M // 256) * -(-N // u) for M, K, N in shapes)
+        assert tiles > W_ and 0 < tiles % W_ <= 3 * W_ // 8
+        keep, outs, want = [], [], []
+        def stage(M, K, N):
+            X = rng.integers(-2, 3, (M, K)).astype(np.float32)
+            Ws = [rng.integers(-1, 2, (K, N)).astype(np.float32) for _ in range(2 if gated else 1)]
+            b = None if gated else rng.integers(-8, 9, N).astype(np.float32)
+            dX = R.device_tensor_from_bits(U.to_bits(X, dtype_name), dt, U.DEV)
+            dW = [R.pack_weights(R.device_tensor_from_bits(U.to_bits(w, dtype_name), dt, U.DEV), dt) for w in Ws]
+            db = None if b is None else torch.from_numpy(b).to(U.DEV)
+            dY = torch.zeros((M, N), dtype=torch.bfloat16, device=U.DEV)
+            keep.extend([dX, db] + dW)
+            outs.append(dY)
+            if gated:
+                z, up = X.astype(np.float64) @ Ws[0], X.astype(np.float64) @ Ws[1]
+                want.append(z / (1 + np.exp(-z)) * up)
+                return R.group_args(dX, dW[0], dY, M, K, N, "swiglu", W2=dW[1])
+            want.append(ref.dense_forward(X.astype(np.float64), Ws[0].astype(np.float64), b, "relu"))
+            return R.group_args(dX, dW[0], dY, M, K, N, "relu", bias=db)
+        args = [stage(*sh) for sh in shapes]
+        other = stage(65, shapes[0][1] + 64, 40)
+        bits = []
+        for groups in (args, args + [other]):
+            plan = R.LaunchPlan(np.array(groups, dtype=B.GROUP_ARGS), dt, U.DEV, W_)
+            assert int(plan.classes[-1][1]) == 256 and plan.n_panel_split_tiles == 0
+            for rep in range(2):
+                for y in outs:
+                    y.fill_(float("nan"))
+                R.grouped_forward(plan, B.EPARA_BF16)
+                torch.cuda.synchronize()
+            bits.append([y.view(torch.int16).clone() for y in outs[:len(shapes)]])
+        for sh, quarters, whole, y, w in zip(shapes, *bits, outs, want):
+            assert torch.equal(quarters, whole), sh
+            if gated:
+                assert_close(U.fetch(y), w, TOL[dtype_name], str(sh))
+            else:
+                assert np.array_equal(U.fetch(y), ref.bf16_decode(ref.bf16_encode(w))), sh
