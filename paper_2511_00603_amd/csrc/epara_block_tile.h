@@ -14,8 +14,8 @@
 // while one workgroup waits for its first operands or stores, the other one multiplies.  Sums run over K in the
 // same order and with the same instructions as in a panel tile: the results agree bit for bit.
 //
-// Weights of a group of a single row tile are read by one workgroup once, with the non-temporal hint, so that they don't push the
-// activations out of the die's L2: three SwiGLU services of 75 rows, 4096 -> 11008, 120.6 -> 112.0 us, of 120 rows 134.4 -> 128.6,
+// Weights of a group of a single row tile are read by one workgroup once.  In launches too large for the last-level cache (`once`) that is done with
+// the non-temporal hint: three SwiGLU services of 75 rows, 4096 -> 11008, 120.6 -> 112.0 us, of 120 rows 134.4 -> 128.6,
 // four of 96 rows, 11008 -> 4096, 77.3 -> 69.8.  Where several row tiles share them the hint costs (75 + 130 + 237 rows, a pass
 // 236 -> 262 us), and so it does on activations (291).
 #ifndef EPARA_BLOCK_TILE_H
@@ -383,7 +383,7 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
 template <int DT, bool GATED>
 __global__ __launch_bounds__(NT, 2) void grouped_block_kernel(const epara_group_args* __restrict__ args, const epara_tile* __restrict__ tiles,
                                                               const int32_t* __restrict__ order, long n_slots, int out_dtype,
-                                                              uint32_t* split_ws, int n_split, int n_counters, int n_tiles)
+                                                              uint32_t* split_ws, int n_split, int n_counters, int n_tiles, int once)
 {
     const split_ctx sp = {split_ws, n_split, n_counters, n_tiles};
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(NT, 2) void grouped_block_kernel(const epara_group_
         if (tl.cls < N_STREAM_CLASSES) continue;                 // the streaming tiles of the launch have a kernel of their own
         const epara_group_args ga = args[tl.group];
         const int fm = (tl.rows + 31) >> 5;
-        if (ga.M <= EPARA_BLOCK_ROWS) {                          // and more than 64
+        if (once && ga.M <= EPARA_BLOCK_ROWS) {                  // and more than 64
             if (fm > 3)   block_tile<DT, GATED, 4, true>(ga, tl, t, out_dtype, lds, sp);
             else          block_tile<DT, GATED, 3, true>(ga, tl, t, out_dtype, lds, sp);
         }
@@ -407,12 +407,12 @@ __global__ __launch_bounds__(NT, 2) void grouped_block_kernel(const epara_group_
 
 template <int DT, bool GATED>
 hipError_t enqueue_block(unsigned grid, hipStream_t stream, const epara_group_args* args, const epara_tile* tiles,
-                         const int32_t* order, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles)
+                         const int32_t* order, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles, int once)
 {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_block_kernel<DT, GATED>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, BLOCK_LDS_BYTES);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((grouped_block_kernel<DT, GATED>), dim3(grid), dim3(NT), BLOCK_LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, split_ws, n_split, n_counters, n_tiles);
+    hipLaunchKernelGGL((grouped_block_kernel<DT, GATED>), dim3(grid), dim3(NT), BLOCK_LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, split_ws, n_split, n_counters, n_tiles, once);
     return hipGetLastError();
 }
 

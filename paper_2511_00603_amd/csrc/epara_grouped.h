@@ -117,7 +117,7 @@ __device__ __forceinline__ void panel_tail(const epara_group_args* __restrict__ 
     }
 }
 
-template <int DT, bool GATED, bool CHAIN, bool PANEL_ONLY>
+template <int DT, bool GATED, bool CHAIN, bool PANEL_ONLY, bool ONCE = false>
 __device__ __forceinline__ void grouped_body(const epara_group_args* __restrict__ args, const epara_tile* __restrict__ tiles,
                                              const int32_t* __restrict__ order, long n_slots, int out_dtype, int narrow, char* lds,
                                              chain_ctx* chain = nullptr, const split_ctx* sp = nullptr)
@@ -144,10 +144,10 @@ __device__ __forceinline__ void grouped_body(const epara_group_args* __restrict_
         if constexpr (HAS_SPLIT) { if (pend.count >= 63) split_flush<DT, GATED, PANEL_ONLY>(args, tiles, out_dtype, narrow, lds, sp, pend); }
         if constexpr (!PANEL_ONLY) {
             const epara_group_args ga0 = nx.ga;
-            if (tl.cls == 0)      { s = skinny_run<DT, GATED, CHAIN, 0, 1, 2, 4>(args, tiles, order, s, t, tl, ga0, known, n_slots, stride, out_dtype, lds, chain, sp, &pend, nx); continue; }
-            else if (tl.cls == 1) { s = skinny_run<DT, GATED, CHAIN, 1, 2, 4, 3>(args, tiles, order, s, t, tl, ga0, known, n_slots, stride, out_dtype, lds, chain, sp, &pend, nx); continue; }
-            else if (tl.cls == 2 && !narrow) { s = skinny_run<DT, GATED, CHAIN, 2, 4, 8, 2>(args, tiles, order, s, t, tl, ga0, known, n_slots, stride, out_dtype, lds, chain, sp, &pend, nx); continue; }
-            else if (tl.cls == 2) { s = skinny_run<DT, GATED, CHAIN, 2, 4, 4, 3>(args, tiles, order, s, t, tl, ga0, known, n_slots, stride, out_dtype, lds, chain, sp, &pend, nx); continue; }
+            if (tl.cls == 0)      { s = skinny_run<DT, GATED, CHAIN, ONCE, 0, 1, 2, 4>(args, tiles, order, s, t, tl, ga0, known, n_slots, stride, out_dtype, lds, chain, sp, &pend, nx); continue; }
+            else if (tl.cls == 1) { s = skinny_run<DT, GATED, CHAIN, ONCE, 1, 2, 4, 3>(args, tiles, order, s, t, tl, ga0, known, n_slots, stride, out_dtype, lds, chain, sp, &pend, nx); continue; }
+            else if (tl.cls == 2 && !narrow) { s = skinny_run<DT, GATED, CHAIN, ONCE, 2, 4, 8, 2>(args, tiles, order, s, t, tl, ga0, known, n_slots, stride, out_dtype, lds, chain, sp, &pend, nx); continue; }
+            else if (tl.cls == 2) { s = skinny_run<DT, GATED, CHAIN, ONCE, 2, 4, 4, 3>(args, tiles, order, s, t, tl, ga0, known, n_slots, stride, out_dtype, lds, chain, sp, &pend, nx); continue; }
         }
         s = panel_run<DT, GATED, CHAIN, CHAIN>(args, tiles, order, s, n_slots, stride, out_dtype, lds, chain, sp, &pend);
         nx = run_next{};                                         // nothing is carried across a panel run
@@ -155,8 +155,8 @@ __device__ __forceinline__ void grouped_body(const epara_group_args* __restrict_
     if constexpr (HAS_SPLIT) split_flush<DT, GATED, PANEL_ONLY>(args, tiles, out_dtype, narrow, lds, sp, pend);
 }
 
-// TAIL: the lists are visited up to slot tail_slot, what comes after it as panel_tail says.
-template <int DT, bool GATED, bool PANEL_ONLY, bool TAIL>
+// TAIL: the lists are visited up to slot tail_slot, what comes after it as panel_tail says.  ONCE: see epara_stream.h.
+template <int DT, bool GATED, bool PANEL_ONLY, bool TAIL, bool ONCE>
 __global__ __launch_bounds__(NT) void grouped_kernel(const epara_group_args* __restrict__ args,
                                                      const epara_tile* __restrict__ tiles,
                                                      const int32_t* __restrict__ order,
@@ -164,27 +164,28 @@ __global__ __launch_bounds__(NT) void grouped_kernel(const epara_group_args* __r
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const split_ctx sp = {split_ws, n_split, n_panel_split, first_panel_split};
-    grouped_body<DT, GATED, false, PANEL_ONLY>(args, tiles, order, TAIL ? tail_slot : n_slots, out_dtype, narrow, lds, nullptr, &sp);
+    grouped_body<DT, GATED, false, PANEL_ONLY, ONCE>(args, tiles, order, TAIL ? tail_slot : n_slots, out_dtype, narrow, lds, nullptr, &sp);
     if constexpr (TAIL) panel_tail<DT, GATED>(args, tiles, order, tail_slot, n_slots, out_dtype, lds);
 }
 
-template <int DT, bool GATED, bool PANEL_ONLY, bool TAIL>
+template <int DT, bool GATED, bool PANEL_ONLY, bool TAIL, bool ONCE>
 hipError_t enqueue_grouped_as(unsigned grid, hipStream_t stream, const epara_group_args* args, const epara_tile* tiles,
                               const int32_t* order, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot)
 {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_kernel<DT, GATED, PANEL_ONLY, TAIL>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_kernel<DT, GATED, PANEL_ONLY, TAIL, ONCE>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((grouped_kernel<DT, GATED, PANEL_ONLY, TAIL>), dim3(grid), dim3(NT), LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split, tail_slot);
+    hipLaunchKernelGGL((grouped_kernel<DT, GATED, PANEL_ONLY, TAIL, ONCE>), dim3(grid), dim3(NT), LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split, tail_slot);
     return hipGetLastError();
 }
 
 template <int DT, bool GATED>
 hipError_t enqueue_grouped(int panel_only, unsigned grid, hipStream_t stream, const epara_group_args* args, const epara_tile* tiles,
-                           const int32_t* order, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot)
+                           const int32_t* order, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot, int once)
 {
-    auto as = panel_only ? &enqueue_grouped_as<DT, GATED, true, false> : &enqueue_grouped_as<DT, GATED, false, false>;
-    if constexpr (GATED || DT != EPARA_BF16) { if (panel_only && tail_slot >= 0) as = &enqueue_grouped_as<DT, GATED, true, true>; }
+    auto as = panel_only ? &enqueue_grouped_as<DT, GATED, true, false, false>
+            : once ? &enqueue_grouped_as<DT, GATED, false, false, true> : &enqueue_grouped_as<DT, GATED, false, false, false>;
+    if constexpr (GATED || DT != EPARA_BF16) { if (panel_only && tail_slot >= 0) as = &enqueue_grouped_as<DT, GATED, true, true, false>; }
     return as(grid, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split, tail_slot);
 }
 

@@ -29,19 +29,19 @@ struct epara_chain_tables {
 
 // One grouped launch; dtype = EPARA_BF16 / EPARA_FP8_E4M3; panel_only: the tile table holds no streaming tile.  tail_slot >= 0
 // (panel_only): the tiles at that slot or later are cut into quarters (panel_tail in epara_grouped.h); at most EPARA_TAIL_MAX_SLOTS
-// slots, and a grid of whole EPARA_TAIL_DIES.
+// slots, and a grid of whole EPARA_TAIL_DIES.  once: weights that a single tile reads are read with the non-temporal hint.
 #define EPARA_TAIL_MAX_SLOTS 65536
 #define EPARA_TAIL_DIES 8
-EPARA_HIDDEN hipError_t epara_enqueue_bf16_plain(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot);
-EPARA_HIDDEN hipError_t epara_enqueue_bf16_gated(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot);
-EPARA_HIDDEN hipError_t epara_enqueue_fp8_plain(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot);
-EPARA_HIDDEN hipError_t epara_enqueue_fp8_gated(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot);
+EPARA_HIDDEN hipError_t epara_enqueue_bf16_plain(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot, int once);
+EPARA_HIDDEN hipError_t epara_enqueue_bf16_gated(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot, int once);
+EPARA_HIDDEN hipError_t epara_enqueue_fp8_plain(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot, int once);
+EPARA_HIDDEN hipError_t epara_enqueue_fp8_gated(int panel_only, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot, int once);
 EPARA_HIDDEN hipError_t epara_enqueue_f32(unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int G, long n_tiles);
 
 // One grouped launch of block tiles (the block table of epara_kernel_classes).  n_counters: of the split ones, behind the n_split
 // of the streaming tiles; n_tiles: how many of them the workspace holds.
-EPARA_HIDDEN hipError_t epara_enqueue_block_bf16(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles);
-EPARA_HIDDEN hipError_t epara_enqueue_block_fp8(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles);
+EPARA_HIDDEN hipError_t epara_enqueue_block_bf16(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles, int once);
+EPARA_HIDDEN hipError_t epara_enqueue_block_fp8(int gated, unsigned grid, hipStream_t, const epara_group_args*, const epara_tile*, const int32_t*, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles, int once);
 
 // One launch of panel tiles alone, none of them in parts of K and no K above these, multiplied in halves by two workgroups per list (epara_half.h).
 #define EPARA_HALF_MAX_K 2560

@@ -171,6 +171,18 @@ long panel_tail_slot(const epara_launch* L)
     return static_cast<long>(rounds * W);
 }
 
+// Whether the weights of a launch are taken for bytes that no cache keeps until the next pass (the non-temporal hint, epara_stream.h): the
+// last-level cache holds 256 MB, and a gate/up launch has two thirds of the weights of its pass, a down launch a third, a single up
+// launch half.  Passes over the same weights again and again, plain / with the hint: bf16 270 MB 66.6 / 72.9 us, fp8 220 MB 77.2 / 91.7, 66 MB
+// 29.3 / 39.1, 131 MB of small models 55.7 / 60.1; bf16 424 MB 90.8 / 82.4, 541 MB 111.2 / 102.2, 850 MB 167.5 / 152.4.
+int weights_once(const epara_launch* L, int32_t in_dtype, int gated)
+{
+    double bytes = 0;
+    for (int32_t g = 0; g < L->G; ++g)
+        if (L->h_args[g].M > 0) bytes += static_cast<double>(L->h_args[g].K) * L->h_args[g].N * (gated ? 2 : 1) * (in_dtype == EPARA_BF16 ? 2 : 1);
+    return bytes > (gated ? 192e6 : 112e6);
+}
+
 int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int narrow, hipStream_t stream)
 {
     if (L->n_tiles == 0) return EPARA_OK;
@@ -182,6 +194,7 @@ int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int 
     const int panel_only = n_stream == 0;     // launches without streaming tiles run a kernel without that code
     const unsigned grid = static_cast<unsigned>(L->n_workgroups);
     const long n_slots = static_cast<long>(L->n_slots);
+    const int once = weights_once(L, in_dtype, gated);
     (void)hipGetLastError();
     hipError_t e;
     if (narrow == EPARA_TABLE_BLOCK) {
@@ -192,11 +205,11 @@ int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int 
             e = (in_dtype == EPARA_BF16 ? (gated ? epara_enqueue_bf16_gated : epara_enqueue_bf16_plain)
                                         : (gated ? epara_enqueue_fp8_gated : epara_enqueue_fp8_plain))(
                 0, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype, EPARA_STREAM_TILES_ONLY, static_cast<uint32_t*>(L->d_workspace),
-                L->n_split_tiles, n_counters, 0, -1);
+                L->n_split_tiles, n_counters, 0, -1, once);
             if (e != hipSuccess) return EPARA_ERR_HIP;
         }
         e = (in_dtype == EPARA_BF16 ? epara_enqueue_block_bf16 : epara_enqueue_block_fp8)(gated, 2 * grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype,
-                                                                                           static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, n_counters, n_tiles);
+                                                                                           static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, n_counters, n_tiles, once);
         return e == hipSuccess ? EPARA_OK : EPARA_ERR_HIP;
     }
     if (in_dtype == EPARA_BF16 && panel_only && halves(L, gated)) {
@@ -205,8 +218,8 @@ int32_t enqueue(const epara_launch* L, int32_t in_dtype, int32_t out_dtype, int 
     }
     const long tail = panel_only && (in_dtype == EPARA_FP8_E4M3 || (in_dtype == EPARA_BF16 && gated)) ? panel_tail_slot(L) : -1;
     if (in_dtype == EPARA_F32)       e = epara_enqueue_f32(grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, L->G, static_cast<long>(L->n_tiles));
-    else if (in_dtype == EPARA_BF16) e = (gated ? epara_enqueue_bf16_gated : epara_enqueue_bf16_plain)(panel_only, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype, narrow, static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, L->n_panel_split_tiles, static_cast<int>(L->n_tiles - L->n_panel_split_tiles), tail);
-    else                             e = (gated ? epara_enqueue_fp8_gated : epara_enqueue_fp8_plain)(panel_only, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype, narrow, static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, L->n_panel_split_tiles, static_cast<int>(L->n_tiles - L->n_panel_split_tiles), tail);
+    else if (in_dtype == EPARA_BF16) e = (gated ? epara_enqueue_bf16_gated : epara_enqueue_bf16_plain)(panel_only, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype, narrow, static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, L->n_panel_split_tiles, static_cast<int>(L->n_tiles - L->n_panel_split_tiles), tail, once);
+    else                             e = (gated ? epara_enqueue_fp8_gated : epara_enqueue_fp8_plain)(panel_only, grid, stream, L->d_args, L->d_tiles, L->d_order, n_slots, out_dtype, narrow, static_cast<uint32_t*>(L->d_workspace), L->n_split_tiles, L->n_panel_split_tiles, static_cast<int>(L->n_tiles - L->n_panel_split_tiles), tail, once);
     return e == hipSuccess ? EPARA_OK : EPARA_ERR_HIP;
 }
 

@@ -28,8 +28,8 @@ namespace {
 // are not multiplied / not stored.  The scheduling barriers keep the compiler from sinking the
 // prefetch loads down to their first use.
 //
-// Weights are read with the non-temporal hint: nobody reads them again, while the activations, which every tile of the
-// service reads, stay in the dies' L2.  Four services of 11008 -> 4096, all at once: 3 rows each 64.5 -> 56.9 us (6.3 TB/s), 32 rows
+// Weights that no cache would keep until the next pass anyway (ONCE, chosen on the host by the size of the launch) are read with the
+// non-temporal hint: they don't go through the last-level cache and leave the dies' L2 to the activations, which every tile of the service reads.  Four services of 11008 -> 4096, all at once: 3 rows each 64.5 -> 56.9 us (6.3 TB/s), 32 rows
 // 73.8 -> 69.9, 64 rows in tiles of 128 columns 86.5 -> 73.4, of 64 columns 88.7 -> 86.9 (there a unit's own rate binds, 22 GB/s).  The
 // hint on the activations instead: 67.6, 89.3, 96.2, 116.8.
 template <int NFR>
@@ -91,7 +91,7 @@ __device__ __forceinline__ void skinny_setup(skinny_tile_state<NFR>& st, const e
 template <int NFR>
 struct skinny_slot { v4i w[2][NFR]; };
 
-template <int DT, int MB, int NFR>
+template <int DT, int MB, int NFR, bool ONCE>
 __device__ __forceinline__ void skinny_load(const skinny_tile_state<NFR>& st, int i, int wave, int lane, skinny_slot<NFR>& sl,
                                             char* xslot_generic)
 {
@@ -136,7 +136,10 @@ __device__ __forceinline__ void skinny_load(const skinny_tile_state<NFR>& st, in
     for (int e = 0; e < 2; ++e) {
         const int ks = min(2 * p + e, st.KS - 1);                // padding repeats the last fragment
 #pragma unroll
-        for (int f = 0; f < NFR; ++f) sl.w[e][f] = ld16_once(st.w[f] + static_cast<size_t>(ks) * 1024 + lane16);
+        for (int f = 0; f < NFR; ++f) {
+            const gcptr at = st.w[f] + static_cast<size_t>(ks) * 1024 + lane16;
+            sl.w[e][f] = ONCE ? ld16_once(at) : ld16(at);
+        }
     }
 }
 
@@ -370,7 +373,7 @@ struct run_next {
 // Processes slot `slot` (its order entry and tile and, if first_ga_known, its group arguments already read)
 // and every following slot of this workgroup that holds a tile of the same streaming class.  Returns the
 // first slot it did not process (n_slots at the end of the list; a list has no holes) and what it knows of it.
-template <int DT, bool GATED, bool CHAIN, int CLS, int MB, int NFR, int U>
+template <int DT, bool GATED, bool CHAIN, bool ONCE, int CLS, int MB, int NFR, int U>
 __device__ __forceinline__ long skinny_run(const epara_group_args* __restrict__ args, const epara_tile* __restrict__ tiles,
                                            const int32_t* __restrict__ order, long slot, int entry, const epara_tile& first_tile,
                                            const epara_group_args& first_ga, bool first_ga_known, long n_slots, long stride,
@@ -398,7 +401,7 @@ __device__ __forceinline__ long skinny_run(const epara_group_args* __restrict__ 
     // rings of another streaming class: a run ends with every slot consumed, nothing in flight).
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < U; ++u) skinny_load<DT, MB, NFR>(cur, u, wave, lane, ring[u], xring + u * XSLOT_BYTES);
+    for (int u = 0; u < U; ++u) skinny_load<DT, MB, NFR, ONCE>(cur, u, wave, lane, ring[u], xring + u * XSLOT_BYTES);
     __builtin_amdgcn_sched_barrier(0);
 
     typedef skinny_shape<GATED, MB, NFR> S;
@@ -449,7 +452,7 @@ __device__ __forceinline__ long skinny_run(const epara_group_args* __restrict__ 
             for (int u = 0; u < U; ++u) {
                 skinny_mma<DT, MB, NFR, U - 1>(cur, c * U + u, wave, lane, ring[u], xring + u * XSLOT_BYTES, acc);
                 __builtin_amdgcn_sched_barrier(0);
-                skinny_load<DT, MB, NFR>(cur, (c + 1) * U + u, wave, lane, ring[u], xring + u * XSLOT_BYTES);
+                skinny_load<DT, MB, NFR, ONCE>(cur, (c + 1) * U + u, wave, lane, ring[u], xring + u * XSLOT_BYTES);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (stage < 3) advance();
@@ -464,7 +467,7 @@ __device__ __forceinline__ long skinny_run(const epara_group_args* __restrict__ 
             for (int u = 0; u < U; ++u) {
                 skinny_mma<DT, MB, NFR, U - 1>(cur, c_last * U + u, wave, lane, ring[u], xring + u * XSLOT_BYTES, acc);
                 __builtin_amdgcn_sched_barrier(0);
-                skinny_load<DT, MB, NFR>(nxt, u, wave, lane, ring[u], xring + u * XSLOT_BYTES);
+                skinny_load<DT, MB, NFR, ONCE>(nxt, u, wave, lane, ring[u], xring + u * XSLOT_BYTES);
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else {                                                 // nothing follows: the ring drains

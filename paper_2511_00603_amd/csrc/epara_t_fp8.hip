@@ -3,7 +3,7 @@
 #include "epara_internal.h"
 
 hipError_t epara_enqueue_block_fp8(int gated, unsigned grid, hipStream_t stream, const epara_group_args* args, const epara_tile* tiles,
-                                    const int32_t* order, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles)
+                                    const int32_t* order, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles, int once)
 {
-    return (gated ? enqueue_block<EPARA_FP8_E4M3, true> : enqueue_block<EPARA_FP8_E4M3, false>)(grid, stream, args, tiles, order, n_slots, out_dtype, split_ws, n_split, n_counters, n_tiles);
+    return (gated ? enqueue_block<EPARA_FP8_E4M3, true> : enqueue_block<EPARA_FP8_E4M3, false>)(grid, stream, args, tiles, order, n_slots, out_dtype, split_ws, n_split, n_counters, n_tiles, once);
 }

@@ -809,3 +809,45 @@ def test_panel_tiles_of_a_last_round_in_quarters_give_the_bits_of_whole_ones(dty
                 assert_close(U.fetch(y), w, TOL[dtype_name], str(sh))
             else:
                 assert np.array_equal(U.fetch(y), ref.bf16_decode(ref.bf16_encode(w))), sh
+
+
+# ---- weights read with the non-temporal hint ----------------------------------------------------
+
+@pytest.mark.parametrize("dtype_name,gated", [("bf16", False), ("bf16", True), ("fp8", False), ("fp8", True)])
+def test_launches_too_large_for_the_last_level_cache_give_the_bits_of_their_groups_alone(dtype_name, gated):
+    """Launches of more than 112 MB of weights (gated 192) read those of streaming tiles and of block tiles of a single row tile with another kernel
+    than smaller ones: one batch of each streaming class, block tiles of 65 and 128 rows and two row tiles; sums of small integers: the bits of
+    the same groups launched one by one, which stay below the line, and the oracle's."""
+    rng = np.random.default_rng(37)
+    dt, esz, K = B.DTYPE_BY_NAME[dtype_name], 2 if dtype_name == "bf16" else 1, 4096
+    columns = -(-(200 if gated else 120) * 10 ** 6 // ((2 if gated else 1) * esz * K)) // 6
+    shapes = [(M, K, columns + d) for d, M in enumerate((5, 20, 50, 65, 128, 129, 7))]
+    keep, outs, want, args = [], [], [], []
+    for M, _, N in shapes:
+        X = rng.integers(-2, 3, (M, K)).astype(np.float32)
+        Ws = [rng.integers(-1, 2, (K, N), dtype=np.int8).astype(np.float32) for _ in range(2 if gated else 1)]
+        dX = R.device_tensor_from_bits(U.to_bits(X, dtype_name), dt, U.DEV)
+        dW = [R.pack_weights(R.device_tensor_from_bits(U.to_bits(w, dtype_name), dt, U.DEV), dt) for w in Ws]
+        dY = torch.zeros((M, N), dtype=torch.bfloat16, device=U.DEV)
+        keep.extend([dX] + dW)
+        outs.append(dY)
+        z = [X.astype(np.float64) @ w for w in Ws]
+        want.append(z[0] / (1 + np.exp(-z[0])) * z[1] if gated else np.maximum(z[0], 0))
+        args.append(R.group_args(dX, dW[0], dY, M, K, N, "swiglu" if gated else "relu", W2=dW[1] if gated else None))
+    assert sum(K * N * esz * (2 if gated else 1) for _, K, N in shapes) > (192e6 if gated else 112e6)
+    bits = []
+    for launches in ([args], [[a] for a in args]):
+        for y in outs:
+            y.fill_(float("nan"))
+        for groups in launches:
+            plan = R.LaunchPlan(np.array(groups, dtype=B.GROUP_ARGS), dt, U.DEV)
+            assert len(groups) == 1 or int(plan.classes[-1][1]) == 128
+            R.grouped_forward(plan, B.EPARA_BF16)
+            torch.cuda.synchronize()
+        bits.append([y.view(torch.int16).clone() for y in outs])
+    for sh, together, alone, y, w in zip(shapes, *bits, outs, want):
+        assert torch.equal(together, alone), sh
+        if gated:
+            assert_close(U.fetch(y), w, TOL[dtype_name], str(sh))
+        else:
+            assert np.array_equal(U.fetch(y), ref.bf16_decode(ref.bf16_encode(w))), sh
