@@ -155,27 +155,29 @@ __device__ __forceinline__ void grouped_body(const epara_group_args* __restrict_
     if constexpr (HAS_SPLIT) split_flush<DT, GATED, PANEL_ONLY>(args, tiles, out_dtype, narrow, lds, sp, pend);
 }
 
-// TAIL: the lists are visited up to slot tail_slot, what comes after it as panel_tail says.  ONCE: see epara_stream.h.
+// TAIL: the lists are visited up to a slot, which comes in place of first_panel_split (such a launch has no tiles in parts), what comes after
+// it as panel_tail says.  ONCE: see epara_stream.h.
 template <int DT, bool GATED, bool PANEL_ONLY, bool TAIL, bool ONCE>
 __global__ __launch_bounds__(NT) void grouped_kernel(const epara_group_args* __restrict__ args,
                                                      const epara_tile* __restrict__ tiles,
                                                      const int32_t* __restrict__ order,
-                                                     long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot)
+                                                     long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const split_ctx sp = {split_ws, n_split, n_panel_split, first_panel_split};
+    const long tail_slot = first_panel_split;
     grouped_body<DT, GATED, false, PANEL_ONLY, ONCE>(args, tiles, order, TAIL ? tail_slot : n_slots, out_dtype, narrow, lds, nullptr, &sp);
     if constexpr (TAIL) panel_tail<DT, GATED>(args, tiles, order, tail_slot, n_slots, out_dtype, lds);
 }
 
 template <int DT, bool GATED, bool PANEL_ONLY, bool TAIL, bool ONCE>
 hipError_t enqueue_grouped_as(unsigned grid, hipStream_t stream, const epara_group_args* args, const epara_tile* tiles,
-                              const int32_t* order, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split, long tail_slot)
+                              const int32_t* order, long n_slots, int out_dtype, int narrow, uint32_t* split_ws, int n_split, int n_panel_split, int first_panel_split)
 {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_kernel<DT, GATED, PANEL_ONLY, TAIL, ONCE>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((grouped_kernel<DT, GATED, PANEL_ONLY, TAIL, ONCE>), dim3(grid), dim3(NT), LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split, tail_slot);
+    hipLaunchKernelGGL((grouped_kernel<DT, GATED, PANEL_ONLY, TAIL, ONCE>), dim3(grid), dim3(NT), LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split);
     return hipGetLastError();
 }
 
@@ -185,8 +187,10 @@ hipError_t enqueue_grouped(int panel_only, unsigned grid, hipStream_t stream, co
 {
     auto as = panel_only ? &enqueue_grouped_as<DT, GATED, true, false, false>
             : once ? &enqueue_grouped_as<DT, GATED, false, false, true> : &enqueue_grouped_as<DT, GATED, false, false, false>;
-    if constexpr (GATED || DT != EPARA_BF16) { if (panel_only && tail_slot >= 0) as = &enqueue_grouped_as<DT, GATED, true, true, false>; }
-    return as(grid, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split, tail_slot);
+    if constexpr (GATED || DT != EPARA_BF16) {
+        if (panel_only && tail_slot >= 0) { as = &enqueue_grouped_as<DT, GATED, true, true, false>; first_panel_split = static_cast<int>(tail_slot); }
+    }
+    return as(grid, stream, args, tiles, order, n_slots, out_dtype, narrow, split_ws, n_split, n_panel_split, first_panel_split);
 }
 
 // ---- a chain of launches as one kernel: the phases one after the other in every workgroup
