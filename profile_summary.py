@@ -20,9 +20,14 @@ import sys
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(ROOT, "paper_2511_00603_amd", "csrc")
-KERNEL_SOURCES = [os.path.join(CSRC, f) for f in ("epara_device.h", "epara_panel.h", "epara_stream.h", "epara_grouped.h")]
+KERNEL_SOURCES = [os.path.join(CSRC, f) for f in ("epara_device.h", "epara_panel.h", "epara_half.h", "epara_stream.h", "epara_grouped.h")]
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "traffic.txt")
 COPY_BYTES = 1 << 30
+
+
+def is_grouped(name):
+    """A launch of streaming or panel tiles, the latter whole or in halves."""
+    return "grouped_kernel" in name or "grouped_half_kernel" in name
 
 
 def kernel_source_hash():
@@ -43,7 +48,7 @@ def kernels(trace_csv, command, out_txt, launches_per_pass, tail_passes=0, first
          "%-78s %6s %12s %10s %7s" % ("kernel", "calls", "total_us", "avg_us", "pct")]
     for name, d in sorted(by.items(), key=lambda kv: -sum(kv[1]))[:8]:
         L.append("%-78s %6d %12.1f %10.2f %7.2f" % (name[:78], len(d), sum(d), sum(d) / len(d), 100 * sum(d) / total))
-    g = [(r["Kernel_Name"], (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3, r) for r in rows if "grouped_kernel" in r["Kernel_Name"]]
+    g = [(r["Kernel_Name"], (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3, r) for r in rows if is_grouped(r["Kernel_Name"])]
     g.sort(key=lambda t: int(t[2]["Start_Timestamp"]))
     first, last = launches_per_pass, len(g)
     what = "first pass skipped as warm-up"
@@ -82,7 +87,7 @@ def _counter(path, name):
             continue
         key = (int(r["Dispatch_Id"]), r["Kernel_Name"])
         vals[key] = vals.get(key, 0.0) + float(r["Counter_Value"])
-    grouped = [v for (d, k), v in sorted(vals.items()) if "grouped_kernel" in k]
+    grouped = [v for (d, k), v in sorted(vals.items()) if is_grouped(k)]
     copy = [v for (d, k), v in sorted(vals.items()) if "copy_kernel" in k]
     return grouped, copy
 
@@ -192,7 +197,7 @@ def _per_launch(path, launches_per_pass):
     "_us" -> the same for the dispatch durations."""
     vals, dur = {}, {}
     for r in _rows(path):
-        if "grouped_kernel" not in r["Kernel_Name"]:
+        if not is_grouped(r["Kernel_Name"]):
             continue
         d = int(r["Dispatch_Id"])
         vals.setdefault(r["Counter_Name"], {})
