@@ -851,3 +851,36 @@ def test_launches_too_large_for_the_last_level_cache_give_the_bits_of_their_grou
             assert_close(U.fetch(y), w, TOL[dtype_name], str(sh))
         else:
             assert np.array_equal(U.fetch(y), ref.bf16_decode(ref.bf16_encode(w))), sh
+
+
+@pytest.mark.parametrize("K", [16, 136, 392, 1040])
+def test_a_last_row_tile_of_up_to_32_rows_is_multiplied_with_the_one_before(K):
+    """Gated bf16 block tiles of five row fragments: one row to 33 rows past one, two and three row tiles, next to groups without such a tile; ragged
+    columns, K of one pair of stages, of both phases of the ring and ragged.  Sums of small integers: the bits of panel tiles, within the tolerance of the oracle."""
+    rng = np.random.default_rng(43)
+    rows, N = (129, 159, 160, 161, 256, 257, 288, 289, 385, 70, 128), 136
+    keep, outs, want, args = [], [], [], []
+    for M in rows:
+        X = rng.integers(-2, 3, (M, K)).astype(np.float32)
+        Ws = [rng.integers(-1, 2, (K, N)).astype(np.float32) for _ in range(2)]
+        dX = R.device_tensor_from_bits(casts.bf16_bits(X), B.EPARA_BF16, U.DEV)
+        dW = [R.pack_weights(R.device_tensor_from_bits(casts.bf16_bits(w), B.EPARA_BF16, U.DEV), B.EPARA_BF16) for w in Ws]
+        dY = torch.zeros((M, N), dtype=torch.bfloat16, device=U.DEV)
+        keep.extend([dX] + dW)
+        outs.append(dY)
+        z, u = X.astype(np.float64) @ Ws[0], X.astype(np.float64) @ Ws[1]
+        want.append(z / (1 + np.exp(-z)) * u)
+        args.append(R.group_args(dX, dW[0], dY, M, K, N, "swiglu", W2=dW[1]))
+    bits = []
+    for n_workgroups, tall in ((256, 128), (64, 256)):
+        plan = R.LaunchPlan(np.array(args, dtype=B.GROUP_ARGS), B.EPARA_BF16, U.DEV, n_workgroups)
+        assert int(plan.classes[-1][1]) == tall
+        for rep in range(2):
+            for y in outs:
+                y.fill_(float("nan"))
+            R.grouped_forward(plan, B.EPARA_BF16)
+            torch.cuda.synchronize()
+        bits.append([y.view(torch.int16).clone() for y in outs])
+    for M, block, panel, y, w in zip(rows, *bits, outs, want):
+        assert torch.equal(block, panel), M
+        assert_close(U.fetch(y), w, TOL["bf16"], str(M))
