@@ -28,13 +28,6 @@ namespace {
 constexpr int BLOCK_RING = 4;                                    // pairs in flight or being read
 constexpr int BLOCK_LDS_BYTES = BLOCK_RING * 128 * 128;          // 64 KiB; the epilogue parks the tile's outputs in the same place
 
-// Gated bf16 launches (whose tiles are never visited in parts) multiply a last row tile of at most 32 rows together with the one before, as a fifth
-// fragment of rows, instead of reading the same weights for it once more: five fragments take 80 KiB of ring, two workgroups a unit's whole LDS.
-// 4096 -> 11008: 75 + 130 + 237 rows 150 -> 139 us, 130 rows 59 -> 50, 150 + 300 + 400 rows 235 -> 221, 1050 rows 209 -> 205; 650 rows, five row tiles
-// and ten rows, 140 either way.  More than 32 rows need a sixth fragment, for which two workgroups have no LDS.
-template <int DT, bool GATED> constexpr bool BLOCK_TALL = DT == EPARA_BF16 && GATED;
-template <int DT, bool GATED> constexpr int BLOCK_KERNEL_LDS_BYTES = BLOCK_LDS_BYTES / 4 * (BLOCK_TALL<DT, GATED> ? 5 : 4);
-
 // Split block tiles: three of them per slot of the panel tiles' workspace (four parts of 64 KiB each).  They count in
 // front of all partial sums like every other split tile, eight tiles to a counter: partial sums never land on the counters of
 // a launch that uses the same workspace later, unless those take more room.  sp.n_panel: the counters, sp.first_panel: the tiles.
@@ -182,7 +175,7 @@ __device__ __forceinline__ void block_tile(const epara_group_args& ga, const epa
             if constexpr (MODE == 0 || (MODE == 1 && !LAST)) {
                 if (fm == (FM > 2 ? 2 : FM - 1)) {
 #pragma unroll
-                    for (int j = J0; j < (S == STEPS - 2 ? FM : J0 + IPS); ++j)      // a fifth fragment: with the fourth
+                    for (int j = J0; j < J0 + IPS; ++j)
                         if (j < FM) x_issue(LAST ? p + 4 : p + 3, LAST ? slot : (slot + 3) & (BLOCK_RING - 1), j);
                 }
             }
@@ -400,19 +393,6 @@ __global__ __launch_bounds__(NT, 2) void grouped_block_kernel(const epara_group_
         const epara_tile tl = tiles[order_tile(t)];
         if (tl.cls < N_STREAM_CLASSES) continue;                 // the streaming tiles of the launch have a kernel of their own
         const epara_group_args ga = args[tl.group];
-        if constexpr (BLOCK_TALL<DT, GATED>) {
-            const int over = ga.M % EPARA_BLOCK_ROWS, last = ga.M - over;
-            if (over > 0 && over <= 32 && last > 0) {
-                if (tl.m0 == last) continue;                     // multiplied with the row tile before
-                if (tl.m0 == last - EPARA_BLOCK_ROWS) {
-                    epara_tile tall = tl;
-                    tall.rows = EPARA_BLOCK_ROWS + over;
-                    if (once && last == EPARA_BLOCK_ROWS) block_tile<DT, GATED, 5, true>(ga, tall, t, out_dtype, lds, sp);
-                    else                                  block_tile<DT, GATED, 5>(ga, tall, t, out_dtype, lds, sp);
-                    continue;
-                }
-            }
-        }
         const int fm = (tl.rows + 31) >> 5;
         if (once && ga.M <= EPARA_BLOCK_ROWS) {                  // and more than 64
             if (fm > 3)   block_tile<DT, GATED, 4, true>(ga, tl, t, out_dtype, lds, sp);
@@ -430,9 +410,9 @@ hipError_t enqueue_block(unsigned grid, hipStream_t stream, const epara_group_ar
                          const int32_t* order, long n_slots, int out_dtype, uint32_t* split_ws, int n_split, int n_counters, int n_tiles, int once)
 {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_block_kernel<DT, GATED>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, BLOCK_KERNEL_LDS_BYTES<DT, GATED>);
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, BLOCK_LDS_BYTES);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((grouped_block_kernel<DT, GATED>), dim3(grid), dim3(NT), (BLOCK_KERNEL_LDS_BYTES<DT, GATED>), stream, args, tiles, order, n_slots, out_dtype, split_ws, n_split, n_counters, n_tiles, once);
+    hipLaunchKernelGGL((grouped_block_kernel<DT, GATED>), dim3(grid), dim3(NT), BLOCK_LDS_BYTES, stream, args, tiles, order, n_slots, out_dtype, split_ws, n_split, n_counters, n_tiles, once);
     return hipGetLastError();
 }
 

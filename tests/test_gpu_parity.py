@@ -854,8 +854,8 @@ def test_launches_too_large_for_the_last_level_cache_give_the_bits_of_their_grou
 
 
 @pytest.mark.parametrize("K", [16, 136, 392, 1040])
-def test_a_last_row_tile_of_up_to_32_rows_is_multiplied_with_the_one_before(K):
-    """Gated bf16 block tiles of five row fragments: one row to 33 rows past one, two and three row tiles, next to groups without such a tile; ragged
+def test_block_tiles_of_a_short_last_row_tile_give_the_bits_of_panel_tiles(K):
+    """Gated bf16 block tiles, one row to 33 rows past one, two and three row tiles, next to groups without such a tile; ragged
     columns, K of one pair of stages, of both phases of the ring and ragged.  Sums of small integers: the bits of panel tiles, within the tolerance of the oracle."""
     rng = np.random.default_rng(43)
     rows, N = (129, 159, 160, 161, 256, 257, 288, 289, 385, 70, 128), 136
@@ -884,3 +884,41 @@ def test_a_last_row_tile_of_up_to_32_rows_is_multiplied_with_the_one_before(K):
     for M, block, panel, y, w in zip(rows, *bits, outs, want):
         assert torch.equal(block, panel), M
         assert_close(U.fetch(y), w, TOL["bf16"], str(M))
+
+
+@pytest.mark.parametrize("dtype_name,gated", [("bf16", True), ("bf16", False), ("fp8", True)])
+def test_launches_of_some_of_the_tiles_write_those_and_nothing_else(dtype_name, gated):
+    """A service's rows in two launches: the last row tiles in one, the others in another.  Each writes its own rows, with the bits of a launch of all
+    tiles.  Last row tiles of one row, up to 32 and more, behind one whole row tile and two."""
+    rng = np.random.default_rng(47)
+    dt, rows, K, N, W_ = B.DTYPE_BY_NAME[dtype_name], (129, 130, 160, 161, 258, 288), 264 if dtype_name == "bf16" else 272, 136, 256
+    keep, outs, args = [], [], []
+    for M in rows:
+        X = rng.integers(-2, 3, (M, K)).astype(np.float32)
+        dX = R.device_tensor_from_bits(U.to_bits(X, dtype_name), dt, U.DEV)
+        dW = [R.pack_weights(R.device_tensor_from_bits(U.to_bits(rng.integers(-1, 2, (K, N)).astype(np.float32), dtype_name), dt, U.DEV), dt) for _ in range(2 if gated else 1)]
+        outs.append(torch.zeros((M, N), dtype=torch.bfloat16, device=U.DEV))
+        keep.extend([dX] + dW)
+        args.append(R.group_args(dX, dW[0], outs[-1], M, K, N, "swiglu" if gated else "relu", W2=dW[1] if gated else None))
+    plan = R.LaunchPlan(np.array(args, dtype=B.GROUP_ARGS), dt, U.DEV, W_)
+    assert int(plan.classes[-1][1]) == 128 and plan.n_panel_split_tiles == 0
+    R.grouped_forward(plan, B.EPARA_BF16)
+    torch.cuda.synchronize()
+    whole = [y.view(torch.int16).clone() for y in outs]
+    last = np.array([t["m0"] + t["rows"] == rows[t["group"]] for t in plan.tiles])
+    for chosen in (last, ~last):
+        tiles = np.ascontiguousarray(plan.tiles[chosen])
+        order = np.full(-(-len(tiles) // W_) * W_, -1, dtype=np.int32)
+        order[: len(tiles)] = np.arange(len(tiles))
+        d_tiles, d_order = R._upload_all([tiles, order], U.DEV)
+        launch = B.Launch(B._ptr(plan.args), plan.d_args.data_ptr(), B._ptr(tiles), d_tiles.data_ptr(), d_order.data_ptr(), len(tiles), len(order), W_, len(rows), None, 0, 0, 0)
+        for y in outs:
+            y.fill_(float("nan"))
+        empty = outs[0].view(torch.int16)[0, 0].item()
+        B.epara_grouped_forward(launch, dt, B.EPARA_BF16, R.current_stream_handle())
+        torch.cuda.synchronize()
+        for M, y, w in zip(rows, outs, whole):
+            first = (M - 1) // 128 * 128
+            got, mine = y.view(torch.int16), slice(first, M) if chosen is last else slice(0, first)
+            other = slice(0, first) if chosen is last else slice(first, M)
+            assert torch.equal(got[mine], w[mine]) and bool((got[other] == empty).all()), (M, chosen is last)
