@@ -83,7 +83,7 @@ __device__ __forceinline__ void panel_tail(const epara_group_args* __restrict__ 
     __syncthreads();                                             // the operands and sums of the list have been read
     for (int c = wave; c < ballots; c += NT / 64) {
         const int t = c * 64 + lane < n ? order[tail_slot + c * 64 + lane] : -1;
-        const unsigned long long mask = __ballot(t >= 0 && order_parts(t) == 1);
+        const unsigned long long mask = __ballot(t >= 0);        // (an entry that names a part, which no planner makes here: the whole tile, as in a panel run)
         if (lane == 0) found[c] = mask;
     }
     __syncthreads();

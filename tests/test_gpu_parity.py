@@ -922,3 +922,28 @@ def test_launches_of_some_of_the_tiles_write_those_and_nothing_else(dtype_name, 
             got, mine = y.view(torch.int16), slice(first, M) if chosen is last else slice(0, first)
             other = slice(0, first) if chosen is last else slice(first, M)
             assert torch.equal(got[mine], w[mine]) and bool((got[other] == empty).all()), (M, chosen is last)
+
+
+@pytest.mark.parametrize("dtype_name,gated", [("bf16", True), ("fp8", True), ("fp8", False)])
+def test_entries_that_name_a_part_are_whole_tiles_where_nothing_is_visited_in_parts(dtype_name, gated):
+    """Panel tiles of gated bf16 and fp8 launches are never visited in parts of K: an order whose entries name parts all the same gives the bits of the
+    planner's, in whole rounds and in a last one that is cut into quarters."""
+    rng = np.random.default_rng(53)
+    dt, u, W_, K, M = B.DTYPE_BY_NAME[dtype_name], 128 if gated else 256, 16, 1552, 257
+    N = 9 * u - 5                                                # 18 tiles
+    X = rng.integers(-2, 3, (M, K)).astype(np.float32)
+    dX = R.device_tensor_from_bits(U.to_bits(X, dtype_name), dt, U.DEV)
+    dW = [R.pack_weights(R.device_tensor_from_bits(U.to_bits(rng.integers(-1, 2, (K, N)).astype(np.float32), dtype_name), dt, U.DEV), dt) for _ in range(2 if gated else 1)]
+    dY = torch.zeros((M, N), dtype=torch.bfloat16, device=U.DEV)
+    plan = R.LaunchPlan(np.array([R.group_args(dX, dW[0], dY, M, K, N, "swiglu" if gated else "relu", W2=dW[1] if gated else None)], dtype=B.GROUP_ARGS), dt, U.DEV, W_)
+    assert len(plan.tiles) == 18 and int(plan.classes[-1][1]) == 256 and plan.n_panel_split_tiles == 0
+    bits = []
+    for part, parts in ((0, 1), (0, 2), (1, 2), (2, 4)):
+        order = np.where(plan.order < 0, plan.order, plan.order | part << 24 | (parts - 1) << 28).astype(np.int32)
+        d_order, = R._upload_all([order], U.DEV)
+        launch = B.Launch(B._ptr(plan.args), plan.d_args.data_ptr(), B._ptr(plan.tiles), plan.d_tiles.data_ptr(), d_order.data_ptr(), len(plan.tiles), len(order), W_, 1, None, 0, 0, 0)
+        dY.fill_(float("nan"))
+        B.epara_grouped_forward(launch, dt, B.EPARA_BF16, R.current_stream_handle())
+        torch.cuda.synchronize()
+        bits.append(dY.view(torch.int16).clone())
+    assert not torch.isnan(bits[0].view(torch.bfloat16)).any() and all(torch.equal(b, bits[0]) for b in bits[1:])
