@@ -947,3 +947,56 @@ def test_entries_that_name_a_part_are_whole_tiles_where_nothing_is_visited_in_pa
         torch.cuda.synchronize()
         bits.append(dY.view(torch.int16).clone())
     assert not torch.isnan(bits[0].view(torch.bfloat16)).any() and all(torch.equal(b, bits[0]) for b in bits[1:])
+
+
+@pytest.mark.parametrize("dtype_name,gated,out_name", [("bf16", True, "bf16"), ("fp8", True, "bf16"), ("fp8", True, "fp8"), ("fp8", False, "bf16")])
+def test_last_rounds_in_quarters_on_whole_grids(dtype_name, gated, out_name):
+    """The same comparison on grids of 128 and 256 workgroups, cut into panel tiles whatever a plan would choose: 8 to 96 tiles past one and two whole rounds,
+    spread over two and four words of 64 slots, several of them per group of workgroups of a die; E4M3 outputs too.  Nothing may stay unwritten."""
+    gen = torch.Generator(device=U.DEV)
+    gen.manual_seed(59)
+    dt, out_dt, u = B.DTYPE_BY_NAME[dtype_name], B.DTYPE_BY_NAME[out_name], 128 if gated else 256
+    K = 1552 if dtype_name == "bf16" else 16
+    stored = lambda x: x.to(torch.bfloat16) if dt == B.EPARA_BF16 else x.to(torch.float8_e4m3fn).view(torch.uint8)
+    ints = lambda lo, hi, shape: torch.randint(lo, hi + 1, shape, generator=gen, device=U.DEV).float()
+    launches = [(256, [(700, 88 * u)]), (256, [(1000, 72 * u - 3)]), (256, [(970, 88 * u - 9)]), (256, [(600, 100 * u + 1), (70, 49 * u)]), (256, [(1030, 109 * u)]),
+                (128, [(1000, 34 * u - 5)]), (128, [(300, 83 * u)]), (128, [(257, 144 * u - 1)])]
+    rests = []
+    for W_, shapes in launches:
+        args, outs, wants, keep = [], [], [], []
+        for M, N in shapes + [(65, 40)]:
+            k = K if len(args) < len(shapes) else K + 64
+            X, Ws = ints(-2, 2, (M, k)), [ints(-1, 1, (k, N)) for _ in range(2 if gated else 1)]
+            dX, dW = stored(X), [R.pack_weights(stored(w), dt) for w in Ws]
+            dY = torch.empty((M, N), dtype=R.TORCH_DTYPE[out_dt], device=U.DEV)
+            keep.extend([dX] + dW)
+            outs.append(dY)
+            z = [X.double() @ w.double() for w in Ws]
+            wants.append(z[0] / (1 + torch.exp(-z[0])) * z[1] if gated else z[0].clamp(min=0))
+            args.append(R.group_args(dX, dW[0], dY, M, k, N, "swiglu" if gated else "relu", W2=dW[1] if gated else None))
+        bits = []
+        for n in (len(shapes), len(shapes) + 1):                 # with the group of another K: whole tiles
+            table = np.array(args[:n], dtype=B.GROUP_ARGS)
+            groups = R._group_desc(table)
+            cls, n_stream = B.epara_kernel_classes(dt, int(gated), 0)
+            tiles = B.epara_plan_groups(groups, cls)[3]
+            order = B.epara_schedule_tiles(groups, cls, n_stream, tiles, W_, 8, 1, 4)
+            if n == len(shapes):
+                rests.append((len(tiles) // W_, len(tiles) % W_))
+                assert rests[-1][0] >= 1 and 0 < 8 * rests[-1][1] <= 3 * W_, (W_, shapes, rests[-1])
+            d = R._upload_all([table, tiles, order], U.DEV)
+            launch = B.Launch(B._ptr(table), d[0].data_ptr(), B._ptr(tiles), d[1].data_ptr(), d[2].data_ptr(), len(tiles), len(order), W_, n, None, 0, 0, 0)
+            for y in outs:
+                y.view(torch.uint8).fill_(0xFF)                  # a NaN in either type
+            B.epara_grouped_forward(launch, dt, out_dt, R.current_stream_handle())
+            torch.cuda.synchronize()
+            bits.append([y.view(torch.uint8).clone() for y in outs[:len(shapes)]])
+        for (M, N), quarters, whole, y, want in zip(shapes, *bits, outs, wants):
+            assert torch.equal(quarters, whole), (W_, M, N)
+            if out_dt == B.EPARA_FP8_E4M3:
+                assert not bool((quarters == 0xFF).any()), (W_, M, N)
+            elif gated:
+                assert_close(U.fetch(y), want.cpu().numpy(), TOL[dtype_name], str((W_, M, N)))
+            else:
+                assert torch.equal(y, want.to(torch.bfloat16)), (W_, M, N)
+    assert {r for r, _ in rests} == {1, 2} and min(r for _, r in rests) == 8 and max(r for _, r in rests) == 96, rests
