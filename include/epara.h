@@ -390,9 +390,11 @@ int32_t epara_plan_groups(const epara_group_desc* groups, int32_t G,
  *   the weights' way to the chip, sum of K * N * (2 for EPARA_ACT_SWIGLU) * (2 TM + 1) / EPARA_COST_BLOCK_STREAMED over the groups: fetched
  *     once for the first of TM row tiles and two thirds of a time for each other one, at 4.3 TB/s (80 units are a nanosecond of a list for
  *     bf16, 160 for fp8, whose K are half the bytes, as under EPARA_COST_KERNEL; the constants of a visit are then half the time, which fits no worse).
- * On 1196 launches drawn at random, none of them used to choose a constant, and 119 layers of language models and vision transformers
- * (profiles/block_tile_launches.txt, every way timed) the plan takes 1.1 and 0.6 % longer than the best way on average, and more than 10 % in 56 and 3;
- * panel tiles always 56 and 63 %, block tiles always 3.4 and 2.5 %; one list cost per tile instead of the estimate 4.6 and 4.5 %.
+ * The estimate prices panel tiles as whole ones; that short ones run in halves and a small last round in quarters (epara_launch.hip) changes the best way
+ * of few launches.  On 299 launches drawn at random, none of them used to choose a constant, and 119 layers of language models and vision transformers
+ * (profiles/block_tile_launches.txt, every way timed with halves and quarters) the plan takes 1.3 and 0.7 % longer than the best way on average, and more
+ * than 10 % in 18 and 4 (before there were halves and quarters 1.3 and 0.6 %, 16 and 3 on the same launches); panel tiles always 59 and 62 %, block tiles
+ * always 3.8 and 3.4 %.  One list cost per tile instead of the estimate: 4.6 and 4.5 % when it was chosen.
  *
  * Block tiles of a long K.  Few tiles of a long K (a down projection) leave units idle, so the tiles of the groups with
  * K >= the block class's split_K > 0 (EPARA_BLOCK_SPLIT_K for plain bf16 launches; 0 for gated and fp8 ones, whose results do not

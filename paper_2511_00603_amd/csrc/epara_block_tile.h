@@ -14,9 +14,9 @@
 // while one workgroup waits for its first operands or stores, the other one multiplies.  Sums run over K in the
 // same order and with the same instructions as in a panel tile: the results agree bit for bit.
 //
-// Weights of a group of a single row tile are read by one workgroup once.  In launches too large for the last-level cache (`once`) that is done with
-// the non-temporal hint: three SwiGLU services of 75 rows, 4096 -> 11008, 120.6 -> 112.0 us, of 120 rows 134.4 -> 128.6,
-// four of 96 rows, 11008 -> 4096, 77.3 -> 69.8.  Where several row tiles share them the hint costs (75 + 130 + 237 rows, a pass
+// Weights of a group of a single row tile are read by one workgroup once.  In large launches (`once`, by the size of the launch; see weights_once in
+// epara_launch.hip) that is done with the non-temporal hint: three SwiGLU services of 75 rows, 4096 -> 11008, 120.6 -> 112.0 us, of 120 rows
+// 134.4 -> 128.6, four of 96 rows, 11008 -> 4096, 77.3 -> 69.8.  Where several row tiles share them the hint costs (75 + 130 + 237 rows, a pass
 // 236 -> 262 us), and so it does on activations (291).
 #ifndef EPARA_BLOCK_TILE_H
 #define EPARA_BLOCK_TILE_H

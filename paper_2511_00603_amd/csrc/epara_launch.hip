@@ -139,11 +139,12 @@ int32_t validate_launch(const epara_launch* L, int32_t in_dtype, int32_t out_dty
 
 // Whether a bf16 launch of nothing but panel tiles multiplies each of them in halves by two workgroups (epara_half.h): where K is short the
 // start and the epilogue of a tile, which nothing hides when one workgroup has a unit to itself, are what the launch waits for; where it is long
-// the activations read by one workgroup more per tile cost power instead.  The same bits either way, so the line is drawn by time alone: 21 launches of
-// 256 .. 3564 tiles each, every K timed both ways, panel / half: plain K = 384 1.20 .. 1.37, 768 1.05 .. 1.31, 1024 1.07 .. 1.22, 1536
-// 1.05 .. 1.16, 2048 1.00 .. 1.12, 2560 1.00 .. 1.10, 3072 0.99 .. 1.07, 4096 0.98 .. 1.06, 5120 0.95 .. 1.04; gated K = 384 1.23 .. 1.42, 768 1.10 .. 1.24, 1024
-// 1.06 .. 1.17, 1536 1.02 .. 1.08, 2048 0.94 .. 1.06, 2560 0.94 .. 1.05, 5120 0.87 .. 1.01.  A launch with one longer K stays whole: 8 ViT services' QKV (768) next to
-// their FFN-down (3072) 129 us, in halves 134.
+// the activations read by one workgroup more per tile cost power instead.  The same bits either way, so the line is drawn by time alone: 21 launches
+// of 256 .. 3564 tiles each, every K timed both ways, panel / half: plain K = 384 1.20 .. 1.37, 768 1.05 .. 1.31, 1024 1.07 .. 1.22, 1536
+// 1.05 .. 1.16, 2048 1.00 .. 1.12, 2560 1.00 .. 1.10, 3072 0.99 .. 1.07, 4096 0.98 .. 1.06, 5120 0.95 .. 1.04; gated K = 384 1.23 .. 1.42, 768
+// 1.10 .. 1.24, 1024 1.06 .. 1.17, 1536 1.02 .. 1.08, 2048 0.94 .. 1.06, 2560 0.94 .. 1.05, 5120 0.87 .. 1.01.  150 launches drawn at random inside
+// the rule: 1.13 on average, 143 of them 0.98 .. 1.44, the others 0.945 .. 0.976, five of these plain ones of K = 2248 .. 2448 (where 21 gave 1.05 on
+// average).  A launch with one longer K stays whole: 8 ViT services' QKV (768) next to their FFN-down (3072) 129 us, in halves 134.
 bool halves(const epara_launch* L, int gated)
 {
     if (L->n_panel_split_tiles != 0 || L->n_slots > INT32_MAX / 2) return false;
@@ -153,10 +154,11 @@ bool halves(const epara_launch* L, int gated)
 }
 
 // The slot from which the tiles of a launch of nothing but whole panel tiles of one K are multiplied in quarters (panel_tail in epara_grouped.h),
-// or -1.  (Plain bf16 launches visit such tiles in parts of K, or all their tiles in halves.)  Tiles of one cost go round robin, so
-// those that are too few for a round of their own are at the last slots; a workgroup gets a quarter or two of them.  Whole / in quarters, 256 workgroups, 4 and 6 row tiles, K = 2048 and 4096 (gated bf16) or 4096 (fp8, gated and plain):
-// one round and 8 .. 64 tiles 1.25 .. 1.35, and 96 1.07 .. 1.18, and 128 1.00 .. 1.11; two rounds and 4 .. 64 tiles 1.10 .. 1.23.  516 tiles of
-// K = 4096, gated: 273 -> 238 us.
+// or -1.  (Plain bf16 launches visit such tiles in parts of K, or all their tiles in halves.)  Tiles of one cost go round robin, so those that are too
+// few for a round of their own are at the last slots; a workgroup gets a quarter or two of them.  Whole / in quarters, 256 workgroups, 4 and 6 row
+// tiles, K = 2048 and 4096 (gated bf16) or 4096 (fp8, gated and plain): one round and 8 .. 64 tiles 1.25 .. 1.35, and 96 1.07 .. 1.18, and 128
+// 1.00 .. 1.11; two rounds and 4 .. 64 tiles 1.10 .. 1.23.  516 tiles of K = 4096, gated: 273 -> 238 us.  66 launches of one to eight rounds drawn at
+// random, K = 1520 .. 13824, ragged rows and columns: 0.99 .. 1.25, 1.10 on average.
 long panel_tail_slot(const epara_launch* L)
 {
     const int64_t W = L->n_workgroups, rounds = L->n_tiles / W, rest = L->n_tiles % W;
@@ -171,10 +173,15 @@ long panel_tail_slot(const epara_launch* L)
     return static_cast<long>(rounds * W);
 }
 
-// Whether the weights of a launch are taken for bytes that no cache keeps until the next pass (the non-temporal hint, epara_stream.h): the
-// last-level cache holds 256 MB, and a gate/up launch has two thirds of the weights of its pass, a down launch a third, a single up
-// launch half.  Passes over the same weights again and again, plain / with the hint: bf16 270 MB 66.6 / 72.9 us, fp8 220 MB 77.2 / 91.7, 66 MB
-// 29.3 / 39.1, 131 MB of small models 55.7 / 60.1; bf16 424 MB 90.8 / 82.4, 541 MB 111.2 / 102.2, 850 MB 167.5 / 152.4.
+// Whether the weights of a launch are read with the non-temporal hint (epara_stream.h): a guess that no cache holds them from the pass before.
+// What comes between two passes is not known here.  The last-level cache holds 256 MB; a gate/up launch has two thirds of the weights of its
+// pass, a down launch a third, a single up launch half.  With the hint / without, times as fast, K = 4096 and 11008, 4 .. 237 rows a service:
+//   other weights read in between, as by a model of many layers: launches of 60 .. 700 MB 0.94 .. 1.12, on average 1.06 bf16 and 1.045 fp8 (20 MB:
+//     1.00), passes of 150 .. 1000 MB 0.99 .. 1.11, on average 1.06 and 1.04, with batches above 64 rows 1.035 and 1.005.
+//   the same weights again and nothing else: launches of 60 .. 290 MB 0.79 .. 1.18, on average 0.98 and 1.01, from 310 MB on 0.97 .. 1.19, on average
+//     1.06; passes of 150 .. 600 MB 0.79 .. 1.04, on average 0.94 (75 + 100 rows fp8, 380 MB: 97 -> 123 us), from 650 MB on 0.96 .. 1.09, on average 1.02.
+// The line keeps the hint out of passes that the cache holds whole.  Below it a model of many layers would gain the 2 .. 8 %; passes of one to two
+// times the line that repeat with nothing in between lose by it.
 int weights_once(const epara_launch* L, int32_t in_dtype, int gated)
 {
     double bytes = 0;

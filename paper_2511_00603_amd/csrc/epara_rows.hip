@@ -9,9 +9,12 @@
 // once for the maximum, once for the codes) and every destination byte written once.  A
 // workgroup of 256 threads moves 16-KiB chunks with 16-byte accesses per lane (a wave
 // instruction covers 1 KiB of consecutive memory); chunk c belongs to the last segment whose
-// first_chunk is <= c (find_segment; the value is the same for all lanes).  What a kernel does not read again is moved with the
-// non-temporal hint (copied bytes both ways, codes): 8192 x 5120 bf16 quantised and sent back 78.9 -> 71.2 us, 74.5 with the copies alone.
-// Not what is read for the maxima, which the codes are made from next (85.1 us), nor the source of the codes (82.9).
+// first_chunk is <= c (find_segment; the value is the same for all lanes).  What these kernels do not read again is moved with the
+// non-temporal hint (copied bytes both ways, codes).  8192 x 5120 bf16, six sets of requests in turn: quantised and results sent back 79.0 -> 73.7 us,
+// copied and sent back 67.5 -> 60.3; the same requests again and again 78.9 -> 71.2 (the maxima then find rows of the pass before in the last-level
+// cache) and 65.9 -> 57.5.  The launch that reads the batch next pays little for it: forming, gate/up, down and sending back together, 8192, 442 and 105 rows, within
+// 0.5 % of plain copies and codes or faster; 1500 rows x 1024 quantised and multiplied 25.7 -> 26.2 us (24.2 -> 24.8 in turn).  Batches of up to 1500
+// rows formed alone: no difference.  Not what is read for the maxima, which the codes are made from next (85.1 us instead of 71.2), nor the source of the codes (82.9).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -28,10 +28,11 @@ namespace {
 // are not multiplied / not stored.  The scheduling barriers keep the compiler from sinking the
 // prefetch loads down to their first use.
 //
-// Weights that no cache would keep until the next pass anyway (ONCE, chosen on the host by the size of the launch) are read with the
-// non-temporal hint: they don't go through the last-level cache and leave the dies' L2 to the activations, which every tile of the service reads.  Four services of 11008 -> 4096, all at once: 3 rows each 64.5 -> 56.9 us (6.3 TB/s), 32 rows
-// 73.8 -> 69.9, 64 rows in tiles of 128 columns 86.5 -> 73.4, of 64 columns 88.7 -> 86.9 (there a unit's own rate binds, 22 GB/s).  The
-// hint on the activations instead: 67.6, 89.3, 96.2, 116.8.
+// In large launches (ONCE, chosen on the host by their size; weights_once in epara_launch.hip says why there, and what it costs where a cache does
+// hold the weights) weights are read with the non-temporal hint: they don't go through the last-level cache and leave the dies' L2 to the
+// activations, which every tile of the service reads.  Four services of 11008 -> 4096, all at once: 3 rows each 64.5 -> 56.9 us (6.3 TB/s), 32 rows
+// 73.8 -> 69.9, 64 rows in tiles of 128 columns 86.5 -> 73.4, of 64 columns 88.7 -> 86.9 (there a unit's own rate binds, 22 GB/s).  The hint on the
+// activations instead: 67.6, 89.3, 96.2, 116.8.
 template <int NFR>
 struct skinny_tile_state {
     gcptr w[NFR];          // uniform: start of each weight column block's fragment stream
