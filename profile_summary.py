@@ -20,7 +20,10 @@ import sys
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(ROOT, "paper_2511_00603_amd", "csrc")
-KERNEL_SOURCES = [os.path.join(CSRC, f) for f in ("epara_device.h", "epara_panel.h", "epara_half.h", "epara_stream.h", "epara_grouped.h")]
+# what the grouped kernels of the mixes are compiled from and what chooses among them
+KERNEL_SOURCES = [os.path.join(CSRC, f) for f in (
+    "epara_cast.h", "epara_device.h", "epara_internal.h", "epara_plan.h", "epara_panel.h", "epara_block_tile.h", "epara_half.h", "epara_stream.h",
+    "epara_grouped.h", "epara_k_bf16_plain.hip", "epara_k_bf16_gated.hip", "epara_k_fp8_plain.hip", "epara_k_fp8_gated.hip", "epara_h_bf16.hip", "epara_launch.hip")]
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "traffic.txt")
 COPY_BYTES = 1 << 30
 

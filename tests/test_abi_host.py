@@ -1015,3 +1015,18 @@ def test_block_pieces_argument_checks():
 
 def struct_bytes(dtype):
     return dtype.itemsize
+
+
+def test_traffic_records_are_keyed_by_every_source_of_the_grouped_kernels():
+    """What the kernels of streaming, panel and half tiles include, directly or not, and the file that chooses among them: a change to any of them
+    makes the recorded traffic stale."""
+    import profile_summary as S
+    want, todo = set(), ["epara_k_bf16_plain.hip", "epara_k_bf16_gated.hip", "epara_k_fp8_plain.hip", "epara_k_fp8_gated.hip", "epara_h_bf16.hip", "epara_launch.hip"]
+    while todo:
+        f = todo.pop()
+        path = os.path.join(S.CSRC, f)
+        if f in want or not os.path.exists(path):                # (the public header lies elsewhere)
+            continue
+        want.add(f)
+        todo += re.findall(r'^#include "([^"]+)"', open(path).read(), re.M)
+    assert "epara_block_tile.h" in want and {os.path.basename(f) for f in S.KERNEL_SOURCES} >= want
